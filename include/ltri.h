@@ -255,7 +255,8 @@ int32_t ltri_attend(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int32_t seq
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, same
  * results. Where ltri_attend keeps the partial results of a split key range (query blocks of 1 to 4 rows:
  * decoding) in the context's scratch buffer, this call keeps them in a buffer of 2 MiB that the library
- * itself holds on every GPU it runs on, from load until the process ends. The call allocates and frees
+ * itself holds on every GPU it runs on, from load until the process ends (longer blocks use the context's scratch
+ * buffer like ltri_attend). The call allocates and frees
  * nothing. LTRI_ECAPACITY if the partial results of this call need more than 2 MiB (they take
  * seq_count * n_q_heads * splits * n_q * (head_dim + 2) * 4 bytes; 16 sequences of one token at 32 query
  * heads take 1.1 MB); other errors as ltri_attend. All contexts on one GPU share the buffer: calls that

@@ -4,12 +4,13 @@
 //
 // bf16 kernel: flash-style streaming over 64-key tiles on the matrix cores. A workgroup is
 // eight wavefronts that share every K/V tile through LDS: the query heads of one KV head's
-// group (GQA) times two 32-row sub-tiles, each wavefront with its 32 query rows in registers.
+// group (GQA) times two 32-row sub-tiles, or one sub-tile and two groups of keys, each wavefront
+// with its 32 query rows in registers.
 // Scores are computed transposed (S^T = K Q^T) so that one lane owns one query: the softmax
 // statistics need a single cross-lane exchange and the probabilities are already laid out as
 // the B operand of O^T = V^T P^T. The same kernel also attends over a part of the context
-// only (the two parts of a step that overlaps steps 1 and 2), and splits the key range of
-// a block of 2 to 4 query rows. One-token chunks (decode) have a kernel without LDS staging
+// only (the two parts of a step that overlaps steps 1 and 2), and its key range can be split over
+// workgroups (attend_shape). One-token chunks (decode) have a kernel without LDS staging
 // further down; fp32 contexts a plain one-wavefront-per-row kernel.
 #include <hip/hip_ext.h>
 #include "device_common.h"
@@ -20,7 +21,7 @@ namespace ltri {
 struct AttArgs {
   Dims D; DevState st; const void* k_arena; const void* v_arena; const void* q;
   void* out; float* lse; int layer; int seq_count; int n_q;
-  int n_splits; float* part;             // short query blocks: the key range is split over workgroups
+  int n_splits; float* part;             // > 1: the key range is split over workgroups, partial results in part
   int part_mode;                         // ATT_ALL, or one of the two parts of a two-part step
   const int32_t* loclist; int loc_cap;   // ATT_LOCAL: initial | window tokens per sequence [seq_count][loc_cap]
   const float* lse_a;                    // ATT_RETRIEVED: log-sum-exp of the first part, whose output is in `out`
@@ -35,6 +36,15 @@ enum : int { ATT_ALL = 0, ATT_LOCAL = 1, ATT_RETRIEVED = 2 };
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
+
+// Partial results of a split key range: rows [seq][head][split][query row] of 128 unnormalised fp32 sums, then as
+// many (running maximum in the log2 domain, sum) pairs.
+__device__ __forceinline__ size_t part_row(const AttArgs& a, int bi, int head, int split, int qi) {
+  return (((size_t)bi * a.D.Hq + head) * a.n_splits + split) * a.n_q + qi;
+}
+__device__ __forceinline__ float2* part_ml(const AttArgs& a) {
+  return reinterpret_cast<float2*>(a.part + (size_t)a.seq_count * a.D.Hq * a.n_splits * a.n_q * 128);
+}
 
 // two fp32 -> packed bf16 pair, round to nearest even (one v_cvt_pk_bf16_f32)
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -55,8 +65,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // The DMA is issued through inline assembly because the compiler would otherwise wait for ALL
 // outstanding DMA before any LDS read; completion is awaited by hand with s_waitcnt vmcnt(n),
 // n = DMA loads requested later than the tile about to be used. Every wavefront issues the same
-// number of requests in every iteration (its rows of one K/V tile and the token ids of its rows
-// of a later tile; past the last tile the requests fetch the chunk's last row into a free stage),
+// number of requests in every iteration (its rows of one stage's K/V tiles and the token ids of its rows
+// of a later stage; past the last tile the requests fetch the chunk's last row into a free stage),
 // so n is one constant.
 // The K fragments of a tile are requested together by hand (the compiler would serialise them
 // once registers are tight) and consumed in four groups; the DMA requests of a later tile are
@@ -68,9 +78,9 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int ATT_NW = 8;                       // wavefronts per workgroup of the bf16 kernel
-constexpr int DMA_STAGE_BYTES = 32768;          // K tile 16 KB + V tile 16 KB
+constexpr int TILE_BYTES = 16384;               // one 64-key tile of K or V
 constexpr int TOK_SLOTS = 8;                    // ring of token-id tiles (> tokens-ahead distance)
-constexpr int att_lds_bytes(int ns, int nw) { return ns * DMA_STAGE_BYTES + TOK_SLOTS * nw * 32; }
+constexpr int att_lds_bytes(int ks, int ns) { return ks * (ns * 2 * TILE_BYTES + TOK_SLOTS * 256); }
 
 // 16 bytes per lane from base + off into LDS at lds_wave_base + 16 * lane. The idle cycle between the write of
 // M0 and the load that uses it is the wait state the instruction set asks for; inside an assembly block the
@@ -118,18 +128,22 @@ __device__ __forceinline__ void lds_wait(u32x4_t& a, u32x4_t& b, u32x4_t& c, u32
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
 }
 
-// NW wavefronts per workgroup, each with 32 query rows of one head; NS ring stages.
-template <int NW, int NS>
-__global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
-  constexpr int TOK_AHEAD = 2 * (NS - 1) + 1;       // token ids of tile t + TOK_AHEAD are requested in iteration t
-  constexpr int NI = 16 / NW;                       // DMA row groups per wave and tile
-  constexpr int LPT = 2 * NI;                       // K/V requests per lane and tile
-  constexpr int IN_FLIGHT = (NS - 2) * (LPT + 1);   // requests that may be pending when a tile is used
-  static_assert(NS >= 3 && NS <= 4 && TOK_AHEAD < TOK_SLOTS && NI == 2, "request pattern");
+// KS groups of ATT_NW / KS wavefronts, each wavefront with 32 query rows of one head; a ring stage holds KS tiles of
+// 64 keys, one per group. NS ring stages.
+template <int KS, int NS>
+__global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
+  constexpr int NW = ATT_NW, NWQ = NW / KS;         // wavefronts in all, and per group (they cover the workgroup's rows)
+  constexpr int TOK_AHEAD = 2 * (NS - 1) + 1;       // token ids of stage t + TOK_AHEAD are requested in iteration t
+  constexpr int NI = 16 * KS / NW;                  // DMA row groups per wave and stage
+  constexpr int LPT = 2 * NI;                       // K/V requests per lane and stage
+  constexpr int IN_FLIGHT = (NS - 2) * (LPT + 1);   // requests that may be pending when a stage is used
+  constexpr int TPW = 64 * KS / NW;                 // token ids a wave fetches per stage (those of its own rows)
+  constexpr int STAGE_BYTES = KS * 2 * TILE_BYTES, TOK_SLOT_BYTES = KS * 256;
+  static_assert(NS >= 2 && NS <= 4 && TOK_AHEAD < TOK_SLOTS && (NI == 2 || NI == 4), "request pattern");
   extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
   const Dims& D = a.D;
   const int HG = D.G < 4 ? D.G : 4;                 // heads of the group handled by this block
-  const int RS = NW / HG;                           // row sub-tiles per block
+  const int RS = NWQ / HG;                          // row sub-tiles per block
   const int RPB = 32 * RS;                          // query rows per block
   const int gpk = D.G / HG;                         // blocks per KV head
   // KV head along x: consecutive workgroup ids go to different XCDs, so all query tiles of one
@@ -139,18 +153,20 @@ __global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
   const int L = a.n_q, d = 128;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave / NWQ, wq = wave % NWQ;       // the wave's key group, and its place among the group's waves
   const int l32 = lane & 31, hf = lane >> 5;
-  const int head = h * D.G + gsub * HG + (wave % HG);
-  const int split = a.n_splits > 1 ? blockIdx.y : 0;
+  const int head = h * D.G + gsub * HG + (wq % HG);
+  const int n_rb = (int)gridDim.y / a.n_splits;     // row blocks
+  const int split = (int)blockIdx.y % a.n_splits;
   // Query rows of the workgroup. The chunk's rows are cut into sub-tiles of 32; workgroup y takes RS / 2 of them
   // from the low end and RS / 2 from the high end (sub-tiles y RS / 2 .. and their mirror images), so that under
   // the causal mask every workgroup has about the same number of (sub-tile, chunk tile) pairs to compute: the
   // low sub-tiles stop early at their diagonal, the high ones walk on alone. With one sub-tile per workgroup
-  // (RS == 1) rows are taken in order.
-  const int nsub = (RPB == 32) ? (L + 31) / 32 : ((L + RPB - 1) / RPB) * RS;    // sub-tiles, padded to whole workgroups
-  const int yb = a.n_splits > 1 ? 0 : (int)blockIdx.y;
-  const int rs = wave / HG;
-  const int sub = (RS == 1) ? yb : (rs < RS / 2 ? yb * (RS / 2) + rs : nsub - (yb + 1) * (RS / 2) + (rs - RS / 2));
+  // (RS == 1) the last rows, which walk furthest, start first.
+  const int nsub = n_rb * RS;                       // sub-tiles, padded to whole workgroups
+  const int yb = (int)blockIdx.y / a.n_splits;
+  const int rs = wq / HG;
+  const int sub = (RS == 1) ? n_rb - 1 - yb : (rs < RS / 2 ? yb * (RS / 2) + rs : nsub - (yb + 1) * (RS / 2) + (rs - RS / 2));
   const int r0 = sub * 32;                          // first row of this wave
   const int rb_end = (RS == 1) ? min(L, r0 + 32) : min(L, (nsub - yb * (RS / 2)) * 32);   // past the last row of the workgroup
   const int slot = slot_of(D, a.layer, seq, h);
@@ -173,49 +189,52 @@ __global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
   const int crow0 = chunk_tok_row(D, c0, c0);       // row of the chunk's first token (the chunk's rows are consecutive)
   const int n_chunk_tiles = a.part_mode == ATT_RETRIEVED ? 0 : (rb_end + 63) / 64;
   const int n_tiles = n_ctx_tiles + n_chunk_tiles;
-  // with splits, this workgroup takes the context tiles [tile0, tile1); the last split also takes the chunk's tiles
-  const int tile0 = a.n_splits > 1 ? (int)((long long)split * n_ctx_tiles / a.n_splits) : 0;
-  const int tile1 = (a.n_splits > 1 && split + 1 < a.n_splits) ? (int)((long long)(split + 1) * n_ctx_tiles / a.n_splits) : n_tiles;
+  // stages of KS tiles; with splits, this workgroup takes the stages [st0, st1) of context and chunk
+  const int n_st = (n_tiles + KS - 1) / KS;
+  const int st0 = (int)((long long)split * n_st / a.n_splits);
+  const int st1 = (int)((long long)(split + 1) * n_st / a.n_splits);
   const uint32_t ring0 = (uint32_t)(uintptr_t)ring;
-  const uint32_t tok0 = ring0 + NS * DMA_STAGE_BYTES + (uint32_t)wave * 32;       // this wave's 8 ids of slot 0
-  const int32_t* tokring = reinterpret_cast<const int32_t*>(ring + NS * DMA_STAGE_BYTES) + wave * 8;
+  const uint32_t tok0 = ring0 + NS * STAGE_BYTES + (uint32_t)wave * (TPW * 4);       // this wave's ids of slot 0
+  const int32_t* tokring = reinterpret_cast<const int32_t*>(ring + NS * STAGE_BYTES) + wave * TPW;
 
   // ---- requests ----
-  // A wavefront fetches rows 4 NW i + 4 wave + lq (i < NI, lq = lane / 16) of every tile, lane
-  // piece lp = lane % 16 of the row. The token ids of its own eight rows travel through LDS the
-  // same way (lanes 0 .. 7, id j = 4 i + lq), TOK_AHEAD tiles ahead; no other wave reads them, so
+  // A wavefront fetches rows 4 NW i + 4 wave + lq (i < NI, lq = lane / 16) of every stage, lane
+  // piece lp = lane % 16 of the row. The token ids of its own rows travel through LDS the
+  // same way (lanes 0 .. TPW - 1, id j = 4 i + lq), TOK_AHEAD stages ahead; no other wave reads them, so
   // the wave's own wait makes them visible. Tiles past the list read a dummy entry.
   auto request_tokens = [&](int u) {
-    if (lane < 8) {
-      const int row = 4 * NW * (lane >> 2) + 4 * wave + (lane & 3);
-      dma4(list, (uint32_t)((u < n_ctx_tiles ? u * 64 : 0) + row) * 4u, tok0 + (uint32_t)(u % TOK_SLOTS) * (NW * 32));
+    if (lane < TPW) {
+      const int row = 4 * NW * (lane >> 2) + 4 * wave + (lane & 3), t = KS * u + (row >> 6);
+      dma4(list, (uint32_t)((t < n_ctx_tiles ? t * 64 : 0) + (row & 63)) * 4u, tok0 + (uint32_t)(u % TOK_SLOTS) * TOK_SLOT_BYTES);
     }
   };
   const int lq = lane >> 4, lp = lane & 15;
-  uint32_t kpiece[NI], vpiece[NI];
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int row = 4 * NW * i + 4 * wave + lq;
-    kpiece[i] = (uint32_t)((lp ^ (row & 15)) << 4);
-    // V: LDS piece p' of a row holds global piece swap13(p' ^ ((row & 3) << 1)), swap13 = exchange of bits 1 and 3
-    const int vp = lp ^ ((row & 3) << 1);
-    vpiece[i] = (uint32_t)(((vp & 5) | ((vp & 2) << 2) | ((vp & 8) >> 2)) << 4);
-  }
-  // tokens of the rows this lane fetches in tile t (list padding is token 0, masked by position;
+  // 16-byte pieces of a row that this lane fetches (the row's place in groups of 16 does not depend on i)
+  const int prow = 4 * wave + lq;
+  const uint32_t kpiece = (uint32_t)((lp ^ (prow & 15)) << 4);
+  // V: LDS piece p' of a row holds global piece swap13(p' ^ ((row & 3) << 1)), swap13 = exchange of bits 1 and 3
+  const int vp = lp ^ ((prow & 3) << 1);
+  const uint32_t vpiece = (uint32_t)(((vp & 5) | ((vp & 2) << 2) | ((vp & 8) >> 2)) << 4);
+  // tokens of the rows this lane fetches for stage u (list padding is token 0, masked by position;
   // past the last tile: the chunk's last token)
-  auto tile_tokens = [&](int t, int (&tok)[NI]) {
-    if (t < n_ctx_tiles) {
+  auto stage_tokens = [&](int u, int (&tok)[NI]) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) tok[i] = tokring[(t % TOK_SLOTS) * (NW * 8) + 4 * i + lq];
-    } else {
+    for (int k = 0; k < KS; ++k) {
+      const int t = KS * u + k;
+      if (t < n_ctx_tiles) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) tok[i] = crow0 + min((t - n_ctx_tiles) * 64 + 4 * NW * i + 4 * wave + lq, L - 1);
+        for (int i = k * (NI / KS); i < (k + 1) * (NI / KS); ++i) tok[i] = tokring[(u % TOK_SLOTS) * (TOK_SLOT_BYTES / 4) + 4 * i + lq];
+      } else {
+#pragma unroll
+        for (int i = k * (NI / KS); i < (k + 1) * (NI / KS); ++i)
+          tok[i] = crow0 + min((t - n_ctx_tiles) * 64 + 4 * NW * i - 64 * k + prow, L - 1);
+      }
     }
   };
-  auto request_rows = [&](int t, int i, int tok) {
-    const uint32_t dst = ring0 + (uint32_t)(t % NS) * DMA_STAGE_BYTES + (uint32_t)(4 * NW * i + 4 * wave) * 256;
-    dma16(Kb, ((uint32_t)tok << 8) + kpiece[i], dst);
-    dma16(Vb, ((uint32_t)tok << 8) + vpiece[i], dst + 16384u);
+  auto request_rows = [&](int u, int i, int tok) {
+    const uint32_t dst = ring0 + (uint32_t)(u % NS) * STAGE_BYTES + (uint32_t)(4 * NW * i + 4 * wave) * 256;
+    dma16(Kb, ((uint32_t)tok << 8) + kpiece, dst);
+    dma16(Vb, ((uint32_t)tok << 8) + vpiece, dst + KS * TILE_BYTES);
   };
 
   // ---- query fragments: B operand of S^T = K Q^T; lane (l32, hf) holds Q[row l32][16 kk + 8 hf ..] ----
@@ -247,7 +266,7 @@ __global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
   const uint32_t kswz = (uint32_t)((l32 & 14) << 4);
   uint32_t koff[8];                                 // fragment kk of rows l32 and l32 + 32 (+ 8192)
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) koff[kk] = ring0 + kbase + (kswz ^ (uint32_t)(kk << 5));
+  for (int kk = 0; kk < 8; ++kk) koff[kk] = ring0 + kg * TILE_BYTES + kbase + (kswz ^ (uint32_t)(kk << 5));
   const int vj = lane & 15, vgq = (lane >> 4) & 1;
   const int vrow_in = 4 * hf + (vj >> 2);           // key row inside a group of 8
   // V: the fragment of d-block mb needs global piece 4 mb + 2 gq + x (x = (j & 3) / 2). In LDS it sits at
@@ -259,21 +278,22 @@ __global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
   uint32_t voff[4];                                 // d-block mb
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb)
-    voff[mb] = ring0 + 16384u + vbase + (vswz ^ (uint32_t)((((mb & 1) << 2) | ((mb >> 1) << 1)) << 4));
+    voff[mb] = ring0 + (KS + kg) * TILE_BYTES + vbase + (vswz ^ (uint32_t)((((mb & 1) << 2) | ((mb >> 1) << 1)) << 4));
 
-  int tokreg[NI];                                   // tokens of the rows of the next tile to request
+  int tokreg[NI];                                   // tokens of the rows of the next stage to request
 
-  // ---- one iteration: wait for tile t, barrier, S^T = K Q^T with the requests of tile t + NS - 1
-  //      between the products, masks, online softmax (one query per lane pair), O^T += V^T P^T.
+  // ---- one iteration: wait for stage u, barrier, S^T = K Q^T of the group's tile t = KS u + kg with the requests of
+  //      stage u + NS - 1 between the products, masks, online softmax (one query per lane pair), O^T += V^T P^T.
   //      compute = false: a tile this wavefront cannot see (requests, wait and barrier only) ----
-  auto tile = [&](int t, auto mask_kind, auto compute_kind) {
+  auto tile = [&](int u, auto mask_kind, auto compute_kind) {
+    const int t = KS * u + kg;
     constexpr int MK = decltype(mask_kind)::value;
     constexpr bool COMPUTE = decltype(compute_kind)::value;
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IN_FLIGHT) : "memory");
-    __syncthreads();            // tile t is in LDS for every wave; tile t - 1's stage is free
-    const uint32_t sbase = (uint32_t)(t % NS) * DMA_STAGE_BYTES;
+    __syncthreads();            // stage u is in LDS for every wave; stage u - 1's place is free
+    const uint32_t sbase = (uint32_t)(u % NS) * STAGE_BYTES;
     int toknext[NI];
-    tile_tokens(t + NS, toknext);
+    stage_tokens(u + NS, toknext);
     f32x16_t s[2];
     if constexpr (COMPUTE) {
       // all sixteen K fragments are requested at once (index 2 kk + kb) and used in groups of four
@@ -296,17 +316,18 @@ __global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
       };
       // the scheduling barriers keep each group's products between its wait and the next one
       lds_wait<12>(kf[0], kf[1], kf[2], kf[3]);     group(0); __builtin_amdgcn_sched_barrier(0);
-      request_tokens(t + TOK_AHEAD);
-      request_rows(t + NS - 1, 0, tokreg[0]);
+      request_tokens(u + TOK_AHEAD);
+      request_rows(u + NS - 1, 0, tokreg[0]);
       lds_wait<8>(kf[4], kf[5], kf[6], kf[7]);      group(1); __builtin_amdgcn_sched_barrier(0);
-      request_rows(t + NS - 1, 1, tokreg[1]);
+      request_rows(u + NS - 1, 1, tokreg[1]);
       lds_wait<4>(kf[8], kf[9], kf[10], kf[11]);    group(2); __builtin_amdgcn_sched_barrier(0);
+      if constexpr (NI == 4) { request_rows(u + NS - 1, 2, tokreg[2]); request_rows(u + NS - 1, 3, tokreg[3]); }
       lds_wait<0>(kf[12], kf[13], kf[14], kf[15]);  group(3);
       __builtin_amdgcn_s_setprio(0);
     } else {
-      request_tokens(t + TOK_AHEAD);
-      request_rows(t + NS - 1, 0, tokreg[0]);
-      request_rows(t + NS - 1, 1, tokreg[1]);
+      request_tokens(u + TOK_AHEAD);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) request_rows(u + NS - 1, i, tokreg[i]);
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) tokreg[i] = toknext[i];
@@ -397,20 +418,21 @@ __global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
         }
   };
 
-  // ---- prologue: token ids of the first NS tiles, then the steady-state request pattern
-  //      (ids of tile u + TOK_AHEAD, K/V tile u + NS - 1) for u = -(NS - 1) .. -1 ----
-  for (int u = 0; u < NS; ++u) request_tokens(tile0 + u);
+  // ---- prologue: token ids of the first NS stages, then the steady-state request pattern
+  //      (ids of stage u + TOK_AHEAD, K/V of stage u + NS - 1) for u = -(NS - 1) .. -1 ----
+  for (int u = 0; u < NS; ++u) request_tokens(st0 + u);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   for (int u = 0; u < NS - 1; ++u) {
-    request_tokens(tile0 + u + NS);
-    tile_tokens(tile0 + u, tokreg);
-    request_rows(tile0 + u, 0, tokreg[0]);
-    request_rows(tile0 + u, 1, tokreg[1]);
+    request_tokens(st0 + u + NS);
+    stage_tokens(st0 + u, tokreg);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) request_rows(st0 + u, i, tokreg[i]);
   }
-  tile_tokens(tile0 + NS - 1, tokreg);
+  stage_tokens(st0 + NS - 1, tokreg);
 
-  // ---- tile segments of this wavefront ----
+  // ---- tile segments of this wavefront, in stages: past(x) = first stage whose tile of this group is not below x ----
   const bool active = r0 < L;
+  auto past = [&](int x) { return min((x - kg + KS - 1) / KS, st1); };           // (x >= 0: the division truncates at 0)
   const int t_list_end = (list_len & 63) ? n_ctx_tiles - 1 : n_ctx_tiles;       // first masked context tile
   // chunk tile kt (keys 64 kt ..) is fully visible to the wave iff 64 kt + 63 <= r0, visible iff 64 kt <= r0 + 31
   const int t_diag = n_ctx_tiles + (active ? min(n_chunk_tiles, (r0 + 1) / 64) : 0);
@@ -418,103 +440,188 @@ __global__ __launch_bounds__(64 * NW) void attend_bf16_kernel(AttArgs a) {
   using std::integral_constant;
   using std::true_type;
   using std::false_type;
-  int t = tile0;
+  int u = st0;
   if (active) {
-    for (; t < min(t_list_end, tile1); ++t) tile(t, integral_constant<int, MASK_NONE>{}, true_type{});
-    for (; t < min(n_ctx_tiles, tile1); ++t) tile(t, integral_constant<int, MASK_LIST_END>{}, true_type{});
-    for (; t < min(t_diag, tile1); ++t) tile(t, integral_constant<int, MASK_NONE>{}, true_type{});
-    for (; t < min(t_end, tile1); ++t) tile(t, integral_constant<int, MASK_CAUSAL>{}, true_type{});
+    for (; u < past(t_list_end); ++u) tile(u, integral_constant<int, MASK_NONE>{}, true_type{});
+    for (; u < past(n_ctx_tiles); ++u) tile(u, integral_constant<int, MASK_LIST_END>{}, true_type{});
+    for (; u < past(t_diag); ++u) tile(u, integral_constant<int, MASK_NONE>{}, true_type{});
+    for (; u < past(t_end); ++u) tile(u, integral_constant<int, MASK_CAUSAL>{}, true_type{});
   }
-  for (; t < tile1; ++t) tile(t, integral_constant<int, MASK_NONE>{}, false_type{});
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests past the last tile
+  for (; u < st1; ++u) tile(u, integral_constant<int, MASK_NONE>{}, false_type{});
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests past the last stage
 
   // ---- epilogue ----
-  uint16_t* Ob = reinterpret_cast<uint16_t*>(a.out) + (size_t)bi * L * D.Hq * d;
+  float lt = l_run + __shfl_xor(l_run, 32, 64);
+  constexpr int NMB = 4 / KS;                       // d-blocks this wave writes, the first one mb0
+  const int mb0 = NMB * kg;
+  if constexpr (KS == 2) {
+    // The two groups hold the same rows over different keys: each hands the other half of its columns (and its
+    // maximum and sum) through LDS and merges the half it keeps (the log-sum-exp identity).
+    float4* give = reinterpret_cast<float4*>(ring) + wave * 512 + lane;
+    float2* mlx = reinterpret_cast<float2*>(ring + NW * 8192) + wave * 64 + lane;
+    const float4* take = reinterpret_cast<const float4*>(ring) + (wave ^ NWQ) * 512 + lane;
+    __syncthreads();                                // nobody reads the ring or waits for requests into it any more
+#pragma unroll
+    for (int b = 0; b < NMB; ++b)
+#pragma unroll
+      for (int a4 = 0; a4 < 4; ++a4) {
+        float g[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[e] = kg ? o[b][4 * a4 + e] : o[NMB + b][4 * a4 + e];
+        give[(b * 4 + a4) * 64] = make_float4(g[0], g[1], g[2], g[3]);
+      }
+    *mlx = make_float2(m_run, lt);
+    __syncthreads();
+    const float2 other = reinterpret_cast<const float2*>(ring + NW * 8192)[(wave ^ NWQ) * 64 + lane];
+    const float m_new = fmaxf(m_run, other.x);
+    const float f0 = __builtin_amdgcn_exp2f(m_run - m_new), f1 = __builtin_amdgcn_exp2f(other.x - m_new);
+    lt = lt * f0 + other.y * f1;
+    m_run = m_new;
+#pragma unroll
+    for (int b = 0; b < NMB; ++b)
+#pragma unroll
+      for (int a4 = 0; a4 < 4; ++a4) {
+        const float4 g = take[(b * 4 + a4) * 64];
+        const float gv[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float mine = kg ? o[NMB + b][4 * a4 + e] : o[b][4 * a4 + e];
+          o[b][4 * a4 + e] = fmaf(gv[e], f1, mine * f0);
+        }
+      }
+  }
+  const bool writes_ml = hf == 0 && kg == 0;
   const int qi = r0 + l32;
-  const float lt = l_run + __shfl_xor(l_run, 32, 64);
+  if (qi >= L) return;
   if (a.n_splits > 1) {
-    // unnormalised O, running maximum and sum of this split: [seq][head][split][row][d + 2] fp32
-    if (qi < L) {
-      float* pr = a.part + ((((size_t)bi * D.Hq + head) * a.n_splits + split) * L + qi) * (d + 2);
+    // unnormalised O, running maximum and sum of this split (the layout of part_row)
+    const size_t row = part_row(a, bi, head, split, qi);
+    float* pr = a.part + row * d + mb0 * 32 + 4 * hf;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+    for (int b = 0; b < NMB; ++b)
 #pragma unroll
-        for (int a4 = 0; a4 < 4; ++a4)
-          *reinterpret_cast<float4*>(pr + mb * 32 + 8 * a4 + 4 * hf) =
-              make_float4(o[mb][4 * a4 + 0], o[mb][4 * a4 + 1], o[mb][4 * a4 + 2], o[mb][4 * a4 + 3]);
-      if (hf == 0) { pr[d] = m_run; pr[d + 1] = lt; }
-    }
+      for (int a4 = 0; a4 < 4; ++a4)
+        *reinterpret_cast<float4*>(pr + b * 32 + 8 * a4) =
+            make_float4(o[b][4 * a4 + 0], o[b][4 * a4 + 1], o[b][4 * a4 + 2], o[b][4 * a4 + 3]);
+    if (writes_ml) part_ml(a)[row] = make_float2(m_run, lt);
     return;
   }
+  const size_t rh = ((size_t)bi * L + qi) * D.Hq + head;
+  uint16_t* orow = reinterpret_cast<uint16_t*>(a.out) + rh * d + mb0 * 32 + 4 * hf;
   if (a.part_mode == ATT_RETRIEVED) {
     // O = (w_a O_a + w_b O_b) / (w_a + w_b) with w = 2^(lse - max lse) (the log-sum-exp identity, log2 domain);
     // O_b = o / lt and lse_b = m_run + log2(lt), so w_b / lt = 2^(m_run - max). Every lane rewrites the
     // elements of O_a it reads. Without a retrieved key the first part stands as it is.
-    if (qi < L) {
-      const size_t rh = ((size_t)bi * L + qi) * D.Hq + head;
-      const float la = a.lse_a[rh];
-      if (lt > 0.f) {
-        const float la2 = la * 1.4426950408889634f, lb2 = m_run + log2f(lt);
-        const float mx = fmaxf(la2, lb2);
-        const float wa = __builtin_amdgcn_exp2f(la2 - mx), wb = __builtin_amdgcn_exp2f(lb2 - mx);
-        const float inv = 1.f / (wa + wb);
-        const float fa = wa * inv, fb = __builtin_amdgcn_exp2f(m_run - mx) * inv;
-        uint16_t* orow = Ob + ((size_t)qi * D.Hq + head) * d;
+    const float la = a.lse_a[rh];
+    if (lt > 0.f) {
+      const float la2 = la * 1.4426950408889634f, lb2 = m_run + log2f(lt);
+      const float mx = fmaxf(la2, lb2);
+      const float wa = __builtin_amdgcn_exp2f(la2 - mx), wb = __builtin_amdgcn_exp2f(lb2 - mx);
+      const float inv = 1.f / (wa + wb);
+      const float fa = wa * inv, fb = __builtin_amdgcn_exp2f(m_run - mx) * inv;
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+      for (int b = 0; b < NMB; ++b)
 #pragma unroll
-          for (int a4 = 0; a4 < 4; ++a4) {
-            uint2* p = reinterpret_cast<uint2*>(orow + mb * 32 + 8 * a4 + 4 * hf);
-            const uint2 ua = *p;
-            uint2 u;
-            u.x = pack_bf16x2(fa * __uint_as_float(ua.x << 16) + fb * o[mb][4 * a4 + 0],
-                              fa * __uint_as_float(ua.x & 0xFFFF0000u) + fb * o[mb][4 * a4 + 1]);
-            u.y = pack_bf16x2(fa * __uint_as_float(ua.y << 16) + fb * o[mb][4 * a4 + 2],
-                              fa * __uint_as_float(ua.y & 0xFFFF0000u) + fb * o[mb][4 * a4 + 3]);
-            *p = u;
-          }
-        if (a.lse && hf == 0) a.lse[rh] = (mx + log2f(wa + wb)) * 0.6931471805599453f;
-      } else if (a.lse && hf == 0) {
-        a.lse[rh] = la;
-      }
+        for (int a4 = 0; a4 < 4; ++a4) {
+          uint2* p = reinterpret_cast<uint2*>(orow + b * 32 + 8 * a4);
+          const uint2 ua = *p;
+          uint2 u2;
+          u2.x = pack_bf16x2(fa * __uint_as_float(ua.x << 16) + fb * o[b][4 * a4 + 0],
+                             fa * __uint_as_float(ua.x & 0xFFFF0000u) + fb * o[b][4 * a4 + 1]);
+          u2.y = pack_bf16x2(fa * __uint_as_float(ua.y << 16) + fb * o[b][4 * a4 + 2],
+                             fa * __uint_as_float(ua.y & 0xFFFF0000u) + fb * o[b][4 * a4 + 3]);
+          *p = u2;
+        }
+      if (a.lse && writes_ml) a.lse[rh] = (mx + log2f(wa + wb)) * 0.6931471805599453f;
+    } else if (a.lse && writes_ml) {
+      a.lse[rh] = la;
     }
     return;
   }
-  if (qi < L) {
-    const float inv = 1.f / lt;
-    uint16_t* orow = Ob + ((size_t)qi * D.Hq + head) * d;
+  const float inv = 1.f / lt;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+  for (int b = 0; b < NMB; ++b)
 #pragma unroll
-      for (int a4 = 0; a4 < 4; ++a4) {
-        uint2 u;
-        u.x = pack_bf16x2(o[mb][4 * a4 + 0] * inv, o[mb][4 * a4 + 1] * inv);
-        u.y = pack_bf16x2(o[mb][4 * a4 + 2] * inv, o[mb][4 * a4 + 3] * inv);
-        *reinterpret_cast<uint2*>(orow + mb * 32 + 8 * a4 + 4 * hf) = u;
+    for (int a4 = 0; a4 < 4; ++a4) {
+      uint2 u2;
+      u2.x = pack_bf16x2(o[b][4 * a4 + 0] * inv, o[b][4 * a4 + 1] * inv);
+      u2.y = pack_bf16x2(o[b][4 * a4 + 2] * inv, o[b][4 * a4 + 3] * inv);
+      *reinterpret_cast<uint2*>(orow + b * 32 + 8 * a4) = u2;
+    }
+  if (a.lse && writes_ml) a.lse[rh] = (m_run + log2f(lt)) * 0.6931471805599453f;
+}
+
+// ---- merge of the splits: O = sum_s w_s O_s / sum_s w_s l_s, w_s = 2^(m_s - max m) (the log-sum-exp identity).
+//      Half a wavefront per row of (head, query row), four columns per lane; lane s of the half holds split s's maximum
+//      and sum. A wavefront takes PAIRS pairs of consecutive rows and UNROLL splits of each at a time, so that
+//      PAIRS * UNROLL 16-byte loads per lane are in flight. ----
+template <int PAIRS, int UNROLL>
+__global__ __launch_bounds__(256) void attend_merge_kernel(AttArgs a) {
+  const Dims& D = a.D;
+  const int L = a.n_q, ns = a.n_splits, lane = threadIdx.x & 63, hl = lane & 31, bi = blockIdx.y;
+  const int rr0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (2 * PAIRS) + (lane >> 5), n_rows = D.Hq * L;
+  int head[PAIRS], qi[PAIRS];
+  size_t r0[PAIRS];
+  float2 ml[PAIRS];
+#pragma unroll
+  for (int p = 0; p < PAIRS; ++p) {
+    const int rr = min(rr0 + 2 * p, n_rows - 1);
+    head[p] = rr / L; qi[p] = rr - head[p] * L;
+    r0[p] = part_row(a, bi, head[p], 0, qi[p]);
+    ml[p] = part_ml(a)[r0[p] + (size_t)min(hl, ns - 1) * L];
+  }
+  const float4* po = reinterpret_cast<const float4*>(a.part) + hl;
+  float4 v[PAIRS][UNROLL], acc[PAIRS];
+  auto load = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) v[p][u] = po[(r0[p] + (size_t)min(s0 + u, ns - 1) * L) * 32];
+  };
+  load(0);
+  float w[PAIRS], l[PAIRS], mmax[PAIRS];
+#pragma unroll
+  for (int p = 0; p < PAIRS; ++p) {
+    mmax[p] = ml[p].x;                                  // lanes past the last split repeat it
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) mmax[p] = fmaxf(mmax[p], __shfl_xor(mmax[p], o, 64));
+    w[p] = hl < ns ? __builtin_amdgcn_exp2f(ml[p].x - mmax[p]) : 0.f;
+    l[p] = w[p] * ml[p].y;
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) l[p] += __shfl_xor(l[p], o, 64);
+    acc[p] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  for (int s0 = 0; s0 < ns; s0 += UNROLL) {
+    if (s0 > 0) load(s0);
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const float ws = __shfl(w[p], (lane & 32) + ((s0 + u) & 31), 64);       // 0 past the last split
+        acc[p].x = fmaf(ws, v[p][u].x, acc[p].x);
+        acc[p].y = fmaf(ws, v[p][u].y, acc[p].y);
+        acc[p].z = fmaf(ws, v[p][u].z, acc[p].z);
+        acc[p].w = fmaf(ws, v[p][u].w, acc[p].w);
       }
-    if (a.lse && hf == 0)
-      a.lse[((size_t)bi * L + qi) * D.Hq + head] = (m_run + log2f(lt)) * 0.6931471805599453f;
+  }
+#pragma unroll
+  for (int p = 0; p < PAIRS; ++p) {
+    if (rr0 + 2 * p >= n_rows) continue;
+    const float inv = 1.f / l[p];
+    const size_t orow = ((size_t)bi * L + qi[p]) * D.Hq + head[p];
+    uint2 u;
+    u.x = pack_bf16x2(acc[p].x * inv, acc[p].y * inv);
+    u.y = pack_bf16x2(acc[p].z * inv, acc[p].w * inv);
+    reinterpret_cast<uint2*>(a.out)[orow * 32 + hl] = u;
+    if (a.lse && hl == 0) a.lse[orow] = (mmax[p] + log2f(l[p])) * 0.6931471805599453f;
   }
 }
 
-// ---- merge of the splits of a short query block: O = sum_s w_s O_s / sum_s w_s l_s,
-//      w_s = 2^(m_s - max m) (the log-sum-exp identity), one workgroup per (row, head, sequence) ----
-__global__ __launch_bounds__(128) void attend_merge_kernel(AttArgs a) {
-  const Dims& D = a.D;
-  const int qi = blockIdx.x, head = blockIdx.y, bi = blockIdx.z, d = 128, L = a.n_q, c = threadIdx.x;
-  const float* pr = a.part + ((size_t)bi * D.Hq + head) * a.n_splits * L * (d + 2);
-  float mmax = -1e30f;
-  for (int s = 0; s < a.n_splits; ++s) mmax = fmaxf(mmax, pr[((size_t)s * L + qi) * (d + 2) + d]);
-  float acc = 0.f, l = 0.f;
-  for (int s = 0; s < a.n_splits; ++s) {
-    const float* q = pr + ((size_t)s * L + qi) * (d + 2);
-    const float w = __builtin_amdgcn_exp2f(q[d] - mmax);
-    acc = fmaf(w, q[c], acc);
-    l = fmaf(w, q[d + 1], l);
-  }
-  uint16_t* orow = reinterpret_cast<uint16_t*>(a.out) + (((size_t)bi * L + qi) * D.Hq + head) * d;
-  orow[c] = f32_to_bf16(acc / l);
-  if (a.lse && c == 0) a.lse[((size_t)bi * L + qi) * D.Hq + head] = (mmax + log2f(l)) * 0.6931471805599453f;
+static void launch_merge(const AttArgs& a, int seq_count, hipStream_t s) {
+  const int rows = a.D.Hq * a.n_q;
+  // many rows: eight rows per wavefront; few (decoding): two, with eight splits of each in flight
+  if (rows * seq_count >= 8192) attend_merge_kernel<4, 2><<<dim3((rows + 31) / 32, seq_count), 256, 0, s>>>(a);
+  else                          attend_merge_kernel<1, 8><<<dim3((rows + 7) / 8, seq_count), 256, 0, s>>>(a);
 }
 
 // ---- one query row per sequence (decode, G <= 4): keys across wavefronts, nothing staged in LDS ----
@@ -690,9 +797,9 @@ __global__ __launch_bounds__(64 * DEC_WAVES, 3) void attend_decode_kernel(AttArg
       acc = fmaf(wgt, wpart[ww][hh][c], acc);
       l = fmaf(wgt, wpart[ww][hh][d + 1], l);
     }
-    float* pr = a.part + (((size_t)bi * D.Hq + (size_t)h * G + hh) * a.n_splits + split) * (d + 2);
-    pr[c] = acc;
-    if (c == 0) { pr[d] = mmax; pr[d + 1] = l; }
+    const size_t row = part_row(a, bi, h * G + hh, split, 0);
+    a.part[row * d + c] = acc;
+    if (c == 0) part_ml(a)[row] = make_float2(mmax, l);
   }
 }
 
@@ -819,7 +926,7 @@ __global__ __launch_bounds__(256) void gather_pack_kernel(GatherArgs a) {
 }
 
 // ---- how a launch splits the key range of a short query block, and what its partial results need ----
-// kind: 0 = no partial results, 1 = the one-token kernel, 2 = the matrix-core kernel with splits
+// kind: 0 = no short block, 1 = the one-token kernel, 2 = the matrix-core kernel with splits
 static int attend_split_count(const Dims& D, int seq_count, int n_q, int n_cus, int* kind) {
   *kind = 0;
   if (!attend_on_matrix_cores(D) || n_q > ATT_SPLIT_MAX_ROWS) return 1;
@@ -840,6 +947,50 @@ static int attend_split_count(const Dims& D, int seq_count, int n_q, int n_cus, 
   if (ns <= 1) return 1;
   *kind = 2;
   return ns > ATT_MAX_SPLITS ? ATT_MAX_SPLITS : ns;
+}
+
+// Rows of partial results a context's scratch has room for: short query blocks at any batch, and longer ones while
+// a split pays (three rounds of workgroups of 128 rows on 256 compute units).
+size_t attend_part_rows(const Dims& D) {
+  const size_t short_rows = (size_t)D.n_seqs * D.Hq * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS;
+  const size_t all = (size_t)D.n_seqs * D.Hq * D.chunk_max * ATT_MAX_SPLITS;
+  const size_t long_rows = all < 98304 ? all : 98304;
+  return attend_on_matrix_cores(D) ? (short_rows > long_rows ? short_rows : long_rows) : 0;
+}
+
+// ---- shape of a launch of the matrix-core kernel: key groups per workgroup and splits of the key range ----
+// A workgroup (one per compute unit: its registers and LDS fill it) covers 256 (row, head) pairs with every wavefront
+// on all keys (KS = 1), or 128 with two groups on alternate tiles (KS = 2, merged in LDS): twice the workgroups, half
+// the stages, twice the rows fetched per product. Splits divide the stages further but write and read back partial
+// results. The launch takes (rounds of workgroups over the chip) x (stages per workgroup x time of a stage + start) +
+// merge; the least of that model over both KS and 1 .. 16 splits is taken. Its constants are measured at 32 query and
+// 8 KV heads (us): a stage 1.5 on a nearly empty chip .. 1.85 on a full one (the clock falls), 7 % more with KS = 2,
+// 4 to start and drain a workgroup, 5 + 1.7e-4 per partial row for the merge (with the write-back of the rows at the
+// end of the kernel). Launches it changes, before -> after at context + query rows: 8110 + 1024 215 -> 148 (two
+// groups), 3039 + 700 92 -> 59, four sequences of 1999 + 256 66 -> 45, 8166 + 512 206 -> 84 (two groups, two splits),
+// 2003 + 128 58 -> 24. A full chip keeps KS = 1 without splits (12196 + 2048: 413 against 427 with two groups).
+struct AttShape { int ks, ns; };
+static AttShape attend_shape(const Dims& D, int seq_count, int n_q, int n_ctx, int n_chunk, size_t part_rows, int n_cus) {
+  const int HG = D.G < 4 ? D.G : 4;
+  AttShape best{1, 1};
+  float best_cost = 0.f;
+  for (int ks = 1; ks <= 2; ++ks) {
+    const int rs = ATT_NW / ks / HG, rpb = 32 * rs;
+    const long long blocks = (long long)D.Hkv * (D.G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
+    // with one sub-tile per workgroup the causal part is walked on average to three quarters (rows start from the end)
+    const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * (rs == 1 ? 0.75f : 1.f);
+    for (int ns = 1; ns <= ATT_MAX_SPLITS; ++ns) {
+      const size_t rows = (size_t)seq_count * D.Hq * n_q * ns;
+      if (ns > 1 && (rows > part_rows || ns * ks > tiles)) break;
+      const long long rounds = (blocks * ns + n_cus - 1) / n_cus;
+      const float fill = (float)(blocks * ns) / (float)(rounds * n_cus);
+      const float stages = ceilf(tiles / (float)(ks * ns));
+      const float cost = (float)rounds * (stages * (1.5f + 0.35f * fill) * (ks == 2 ? 1.07f : 1.f) + 4.f) +
+                         (ns > 1 ? 5.f + 1.7e-4f * (float)rows : 0.f);
+      if ((ks == 1 && ns == 1) || cost < best_cost) { best_cost = cost; best = AttShape{ks, ns}; }
+    }
+  }
+  return best;
 }
 
 static hipError_t device_cus(int* n_cus) {
@@ -908,44 +1059,51 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     if (D.G == 4)      attend_decode_kernel<4><<<g, 64 * DEC_WAVES, 0, s>>>(a);
     else if (D.G == 2) attend_decode_kernel<2><<<g, 64 * DEC_WAVES, 0, s>>>(a);
     else               attend_decode_kernel<1><<<g, 64 * DEC_WAVES, 0, s>>>(a);
-    attend_merge_kernel<<<dim3(1, D.Hq, seq_count), 128, 0, s>>>(a);
+    launch_merge(a, seq_count, s);
     if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }
     return hipGetLastError();
   }
   if (mfma_ok) {
+    // expected context of the launch (the lists themselves are on the device): only the shape depends on it
+    long long c0 = 0;
+    for (int i = 0; i < seq_count; ++i) c0 = bp.c0[i] > c0 ? bp.c0[i] : c0;
+    const long long near = (long long)D.n_sink + D.window;
+    const long long far = D.budget ? D.budget : D.k_max ? (long long)D.k_max * 256 : c0;
+    long long n_ctx = part_mode == ATT_LOCAL ? near : part_mode == ATT_RETRIEVED ? far : near + far;
+    if (n_ctx > c0) n_ctx = c0;
+    AttShape shape = attend_shape(D, seq_count, n_q, (int)n_ctx, part_mode == ATT_RETRIEVED ? 0 : n_q,
+                                  part && part_mode == ATT_ALL ? attend_part_rows(D) : 0, n_cus);
+    if (n_q <= ATT_SPLIT_MAX_ROWS) shape = AttShape{2, ns_short};
+    const int ks = shape.ks, ns = shape.ns;
     const int HG = D.G < 4 ? D.G : 4;
     const int gpk = D.G / HG;
-    constexpr int NW = ATT_NW;
-    const int RPB = 32 * (NW / HG);
-    dim3 g(D.Hkv * gpk, (n_q + RPB - 1) / RPB, seq_count);
-    if (kind == 2) {
-      a.n_splits = ns_short;
-      g.y = a.n_splits;
-    }
+    const int RPB = 32 * (ATT_NW / ks / HG);
+    a.n_splits = ns;
+    dim3 g(D.Hkv * gpk, (n_q + RPB - 1) / RPB * ns, seq_count);
     static bool attr_set = false;
     if (!attr_set) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<NW, 4>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, att_lds_bytes(4, NW));
-      if (e != hipSuccess) return e;
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_bf16_kernel<NW, 3>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, att_lds_bytes(3, NW));
-      if (e != hipSuccess) return e;
+      for (const void* f : {reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 3>),
+                            reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2>)}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, att_lds_bytes(2, 2));
+        if (e != hipSuccess) return e;
+      }
       attr_set = true;
     }
-    if (t_begin) {
+    auto launch = [&](auto ksc, auto nsc) {
+      constexpr int KS = decltype(ksc)::value, NS = decltype(nsc)::value;
+      constexpr int lds = att_lds_bytes(KS, NS);
       // the events ride in the kernel's own dispatch; with a merge behind it the end is recorded after that
-      const hipEvent_t stop = a.n_splits > 1 ? nullptr : t_end;
-      if (stages == 3)
-        hipExtLaunchKernelGGL((attend_bf16_kernel<NW, 3>), g, dim3(64 * NW), (uint32_t)att_lds_bytes(3, NW), s, t_begin, stop, 0, a);
+      if (t_begin)
+        hipExtLaunchKernelGGL((attend_bf16_kernel<KS, NS>), g, dim3(64 * ATT_NW), (uint32_t)lds, s, t_begin, ns > 1 ? nullptr : t_end, 0, a);
       else
-        hipExtLaunchKernelGGL((attend_bf16_kernel<NW, 4>), g, dim3(64 * NW), (uint32_t)att_lds_bytes(4, NW), s, t_begin, stop, 0, a);
-    } else if (stages == 3) {
-      attend_bf16_kernel<NW, 3><<<g, 64 * NW, att_lds_bytes(3, NW), s>>>(a);
-    } else {
-      attend_bf16_kernel<NW, 4><<<g, 64 * NW, att_lds_bytes(4, NW), s>>>(a);
-    }
-    if (a.n_splits > 1) {
-      attend_merge_kernel<<<dim3(n_q, D.Hq, seq_count), 128, 0, s>>>(a);
+        attend_bf16_kernel<KS, NS><<<g, 64 * ATT_NW, lds, s>>>(a);
+    };
+    using std::integral_constant;
+    if (ks == 2)          launch(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    else if (stages == 3) launch(integral_constant<int, 1>{}, integral_constant<int, 3>{});
+    else                  launch(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    if (ns > 1) {
+      launch_merge(a, seq_count, s);
       if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }
     }
   } else {

@@ -166,7 +166,7 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   CL.qpart = o;  o = align_up(o + (size_t)2 * P * (Lp / 128 + Lp) * D.d * 8, 256);
   CL.bounds = o; o = align_up(o + (size_t)c.n_kv_heads * (c.chunk_max + 2) * 4, 256);
   CL.selflag = o; o = align_up(o + (size_t)c.n_seqs * c.n_kv_heads * D.max_spans, 256);
-  CL.att_part = o; o = align_up(o + (size_t)c.n_seqs * c.n_q_heads * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS * (D.d + 2) * 4, 256);
+  CL.att_part = o; o = align_up(o + attend_part_rows(D) * (D.d + 2) * 4, 256);
   CL.tokspan = o; o = align_up(o + (size_t)P * Lp * 4, 256);
   CL.dyn = o;     o = align_up(o + (size_t)P * 3 * Lp * 8, 256);
   CL.qhist = o;   o = align_up(o + (size_t)P * QUANT_BINS * 4, 256);
@@ -688,7 +688,7 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
       return fail(c, LTRI_ESTATE, "sequence %d: no selection for the last chunk (call ltri_retrieve first)",
                   seq_begin + s);
   float* part = c->dc.att_part;
-  if (own_buffer) {
+  if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS) {
     // a dry context sizes the request for a device of 256 compute units
     const size_t bytes = attend_partial_bytes(c->D, seq_count, n_q, c->dry ? 256 : c->n_cus);
     if (bytes > ATT_STATIC_SCRATCH_BYTES)

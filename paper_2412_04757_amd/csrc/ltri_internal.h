@@ -31,8 +31,8 @@ constexpr int QUANT_STATE_WORDS = 8 + QUANT_LISTS;   // per problem: key prefix,
 constexpr int QUANT_LIST_CAP = 1 << 14;      // cells collected for the final exact selection, at most
 constexpr int IDX_MASK_WORDS = SEG_MAX_L / 32;   // one bit per token of a chunk
 constexpr int ATT_BN = 64;               // keys per attention tile; token lists are padded to it
-constexpr int ATT_MAX_SPLITS = 16;       // key-range splits of a short query block (decode)
-constexpr int ATT_SPLIT_MAX_ROWS = 4;    // longest query block that is split
+constexpr int ATT_MAX_SPLITS = 16;       // key-range splits of an attention launch, at most
+constexpr int ATT_SPLIT_MAX_ROWS = 4;    // longest query block whose split does not depend on the context (decoding)
 constexpr size_t ATT_STATIC_SCRATCH_BYTES = 2u << 20;   // the library's own buffer for such partial results (ltri_attend_static)
 
 // Byte offsets of the arrays inside the caller's `state` buffer.
@@ -70,7 +70,7 @@ struct ScratchLayout {
                    //        chunk's query rows [0] and key rows [1]
   size_t bounds;   // int32  [Hkv][chunk_max + 1] + int32 [Hkv]  (append_with_spans)
   size_t selflag;  // uint8  [n_seqs * Hkv][max_spans]  1 = span selected (between the two selection kernels)
-  size_t att_part; // float  [n_seqs][Hq][ATT_MAX_SPLITS][ATT_SPLIT_MAX_ROWS][d + 2]  partial attention results
+  size_t att_part; // float  [attend_part_rows][d + 2]  partial results of an attention whose key range is split
   size_t tokspan;  // int32  [P][Lp]      span (within the chunk) of every token (dynamic index vectors)
   size_t dyn;      // double [P][3][Lp]   votes, in-span row sums, whole row sums of the softmax map
   size_t qhist;    // uint32 [P][QUANT_BINS]  histogram of one digit of the map cells' order keys (percentile theta)
@@ -208,6 +208,7 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
 // marker is queued that the neighbouring launches would wait behind); other shapes record them around the launches.
 // bytes of partial results a launch over seq_count sequences with n_q query rows needs (0: the key range is not split)
 size_t attend_partial_bytes(const Dims& D, int seq_count, int n_q, int n_cus);
+size_t attend_part_rows(const Dims& D);          // rows of (head_dim + 2) floats in a context's buffer of partial results
 // device address, on the current device, of the library's own buffer of ATT_STATIC_SCRATCH_BYTES for partial results
 hipError_t attend_static_scratch(float** ptr);
 bool attend_on_matrix_cores(const Dims& D);      // the bf16 kernel takes this shape (else one wavefront per query row)
