@@ -71,12 +71,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // The K fragments of a tile are requested together by hand (the compiler would serialise them
 // once registers are tight) and consumed in four groups; the DMA requests of a later tile are
 // issued between the groups, under the matrix products. The rescale of O is skipped while no
-// lane's running maximum moves.
+// score passes the reference of the exponentials by much.
 // The tile loop is cut into segments (context tiles, the ragged last context tile, chunk tiles
 // below the diagonal, chunk tiles on the diagonal, tiles this wavefront cannot see) so that the
 // body of each segment is straight-line code, with the masks compiled in or out.
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
+constexpr float RESCALE_SLACK = 8.f;            // powers of two a score may pass the reference by before O is rescaled
 constexpr int ATT_NW = 8;                       // wavefronts per workgroup of the bf16 kernel
 constexpr int TILE_BYTES = 16384;               // one 64-key tile of K or V
 constexpr int TOK_SLOTS = 8;                    // ring of token-id tiles (> tokens-ahead distance)
@@ -361,11 +362,21 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
       m4[c] = max3(m4[c], s[kb][v0 + 5], s[kb][v0 + 6]);
     }
     float mx = max3(max3(m4[0], s[0][7], s[0][15]), max3(m4[1], s[1][7], s[1][15]), fmaxf(m4[2], m4[3]));
-    mx = pair_max(mx);
-    const float m_new = fmaxf(m_run, mx * sc);
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    const bool changed = m_new != m_run;
-    m_run = m_new;
+    mx = pair_max(mx) * sc;
+    // The reference of the exponentials moves only when a score passes it by more than RESCALE_SLACK: until then the
+    // probabilities exceed 1 by at most 2^RESCALE_SLACK, which costs fp32 sums and bf16 probabilities no precision
+    // (both are relative), and the rescale of O and of the sum (64 products per lane) is left out of nearly every
+    // tile; with the running maximum itself as the reference a third of the tiles of a 12K-key context needed it.
+    if (__any(mx > m_run + RESCALE_SLACK)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[mb][v] *= alpha;
+    }
     // probabilities, rounded to bf16 in B-operand order; the row sum is taken over the rounded
     // values (the ones PV multiplies), two per instruction
     uint4 pf[2][2];
@@ -374,7 +385,7 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
     for (int kb = 0; kb < 2; ++kb) {
       float pv[16];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) pv[v] = __builtin_amdgcn_exp2f(fmaf(s[kb][v], sc, -m_new));
+      for (int v = 0; v < 16; ++v) pv[v] = __builtin_amdgcn_exp2f(fmaf(s[kb][v], sc, -m_run));
 #pragma unroll
       for (int a2 = 0; a2 < 2; ++a2) {
         uint4 u;
@@ -389,13 +400,7 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
         ps = pair_sum(u.w, ps);
       }
     }
-    l_run = l_run * alpha + ps;
-    if (__any(changed)) {                           // the running maximum rarely moves after the first tiles
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[mb][v] *= alpha;
-    }
+    l_run += ps;
     typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
     // one LDS address per d-block; the (kb, a2, row group) part is a constant offset of the read
     lds_s16x4_ptr vptr[4];

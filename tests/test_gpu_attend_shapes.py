@@ -75,3 +75,27 @@ def test_attention_launch_shapes(gpu_device, hq, hkv, seqs, window, budget, hist
         assert float((out[s].double() - want).abs().max()) <= 2e-2
         assert float((lse[s].double() - want_lse).abs().max()) <= 2e-3
     assert ctx.sync_status() == 0
+
+
+def test_attention_scores_that_keep_growing(gpu_device):
+    """Scores whose running maximum climbs through the whole context by far more than the slack of the rescale: keys of
+    later tokens are longer, so that nearly all weight sits on the last keys and every tile moves the reference."""
+    w = Workload("growing", 8, 2, 128, "bf16", 2048 + 64, 512, 4, 2048, 0, 64, "uniform", 16, 96)
+    cfg = config_from_workload(w, theta=theta_default(128), n_layers=1, n_seqs=1)
+    ctx = LtriContext(cfg, gpu_device)
+    ka, va = ctx.arena_views()
+    g = torch.Generator(device=str(gpu_device)).manual_seed(5)
+    base = torch.randn((2, 1, 128), generator=g, device=gpu_device)
+    grow = torch.linspace(0.0, 6.0, 2048 + 64, device=gpu_device)[None, :, None]
+    ka[0, 0].copy_(base * grow)
+    va[0, 0].copy_(torch.randn(va[0, 0].shape, generator=g, device=gpu_device))
+    q = (base.repeat_interleave(4, 0)[:, 0] + 0.1 * torch.randn((64, 8, 128), generator=g, device=gpu_device)).bfloat16()
+    for c0 in range(0, 2048, 512):
+        ctx.append_chunk(0, 0, 1, 512)
+    ctx.append_chunk(0, 0, 1, 64)
+    ctx.retrieve(0, 0, 1, q.unsqueeze(0).contiguous())
+    lse = torch.empty((1, 64, 8), dtype=torch.float32, device=gpu_device)
+    out = ctx.attend(0, 0, 1, q.unsqueeze(0).contiguous(), lse=lse)
+    want, want_lse = attend_reference(ctx, w, 0, 2048, q)
+    assert float((out[0].double() - want).abs().max()) <= 2e-2
+    assert float((lse[0].double() - want_lse).abs().max()) <= 2e-3
