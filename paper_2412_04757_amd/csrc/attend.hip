@@ -11,22 +11,13 @@
 // the B operand of O^T = V^T P^T. The same kernel also attends over a part of the context
 // only (the two parts of a step that overlaps steps 1 and 2), and its key range can be split over
 // workgroups (attend_shape). One-token chunks (decode) have a kernel without LDS staging
-// further down; fp32 contexts a plain one-wavefront-per-row kernel.
+// further down; fp32 contexts have attend_f32.hip.
 #include <hip/hip_ext.h>
 #include "device_common.h"
+#include "attend_args.h"
 #include <type_traits>
 
 namespace ltri {
-
-struct AttArgs {
-  Dims D; DevState st; const void* k_arena; const void* v_arena; const void* q;
-  void* out; float* lse; int layer; int seq_count; int n_q;
-  int n_splits; float* part;             // > 1: the key range is split over workgroups, partial results in part
-  int part_mode;                         // ATT_ALL, or one of the two parts of a two-part step
-  const int32_t* loclist; int loc_cap;   // ATT_LOCAL: initial | window tokens per sequence [seq_count][loc_cap]
-  const float* lse_a;                    // ATT_RETRIEVED: log-sum-exp of the first part, whose output is in `out`
-  BatchPos bp;
-};
 
 // A step whose retrieved rows first have to come from host memory attends in two parts: the one that does
 // not depend on the retrieval (initial and window tokens and the chunk itself) runs while the chunk is being
@@ -817,74 +808,6 @@ __global__ __launch_bounds__(256) void local_list_kernel(Dims D, BatchPos bp, in
   if (r < loc_cap) loclist[(size_t)bi * loc_cap + r] = r < n_init ? r : (r < len ? window_tok_row(D, w0 + r - n_init) : 0);
 }
 
-// ---- fp32 kernel: one wavefront per (query row, head); keys across lanes ----
-template <int DT>
-__global__ __launch_bounds__(64) void attend_simple_kernel(AttArgs a) {
-  typedef typename Elt<DT>::type T;
-  __shared__ float qs[128];
-  __shared__ float ps[64];
-  __shared__ int toks[64];
-  const Dims& D = a.D;
-  const int qi = blockIdx.x, head = blockIdx.y, bi = blockIdx.z;
-  const int h = head / D.G, d = D.d, per = d / 64;
-  const int seq = a.bp.seq[bi], c0 = a.bp.c0[bi], L = a.n_q;
-  const int lane = threadIdx.x;
-  const int slot = slot_of(D, a.layer, seq, h);
-  const T* Kb = reinterpret_cast<const T*>(a.k_arena) + arena_off(D, slot);
-  const T* Vb = reinterpret_cast<const T*>(a.v_arena) + arena_off(D, slot);
-  const int32_t* meta = a.st.meta + (size_t)slot * META_WORDS;
-  const int list_len = meta[META_LIST_LEN];
-  const int32_t* list = a.st.row_list + (size_t)slot * D.list_cap;
-  const T* qrow = reinterpret_cast<const T*>(a.q) + (((size_t)bi * L + qi) * D.Hq + head) * d;
-  for (int c = lane; c < d; c += 64) qs[c] = Elt<DT>::to_f32(qrow[c]);
-  __syncthreads();
-  const float scale = 1.0f / sqrtf((float)d);
-  const int n_keys = list_len + qi + 1;
-  float m_run = -1e30f, l_run = 0.f, o0 = 0.f, o1 = 0.f;
-  for (int k0 = 0; k0 < n_keys; k0 += 64) {
-    const int k = k0 + lane;
-    int tok = -1;
-    if (k < list_len) tok = list[k];
-    else if (k < n_keys) tok = chunk_tok_row(D, c0, c0) + (k - list_len);
-    float z = -INFINITY;
-    if (tok >= 0) {
-      const T* krow = Kb + (size_t)tok * d;
-      float acc = 0.f;
-      for (int c = 0; c < d; ++c) acc = fmaf(qs[c], Elt<DT>::to_f32(krow[c]), acc);
-      z = acc * scale;
-    }
-    float mx = z;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = expf(m_run - m_new);
-    const float pz = expf(z - m_new);
-    float sum = pz;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    l_run = l_run * alpha + sum;
-    m_run = m_new;
-    __syncthreads();
-    ps[lane] = pz;
-    toks[lane] = tok;
-    __syncthreads();
-    o0 *= alpha; o1 *= alpha;
-    const int cnt = min(64, n_keys - k0);
-    for (int kk = 0; kk < cnt; ++kk) {
-      const int tk = toks[kk];
-      if (tk < 0) continue;
-      const T* vrow = Vb + (size_t)tk * d + lane * per;
-      o0 = fmaf(ps[kk], Elt<DT>::to_f32(vrow[0]), o0);
-      if (per == 2) o1 = fmaf(ps[kk], Elt<DT>::to_f32(vrow[1]), o1);
-    }
-  }
-  T* orow = reinterpret_cast<T*>(a.out) + (((size_t)bi * L + qi) * D.Hq + head) * d + lane * per;
-  const float inv = 1.f / l_run;
-  orow[0] = Elt<DT>::from_f32(o0 * inv);
-  if (per == 2) orow[1] = Elt<DT>::from_f32(o1 * inv);
-  if (a.lse && lane == 0) a.lse[((size_t)bi * L + qi) * D.Hq + head] = m_run + logf(l_run);
-}
-
 // ---- standalone gather: K/V rows of the context list into packed buffers ----
 struct GatherArgs { Dims D; DevState st; const void* k_arena; const void* v_arena; int layer, seq;
                     void* k_packed; void* v_packed; int32_t* n_tokens; };
@@ -1112,10 +1035,8 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
       if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }
     }
   } else {
-    dim3 g(n_q, D.Hq, seq_count);
     if (t_begin) { if (hipError_t e = hipEventRecord(t_begin, s); e != hipSuccess) return e; }
-    if (D.dtype == LTRI_BF16) attend_simple_kernel<LTRI_BF16><<<g, 64, 0, s>>>(a);
-    else                      attend_simple_kernel<LTRI_F32><<<g, 64, 0, s>>>(a);
+    if (hipError_t e = launch_attend_f32(a, s); e != hipSuccess) return e;
     if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }
   }
   return hipGetLastError();

@@ -1,0 +1,201 @@
+// Step 3 for fp32 contexts: the same exact attention, on the fp32 matrix cores.
+//
+// v_mfma_f32_16x16x4f32 with 16 (query row, head) pairs of one KV head as columns, so that every group size fills the
+// tile and the rows of a tile are few (the causal edge costs one tile). A wavefront walks every 8th tile of 16 keys of
+// its workgroup's pairs with all operands in registers: nothing is shared between wavefronts but the caches, and a
+// chunk of 256 rows x 4 heads still runs 512 wavefronts. S^T = K Q^T leaves the probabilities of one query in four
+// lanes as the B operand of O^T = V^T P^T; key k of a tile is fed as product step k % 4, lane group k / 4, which is the
+// order they come in. The partial results of the wavefronts (own maximum, sum and O) are merged in LDS at the end, in a
+// fixed order.
+// What bounds it: the fp32 matrix rate (256 flop per cycle and compute unit) of the compute units it reaches, 64 for
+// the chunk of 256 rows, plus the chain list -> rows -> products before and the merge after (10 us).
+// Measured against one wavefront per row and head on the vector ALU, context + rows (us): 4 / 1 heads x 64
+// wide, 1028 + 256: 223 -> 22, 1540 + 1: 249 -> 22; 8 / 2 x 64, 1504 + 1000: 680 -> 75; 4 / 2 x 128, 1504 + 512:
+// 673 -> 61, two sequences of 1504 + 2048: 4692 -> 311. Error against fp64 there: 6e-7 .. 1e-6 -> 3e-7 .. 5e-7.
+// 16 wavefronts per workgroup: 24.5 (a smaller share of the tiles each, a larger merge), 4: 25.9; 32 pairs per
+// wavefront (half the row loads): 37.4 and no faster on large launches.
+#include "device_common.h"
+#include "attend_args.h"
+
+namespace ltri {
+
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));      // the caller's query rows: element alignment
+
+__device__ __forceinline__ bool not_finite(float x) { return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u; }
+__device__ __forceinline__ float group_max(float v) {      // over the four lanes of a query
+  v = fmaxf(v, __uint_as_float(lane_xor_c<16>(__float_as_uint(v))));
+  return fmaxf(v, __uint_as_float(lane_xor_c<32>(__float_as_uint(v))));
+}
+
+constexpr int F32_WAVES = 8;                                 // wavefronts per workgroup
+constexpr int F32_PITCH = 68;                                // floats per query of a wavefront's 64 columns in LDS
+
+template <int DIM>
+__global__ __launch_bounds__(64 * F32_WAVES, DIM == 64 ? 4 : 2) void attend_f32_kernel(AttArgs a) {
+  constexpr int NP = DIM / 16;                               // 4-element pieces of a row for each of its four lanes
+  constexpr int NC = DIM / 64;                               // 64-column parts of a row
+  __shared__ float part[F32_WAVES * 16 * F32_PITCH];
+  __shared__ float s_m[F32_WAVES][16], s_l[F32_WAVES][16];
+  const Dims& D = a.D;
+  const int G = D.G, L = a.n_q;
+  const int h = blockIdx.y, bi = blockIdx.z;
+  const int p0 = (gridDim.x - 1 - blockIdx.x) * 16;          // the latest rows, which see the most keys, first
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+  const int seq = a.bp.seq[bi], c0 = a.bp.c0[bi];
+  const int slot = slot_of(D, a.layer, seq, h);
+  const float* Kb = reinterpret_cast<const float*>(a.k_arena) + arena_off(D, slot);
+  const float* Vb = reinterpret_cast<const float*>(a.v_arena) + arena_off(D, slot);
+  const int list_len = a.st.meta[(size_t)slot * META_WORDS + META_LIST_LEN];
+  const int32_t* list = a.st.row_list + (size_t)slot * D.list_cap;
+  const int chunk_row = chunk_tok_row(D, c0, c0);
+  const int last_pair = min(p0 + 16, L * G) - 1;
+  const int n_keys = list_len + last_pair / G + 1;           // keys the latest row of the workgroup sees
+  const int n_open = list_len + p0 / G + 1;                  // keys every row of it sees
+  const int n_tiles = (n_keys + 15) / 16;
+  const float scale = 1.0f / sqrtf((float)DIM);
+
+  const int pair = min(p0 + r, last_pair);
+  const int vis = list_len + pair / G + 1;                   // keys the lane's query sees
+  f32x4_t qf[NP];
+  {
+    const float* qrow = reinterpret_cast<const float*>(a.q) + (((size_t)bi * L + pair / G) * D.Hq + h * G + pair % G) * DIM;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) qf[u] = *reinterpret_cast<const f32x4u_t*>(qrow + 4 * (g + 4 * u));
+  }
+  f32x4_t o[NC][4];                                          // O[query r][64 c + 16 g + 4 v + e] = o[c][e][v]
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[c][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m_run = -1e30f, l_run = 0.f;                         // l_run: the lane's own keys only
+
+  auto token = [&](int t) -> int {                           // row of key 16 t + r (past the end: the last key)
+    const int k = min(16 * t + r, n_keys - 1);
+    return k < list_len ? list[k] : chunk_row + (k - list_len);
+  };
+  f32x4_t kf[NP], vf[4][NC];
+  auto load_k = [&](int tok) {
+    const float* row = Kb + (size_t)tok * DIM + 4 * g;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) kf[u] = *reinterpret_cast<const f32x4_t*>(row + 16 * u);
+  };
+  auto load_v = [&](int tok) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float* row = Vb + (size_t)__shfl(tok, 4 * g + v, 64) * DIM + 4 * r;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) vf[v][c] = *reinterpret_cast<const f32x4_t*>(row + 64 * c);
+    }
+  };
+  int tok = token(wave), tok_next = token(wave + F32_WAVES);
+  load_k(tok);
+  load_v(tok);
+  for (int t = wave; t < n_tiles; t += F32_WAVES) {
+    f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < NP; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][e], qf[u][e], s, 0, 0, 0);
+    // the rows of the wavefront's next tile are requested as soon as this one's registers are free
+    tok = tok_next;
+    load_k(tok);
+    tok_next = token(t + 2 * F32_WAVES);
+    const bool edge = 16 * t + 16 > n_open;                  // uniform: some row does not see the whole tile
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      s[v] *= scale;
+      if (edge && 16 * t + 4 * g + v >= vis) s[v] = -INFINITY;
+    }
+    const float m_new = fmaxf(m_run, group_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
+    if (__any(m_new > m_run)) {
+      const float alpha = expf(m_run - m_new);
+      l_run *= alpha;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[c][e] *= alpha;
+      m_run = m_new;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[v] = expf(s[v] - m_run);
+    l_run += (s[0] + s[1]) + (s[2] + s[3]);
+    bool apart = false;                                      // an infinity or NaN in a row that some query must not see
+    if (edge) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) apart |= not_finite(vf[v][c][e]);
+      apart = __any(apart);
+    }
+    if (!apart) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v][c][e], s[v], o[c][e], 0, 0, 0);
+    } else {
+      // key by key; a query that must not see a key keeps its sums (a product with a probability of 0 would not do)
+      for (int gg = 0; gg < 4; ++gg)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x4f32(g == gg ? vf[v][c][e] : 0.f, g == gg ? s[v] : 0.f,
+                                                                    o[c][e], 0, 0, 0);
+              if (16 * t + 4 * gg + v < vis) o[c][e] = x;
+            }
+    }
+    load_v(tok);
+  }
+
+  // ---- merge of the wavefronts, in a fixed order ----
+  l_run += __uint_as_float(lane_xor_c<16>(__float_as_uint(l_run)));
+  l_run += __uint_as_float(lane_xor_c<32>(__float_as_uint(l_run)));
+  if (g == 0) { s_m[wave][r] = m_run; s_l[wave][r] = l_run; }
+  __syncthreads();
+  float m_all = -1e30f;
+#pragma unroll
+  for (int w = 0; w < F32_WAVES; ++w) m_all = fmaxf(m_all, s_m[w][r]);
+  const float f = expf(m_run - m_all);                       // 0 for a wavefront without a key
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    if (c) __syncthreads();                                  // the columns before are read
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      *reinterpret_cast<f32x4_t*>(part + (wave * 16 + r) * F32_PITCH + 16 * g + 4 * v) =
+          f32x4_t{o[c][0][v] * f, o[c][1][v] * f, o[c][2][v] * f, o[c][3][v] * f};
+    __syncthreads();
+#pragma unroll
+    for (int qq = 0; qq < 16 / F32_WAVES; ++qq) {            // one query per wavefront, a column per lane
+      const int q = wave + F32_WAVES * qq, p = p0 + q;
+      if (p <= last_pair) {
+        float m = -1e30f, l = 0.f, sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < F32_WAVES; ++w) m = fmaxf(m, s_m[w][q]);
+#pragma unroll
+        for (int w = 0; w < F32_WAVES; ++w) {
+          l = fmaf(s_l[w][q], expf(s_m[w][q] - m), l);
+          sum += part[(w * 16 + q) * F32_PITCH + lane];
+        }
+        const size_t rh = ((size_t)bi * L + p / G) * D.Hq + h * G + p % G;
+        reinterpret_cast<float*>(a.out)[rh * DIM + 64 * c + lane] = sum * (1.f / l);
+        if (c == 0 && a.lse && lane == 0) a.lse[rh] = m + logf(l);
+      }
+    }
+  }
+}
+
+hipError_t launch_attend_f32(const AttArgs& a, hipStream_t s) {
+  const Dims& D = a.D;
+  const dim3 grid((a.n_q * D.G + 15) / 16, D.Hkv, a.seq_count);
+  if (D.d == 64) attend_f32_kernel<64><<<grid, 64 * F32_WAVES, 0, s>>>(a);
+  else           attend_f32_kernel<128><<<grid, 64 * F32_WAVES, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+}  // namespace ltri

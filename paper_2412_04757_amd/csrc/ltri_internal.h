@@ -211,7 +211,7 @@ size_t attend_partial_bytes(const Dims& D, int seq_count, int n_q, int n_cus);
 size_t attend_part_rows(const Dims& D);          // rows of (head_dim + 2) floats in a context's buffer of partial results
 // device address, on the current device, of the library's own buffer of ATT_STATIC_SCRATCH_BYTES for partial results
 hipError_t attend_static_scratch(float** ptr);
-bool attend_on_matrix_cores(const Dims& D);      // the bf16 kernel takes this shape (else one wavefront per query row)
+bool attend_on_matrix_cores(const Dims& D);      // the bf16 kernel takes this shape (else attend_f32.hip)
 hipError_t launch_local_list(const Dims& D, const BatchPos& bp, int seq_count, int32_t* loclist, int loc_cap,
                              hipStream_t s);
 hipError_t launch_gather_pack(const Dims& D, const DevState& st, const void* k_arena, const void* v_arena,

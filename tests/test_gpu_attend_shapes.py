@@ -99,3 +99,51 @@ def test_attention_scores_that_keep_growing(gpu_device):
     want, want_lse = attend_reference(ctx, w, 0, 2048, q)
     assert float((out[0].double() - want).abs().max()) <= 2e-2
     assert float((lse[0].double() - want_lse).abs().max()) <= 2e-3
+
+
+# fp32: (query heads, KV heads, head_dim, sequences, window, budget, history, query rows)
+F32_SHAPES = [
+    (4, 1, 64, 1, 64, 0, 0, 2),          # fewer tiles than wavefronts, no context
+    (4, 1, 64, 1, 11, 0, 40, 1),         # one row; a context of one ragged tile
+    (4, 1, 64, 1, 512, 512, 1500, 256),
+    (6, 2, 64, 2, 100, 77, 700, 85),     # a group of three heads: the last workgroup's pairs are ragged
+    (1, 1, 128, 1, 60, 64, 700, 33),     # one head: 16 rows per workgroup
+    (40, 2, 128, 1, 123, 100, 900, 7),   # more heads than pairs of a workgroup
+    (4, 2, 128, 3, 130, 200, 1000, 97),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,dim,seqs,window,budget,history,rows", F32_SHAPES)
+def test_fp32_attention(gpu_device, hq, hkv, dim, seqs, window, budget, history, rows):
+    """Every row and head against the fp64 reference; then with an infinity in the values of the chunk's last token,
+    which only the last row sees."""
+    w = Workload("f32", hq, hkv, dim, "f32", history + rows, 256, 4, window, 0, budget, "uniform", 8, 48)
+    ctx = LtriContext(config_from_workload(w, theta=theta_default(dim), n_layers=1, n_seqs=seqs), gpu_device)
+    ka, va = ctx.arena_views()
+    q = []
+    for s in range(seqs):
+        K, V, Q, _ = planted_stream(w, 700 + s, device=str(gpu_device), context=history + rows)
+        ka[0, s].copy_(K)
+        va[0, s].copy_(V)
+        q.append(Q[history:])
+    for c0 in range(0, history, 256):
+        ctx.append_chunk(0, 0, seqs, min(256, history - c0))
+    q = torch.stack(q).contiguous()
+    lse = torch.empty(q.shape[:3], dtype=torch.float32, device=gpu_device)
+    out = torch.full_like(q, float("nan"))
+    ctx.append_chunk(0, 0, seqs, rows)
+    ctx.retrieve(0, 0, seqs, q)
+    ctx.attend(0, 0, seqs, q, out=out, lse=lse)
+    for s in range(seqs):
+        want, want_lse = attend_reference(ctx, w, s, history, q[s])
+        # scores of up to 128 fp32 products of values around 1 and |score| <= 8: 128 * 2^-24 * 8 at the very most in the
+        # exponent, as a relative error of the weights; the sums of weights and outputs (below a few units) add less
+        assert float((out[s].double() - want).abs().max()) <= 6e-5
+        assert float((lse[s].double() - want_lse).abs().max()) <= 6e-5
+    va[0, :, :, history + rows - 1] = float("inf")
+    poisoned = torch.full_like(q, float("nan"))
+    ctx.attend(0, 0, seqs, q, out=poisoned)
+    # the last tile's 16 keys are then added one by one: 16 roundings of sums below 4 (2^-23 each) in another order
+    assert bool(((poisoned[:, :-1] - out[:, :-1]).abs() <= 4e-6).all())
+    assert not torch.isfinite(poisoned[:, -1]).any()
+    assert ctx.sync_status() == 0
