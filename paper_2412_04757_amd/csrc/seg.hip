@@ -200,12 +200,8 @@ __device__ __forceinline__ void qstore(unsigned long long* p, unsigned long long
 
 struct QuantShared {
   uint32_t hist[QUANT_BINS];
-  unsigned long long part[256];
-  unsigned long long prefix, rank, base, count;
-  unsigned long long wtot[4];
-  uint32_t len[QUANT_LISTS];
+  unsigned long long base;
   uint32_t cnt;
-  int digit;
 };
 
 __global__ __launch_bounds__(256) void quant_init_kernel(SegArgs a, unsigned long long rank, unsigned long long n_cells) {
@@ -289,21 +285,42 @@ __device__ __forceinline__ void quant_tile_step(const SegArgs& a, int p, int I, 
   quant_tile_cells(a, p, I, J, status, Ms, S);
 }
 
-// The step after a tile pass (all 256 threads of one workgroup per problem): after a counting pass, the digit
-// that holds the rank; after a collecting pass, the rest of the selection on the list (the same digit steps, over
-// the list's keys instead of the tiles).
-__device__ __forceinline__ void quant_pick_step(const SegArgs& a, int p, unsigned long long status, QuantShared& S) {
+// Counters of a digit step over a list: QUANT_COPIES interleaved histograms (lanes use copy lane % QUANT_COPIES).
+// The first digit of a key is its sign and exponent, which most cells of a map share, and additions to one LDS word
+// are served one lane at a time.
+constexpr int QUANT_COPIES = 8;
+constexpr int QUANT_DIRECT = 256;                       // keys that are ranked by comparing them all
+
+struct QuantPickShared {
+  uint32_t hist[QUANT_BINS * QUANT_COPIES];             // [bin][copy]; a counting pass uses copy 0 of packed bins
+  unsigned long long wtot[16];
+  unsigned long long prefix, rank, count;
+  unsigned long long few[QUANT_DIRECT];
+  uint32_t off[QUANT_LISTS + 1];
+  uint32_t n_few;
+  int digit;
+};
+
+// The step after a tile pass (all NT threads of one workgroup per problem): after a counting pass, the digit that
+// holds the rank; after a collecting pass, the rest of the selection on the list. The list's keys (at most
+// QUANT_LIST_CAP, 16 per thread of 1024) are read once into registers and counted by digit, as in a counting pass,
+// until at most QUANT_DIRECT of them are left, and those are ranked by comparing each with all others.
+template <int NT>
+__device__ __forceinline__ void quant_pick_step(const SegArgs& a, int p, unsigned long long status, QuantPickShared& S) {
   const int tid = threadIdx.x;
-  constexpr int PER = QUANT_BINS / 256;
+  constexpr int PER = QUANT_BINS / NT;
   unsigned long long* st = a.sc.qstate + (size_t)p * QUANT_STATE_WORDS;
   const bool collected = quant_count(status) <= (unsigned long long)QUANT_LIST_CAP;
   uint32_t* gh = a.sc.qhist + (size_t)p * QUANT_BINS;
-  // One digit step on the histogram in S.hist with S.part[t] = the sum of thread t's PER bins (all threads call
-  // it after a barrier; S.prefix / S.rank hold the state and are updated, S.count gets the picked bin's count):
-  // a scan of S.part over the workgroup finds the thread whose bins hold the rank, that thread walks its bins.
-  auto pick_digit = [&](int digit) {
+  // One digit step, with cnt[] = the counts of this thread's PER bins (all threads call it after a barrier;
+  // S.prefix / S.rank hold the state and are updated, S.count gets the picked bin's count): a scan over the
+  // workgroup finds the thread whose bins hold the rank, that thread walks its bins.
+  auto pick_digit = [&](int digit, const uint32_t (&cnt)[PER]) {
     const int lane = tid & 63, wave = tid >> 6;
-    const unsigned long long own = S.part[tid], rank = S.rank;
+    const unsigned long long rank = S.rank;
+    unsigned long long own = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) own += cnt[e];
     unsigned long long incl = own;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -316,29 +333,32 @@ __device__ __forceinline__ void quant_pick_step(const SegArgs& a, int p, unsigne
     const unsigned long long excl = incl - own;
     // exactly one thread holds the rank; the last one also takes a rank beyond the total (cannot happen with
     // consistent counts)
-    if (rank >= excl && (rank < incl || tid == 255)) {
+    if (rank >= excl && (rank < incl || tid == NT - 1)) {
       unsigned long long below = excl;
-      int b = tid * PER;
-      while (b < tid * PER + PER - 1 && below + S.hist[b] <= rank) { below += S.hist[b]; ++b; }
-      S.prefix |= (uint64_t)b << quant_shift(digit);
+      int b = PER - 1;
+      uint32_t c = cnt[PER - 1];
+      bool open = true;
+#pragma unroll
+      for (int e = 0; e < PER - 1; ++e) {
+        const bool here = open && below + cnt[e] > rank;
+        if (here) { b = e; c = cnt[e]; open = false; }
+        if (open) below += cnt[e];
+      }
+      S.prefix |= (uint64_t)(tid * PER + b) << quant_shift(digit);
       S.rank = rank - below;
-      S.count = S.hist[b];
+      S.count = c;
     }
     __syncthreads();
   };
   __syncthreads();
-  if (tid == 0) { S.prefix = qload(st + 0); S.rank = qload(st + 1); S.digit = quant_digits(status); }
+  if (tid == 0) { S.prefix = qload(st + 0); S.rank = qload(st + 1); S.digit = quant_digits(status); S.n_few = 0u; }
   if (!collected) {
-    unsigned long long mine = 0;
-    for (int e = 0; e < PER; ++e) {
-      const uint32_t v = atomicExch(&gh[tid * PER + e], 0u);        // read and clear for the next pass
-      S.hist[tid * PER + e] = v;
-      mine += v;
-    }
-    S.part[tid] = mine;
+    uint32_t cnt[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) cnt[e] = atomicExch(&gh[tid * PER + e], 0u);        // read and clear for the next pass
     __syncthreads();
     const int digit = S.digit;
-    pick_digit(digit);
+    pick_digit(digit, cnt);
     if (tid == 0) {
       qstore(st + 0, S.prefix);
       qstore(st + 1, S.rank);
@@ -351,38 +371,80 @@ __device__ __forceinline__ void quant_pick_step(const SegArgs& a, int p, unsigne
   // the lists hold every cell that shares the prefix: the remaining digits on the lists
   // (plain loads: nothing of the lists was in this compute unit's cache before they were written)
   const unsigned long long* lists = a.sc.qlist + (size_t)p * QUANT_LISTS * QUANT_LIST_CAP;
-  if (tid < QUANT_LISTS) {
-    const unsigned long long n_raw = qload(st + 8 + tid);
-    S.len[tid] = (uint32_t)(n_raw < (unsigned long long)QUANT_LIST_CAP ? n_raw : (unsigned long long)QUANT_LIST_CAP);
+  if (tid < 64) {                                         // offsets of the sub-lists in their concatenation
+    const unsigned long long n_raw = tid < QUANT_LISTS ? qload(st + 8 + tid) : 0ull;
+    const uint32_t len = (uint32_t)(n_raw < (unsigned long long)QUANT_LIST_CAP ? n_raw : (unsigned long long)QUANT_LIST_CAP);
+    uint32_t incl = len;
+#pragma unroll
+    for (int o = 1; o < QUANT_LISTS; o <<= 1) {
+      const uint32_t v = __shfl_up(incl, o, 64);
+      if (tid >= o) incl += v;
+    }
+    if (tid < QUANT_LISTS) S.off[tid + 1] = incl;
+    if (tid == 0) S.off[0] = 0u;
   }
   __syncthreads();
-  const int first_digit = S.digit;
-  // the first 256 entries of every sub-list stay in registers over the digit steps (one independent load each);
-  // longer sub-lists are walked again per digit
-  unsigned long long kreg[QUANT_LISTS];
+  const uint32_t total = S.off[QUANT_LISTS];
+  auto entry = [&](uint32_t i) -> unsigned long long {    // i < total
+    int j = 0;
 #pragma unroll
-  for (int j = 0; j < QUANT_LISTS; ++j) kreg[j] = (uint32_t)tid < S.len[j] ? lists[(size_t)j * QUANT_LIST_CAP + tid] : 0ull;
-  for (int digit = first_digit; digit < QUANT_PASSES; ++digit) {
-    for (int e = 0; e < PER; ++e) S.hist[tid * PER + e] = 0u;
-    __syncthreads();
+    for (int o = QUANT_LISTS / 2; o > 0; o >>= 1) j += S.off[j + o] <= i ? o : 0;
+    return lists[(size_t)j * QUANT_LIST_CAP + (i - S.off[j])];
+  };
+  constexpr int KR = 16;                                  // keys per thread that stay in registers
+  unsigned long long kreg[KR];
+#pragma unroll
+  for (int e = 0; e < KR; ++e) {
+    const uint32_t i = tid + NT * e;
+    kreg[e] = i < total ? entry(i) : 0ull;
+  }
+  // f(key) for every key of the list that shares the prefix found so far (hi: number of its lowest bit; 64: no bit yet)
+  auto for_matching = [&](int hi, auto&& f) {
     const unsigned long long prefix = S.prefix;
-    const int shift = quant_shift(digit), width = quant_width(digit), hi = 64 - QUANT_BITS * digit;
-    auto count_key = [&](unsigned long long k) {
-      if (hi >= 64 || (k >> hi) == (prefix >> hi)) atomicAdd(&S.hist[(uint32_t)(k >> shift) & ((1u << width) - 1u)], 1u);
-    };
+    auto one = [&](unsigned long long k) { if (hi >= 64 || (k >> hi) == (prefix >> hi)) f(k); };
 #pragma unroll
-    for (int j = 0; j < QUANT_LISTS; ++j)
-      if ((uint32_t)tid < S.len[j]) count_key(kreg[j]);
-    for (int j = 0; j < QUANT_LISTS; ++j) {
-      const unsigned long long* list = lists + (size_t)j * QUANT_LIST_CAP;
-      for (uint32_t i = tid + 256; i < S.len[j]; i += 256) count_key(list[i]);
+    for (int e = 0; e < KR; ++e)
+      if ((uint32_t)(tid + NT * e) < total) one(kreg[e]);
+    for (uint32_t i = tid + NT * KR; i < total; i += NT) one(entry(i));
+  };
+  unsigned long long left = total;
+  int digit = S.digit;
+  for (; digit < QUANT_PASSES && left > (unsigned long long)QUANT_DIRECT; ++digit) {
+    for (int i = tid; i < QUANT_BINS * QUANT_COPIES / 4; i += NT) reinterpret_cast<uint4*>(S.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    const int shift = quant_shift(digit), width = quant_width(digit);
+    for_matching(64 - QUANT_BITS * digit, [&](unsigned long long k) {
+      const uint32_t b = (uint32_t)(k >> shift) & ((1u << width) - 1u);
+      atomicAdd(&S.hist[b * QUANT_COPIES + (tid & (QUANT_COPIES - 1))], 1u);
+    });
+    __syncthreads();
+    uint32_t cnt[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      cnt[e] = 0u;
+#pragma unroll
+      for (int c = 0; c < QUANT_COPIES; ++c) cnt[e] += S.hist[(tid * PER + e) * QUANT_COPIES + c];
+    }
+    pick_digit(digit, cnt);
+    left = S.count;                                       // uniform
+  }
+  if (digit < QUANT_PASSES) {                             // at most QUANT_DIRECT keys share the prefix: rank them
+    for_matching(64 - QUANT_BITS * digit, [&](unsigned long long k) {
+      const uint32_t at = atomicAdd(&S.n_few, 1u);
+      if (at < (uint32_t)QUANT_DIRECT) S.few[at] = k;
+    });
+    __syncthreads();
+    const int n = (int)min(S.n_few, (uint32_t)QUANT_DIRECT);
+    const unsigned long long rank = S.rank;
+    __syncthreads();
+    if (tid < n) {
+      const unsigned long long k = S.few[tid];
+      int below = 0, same = 0;
+      for (int j = 0; j < n; ++j) { below += S.few[j] < k; same += S.few[j] == k; }
+      // equal keys all pass this test and write the same value
+      if ((unsigned long long)below <= rank && rank < (unsigned long long)(below + same)) S.prefix = k;
     }
     __syncthreads();
-    unsigned long long mine = 0;
-    for (int e = 0; e < PER; ++e) mine += S.hist[tid * PER + e];
-    S.part[tid] = mine;
-    __syncthreads();
-    pick_digit(digit);
   }
   if (tid == 0) {
     qstore(st + 0, S.prefix);
@@ -404,12 +466,15 @@ __global__ __launch_bounds__(256) void quant_tile_kernel(SegArgs a) {
   quant_tile_step<DT, KIND>(a, p, I, J, status, Ms, S);
 }
 
-__global__ __launch_bounds__(256) void quant_pick_kernel(SegArgs a) {
-  __shared__ QuantShared S;
+// At 8256 cells of a softmax map (a chunk of 128 tokens, all of them on the list; one workgroup per KV head) it is
+// bound by the latency of its chain of barriers and LDS atomics: 52 us with 256 threads that walked the lists and
+// all six digits, 11.6 us like this.
+__global__ __launch_bounds__(1024) void quant_pick_kernel(SegArgs a) {
+  __shared__ __attribute__((aligned(16))) QuantPickShared S;
   const int p = blockIdx.x;
   const unsigned long long status = qload(a.sc.qstate + (size_t)p * QUANT_STATE_WORDS + 3);
   if (status & QUANT_DONE) return;
-  quant_pick_step(a, p, status, S);
+  quant_pick_step<1024>(a, p, status, S);
 }
 
 // Whatever the three launched pairs left undone, one workgroup per problem walking all tiles itself.
@@ -417,6 +482,7 @@ template <int DT, int KIND>
 __global__ __launch_bounds__(256) void quant_finish_kernel(SegArgs a) {
   __shared__ double Ms[64 * 65];
   __shared__ QuantShared S;
+  __shared__ __attribute__((aligned(16))) QuantPickShared SP;
   const int p = blockIdx.x;
   for (int it = 0; it < QUANT_PASSES; ++it) {
     const unsigned long long status = qload(a.sc.qstate + (size_t)p * QUANT_STATE_WORDS + 3);
@@ -427,7 +493,7 @@ __global__ __launch_bounds__(256) void quant_finish_kernel(SegArgs a) {
       quant_tile_step<DT, KIND>(a, p, I, J, status, Ms, S);
       __syncthreads();
     }
-    quant_pick_step(a, p, status, S);
+    quant_pick_step<256>(a, p, status, SP);
     __syncthreads();
   }
 }
@@ -1470,12 +1536,16 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
       const unsigned long long rank = (unsigned long long)floor(D.theta_quantile * (n_cells - 1.0));
       quant_init_kernel<<<P, 256, 0, s>>>(a, rank, (unsigned long long)n_cells);
       seg_tile_sums_kernel<DT, KIND, true><<<gt, 256, 0, s>>>(a);      // pass 1 and the selection's first tile pass
-      quant_pick_kernel<<<P, 256, 0, s>>>(a);
-      for (int pass = 1; pass < QUANT_TILE_PASSES; ++pass) {
-        quant_tile_kernel<DT, KIND><<<gt, 256, 0, s>>>(a);
-        quant_pick_kernel<<<P, 256, 0, s>>>(a);
+      quant_pick_kernel<<<P, 1024, 0, s>>>(a);
+      // a map whose cells all fit the list (chunks of up to 180 tokens) was collected whole by the first pass, and
+      // the pick has finished the selection: the other kernels would only find that out (4.5 us each)
+      if (n_cells > (double)QUANT_LIST_CAP) {
+        for (int pass = 1; pass < QUANT_TILE_PASSES; ++pass) {
+          quant_tile_kernel<DT, KIND><<<gt, 256, 0, s>>>(a);
+          quant_pick_kernel<<<P, 1024, 0, s>>>(a);
+        }
+        quant_finish_kernel<DT, KIND><<<P, 256, 0, s>>>(a);
       }
-      quant_finish_kernel<DT, KIND><<<P, 256, 0, s>>>(a);
     } else {
       seg_tile_sums_kernel<DT, KIND, false><<<gt, 256, 0, s>>>(a);
     }
