@@ -361,10 +361,17 @@ __device__ __forceinline__ void item_range(const Dims& D, const int32_t* sstart,
 // the token list and their lengths. Called by all 1024 threads of the block.
 constexpr int EMIT_CAP = 2048;     // selected spans whose tokens are written cooperatively
 
+// LDS of the list writer, which the selection before it uses as well (select_prefix; a barrier lies between the two).
+struct EmitShared {
+  __attribute__((aligned(16))) int a[EMIT_CAP];
+  int len[EMIT_CAP], off[EMIT_CAP];
+  int wcnt[16], wtok[16], base_cnt, base_tok;
+};
+
 __device__ __forceinline__ void emit_selection(const Dims& D, const DevState& st, int slot, const uint32_t* selmask,
-                               int n, int32_t* ids_out, int32_t* cnt_out) {
-  __shared__ int s_wcnt[16], s_wtok[16], s_base_cnt, s_base_tok;
-  __shared__ int e_a[EMIT_CAP], e_len[EMIT_CAP], e_off[EMIT_CAP];
+                               int n, int32_t* ids_out, int32_t* cnt_out, EmitShared& E) {
+  int (&s_wcnt)[16] = E.wcnt, (&s_wtok)[16] = E.wtok, &s_base_cnt = E.base_cnt, &s_base_tok = E.base_tok;
+  int (&e_a)[EMIT_CAP] = E.a, (&e_len)[EMIT_CAP] = E.len, (&e_off)[EMIT_CAP] = E.off;
   int32_t* meta = st.meta + (size_t)slot * META_WORDS;
   const int c0 = meta[META_CHUNK_START];
   const int ns = min(D.n_sink, c0), ws = max(ns, c0 - D.window);
@@ -530,6 +537,7 @@ __global__ __launch_bounds__(256) void select_rank_kernel(RetArgs a) {
 // KV head).
 __global__ __launch_bounds__(1024) void select_emit_kernel(RetArgs a) {
   __shared__ uint32_t selmask[SEL_MAX_SPANS / 32];
+  __shared__ EmitShared E;
   const Dims& D = a.D;
   const int p = blockIdx.x, bi = p / D.Hkv, h = p - bi * D.Hkv;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
@@ -547,7 +555,7 @@ __global__ __launch_bounds__(1024) void select_emit_kernel(RetArgs a) {
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out);
+  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
 }
 
 // ---- step 2 for a one-token chunk (decode) in one launch: one workgroup per (sequence, KV head) ----
@@ -653,6 +661,131 @@ __device__ __forceinline__ void select_sorted_prefix(const Dims& D, uint64_t* sk
   }
 }
 
+// The same rule without the sort (the order of the items is not left behind): item i is selected iff the eligible
+// items up to and including it in the order are at most k_max and their clipped tokens fit the budget, and both
+// sums are monotone in the order, so only the items near the limit need their exact place.
+// Up to SEL_DIRECT items: every item is compared with all others (1024 / npow lanes share an item).
+// More: the scores (in fp32, a monotone coarsening) are cut into 1024 equal pieces of their range, from the largest
+// down; counts and tokens of the pieces are scanned; pieces that fit whole are selected, the first that does not is
+// resolved by comparing its items with each other. Where that piece holds more than SEL_DIRECT items (most scores
+// are about equal) or a score is not finite in fp32, the items are sorted after all.
+// The sort is a chain of 28 (81 items) to 55 (604) dependent exchanges; the sort and the scan behind it took 5.0 and
+// 9.6 us of a one-token retrieve of one sequence and of 16, this takes 2.0 and 3.7 (launches 16.9 -> 13.9, 27.6 -> 21.7).
+// skey, sidx, clip, npow, selmask and wave_tot as above; n: items; E: LDS scratch. A barrier has to follow.
+constexpr int SEL_DIRECT = 256;
+constexpr int SEL_BINS = 1024;
+// Items ids[0..m) (ids NULL: items 0..m), m <= SEL_DIRECT, npow = rt1_pow2(m): cnt0 items with tok0 tokens come
+// before all of them.
+__device__ __forceinline__ void select_direct(const Dims& D, const uint64_t* skey, const int* clip, const int* ids, int m,
+                                              int npow, int cnt0, int tok0, uint32_t* selmask) {
+  const int parts = 1024 / npow, lp = __ffs(parts) - 1;
+  const int t = threadIdx.x >> lp, part = threadIdx.x & (parts - 1);
+  const int tc = min(t, m - 1), i = ids ? ids[tc] : tc;
+  const uint64_t ki = skey[i];
+  int cnt = 0, tok = 0;
+  for (int u = part; u < m; u += parts) {
+    const int j = ids ? ids[u] : u;
+    const uint64_t kj = skey[j];
+    const int cj = clip[j];
+    const bool upto = cj > 0 && (kj < ki || (kj == ki && j <= i));
+    cnt += upto ? 1 : 0;
+    tok += upto ? cj : 0;
+  }
+  for (int o = 1; o < parts; o <<= 1) { cnt += __shfl_xor(cnt, o, 64); tok += __shfl_xor(tok, o, 64); }
+  const bool sel = part == 0 && t < m && clip[i] > 0 && (D.k_max == 0 || cnt0 + cnt <= D.k_max) &&
+                   (D.budget == 0 || (long long)tok0 + tok <= D.budget);
+  if (sel) atomicOr(&selmask[i >> 5], 1u << (i & 31));
+}
+
+__device__ __forceinline__ float key_score_f32(uint64_t key) {           // the score of a score_key, rounded to fp32
+  const uint64_t up = ~key;
+  return (float)__longlong_as_double((long long)((up >> 63) ? (up & 0x7fffffffffffffffull) : ~up));
+}
+
+__device__ __forceinline__ void select_prefix(const Dims& D, uint64_t* skey, uint32_t* sidx, const int* clip, int n, int npow,
+                                              uint32_t* selmask, long long* wave_tot, EmitShared& E) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (n <= SEL_DIRECT) {
+    if (n > 0) select_direct(D, skey, clip, nullptr, n, npow, 0, 0, selmask);
+    return;
+  }
+  static_assert(sizeof(E.a) == SEL_BINS * sizeof(unsigned long long) && EMIT_CAP >= SEL_DIRECT, "LDS of the selection");
+  unsigned long long* bins = reinterpret_cast<unsigned long long*>(E.a);   // items << 32 | tokens of a piece
+  int* edge = E.len;                                                       // items of the piece that does not fit whole
+  int* edge_n = E.off, *edge_bin = E.off + 1, *edge_cnt = E.off + 2, *edge_tok = E.off + 3;
+  float* wmax = reinterpret_cast<float*>(E.off + 16), *wmin = reinterpret_cast<float*>(E.off + 32);
+  bins[tid] = 0ull;
+  if (tid == 0) { *edge_n = 0; *edge_bin = SEL_BINS; }
+  // range of the eligible scores; one that is not finite makes the range so
+  float hi = -INFINITY, lo = INFINITY;
+  for (int i = tid; i < n; i += SEL_BINS) {
+    if (clip[i] <= 0) continue;
+    const float v = key_score_f32(skey[i]);
+    const bool ok = fabsf(v) < INFINITY;                                   // false for NaN
+    hi = fmaxf(hi, ok ? v : INFINITY);
+    lo = fminf(lo, ok ? v : -INFINITY);
+  }
+  for (int o = 1; o < 64; o <<= 1) { hi = fmaxf(hi, __shfl_xor(hi, o, 64)); lo = fminf(lo, __shfl_xor(lo, o, 64)); }
+  if (lane == 0) { wmax[wave] = hi; wmin[wave] = lo; }
+  __syncthreads();
+  hi = wmax[lane & 15]; lo = wmin[lane & 15];
+  for (int o = 1; o < 16; o <<= 1) { hi = fmaxf(hi, __shfl_xor(hi, o, 64)); lo = fminf(lo, __shfl_xor(lo, o, 64)); }
+  if (hi < lo) return;                                                     // no eligible item (uniform)
+  const float range = hi - lo, scale = range > 0.f ? (float)(SEL_BINS - 1) / range : 0.f;
+  const bool sorted = !(range < INFINITY && scale < INFINITY);             // uniform, as hi and lo are
+  if (!sorted) {
+    for (int i = tid; i < n; i += SEL_BINS) {
+      const int c = clip[i];
+      if (c <= 0) continue;                                                // (its sidx is RT1_PAD)
+      const int b = min((int)((hi - key_score_f32(skey[i])) * scale), SEL_BINS - 1);
+      sidx[i] = (uint32_t)b;
+      atomicAdd(&bins[b], (1ull << 32) | (unsigned long long)(uint32_t)c);
+    }
+    __syncthreads();
+    const unsigned long long own = bins[tid];
+    unsigned long long incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) wave_tot[wave] = (long long)incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += (unsigned long long)wave_tot[w];
+    auto fits = [&](unsigned long long v) {
+      return (D.k_max == 0 || (int)(v >> 32) <= D.k_max) && (D.budget == 0 || (long long)(uint32_t)v <= D.budget);
+    };
+    // the first piece that does not fit whole: its predecessors' sum fits (one thread at most)
+    if (!fits(incl) && fits(incl - own)) {
+      *edge_bin = tid;
+      *edge_cnt = (int)((incl - own) >> 32);
+      *edge_tok = (int)(uint32_t)(incl - own);
+    }
+    __syncthreads();
+    const uint32_t eb = (uint32_t)*edge_bin;
+    for (int i = tid; i < n; i += SEL_BINS) {
+      const uint32_t b = sidx[i];
+      if (b < eb) {
+        atomicOr(&selmask[i >> 5], 1u << (i & 31));
+      } else if (b == eb) {
+        const int at = atomicAdd(edge_n, 1);
+        if (at < SEL_DIRECT) edge[at] = i;
+      }
+    }
+    __syncthreads();
+    const int m = *edge_n;
+    if (m == 0) return;
+    if (m <= SEL_DIRECT) {
+      select_direct(D, skey, clip, edge, m, rt1_pow2(m), *edge_cnt, *edge_tok, selmask);
+      return;
+    }
+    for (int w = tid; w < (n + 31) / 32 + 2; w += SEL_BINS) selmask[w] = 0u;
+    for (int i = tid; i < n; i += SEL_BINS) sidx[i] = clip[i] > 0 ? (uint32_t)i : RT1_PAD;
+    __syncthreads();
+  }
+  select_sorted_prefix(D, skey, sidx, clip, npow, selmask, wave_tot);
+}
+
 template <int DT>
 __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int bound) {
   typedef typename Elt<DT>::type T;
@@ -661,6 +794,7 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   __shared__ double qv[128];
   __shared__ uint32_t selmask[RT1_MAX_SPANS / 32 + 2];
   __shared__ long long wave_tot[16];
+  __shared__ EmitShared E;
   const Dims& D = a.D;
   const int p = blockIdx.x, bi = p / D.Hkv, h = p - bi * D.Hkv;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
@@ -776,11 +910,11 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
     }
   }
   __syncthreads();
-  select_sorted_prefix(D, skey, sidx, clip, npow, selmask, wave_tot);
+  select_prefix(D, skey, sidx, clip, n, npow, selmask, wave_tot, E);
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out);
+  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
 }
 
 // ---- step 2 of a long chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
@@ -799,6 +933,7 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   __shared__ uint32_t selmask[RT1_MAX_SPANS / 32 + 2];
   __shared__ long long wave_tot[16];
   __shared__ int s_last;
+  __shared__ EmitShared E;
   const Dims& D = a.D;
   const int pl = blockIdx.x, bi = a.batch_off + pl / D.Hkv, h = pl % D.Hkv, pg = bi * D.Hkv + h;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
@@ -894,11 +1029,11 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
     sidx[i] = c > 0 ? (uint32_t)i : RT1_PAD;
   }
   __syncthreads();
-  select_sorted_prefix(D, skey, sidx, clip, npow, selmask, wave_tot);
+  select_prefix(D, skey, sidx, clip, n, npow, selmask, wave_tot, E);
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)pg * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + pg : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out);
+  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
 }
 
 // ---- retrieval by memory units (Eq. 9 as written): a unit scores the maximum over its spans; the
@@ -908,6 +1043,7 @@ __global__ __launch_bounds__(1024) void unit_select_kernel(RetArgs a, int unit_b
   extern __shared__ __attribute__((aligned(16))) unsigned char rt1_lds[];
   __shared__ uint32_t selmask[RT1_MAX_SPANS / 32 + 2];
   __shared__ long long wave_tot[16];
+  __shared__ EmitShared E;
   const Dims& D = a.D;
   const int p = blockIdx.x, bi = p / D.Hkv, h = p - bi * D.Hkv;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
@@ -941,11 +1077,11 @@ __global__ __launch_bounds__(1024) void unit_select_kernel(RetArgs a, int unit_b
     sidx[u] = c > 0 ? (uint32_t)u : RT1_PAD;
   }
   __syncthreads();
-  select_sorted_prefix(D, skey, sidx, clip, npow, selmask, wave_tot);
+  select_prefix(D, skey, sidx, clip, n, npow, selmask, wave_tot, E);
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out);
+  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
 }
 
 // ---- collaborative voting over memory units (Sec. 3.5): the layer selects on its own, then the
@@ -960,6 +1096,7 @@ __global__ __launch_bounds__(1024) void unit_vote_select_kernel(RetArgs a, int u
   extern __shared__ __attribute__((aligned(16))) unsigned char rt1_lds[];
   __shared__ uint32_t selmask[RT1_MAX_SPANS / 32 + 2], ownmask[RT1_MAX_SPANS / 32 + 2];
   __shared__ long long wave_tot[16];
+  __shared__ EmitShared E;
   const Dims& D = a.D;
   const int p = blockIdx.x, bi = p / D.Hkv, h = p - bi * D.Hkv;
   const int seq = a.bp.seq[bi];
@@ -1026,7 +1163,7 @@ __global__ __launch_bounds__(1024) void unit_vote_select_kernel(RetArgs a, int u
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out);
+  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
 }
 
 // ---- caller-forced selection: ids already copied (ascending, unique) into sel_ids ----
@@ -1034,6 +1171,7 @@ struct ForceArgs { Dims D; DevState st; int layer, seq, h, n_ids; };
 
 __global__ __launch_bounds__(1024) void force_list_kernel(ForceArgs a) {
   __shared__ uint32_t selmask[SEL_MAX_SPANS / 32];
+  __shared__ EmitShared E;
   const Dims& D = a.D;
   const int slot = slot_of(D, a.layer, a.seq, a.h);
   const int32_t* meta = a.st.meta + (size_t)slot * META_WORDS;
@@ -1054,7 +1192,7 @@ __global__ __launch_bounds__(1024) void force_list_kernel(ForceArgs a) {
     }
   }
   __syncthreads();
-  emit_selection(D, a.st, slot, selmask, n, nullptr, nullptr);
+  emit_selection(D, a.st, slot, selmask, n, nullptr, nullptr, E);
 }
 
 bool retrieve_is_one_launch(const Dims& D, int n_q, int span_bound) {
@@ -1199,6 +1337,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
 //      token list is rebuilt for the slot's current chunk (the window has moved on) ----
 __global__ __launch_bounds__(1024) void persist_list_kernel(RetArgs a) {
   __shared__ uint32_t selmask[SEL_MAX_SPANS / 32];
+  __shared__ EmitShared E;
   const Dims& D = a.D;
   const int p = blockIdx.x, bi = p / D.Hkv, h = p - bi * D.Hkv;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
@@ -1221,7 +1360,7 @@ __global__ __launch_bounds__(1024) void persist_list_kernel(RetArgs a) {
     }
   }
   __syncthreads();
-  emit_selection(D, a.st, slot, selmask, n, nullptr, nullptr);
+  emit_selection(D, a.st, slot, selmask, n, nullptr, nullptr, E);
 }
 
 hipError_t launch_persist_list(const Dims& D, const DevState& st, int layer, const BatchPos& bp, int seq_count,
