@@ -173,10 +173,9 @@ __global__ __launch_bounds__(1024) void qrep_partial_kernel(RetArgs a) {
 
 // ---- long chunks, mean representatives: the running sums as a launch of their own (when the segmentation's
 //      first launch has not taken them along) ----
-template <int DT>
 __global__ __launch_bounds__(1024) void running_sums_kernel(RetArgs a) {
-  __shared__ double wt[16 * 16 * 8];
-  running_sums_block<DT, 16>(a.D, a.bp, a.layer, a.batch_off, a.rs, blockIdx.x, blockIdx.y, wt);
+  __shared__ __attribute__((aligned(16))) double wt[16 * 128];
+  running_sums_block(a.D, a.bp, a.layer, a.batch_off, a.rs, blockIdx.x, blockIdx.y, wt);
 }
 
 template <int DT>
@@ -1280,7 +1279,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
       a.qrep_by_last = one_tail;
       a.ticket_base = sc_max_problems;                      // the second half of the counters
       if (from_sums) {
-        if (!sums_ready) running_sums_kernel<LTRI_BF16><<<dim3(running_sums_blocks(a.rs, 16), cnt * D.Hkv), 1024, 0, s>>>(a);
+        if (!sums_ready) running_sums_kernel<<<dim3(running_sums_blocks(a.rs), cnt * D.Hkv), 1024, 0, s>>>(a);
         a.qrep_from_sums = 1;
       } else {
         if (bf) qrep_partial_kernel<LTRI_BF16><<<gp, 1024, 0, s>>>(a);

@@ -4,7 +4,7 @@
 // span boundaries, so they are taken while, or before, the chunk is segmented.
 // Layout: out[problem][token][128] (fp64, `rows` rows per problem) holds, for token t, the sum of the rows of the
 // tokens of t's block of RUNSUM_BLOCK tokens up to and including t; the reader adds the last rows of the earlier
-// blocks. The key rows' sums follow `keys_off` elements behind the query rows'. head_dim 128 only. Sums of bf16
+// blocks. The key rows' sums follow `keys_off` elements behind the query rows'. bf16 rows, head_dim 128 only. Sums of bf16
 // values in fp64 are exact while the values of a column span less than 2^30 in magnitude over the chunk (8 bits
 // each, 13 for the row count, 53 in all), so the result does not depend on the order of the additions and a
 // difference of two running sums is the sum over the rows between them.
@@ -15,107 +15,83 @@ namespace ltri {
 
 constexpr int RUNSUM_BLOCK = 128;
 
-// Workgroups per problem that running_sums_block<DT, CG> is to be called by: one per block of query rows and
-// column slab, one per two blocks of key rows (a key block is a quarter of the rows of a query block of the
-// paper's model) and column slab.
-__host__ __device__ inline int running_sums_blocks(const RunSums& r, int cg) {
+// Workgroups per problem that running_sums_block is to be called by: one per block of query rows, one per two blocks of
+// key rows (a key block is a quarter of the rows of a query block of the paper's model).
+__host__ __device__ inline int running_sums_blocks(const RunSums& r) {
   const int nblk = (r.n_q + RUNSUM_BLOCK - 1) / RUNSUM_BLOCK;
-  return (nblk + (r.k_arena ? (nblk + 1) / 2 : 0)) * (16 / cg);
+  return nblk + (r.k_arena ? (nblk + 1) / 2 : 0);
 }
 
-// One block of tokens (query or key rows) and CG of the 16 groups of 8 columns, for problem p = (sequence
-// batch_off + p / Hkv, KV head p % Hkv). Called by all 64 * CG threads of a workgroup (CG = 4 or 16); wt: LDS,
-// CG x CG x 8 doubles. A thread takes two tokens and 8 columns, the lanes of a wavefront CG column groups and
-// 64 / CG pairs of tokens, so that every row is read in pieces of CG * 16 bytes.
-template <int DT, int CG>
+// One block of tokens (query or key rows) for problem p = (sequence batch_off + p / Hkv, KV head p % Hkv). Called by all
+// 1024 threads of a workgroup; wt: LDS, 16 x 128 doubles. A wavefront takes 8 tokens and a lane two columns of them, so
+// that the running sums of a lane's tokens need no exchange, a row is read in one piece and a token's sums are written
+// in one piece; the 16 wavefronts meet once, over the totals of their tokens. A chunk of 1024 tokens (96 workgroups on
+// an otherwise idle chip, 10 MB in and 16 MB out) is bound by the latency of a workgroup. With 8 columns and two tokens
+// per lane, whose sums went through 48 lane exchanges and left in 16-byte pieces 64 bytes apart, it took 12 us and the
+// launch it rides in 19.4; now that launch takes 13.5 (700 tokens: 18.1 and 10.4) and its selections bound it.
 __device__ __forceinline__ void running_sums_one(const Dims& D, const BatchPos& bp, int layer, int batch_off,
-                                                 const RunSums& r, int blk, int slab, bool keys, int p, double* wt) {
-  typedef typename Elt<DT>::type T;
-  constexpr int N = 16 / (int)sizeof(T);                // elements per 16-byte piece
-  constexpr int NP = 8 / N;                             // pieces per 8 columns
-  const int d = 128, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cgl = tid % CG, tp = tid / CG;              // column group inside the slab, pair of tokens
-  const int col = (slab * CG + cgl) * 8;
+                                                 const RunSums& r, int blk, bool keys, int p, double* wt) {
+  constexpr int TOK = RUNSUM_BLOCK / 16;                // tokens per wavefront
+  const int d = 128, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = 2 * lane;
   const int bi = batch_off + p / D.Hkv, h = p % D.Hkv;
   const int inner = keys ? 1 : D.G;                     // rows per token
   const size_t tok_stride = keys ? (size_t)d : (size_t)D.Hq * d;
-  const T* base;
+  const uint16_t* base;
   if (keys) {
     const int c0 = bp.c0[bi];
-    base = reinterpret_cast<const T*>(r.k_arena) + arena_off(D, slot_of(D, layer, bp.seq[bi], h)) +
+    base = reinterpret_cast<const uint16_t*>(r.k_arena) + arena_off(D, slot_of(D, layer, bp.seq[bi], h)) +
            (size_t)chunk_tok_row(D, c0, c0) * d + col;
   } else {
-    base = reinterpret_cast<const T*>(r.q) + (size_t)bi * r.n_q * D.Hq * d + (size_t)h * D.G * d + col;
+    base = reinterpret_cast<const uint16_t*>(r.q) + (size_t)bi * r.n_q * D.Hq * d + (size_t)h * D.G * d + col;
   }
-  double* out = r.out + (keys ? r.keys_off : (size_t)0) + (size_t)p * r.rows * d + col;
-  const int t0 = blk * RUNSUM_BLOCK + 2 * tp;
-  const bool ok0 = t0 < r.n_q, ok1 = t0 + 1 < r.n_q;
-  const T* r0 = base + (size_t)min(t0, r.n_q - 1) * tok_stride;
-  const T* r1 = base + (size_t)min(t0 + 1, r.n_q - 1) * tok_stride;
-  double acc0[8], acc1[8];
+  const int t0 = blk * RUNSUM_BLOCK + TOK * wave;
+  double x[TOK], y[TOK];                                // sums of a token's rows, then running sums over the tokens
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc0[e] = acc1[e] = 0.0;
-#pragma unroll 4
-  for (int g = 0; g < inner; ++g) {
-    uint4 v0[NP], v1[NP];
+  for (int t = 0; t < TOK; ++t) x[t] = y[t] = 0.0;
+  for (int g0 = 0; g0 < inner; g0 += 4) {               // 4 rows of 8 tokens in flight
+    uint32_t v[4][TOK];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
-      v0[q] = reinterpret_cast<const uint4*>(r0 + (size_t)g * d)[q];
-      v1[q] = reinterpret_cast<const uint4*>(r1 + (size_t)g * d)[q];
+    for (int g = 0; g < 4; ++g) {
+      if (g0 + g >= inner) break;                       // uniform
+#pragma unroll
+      for (int t = 0; t < TOK; ++t)
+        v[g][t] = *reinterpret_cast<const uint32_t*>(base + (size_t)min(t0 + t, r.n_q - 1) * tok_stride + (size_t)(g0 + g) * d);
     }
-    const T* e0 = reinterpret_cast<const T*>(v0);
-    const T* e1 = reinterpret_cast<const T*>(v1);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      acc0[e] += Elt<DT>::to_f64(e0[e]);
-      acc1[e] += Elt<DT>::to_f64(e1[e]);
+    for (int g = 0; g < 4; ++g) {
+      if (g0 + g >= inner) break;
+#pragma unroll
+      for (int t = 0; t < TOK; ++t) {
+        x[t] += (double)__uint_as_float(v[g][t] << 16);
+        y[t] += (double)__uint_as_float(v[g][t] & 0xffff0000u);
+      }
     }
   }
-  double ex[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    acc0[e] = ok0 ? acc0[e] : 0.0;
-    acc1[e] = acc0[e] + (ok1 ? acc1[e] : 0.0);          // the pair's total
-    // running sum over the wavefront's pairs of tokens (lanes CG apart)
-    double v = acc1[e];
-#pragma unroll
-    for (int o = CG; o < 64; o <<= 1) {
-      const double u = __shfl_up(v, o, 64);
-      if (lane >= o) v += u;
-    }
-    const double u = __shfl_up(v, CG, 64);
-    ex[e] = lane >= CG ? u : 0.0;
-    if (lane >= 64 - CG) wt[(wave * CG + cgl) * 8 + e] = v;
-  }
+  for (int t = 1; t < TOK; ++t) { x[t] += x[t - 1]; y[t] += y[t - 1]; }   // (tokens past the chunk come last and are not written)
+  *reinterpret_cast<double2*>(wt + wave * d + col) = make_double2(x[TOK - 1], y[TOK - 1]);
   __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    double c0 = ex[e], c1 = ex[e + 1];
-    for (int ww = 0; ww < wave; ++ww) {                 // CG wavefronts in all
-      c0 += wt[(ww * CG + cgl) * 8 + e];
-      c1 += wt[(ww * CG + cgl) * 8 + e + 1];
-    }
-    if (ok0) *reinterpret_cast<double2*>(out + (size_t)t0 * d + e) = make_double2(c0 + acc0[e], c1 + acc0[e + 1]);
-    if (ok1) *reinterpret_cast<double2*>(out + (size_t)(t0 + 1) * d + e) = make_double2(c0 + acc1[e], c1 + acc1[e + 1]);
+  double cx = 0.0, cy = 0.0;
+  for (int w = 0; w < wave; ++w) {
+    const double2 u = *reinterpret_cast<const double2*>(wt + w * d + col);
+    cx += u.x;
+    cy += u.y;
   }
+  double* out = r.out + (keys ? r.keys_off : (size_t)0) + ((size_t)p * r.rows + t0) * d + col;
+#pragma unroll
+  for (int t = 0; t < TOK; ++t)
+    if (t0 + t < r.n_q) *reinterpret_cast<double2*>(out + (size_t)t * d) = make_double2(cx + x[t], cy + y[t]);
 }
 
 // Workgroup `w` (0 .. running_sums_blocks - 1) of problem p.
-template <int DT, int CG>
 __device__ __forceinline__ void running_sums_block(const Dims& D, const BatchPos& bp, int layer, int batch_off,
                                                    const RunSums& r, int w, int p, double* wt) {
-  constexpr int SLABS = 16 / CG;                        // workgroups that share a block's columns
   const int nblk = (r.n_q + RUNSUM_BLOCK - 1) / RUNSUM_BLOCK;
-  const int slab = w % SLABS, wb = w / SLABS;
-  if (wb < nblk) {
-    running_sums_one<DT, CG>(D, bp, layer, batch_off, r, wb, slab, false, p, wt);
-    return;
-  }
-  const int b0 = 2 * (wb - nblk);
-  running_sums_one<DT, CG>(D, bp, layer, batch_off, r, b0, slab, true, p, wt);
-  if (b0 + 1 < nblk) {                                  // uniform over the workgroup
-    __syncthreads();                                    // wt is written again
-    running_sums_one<DT, CG>(D, bp, layer, batch_off, r, b0 + 1, slab, true, p, wt);
+  const bool keys = w >= nblk;
+  const int b0 = keys ? 2 * (w - nblk) : w, b1 = keys ? min(b0 + 2, nblk) : w + 1;
+  for (int b = b0; b < b1; ++b) {                       // uniform over the workgroup
+    if (b > b0) __syncthreads();                        // wt is written again
+    running_sums_one(D, bp, layer, batch_off, r, b, keys, p, wt);
   }
 }
 

@@ -798,9 +798,8 @@ __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
     // Not a selection: running sums of the chunk's query and key rows (bf16, head_dim 128), which step 2 reads once
     // the spans are known. They need nothing of the segmentation, and this launch leaves all but a few compute
     // units idle, so they ride along here (gridDim.y - 1 workgroups per problem, dispatched after the selections).
-    static_assert(sizeof(kept) >= 16 * 16 * 8 * sizeof(double), "staging of the running sums");
-    running_sums_block<LTRI_BF16, 16>(a.D, a.bp, a.layer, a.batch_off, a.rs, (int)blockIdx.y - 1, blockIdx.x,
-                                      reinterpret_cast<double*>(kept));
+    static_assert(sizeof(kept) >= 16 * 128 * sizeof(double), "staging of the running sums");
+    running_sums_block(a.D, a.bp, a.layer, a.batch_off, a.rs, (int)blockIdx.y - 1, blockIdx.x, reinterpret_cast<double*>(kept));
     return;
   }
   __shared__ uint64_t s_w1[2][16];
@@ -1517,7 +1516,7 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
   if (sums) {
     if (D.d != 128 || D.dtype != LTRI_BF16 || sums->n_q != n_new) return hipErrorInvalidValue;
     a.rs = *sums;
-    a.sum_wgs = running_sums_blocks(a.rs, 16);
+    a.sum_wgs = running_sums_blocks(a.rs);
   }
   const int P = seq_count * D.Hkv;
   const bool bf = D.dtype == LTRI_BF16;

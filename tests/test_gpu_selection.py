@@ -1,4 +1,5 @@
-"""Which spans step 2 selects, at the span counts where its kernels change method. Keys and queries are whole multiples of powers of two, so every score is exact and ties are real ties."""
+"""Which spans step 2 selects, at the span counts where its kernels change method. Keys and queries are whole multiples
+of powers of two, so every score is exact and ties are real ties."""
 import numpy as np
 import pytest
 import torch
