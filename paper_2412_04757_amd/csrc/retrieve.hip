@@ -790,7 +790,7 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   typedef typename Elt<DT>::type T;
   constexpr int N = 16 / (int)sizeof(T);                // elements per 16-byte piece
   extern __shared__ __attribute__((aligned(16))) unsigned char rt1_lds[];
-  __shared__ double qv[128];
+  __shared__ __attribute__((aligned(16))) float qv[128];           // Q^R: values of the element type
   __shared__ uint32_t selmask[RT1_MAX_SPANS / 32 + 2];
   __shared__ long long wave_tot[16];
   __shared__ EmitShared E;
@@ -840,13 +840,13 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   const int32_t* sstart = a.st.span_start + (size_t)slot * D.max_spans;
   const int32_t* slen = a.st.span_len + (size_t)slot * D.max_spans;
   constexpr int PPL = 128 / N / 4;                      // 16-byte pieces per lane (d = 128)
-  constexpr int PASSES = DT == LTRI_BF16 ? 3 : 1;       // spans per thread whose loads are in flight together
+  constexpr int PASSES = DT == LTRI_BF16 ? 2 : 1;       // spans per thread whose loads are in flight together (3 spill)
   const int part = tid & 3;
   uint4 kv[PASSES][PPL];
   int ss[PASSES], sl[PASSES];                           // the spans' extents travel with their keys
-  auto load_batch = [&](int i00) {
+  auto load_batch = [&](auto uc, int i00) {
 #pragma unroll
-    for (int u = 0; u < PASSES; ++u) {
+    for (int u = 0; u < decltype(uc)::value; ++u) {
       const int ic = max(min(i00 + 256 * u + (tid >> 2), n - 1), 0);
       const uint4* krow = reinterpret_cast<const uint4*>(krep + (size_t)ic * d);
 #pragma unroll
@@ -855,7 +855,10 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
       sl[u] = slen[ic];
     }
   };
-  load_batch(0);                                        // in flight while the query row is fetched
+  // up to 256 spans go by one span per thread, more by PASSES of them
+  using One = std::integral_constant<int, 1>;
+  using All = std::integral_constant<int, PASSES>;
+  if (n <= 256) load_batch(One{}, 0); else load_batch(All{}, 0);      // in flight while the query row is fetched
   // Q^R of the chunk's one span
   if (tid < d) {
     const T* Qb = reinterpret_cast<const T*>(a.q) + (size_t)bi * D.Hq * d + (size_t)h * D.G * d;
@@ -863,49 +866,59 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
     for (int g = 0; g < D.G; ++g) sum += Elt<DT>::to_f64(Qb[(size_t)g * d + tid]);
     const T r = Elt<DT>::from_f64(sum);
     reinterpret_cast<T*>(a.sc.qrep)[(size_t)p * a.Lp * d + tid] = r;
-    qv[tid] = Elt<DT>::to_f64(r);
+    qv[tid] = Elt<DT>::to_f32(r);
   }
   for (int w = tid; w < (n + 31) / 32 + 2; w += blockDim.x) selmask[w] = 0u;
+  for (int i = n + tid; i < npow; i += blockDim.x) { skey[i] = ~0ull; sidx[i] = RT1_PAD; }
   __syncthreads();
-  for (int i00 = 0; i00 < npow; i00 += 256 * PASSES) {
-    if (i00 > 0) load_batch(i00);
+  auto score_batch = [&](auto uc, int i00) {
+    constexpr int U = decltype(uc)::value;
+    // the query's elements are read from LDS once for all spans of the thread (when every span had its own reads, in
+    // fp64, they bounded this loop: launch over 81 spans 13.9 us, now 12.2; 604 spans, 16 sequences 21.7 and 21.1)
+    double accs[U];
 #pragma unroll
-    for (int u = 0; u < PASSES; ++u) {
-      const int i = i00 + 256 * u + (tid >> 2);
-      double acc = 0.0;
+    for (int u = 0; u < U; ++u) accs[u] = 0.0;
 #pragma unroll
-      for (int q = 0; q < PPL; ++q) {
-        const int pc = part + 4 * q;
-        double k[8];
-        if constexpr (DT == LTRI_BF16) {
-          const uint32_t w[4] = {kv[u][q].x, kv[u][q].y, kv[u][q].z, kv[u][q].w};
+    for (int q = 0; q < PPL; ++q) {
+      const int pc = part + 4 * q;
+      float qf[N];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            k[2 * e] = (double)__uint_as_float(w[e] << 16);
-            k[2 * e + 1] = (double)__uint_as_float(w[e] & 0xffff0000u);
-          }
-        } else {
-          k[0] = (double)__uint_as_float(kv[u][q].x); k[1] = (double)__uint_as_float(kv[u][q].y);
-          k[2] = (double)__uint_as_float(kv[u][q].z); k[3] = (double)__uint_as_float(kv[u][q].w);
+      for (int e = 0; e < N; e += 4) *reinterpret_cast<float4*>(qf + e) = *reinterpret_cast<const float4*>(qv + pc * N + e);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t w[4] = {kv[u][q].x, kv[u][q].y, kv[u][q].z, kv[u][q].w};
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          const uint32_t b = DT == LTRI_BF16 ? ((e & 1) ? (w[e / 2] & 0xffff0000u) : (w[e / 2] << 16)) : w[e & 3];
+          accs[u] = fma((double)__uint_as_float(b), (double)qf[e], accs[u]);
         }
-#pragma unroll
-        for (int e = 0; e < N; ++e) acc = fma(k[e], qv[pc * N + e], acc);
       }
+      __builtin_amdgcn_sched_barrier(0);                  // (conversions of later pieces moved up here spill registers)
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i00 + 256 * u + (tid >> 2);
+      double acc = accs[u];
       acc += __shfl_xor(acc, 1, 64);
       acc += __shfl_xor(acc, 2, 64);
-      if (part == 0 && i < npow) {
-        int c = 0;
-        if (i < n) {
-          int lo, hi;
-          clip_span(D, c0, ss[u], sl[u], lo, hi);
-          c = max(hi - lo, 0);
-          scores[i] = acc;
-          clip[i] = c;
-        }
+      if (part == 0 && i < n) {
+        int lo, hi;
+        clip_span(D, c0, ss[u], sl[u], lo, hi);
+        const int c = max(hi - lo, 0);
+        scores[i] = acc;
+        clip[i] = c;
         // spans that cannot be retrieved go to the end of the order with the padding
         skey[i] = c > 0 ? score_key(acc) : ~0ull;
         sidx[i] = c > 0 ? (uint32_t)i : RT1_PAD;
       }
+    }
+  };
+  if (n <= 256) {
+    score_batch(One{}, 0);
+  } else {
+    for (int i00 = 0; i00 < n; i00 += 256 * PASSES) {
+      if (i00 > 0) load_batch(All{}, i00);
+      score_batch(All{}, i00);
     }
   }
   __syncthreads();
@@ -918,8 +931,8 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
 
 // ---- step 2 of a long chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
 //      in Eq. 9), the budgeted selection by sorting and the lists. gridDim.x = (sequence, KV head) problems;
-//      the gridDim.y workgroups of a problem share its scoring, 256 spans at a time each, so that the stored vectors
-//      stream in through many compute units, and the one that finishes last (a ticket counter, left at zero again)
+//      the gridDim.y workgroups of a problem share its scoring in tiles of 16 spans, so that the stored vectors
+//      stream in and are multiplied on many compute units, and the one that finishes last (a ticket counter, left at zero again)
 //      sorts and writes the lists. Q^R is either in place (qrep_partial_kernel) or, with qrep_from_sums, built
 //      here from the running sums of the chunk's query rows, two rows per query span, and so are, with rs.k_arena, the
 //      mean keys of the chunk's own spans (Sec. 3.3.1): every workgroup of a problem writes the same values to
@@ -944,7 +957,7 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   const int32_t* slen = a.st.span_len + (size_t)slot * D.max_spans;
   T* qrep = reinterpret_cast<T*>(a.sc.qrep) + (size_t)pg * a.Lp * d;
   T* krep_w = reinterpret_cast<T*>(a.st.krep) + (size_t)slot * D.max_spans * d;
-  if (a.qrep_from_sums && 256 * (int)blockIdx.y < n) {      // (a workgroup without spans to score needs none of it)
+  if (a.qrep_from_sums && 16 * (int)blockIdx.y < n) {      // (a workgroup without spans to score needs none of it)
     // representative = (running sum at the span's end - running sum at its start) / length, rounded to the dtype
     const int n_q = a.rs.n_q, nblk = (n_q + RUNSUM_BLOCK - 1) / RUNSUM_BLOCK;
     double* carry = reinterpret_cast<double*>(rt1_lds);   // [2][blocks][128]: sum of the rows of all earlier blocks
@@ -989,7 +1002,9 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   const int n_score = (int)gridDim.y;
   const T* krep = reinterpret_cast<const T*>(a.st.krep) + (size_t)slot * D.max_spans * d;
   double* scores = a.st.scores + (size_t)slot * D.max_spans;
-  for (int i0 = 256 * (int)blockIdx.y + 16 * wave; i0 < n; i0 += 256 * n_score) {   // a tile of 16 spans per wavefront
+  // a tile of 16 spans per wavefront, dealt out over the workgroups first: a compute unit takes 0.9 us of fp64 matrix
+  // products per tile and SIMD, so the tiles of a problem belong on as many of them as there are workgroups
+  for (int i0 = 16 * (wave * n_score + (int)blockIdx.y); i0 < n; i0 += 256 * n_score) {
     double best[4];
     score_tile_f64<DT>(krep, n, i0, qrep, nqs, d, best);
     if ((lane & 15) == 0) {
@@ -1286,7 +1301,10 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
         else    qrep_partial_kernel<LTRI_F32><<<gp, 1024, 0, s>>>(a);
       }
       if (one_tail) {
-        const dim3 gt(cnt * D.Hkv, (span_bound + 255) / 256);
+        // one workgroup per 128 spans that there can be: the bound is about twice the spans there are, so that is about
+        // one tile per SIMD (with 256 spans per workgroup, held together, a launch over 100 to 300 spans took 18.7 us,
+        // now 16.6)
+        const dim3 gt(cnt * D.Hkv, (span_bound + 127) / 128);
         if (bf) retrieve_chunk_kernel<LTRI_BF16><<<gt, 1024, lds, s>>>(a, span_bound);
         else    retrieve_chunk_kernel<LTRI_F32><<<gt, 1024, lds, s>>>(a, span_bound);
       } else {
