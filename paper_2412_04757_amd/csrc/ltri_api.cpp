@@ -347,11 +347,13 @@ static int32_t check_range(ltri_ctx* c, int layer, int seq_begin, int seq_count)
 static size_t ls_index(const ltri_ctx* c, int layer, int seq) { return (size_t)layer * c->D.n_seqs + seq; }
 
 // Host-offloaded KV: once a selection's token list is written, the rows of its retrieved tokens are fetched from
-// the host arenas into the device pool, on the context's stream, before anything attends.
-static int32_t fetch_retrieved(ltri_ctx* c, int layer, const BatchPos& bp, int seq_count, hipStream_t s = nullptr) {
+// the host arenas into the device pool, on the context's stream, before anything attends. k_chunk / v_chunk (or NULL):
+// rows of the chunk at bp that the append has not written to the host arenas and this launch does.
+static int32_t fetch_retrieved(ltri_ctx* c, int layer, const BatchPos& bp, int seq_count, hipStream_t s = nullptr,
+                               const void* k_chunk = nullptr, const void* v_chunk = nullptr, int n_new = 0) {
   if (!c->D.offload || c->dry) return LTRI_OK;
   return check_hip(c, launch_fetch_retrieved(c->D, c->ds, c->k_arena, c->v_arena, c->k_host, c->v_host, layer, bp,
-                                             seq_count, s ? s : c->stream), "fetch retrieved rows");
+                                             seq_count, k_chunk, v_chunk, n_new, s ? s : c->stream), "fetch retrieved rows");
 }
 
 extern "C" {
@@ -373,8 +375,9 @@ int32_t ltri_reset(ltri_ctx* c, int32_t seq) {
   return LTRI_OK;
 }
 
+// host_rows_later: the caller has the chunk's rows written to the host arenas itself (host-offloaded KV).
 static int32_t append_common(ltri_ctx* c, int layer, int seq_begin, int seq_count, const void* k_chunk,
-                             const void* v_chunk, int n_new, BatchPos& bp) {
+                             const void* v_chunk, int n_new, BatchPos& bp, bool host_rows_later = false) {
   int32_t r = check_range(c, layer, seq_begin, seq_count);
   if (r != LTRI_OK) return r;
   if (n_new < 1 || n_new > c->D.chunk_max)
@@ -393,7 +396,8 @@ static int32_t append_common(ltri_ctx* c, int layer, int seq_begin, int seq_coun
   }
   if (k_chunk && !c->dry) {
     r = check_hip(c, launch_copy_chunk(c->D, c->k_arena, c->v_arena, k_chunk, v_chunk, layer, bp, seq_count,
-                                       n_new, c->k_host, c->v_host, c->stream), "copy chunk");
+                                       n_new, host_rows_later ? nullptr : c->k_host, host_rows_later ? nullptr : c->v_host,
+                                       c->stream), "copy chunk");
     if (r != LTRI_OK) return r;
   }
   return LTRI_OK;
@@ -533,10 +537,11 @@ static int32_t check_query_chunk(ltri_ctx* c, int layer, int seq_begin, int seq_
 }
 
 // fork and fetch_stream (both or neither; host-offloaded KV): the fetch of the retrieved rows is queued on that
-// stream behind the event, which is recorded behind the kernels of step 2.
+// stream behind the event, which is recorded behind the kernels of step 2. k_chunk / v_chunk: as in fetch_retrieved.
 static int32_t retrieve_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_count, const void* q,
                              int32_t n_q, int32_t* sel_ids, int32_t* sel_cnt, bool store_rep_keys,
-                             bool sums_ready = false, hipEvent_t fork = nullptr, hipStream_t fetch_stream = nullptr) {
+                             bool sums_ready = false, hipEvent_t fork = nullptr, hipStream_t fetch_stream = nullptr,
+                             const void* k_chunk = nullptr, const void* v_chunk = nullptr) {
   BatchPos bp;
   memset(&bp, 0, sizeof bp);
   int32_t r = check_query_chunk(c, layer, seq_begin, seq_count, q, n_q, bp);
@@ -553,7 +558,7 @@ static int32_t retrieve_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int3
       if (r == LTRI_OK) r = check_hip(c, hipStreamWaitEvent(fetch_stream, fork, 0), "fork");
       if (r != LTRI_OK) return r;
     }
-    r = fetch_retrieved(c, layer, bp, seq_count, fetch_stream);
+    r = fetch_retrieved(c, layer, bp, seq_count, fetch_stream, k_chunk, v_chunk, n_q);
     if (r != LTRI_OK) return r;
   }
   for (int s = 0; s < seq_count; ++s) {
@@ -828,7 +833,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   }
   BatchPos bp;
   memset(&bp, 0, sizeof bp);
-  int32_t r = append_common(c, layer, seq_begin, seq_count, k_chunk, v_chunk, n_new, bp);
+  int32_t r = append_common(c, layer, seq_begin, seq_count, k_chunk, v_chunk, n_new, bp, c->D.offload != 0);
   if (r != LTRI_OK) return r;
   const bool keys_with_step2 = retrieve_stores_rep_keys(c->D, n_new);
   StepTiming timing(c);
@@ -860,7 +865,8 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   // fills the host link, a launch on another stream starts 100-200 us late. Measured alternatives: beside the small
   // kernels of steps 1 and 2 the first part holds every compute unit's LDS and step 2's last launch waits for it to
   // end; and the chunk's rows written out to the host beside step 1, by a kernel of any size or by copies, slow
-  // step 1's kernels by as much as the overlap gains: 21 -> 140 us for the first tile kernel.)
+  // step 1's kernels by as much as the overlap gains: 21 -> 140 us for the first tile kernel. So they go out with the
+  // fetch, in the link's other direction.)
   float* lse_a = c->dc.att_lse2;
   bool side_queued = false;
   auto both_streams = [&]() -> int32_t {
@@ -871,8 +877,12 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     append_commit(c, layer, seq_begin, seq_count, n_new);
     side_queued = true;                  // (from here on the second stream may hold work of this step)
     e = retrieve_impl(c, layer, seq_begin, seq_count, q, n_new, nullptr, nullptr, keys_with_step2, sums_ready, c->ev_fork,
-                      c->side);
-    if (e != LTRI_OK) return e;
+                      c->side, k_chunk, v_chunk);
+    if (e != LTRI_OK) {                  // the tokens count already: their host rows must not be missing
+      (void)launch_copy_chunk(c->D, c->k_arena, c->v_arena, k_chunk, v_chunk, layer, bp, seq_count, n_new, c->k_host,
+                              c->v_host, c->stream);
+      return e;
+    }
     e = timing_mark(c, c->stream);
     if (e == LTRI_OK)
       e = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_new, out, lse_a,

@@ -165,12 +165,15 @@ inline RunSums running_sums_of(const Dims& D, const DevScratch& sc, int sc_max_p
 
 // ---- launchers (each returns the hipError_t of the launch) ----
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
+// k_host / v_host: the host arenas of an offloaded context, which get the rows as well, or NULL
 hipError_t launch_copy_chunk(const Dims& D, void* k_arena, void* v_arena, const void* k_chunk,
                              const void* v_chunk, int layer, const BatchPos& bp, int seq_count,
-                             int n_new, void* k_host, void* v_host, hipStream_t s);   // k_host / v_host: the host arenas of an offloaded context, else NULL
-// host-offloaded KV: rows of the retrieved tokens of the current list, host arenas -> device pool
-hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_pool, void* v_pool, const void* k_host,
-                                  const void* v_host, int layer, const BatchPos& bp, int seq_count, hipStream_t s);
+                             int n_new, void* k_host, void* v_host, hipStream_t s);
+// host-offloaded KV: rows of the retrieved tokens of the current list, host arenas -> device pool; with k_chunk / v_chunk
+// (both or neither) the same launch writes the n_new rows of the chunk at bp out to the host arenas
+hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_pool, void* v_pool, void* k_host,
+                                  void* v_host, int layer, const BatchPos& bp, int seq_count, const void* k_chunk,
+                                  const void* v_chunk, int n_new, hipStream_t s);
 hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                           const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
                           int n_new, hipEvent_t after_tiles, const RunSums* sums, hipStream_t s);

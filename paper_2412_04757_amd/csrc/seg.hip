@@ -1401,19 +1401,38 @@ __global__ __launch_bounds__(256) void copy_chunk_kernel(CopyArgs a) {
       const size_t w = (size_t)(c0 + r) * r16 + piece;
       kp[w] = kv; vp[w] = vv;
     }
-    kh[i] = kv; vh[i] = vv;                                  // host arenas: every token, in place
+    if (a.k_host) { kh[i] = kv; vh[i] = vv; }                // host arenas: every token, in place
   }
 }
 
 // ---- host-offloaded KV: rows of the retrieved tokens, host arenas -> the staging rows of the device pool ----
 // The context list is initial | retrieved | window; entry ns + j of the token list goes to pool row stage0 + j.
-struct FetchArgs { Dims D; DevState st; void* k_pool; void* v_pool; const void* k_host; const void* v_host;
-                   int layer; BatchPos bp; };
+// With k_chunk, workgroups FETCH_WGS and up of a problem write the chunk's rows out to the host arenas meanwhile: the
+// two directions of the link do not share its bandwidth, and no retrieved row is a row of the chunk. (A chunk of 1024
+// tokens beside 4096 retrieved ones: 78 + 295 us one after the other, together 323.)
+constexpr int FETCH_WGS = 16;      // per (sequence, KV head): 128 or more in all keep enough 16-byte reads in flight on the host link
+constexpr int WRITE_OUT_WGS = 4;   // as many as the writes need: they are sent without waiting for an answer
+struct FetchArgs { Dims D; DevState st; void* k_pool; void* v_pool; void* k_host; void* v_host;
+                   int layer; BatchPos bp; const void* k_chunk; const void* v_chunk; int n_new; };
 
 __global__ __launch_bounds__(256) void fetch_retrieved_kernel(FetchArgs a) {
   const Dims& D = a.D;
   const int p = blockIdx.y, bi = p / D.Hkv, h = p - bi * D.Hkv;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
+  if ((int)blockIdx.x >= FETCH_WGS) {
+    const size_t row_bytes = (size_t)D.d * D.elt, n16 = (size_t)a.n_new * row_bytes / 16;
+    const size_t src_off = (size_t)p * a.n_new * row_bytes;
+    const size_t dst_off = ((size_t)slot * (size_t)D.max_tokens + (size_t)a.bp.c0[bi]) * row_bytes;
+    const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.k_chunk) + src_off);
+    const uint4* vs = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.v_chunk) + src_off);
+    uint4* kd = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.k_host) + dst_off);
+    uint4* vd = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.v_host) + dst_off);
+    for (size_t i = (size_t)(blockIdx.x - FETCH_WGS) * 256 + threadIdx.x; i < n16; i += (size_t)WRITE_OUT_WGS * 256) {
+      kd[i] = ks[i];
+      vd[i] = vs[i];
+    }
+    return;
+  }
   const int32_t* meta = a.st.meta + (size_t)slot * META_WORDS;
   const int c0 = meta[META_CHUNK_START];
   const int ns = min(D.n_sink, c0), n_win = c0 - max(ns, c0 - D.window);
@@ -1426,7 +1445,7 @@ __global__ __launch_bounds__(256) void fetch_retrieved_kernel(FetchArgs a) {
   const uint4* vh = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.v_host) + (size_t)slot * (size_t)D.max_tokens * row_bytes);
   uint4* kp = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.k_pool) + arena_off(D, slot) * D.elt) + (size_t)D.stage0 * r16;
   uint4* vp = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.v_pool) + arena_off(D, slot) * D.elt) + (size_t)D.stage0 * r16;
-  for (int j = blockIdx.x * rows_per_pass + r_in; j < n_ret; j += gridDim.x * rows_per_pass) {
+  for (int j = blockIdx.x * rows_per_pass + r_in; j < n_ret; j += FETCH_WGS * rows_per_pass) {
     const int tok = list[j];
     const uint4 kv = kh[(size_t)tok * r16 + piece];
     const uint4 vv = vh[(size_t)tok * r16 + piece];
@@ -1453,7 +1472,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
 hipError_t launch_copy_chunk(const Dims& D, void* k_arena, void* v_arena, const void* k_chunk,
                              const void* v_chunk, int layer, const BatchPos& bp, int seq_count,
                              int n_new, void* k_host, void* v_host, hipStream_t s) {
-  if (D.offload && (!k_host || !v_host)) return hipErrorInvalidValue;
+  if (!k_host != !v_host) return hipErrorInvalidValue;
   CopyArgs a{D, k_arena, v_arena, k_chunk, v_chunk, layer, seq_count, n_new, bp, k_host, v_host};
   const size_t n16 = (size_t)n_new * D.d * D.elt / 16;
   const int bx = (int)((n16 + 255) / 256 < 64 ? (n16 + 255) / 256 : 64);
@@ -1461,12 +1480,12 @@ hipError_t launch_copy_chunk(const Dims& D, void* k_arena, void* v_arena, const 
   return hipGetLastError();
 }
 
-hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_pool, void* v_pool, const void* k_host,
-                                  const void* v_host, int layer, const BatchPos& bp, int seq_count, hipStream_t s) {
-  if (!D.offload || !k_host || !v_host) return hipErrorInvalidValue;
-  FetchArgs a{D, st, k_pool, v_pool, k_host, v_host, layer, bp};
-  // 16 workgroups per (sequence, KV head): 128 or more in all keep enough 16-byte reads in flight on the host link
-  fetch_retrieved_kernel<<<dim3(16, seq_count * D.Hkv), 256, 0, s>>>(a);
+hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_pool, void* v_pool, void* k_host,
+                                  void* v_host, int layer, const BatchPos& bp, int seq_count, const void* k_chunk,
+                                  const void* v_chunk, int n_new, hipStream_t s) {
+  if (!D.offload || !k_host || !v_host || !k_chunk != !v_chunk) return hipErrorInvalidValue;
+  FetchArgs a{D, st, k_pool, v_pool, k_host, v_host, layer, bp, k_chunk, v_chunk, n_new};
+  fetch_retrieved_kernel<<<dim3(FETCH_WGS + (k_chunk ? WRITE_OUT_WGS : 0), seq_count * D.Hkv), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
