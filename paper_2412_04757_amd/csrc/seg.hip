@@ -1136,7 +1136,21 @@ __device__ __forceinline__ uint64_t vote_key(double s) {
   return ~up;
 }
 
-// per span: area ratio, number of index tokens (Eq. 7), the tokens, the sum of their keys
+__device__ __forceinline__ int wave_sum_i32(int v) {
+  v += (int)lane_xor_c<1>((uint32_t)v);
+  v += (int)lane_xor_c<2>((uint32_t)v);
+  v += (int)lane_xor_c<4>((uint32_t)v);
+  v += (int)lane_xor_c<8>((uint32_t)v);
+  v += (int)lane_xor_c<16>((uint32_t)v);
+  v += (int)lane_xor_c<32>((uint32_t)v);
+  return v;
+}
+
+// per span: area ratio, number of index tokens (Eq. 7), the tokens, the sum of their keys. One workgroup per span, and
+// bound by the latency of its chain of steps: 18.5 us a chunk of 128 tokens and 12 index tokens per block with a sort of
+// the tokens and a block's budget levelled by one thread, 11.6 us with tokens ranked by comparing them (spans up to
+// DYN_DIRECT tokens; longer ones are sorted, the comparisons grow with the square) and levelled by a wavefront.
+constexpr int DYN_DIRECT = 256;
 template <int DT>
 __global__ __launch_bounds__(1024) void dyn_span_kernel(SegArgs a) {
   typedef typename Elt<DT>::type T;
@@ -1161,41 +1175,39 @@ __global__ __launch_bounds__(1024) void dyn_span_kernel(SegArgs a) {
     const int start = a.st.span_start[(size_t)slot * D.max_spans + sid];
     const int len = a.st.span_len[(size_t)slot * D.max_spans + sid];
     const int a0 = start - c0;                          // chunk-local
-    // sums over the span's tokens in a fixed order: per thread, per wave, then over the waves
-    double sv = 0.0, sin = 0.0, sall = 0.0;
-    for (int t = tid; t < len; t += blockDim.x) {
-      sv += dyn[a0 + t]; sin += dyn[a.Lp + a0 + t]; sall += dyn[2 * a.Lp + a0 + t];
-    }
-    sv = wave_sum_f64(sv); sin = wave_sum_f64(sin); sall = wave_sum_f64(sall);
-    if (lane == 0) { red[0][wave] = sv; red[1][wave] = sin; red[2][wave] = sall; }
     for (int w = tid; w < IDX_MASK_WORDS + 1; w += blockDim.x) smask[w] = 0u;
-    __syncthreads();
-    if (tid == 0) {
-      double votes = 0.0, tri = 0.0, rows = 0.0;
-      for (int w = 0; w < 16; ++w) { votes += red[0][w]; tri += red[1][w]; rows += red[2][w]; }
-      // triangle + row neighbours = the span's rows; triangle + column neighbours = its votes
-      const double den = D.ratio_mode == LTRI_RATIO_ROW ? rows
-                       : D.ratio_mode == LTRI_RATIO_COL ? votes : rows + votes - tri;
-      const double r_a = tri / den;
-      const double r_v = 1.0 / exp(D.lambda * (1.0 - r_a));
-      int n = (int)rint((double)len * r_v);
-      n = max(n, D.index_min);
-      if (D.index_max > 0) n = min(n, D.index_max);
-      s_count = max(1, min(n, len));
-    }
-    if (D.index_block_max > 0) {
+    if (D.index_block_max == 0) {
+      // sums over the span's tokens in a fixed order: per thread, per wave, then over the waves
+      double sv = 0.0, sin = 0.0, sall = 0.0;
+      for (int t = tid; t < len; t += blockDim.x) {
+        sv += dyn[a0 + t]; sin += dyn[a.Lp + a0 + t]; sall += dyn[2 * a.Lp + a0 + t];
+      }
+      sv = wave_sum_f64(sv); sin = wave_sum_f64(sin); sall = wave_sum_f64(sall);
+      if (lane == 0) { red[0][wave] = sv; red[1][wave] = sin; red[2][wave] = sall; }
+      __syncthreads();
+      if (tid == 0) {
+        double votes = 0.0, tri = 0.0, rows = 0.0;
+        for (int w = 0; w < 16; ++w) { votes += red[0][w]; tri += red[1][w]; rows += red[2][w]; }
+        // triangle + row neighbours = the span's rows; triangle + column neighbours = its votes
+        const double den = D.ratio_mode == LTRI_RATIO_ROW ? rows
+                         : D.ratio_mode == LTRI_RATIO_COL ? votes : rows + votes - tri;
+        const double r_a = tri / den;
+        const double r_v = 1.0 / exp(D.lambda * (1.0 - r_a));
+        int n = (int)rint((double)len * r_v);
+        n = max(n, D.index_min);
+        if (D.index_max > 0) n = min(n, D.index_max);
+        s_count = max(1, min(n, len));
+      }
+    } else {
       // A budget of index vectors per memory block (the piece of a unit inside this chunk), shared over the
       // block's spans: every span of the block gets its own count by one and the same routine (one wavefront
       // per span, so that all workgroups of a block agree to the bit), then the largest counts are levelled
       // down to the highest level that fits and what is left goes to the earliest spans still short.
+      if (tid == 0) { s_mlo = q; s_mhi = q; }
       __syncthreads();
-      if (tid == 0) {
-        const int blk = start / D.unit;
-        int lo = q, hi = q;
-        while (lo > 0 && a.st.span_start[(size_t)slot * D.max_spans + first + lo - 1] / D.unit == blk) --lo;
-        while (hi + 1 < nsp && a.st.span_start[(size_t)slot * D.max_spans + first + hi + 1] / D.unit == blk) ++hi;
-        s_mlo = lo; s_mhi = hi;
-      }
+      const int blk = start / D.unit;                     // spans are stored in stream order: a block's are neighbours
+      for (int m = tid; m < nsp; m += blockDim.x)
+        if (a.st.span_start[(size_t)slot * D.max_spans + first + m] / D.unit == blk) { atomicMin(&s_mlo, m); atomicMax(&s_mhi, m); }
       __syncthreads();
       const int mlo = s_mlo, mhi = s_mhi;
       for (int m = mlo + wave; m <= mhi; m += 16) {
@@ -1214,63 +1226,74 @@ __global__ __launch_bounds__(1024) void dyn_span_kernel(SegArgs a) {
         }
       }
       __syncthreads();
-      if (tid == 0) {
-        const int nm = mhi - mlo + 1, budget = D.index_block_max;
-        long long total = 0;
-        int cmax = 1;
-        for (int m = 0; m < nm; ++m) { total += s_cnt[m]; cmax = max(cmax, s_cnt[m]); }
-        int mine = s_cnt[q - mlo];
-        if (total > budget) {
-          int lvl_lo = 1, lvl_hi = cmax;                  // the largest level whose levelled total fits (1 if none does)
+      const int nm = mhi - mlo + 1, budget = D.index_block_max;
+      if (wave == 0) {                                    // a lane per span, or several spans where there are more than 64
+        auto levelled = [&](int level) {                  // total of the counts cut off at this level
+          int sum = 0;
+          for (int m = lane; m < nm; m += 64) sum += min(s_cnt[m], level);
+          return wave_sum_i32(sum);
+        };
+        int share = s_cnt[q - mlo];
+        if (levelled(SEG_MAX_L) > budget) {
+          int lvl_lo = 1, lvl_hi = min(SEG_MAX_L, budget);   // the largest level whose levelled total fits (1 if none does)
           while (lvl_lo < lvl_hi) {
             const int mid = (lvl_lo + lvl_hi + 1) >> 1;
-            long long sum = 0;
-            for (int m = 0; m < nm; ++m) sum += min(s_cnt[m], mid);
-            if (sum <= budget) lvl_lo = mid; else lvl_hi = mid - 1;
+            if (levelled(mid) <= budget) lvl_lo = mid; else lvl_hi = mid - 1;
           }
-          const int level = lvl_lo;
-          long long sum = 0;
-          for (int m = 0; m < nm; ++m) sum += min(s_cnt[m], level);
-          long long left = budget - sum;
-          int share = min(mine, level);
-          for (int m = 0; m < nm && left > 0; ++m) {
-            if (s_cnt[m] > level) {
-              if (m == q - mlo) ++share;
-              --left;
+          const int level = lvl_lo, left = budget - levelled(level);
+          int before = 0;                                 // spans in front of this one that are still short
+          for (int m = lane; m < q - mlo; m += 64) before += s_cnt[m] > level ? 1 : 0;
+          before = wave_sum_i32(before);
+          share = min(share, level) + (share > level && before < left ? 1 : 0);
+        }
+        if (lane == 0) s_count = share;
+      }
+    }
+    // the tokens with the most votes, the earlier one first where votes are equal
+    if (len <= DYN_DIRECT) {
+      // every token is compared with all others, 1024 / npow lanes to a token
+      int npow = 64;
+      while (npow < len) npow <<= 1;
+      for (int t = tid; t < len; t += blockDim.x) skey[t] = vote_key(dyn[a0 + t]);
+      __syncthreads();
+      const int parts = 1024 / npow, t = tid / parts, part = tid & (parts - 1), tc = min(t, len - 1);
+      const uint64_t kt = skey[tc];
+      int rank = 0;
+      for (int u = part; u < len; u += parts) {
+        const uint64_t ku = skey[u];
+        rank += (ku < kt || (ku == kt && u < tc)) ? 1 : 0;
+      }
+      for (int o = 1; o < parts; o <<= 1) rank += __shfl_xor(rank, o, 64);
+      if (part == 0 && t < len && rank < s_count) atomicOr(&smask[t >> 5], 1u << (t & 31));
+    } else {
+      // bitonic network over (key, position), ascending
+      int npow = 2;
+      while (npow < len) npow <<= 1;
+      for (int t = tid; t < npow; t += blockDim.x) {
+        skey[t] = t < len ? vote_key(dyn[a0 + t]) : ~0ull;
+        spos[t] = (uint16_t)t;
+      }
+      __syncthreads();
+      for (int k = 2; k <= npow; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+          for (int t = tid; t < npow / 2; t += blockDim.x) {
+            const int lo = ((t & ~(j - 1)) << 1) | (t & (j - 1)), hi = lo | j;
+            const uint64_t ka = skey[lo], kb = skey[hi];
+            const uint16_t pa = spos[lo], pb = spos[hi];
+            const bool a_after_b = (ka > kb) | ((ka == kb) & (pa > pb));
+            if (a_after_b == ((lo & k) == 0)) {
+              skey[lo] = kb; skey[hi] = ka;
+              spos[lo] = pb; spos[hi] = pa;
             }
           }
-          mine = share;
+          __syncthreads();
         }
-        s_count = mine;
       }
-    }
-    // tokens by votes: bitonic network over (key, position), ascending
-    int npow = 2;
-    while (npow < len) npow <<= 1;
-    for (int t = tid; t < npow; t += blockDim.x) {
-      skey[t] = t < len ? vote_key(dyn[a0 + t]) : ~0ull;
-      spos[t] = (uint16_t)t;
-    }
-    __syncthreads();
-    for (int k = 2; k <= npow; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int t = tid; t < npow / 2; t += blockDim.x) {
-          const int lo = ((t & ~(j - 1)) << 1) | (t & (j - 1)), hi = lo | j;
-          const uint64_t ka = skey[lo], kb = skey[hi];
-          const uint16_t pa = spos[lo], pb = spos[hi];
-          const bool a_after_b = (ka > kb) | ((ka == kb) & (pa > pb));
-          if (a_after_b == ((lo & k) == 0)) {
-            skey[lo] = kb; skey[hi] = ka;
-            spos[lo] = pb; spos[hi] = pa;
-          }
-        }
-        __syncthreads();
+      const int count = s_count;
+      for (int r = tid; r < count; r += blockDim.x) {
+        const int t = spos[r];
+        atomicOr(&smask[t >> 5], 1u << (t & 31));
       }
-    }
-    const int count = s_count;
-    for (int r = tid; r < count; r += blockDim.x) {
-      const int t = spos[r];
-      atomicOr(&smask[t >> 5], 1u << (t & 31));
     }
     __syncthreads();
     // the chunk's mask (spans share words at their edges)
