@@ -29,6 +29,7 @@ struct SegArgs {
   BatchPos bp;
   int sum_wgs;     // further workgroups per problem of seg_select_kernel's launch that take running sums for step 2
   RunSums rs;
+  unsigned long long quant_rank, quant_cells;   // percentile theta: rank of the cell and number of cells; cells 0: nothing to set up
 };
 
 __device__ __forceinline__ void tile_decode(int t, int& I, int& J) {
@@ -204,17 +205,18 @@ struct QuantShared {
   uint32_t cnt;
 };
 
-__global__ __launch_bounds__(256) void quant_init_kernel(SegArgs a, unsigned long long rank, unsigned long long n_cells) {
-  const int p = blockIdx.x;
+// State of the selection of problem p before its first pass (all threads of one workgroup).
+__device__ __forceinline__ void quant_init(const SegArgs& a, int p) {
   for (int b = threadIdx.x; b < QUANT_BINS; b += blockDim.x) a.sc.qhist[(size_t)p * QUANT_BINS + b] = 0u;
   if (threadIdx.x == 0) {
     unsigned long long* st = a.sc.qstate + (size_t)p * QUANT_STATE_WORDS;
     st[0] = 0ull;
-    st[1] = rank;
-    st[3] = n_cells;          // no digit fixed yet, not done
+    st[1] = a.quant_rank;
+    st[3] = a.quant_cells;    // no digit fixed yet, not done
     for (int j = 0; j < QUANT_LISTS; ++j) st[8 + j] = 0ull;
   }
 }
+__global__ __launch_bounds__(256) void quant_init_kernel(SegArgs a) { quant_init(a, blockIdx.x); }
 
 // One tile of a tile pass (all 256 threads), in two parts: quant_tile_clear before the tile is computed (a barrier
 // lies between the two), quant_tile_cells once it is in Ms (which it only reads). status: the problem's status
@@ -1029,6 +1031,9 @@ __global__ __launch_bounds__(256) void lse_tile_kernel(SegArgs a) {
 }
 
 __global__ __launch_bounds__(256) void lse_reduce_kernel(SegArgs a) {
+  // the launch before the map's first pass: the percentile's selection is set up here (a launch of its own, which LOGIT
+  // maps take, is 2.4 us and a gap)
+  if (a.quant_cells && blockIdx.x == 0) quant_init(a, blockIdx.y);
   const int p = blockIdx.y, nb = a.nb, Lp = a.Lp;
   const int n_h = a.q_seg ? a.D.G : 1;
   const int id = blockIdx.x * blockDim.x + threadIdx.x;        // (g, i) flattened
@@ -1522,6 +1527,7 @@ hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScrat
   a.bp = bp;
   a.sum_wgs = 0;
   a.rs = RunSums{};
+  a.quant_rank = a.quant_cells = 0;
   const int P = seq_count * D.Hkv;
   const bool bf = D.dtype == LTRI_BF16;
   dim3 gl((a.Lp + 255) / 256, P), gt(a.ntiles, P);
@@ -1563,6 +1569,11 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
   const int P = seq_count * D.Hkv;
   const bool bf = D.dtype == LTRI_BF16;
   dim3 gt(a.ntiles, P);
+  a.quant_rank = a.quant_cells = 0;
+  if (D.theta_quantile > 0.0) {
+    a.quant_cells = (unsigned long long)n_new * (unsigned long long)(n_new + 1) / 2;
+    a.quant_rank = (unsigned long long)floor(D.theta_quantile * ((double)a.quant_cells - 1.0));
+  }
   if (D.seg_map == LTRI_MAP_SOFTMAX) {
     const int n_h = q_seg ? D.G : 1;
     if (bf) lse_tile_kernel<LTRI_BF16><<<gt, 256, 0, s>>>(a);
@@ -1573,14 +1584,12 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
   auto tiles = [&](auto dt, auto kind) {
     constexpr int DT = decltype(dt)::value, KIND = decltype(kind)::value;
     if (D.theta_quantile > 0.0) {
-      const double n_cells = (double)n_new * (double)(n_new + 1) / 2.0;
-      const unsigned long long rank = (unsigned long long)floor(D.theta_quantile * (n_cells - 1.0));
-      quant_init_kernel<<<P, 256, 0, s>>>(a, rank, (unsigned long long)n_cells);
+      if (KIND == LTRI_MAP_LOGIT) quant_init_kernel<<<P, 256, 0, s>>>(a);
       seg_tile_sums_kernel<DT, KIND, true><<<gt, 256, 0, s>>>(a);      // pass 1 and the selection's first tile pass
       quant_pick_kernel<<<P, 1024, 0, s>>>(a);
       // a map whose cells all fit the list (chunks of up to 180 tokens) was collected whole by the first pass, and
       // the pick has finished the selection: the other kernels would only find that out (4.5 us each)
-      if (n_cells > (double)QUANT_LIST_CAP) {
+      if (a.quant_cells > (unsigned long long)QUANT_LIST_CAP) {
         for (int pass = 1; pass < QUANT_TILE_PASSES; ++pass) {
           quant_tile_kernel<DT, KIND><<<gt, 256, 0, s>>>(a);
           quant_pick_kernel<<<P, 1024, 0, s>>>(a);
