@@ -70,6 +70,12 @@ __device__ __forceinline__ int window_tok_row(const Dims& D, int tok) {
   return D.ring0 + (tok & D.ring_mask);
 }
 
+// Waits until the wavefront's own stores are complete. A workgroup barrier does not do that (it orders a workgroup's
+// accesses to the caches of its compute unit only): where another workgroup is told by an atomic that it may read, every
+// wavefront that stored waits here, in front of the barrier behind which one thread does the atomic. Stores at device scope
+// are then visible to loads at device scope on the whole chip.
+__device__ __forceinline__ void wait_for_own_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

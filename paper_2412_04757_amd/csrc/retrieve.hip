@@ -146,10 +146,11 @@ __global__ __launch_bounds__(1024) void qrep_partial_kernel(RetArgs a) {
   if (!a.qrep_by_last) return;
   // The workgroup of a problem that finishes last adds the pieces up into Q^R and leaves the ticket counter at
   // zero for the next launch. The sums are stored and loaded at device scope (they bypass the caches that the
-  // compute units of one die do not share with the others), every store of a workgroup has completed at the
-  // barrier before its ticket is taken, and the ticket is a device-scope atomic: no device-wide fence, which
+  // compute units of one die do not share with the others), every wavefront waits for its own stores before the
+  // barrier behind which the ticket is taken, and the ticket is a device-scope atomic: no device-wide fence, which
   // would write back and invalidate the whole level-2 cache, is needed.
   __shared__ int s_last;
+  wait_for_own_stores();
   __syncthreads();
   if (threadIdx.x == 0) s_last = atomicAdd(&a.sc.tickets[p], 1) == QREP_GRID_X - 1;
   __syncthreads();
@@ -1016,7 +1017,8 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
       }
     }
   }
-  __syncthreads();                                        // the workgroup's stores have completed
+  wait_for_own_stores();                                  // the last workgroup reads them once every ticket is taken
+  __syncthreads();
   if (n_score > 1) {
     if (tid == 0) s_last = atomicAdd(&a.sc.tickets[a.ticket_base + pl], 1) == n_score - 1;
     __syncthreads();
