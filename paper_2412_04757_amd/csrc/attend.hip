@@ -61,14 +61,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // so n is one constant.
 // The K fragments of a tile are requested together by hand (the compiler would serialise them
 // once registers are tight) and consumed in four groups; the DMA requests of a later tile are
-// issued between the groups, under the matrix products. The rescale of O is skipped while no
-// score passes the reference of the exponentials by much.
+// issued between the groups, under the matrix products. The rescale of O is skipped when no
+// lane's running maximum moves.
 // The tile loop is cut into segments (context tiles, the ragged last context tile, chunk tiles
 // below the diagonal, chunk tiles on the diagonal, tiles this wavefront cannot see) so that the
 // body of each segment is straight-line code, with the masks compiled in or out.
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-constexpr float RESCALE_SLACK = 8.f;            // powers of two a score may pass the reference by before O is rescaled
 constexpr int ATT_NW = 8;                       // wavefronts per workgroup of the bf16 kernel
 constexpr int TILE_BYTES = 16384;               // one 64-key tile of K or V
 constexpr int TOK_SLOTS = 8;                    // ring of token-id tiles (> tokens-ahead distance)
@@ -354,11 +353,12 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
     }
     float mx = max3(max3(m4[0], s[0][7], s[0][15]), max3(m4[1], s[1][7], s[1][15]), fmaxf(m4[2], m4[3]));
     mx = pair_max(mx) * sc;
-    // The reference of the exponentials moves only when a score passes it by more than RESCALE_SLACK: until then the
-    // probabilities exceed 1 by at most 2^RESCALE_SLACK, which costs fp32 sums and bf16 probabilities no precision
-    // (both are relative), and the rescale of O and of the sum (64 products per lane) is left out of nearly every
-    // tile; with the running maximum itself as the reference a third of the tiles of a 12K-key context needed it.
-    if (__any(mx > m_run + RESCALE_SLACK)) {
+    // The reference of the exponentials is the running maximum: the probability of a key that raises it is then 1, which
+    // bf16 holds exactly, and such keys carry the largest weights. A reference that lags behind it by up to 2^8 would save
+    // most of the rescales (2 to 3 % of a stream), but rounds those keys' probabilities like all others: measured against
+    // fp64 over 12292 keys, the error of the output 2.32e-3 -> 2.34e-3, with queries of four times the size 2.03e-3 ->
+    // 2.16e-3 and of the log-sum-exp 0.9e-3 -> 1.5e-3; and the sums overflow 2^8 earlier.
+    if (__any(mx > m_run)) {
       const float m_new = fmaxf(m_run, mx);
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
       m_run = m_new;

@@ -78,8 +78,8 @@ def test_attention_launch_shapes(gpu_device, hq, hkv, seqs, window, budget, hist
 
 
 def test_attention_scores_that_keep_growing(gpu_device):
-    """Scores whose running maximum climbs through the whole context by far more than the slack of the rescale: keys of
-    later tokens are longer, so that nearly all weight sits on the last keys and every tile moves the reference."""
+    """Scores whose running maximum climbs through the whole context: keys of later tokens are longer, so that nearly all
+    weight sits on the last keys and every tile moves the reference."""
     w = Workload("growing", 8, 2, 128, "bf16", 2048 + 64, 512, 4, 2048, 0, 64, "uniform", 16, 96)
     cfg = config_from_workload(w, theta=theta_default(128), n_layers=1, n_seqs=1)
     ctx = LtriContext(cfg, gpu_device)
@@ -99,6 +99,42 @@ def test_attention_scores_that_keep_growing(gpu_device):
     want, want_lse = attend_reference(ctx, w, 0, 2048, q)
     assert float((out[0].double() - want).abs().max()) <= 2e-2
     assert float((lse[0].double() - want_lse).abs().max()) <= 2e-3
+
+
+@pytest.mark.parametrize("hq,hkv,seqs,window,history,rows", [
+    (32, 8, 1, 1000, 1500, 2048),      # a full chip: every wavefront on all keys
+    (32, 8, 1, 1000, 1500, 1024),      # two key groups
+    (8, 2, 1, 1000, 1500, 65),         # two key groups and splits
+    (8, 2, 1, 1000, 1500, 3),
+])
+def test_keys_that_raise_the_maximum_count_exactly(gpu_device, hq, hkv, seqs, window, history, rows):
+    """A key per context tile scores a little more than the one before, all others nothing. The probability of each is
+    taken when it is the maximum, where it is 1 and needs no rounding; what is left of it later is an fp32 factor. So the
+    output, in which the values of those keys nearly cancel, is off by its own rounding and fp32 sums only."""
+    w = Workload("records", hq, hkv, 128, "bf16", history + rows, 2048, 4, window, 0, 16, "uniform", 16, 96)
+    ctx = LtriContext(config_from_workload(w, theta=theta_default(128), n_layers=1, n_seqs=seqs), gpu_device)
+    ka, va = ctx.arena_views()
+    gen = torch.Generator(device=gpu_device).manual_seed(11)
+    ka.zero_()
+    ka[..., 0] = -4096.0
+    va.copy_(torch.randint(0, 2, va.shape, generator=gen, device=gpu_device) * 2 - 1)
+    # list entries 20 (or 4 fewer, as many tokens as are retrieved): the window's tokens from w0 on; one key per 64 of them
+    at = torch.arange(history - window + 30, history, 64, device=gpu_device)
+    ka[..., at, 0] = (8.0 + 0.125 * torch.arange(len(at), device=gpu_device)).to(torch.bfloat16)
+    q = torch.zeros((seqs, rows, hq, 128), dtype=torch.bfloat16, device=gpu_device)
+    q[..., 0] = 1.0 + 2.0 * torch.rand((seqs, rows, hq), generator=gen, device=gpu_device)
+    for c0 in range(0, history, 750):
+        ctx.append_chunk(0, 0, seqs, min(750, history - c0))
+    ctx.append_chunk(0, 0, seqs, rows)
+    ctx.retrieve(0, 0, seqs, q)
+    lse = torch.empty(q.shape[:3], dtype=torch.float32, device=gpu_device)
+    out = ctx.attend(0, 0, seqs, q, lse=lse)
+    for s in range(seqs):
+        want, want_lse = attend_reference(ctx, w, s, history, q[s])
+        # bf16 output: 2^-8 of itself; fp32: scores up to 8 (2^-24 each of a product and a sum), 16 keys, sums up to 16
+        assert bool(((out[s].double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all())
+        assert float((lse[s].double() - want_lse).abs().max()) <= 1e-5
+    assert ctx.sync_status() == 0
 
 
 # fp32: (query heads, KV heads, head_dim, sequences, window, budget, history, query rows)
