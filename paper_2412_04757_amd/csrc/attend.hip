@@ -68,7 +68,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // body of each segment is straight-line code, with the masks compiled in or out.
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int ATT_NW = 8;                       // wavefronts per workgroup of the bf16 kernel
 constexpr int TILE_BYTES = 16384;               // one 64-key tile of K or V
 constexpr int TOK_SLOTS = 8;                    // ring of token-id tiles (> tokens-ahead distance)
 constexpr int att_lds_bytes(int ks, int ns) { return ks * (ns * 2 * TILE_BYTES + TOK_SLOTS * 256); }
@@ -877,48 +876,12 @@ static int attend_split_count(const Dims& D, int seq_count, int n_q, int n_cus, 
   return ns > ATT_MAX_SPLITS ? ATT_MAX_SPLITS : ns;
 }
 
-// Rows of partial results a context's scratch has room for: short query blocks at any batch, and longer ones while
-// a split pays (three rounds of workgroups of 128 rows on 256 compute units).
+// Rows of partial results a context's scratch has room for: short query blocks at any batch, and longer ones.
 size_t attend_part_rows(const Dims& D) {
   const size_t short_rows = (size_t)D.n_seqs * D.Hq * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS;
   const size_t all = (size_t)D.n_seqs * D.Hq * D.chunk_max * ATT_MAX_SPLITS;
-  const size_t long_rows = all < 98304 ? all : 98304;
+  const size_t long_rows = all < ATT_PART_MAX_ROWS ? all : ATT_PART_MAX_ROWS;
   return attend_on_matrix_cores(D) ? (short_rows > long_rows ? short_rows : long_rows) : 0;
-}
-
-// ---- shape of a launch of the matrix-core kernel: key groups per workgroup and splits of the key range ----
-// A workgroup (one per compute unit: its registers and LDS fill it) covers 256 (row, head) pairs with every wavefront
-// on all keys (KS = 1), or 128 with two groups on alternate tiles (KS = 2, merged in LDS): twice the workgroups, half
-// the stages, twice the rows fetched per product. Splits divide the stages further but write and read back partial
-// results. The launch takes (rounds of workgroups over the chip) x (stages per workgroup x time of a stage + start) +
-// merge; the least of that model over both KS and 1 .. 16 splits is taken. Its constants are measured at 32 query and
-// 8 KV heads (us): a stage 1.5 on a nearly empty chip .. 1.85 on a full one (the clock falls), 7 % more with KS = 2,
-// 4 to start and drain a workgroup, 5 + 1.7e-4 per partial row for the merge (with the write-back of the rows at the
-// end of the kernel). Launches it changes, before -> after at context + query rows: 8110 + 1024 215 -> 148 (two
-// groups), 3039 + 700 92 -> 59, four sequences of 1999 + 256 66 -> 45, 8166 + 512 206 -> 84 (two groups, two splits),
-// 2003 + 128 58 -> 24. A full chip keeps KS = 1 without splits (12196 + 2048: 413 against 427 with two groups).
-struct AttShape { int ks, ns; };
-static AttShape attend_shape(const Dims& D, int seq_count, int n_q, int n_ctx, int n_chunk, size_t part_rows, int n_cus) {
-  const int HG = D.G < 4 ? D.G : 4;
-  AttShape best{1, 1};
-  float best_cost = 0.f;
-  for (int ks = 1; ks <= 2; ++ks) {
-    const int rs = ATT_NW / ks / HG, rpb = 32 * rs;
-    const long long blocks = (long long)D.Hkv * (D.G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
-    // with one sub-tile per workgroup the causal part is walked on average to three quarters (rows start from the end)
-    const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * (rs == 1 ? 0.75f : 1.f);
-    for (int ns = 1; ns <= ATT_MAX_SPLITS; ++ns) {
-      const size_t rows = (size_t)seq_count * D.Hq * n_q * ns;
-      if (ns > 1 && (rows > part_rows || ns * ks > tiles)) break;
-      const long long rounds = (blocks * ns + n_cus - 1) / n_cus;
-      const float fill = (float)(blocks * ns) / (float)(rounds * n_cus);
-      const float stages = ceilf(tiles / (float)(ks * ns));
-      const float cost = (float)rounds * (stages * (1.5f + 0.35f * fill) * (ks == 2 ? 1.07f : 1.f) + 4.f) +
-                         (ns > 1 ? 5.f + 1.7e-4f * (float)rows : 0.f);
-      if ((ks == 1 && ns == 1) || cost < best_cost) { best_cost = cost; best = AttShape{ks, ns}; }
-    }
-  }
-  return best;
 }
 
 static hipError_t device_cus(int* n_cus) {
@@ -999,8 +962,9 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     const long long far = D.budget ? D.budget : D.k_max ? (long long)D.k_max * 256 : c0;
     long long n_ctx = part_mode == ATT_LOCAL ? near : part_mode == ATT_RETRIEVED ? far : near + far;
     if (n_ctx > c0) n_ctx = c0;
-    AttShape shape = attend_shape(D, seq_count, n_q, (int)n_ctx, part_mode == ATT_RETRIEVED ? 0 : n_q,
-                                  part && part_mode == ATT_ALL ? attend_part_rows(D) : 0, n_cus);
+    const size_t part_rows = attend_part_rows(D) < ATT_PART_MAX_ROWS ? attend_part_rows(D) : ATT_PART_MAX_ROWS;
+    AttShape shape = attend_shape(D.Hq, D.Hkv, seq_count, n_q, (int)n_ctx, part_mode == ATT_RETRIEVED ? 0 : n_q,
+                                  part && part_mode == ATT_ALL ? part_rows : 0, n_cus);
     if (n_q <= ATT_SPLIT_MAX_ROWS) shape = AttShape{2, ns_short};
     const int ks = shape.ks, ns = shape.ns;
     const int HG = D.G < 4 ? D.G : 4;

@@ -1,0 +1,57 @@
+// How a launch of the matrix-core attention is shaped: key groups per workgroup and splits of the key range. Plain C++.
+//
+// A workgroup (one per compute unit: its registers fill it) covers 256 (row, head) pairs with every wavefront on all keys
+// (KS = 1), or 128 with two groups on alternate tiles (KS = 2, merged in LDS): twice the workgroups, half the stages, twice
+// the rows fetched per product. Splits divide the stages further but write and read back partial results. The launch takes
+// (rounds of workgroups over the chip) x (stages per workgroup x time of a stage + start) + merge; the least of that model
+// over both KS and 1 .. 16 splits is taken. Its constants (us): a stage 1.5 on a nearly empty chip .. 1.85 on a full one
+// (the clock falls), 7 % more with KS = 2, 4 to start and drain a workgroup, 5 + 1.7e-4 per partial row for the merge (with
+// the write-back of the rows at the end of the kernel).
+// Measured at 77 launches (32, 64, 16 and 8 query heads on 8 or 2 KV heads, 1 to 8 sequences, 64 to 2048 rows behind 1500 to
+// 12300 context tokens) in every shape: the model is 4 % low with 8 % of scatter, what it takes is 1.6 % above the best
+// shape in the geometric mean, and never slower than one group without splits, which all launches were before. That one
+// against what is taken, context + rows, 32 heads: 12292 + 1024 337 -> 230 (two groups), 2052 + 700 77 -> 50, four
+// sequences of 2052 + 256 74 -> 51, 12292 + 512 316 -> 126 (two groups, two splits), 2052 + 128 63 -> 24. A full chip keeps
+// one group (12292 + 2048: 438 against 463 with two, 2052 + 2048: 119 against 125).
+#pragma once
+#include <math.h>
+#include <stddef.h>
+
+namespace ltri {
+
+constexpr int ATT_NW = 8;                // wavefronts per workgroup of the matrix-core kernel
+constexpr int ATT_MAX_SPLITS = 16;       // key-range splits of an attention launch, at most
+constexpr int ATT_SPLIT_MAX_ROWS = 4;    // longest query block whose split does not depend on the context (decoding)
+// Partial rows of a longer block, at most (34 MB at head_dim 128). Twice what one round of workgroups writes: with more,
+// 1100 to 1536 rows of 32 heads would be split into three rounds of workgroups, which the model favours over the two
+// rounds of one group but which took 1 to 5 % longer (12292 + 1400: 354 against 337, 12292 + 1536: 368 against 358).
+constexpr size_t ATT_PART_MAX_ROWS = 65536;
+
+struct AttShape { int ks, ns; };
+
+// n_ctx context and n_chunk chunk tokens; part_rows: partial rows there is room for.
+inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, int n_chunk, size_t part_rows, int n_cus) {
+  const int G = Hq / Hkv, HG = G < 4 ? G : 4;
+  AttShape best{1, 1};
+  float best_cost = 0.f;
+  for (int ks = 1; ks <= 2; ++ks) {
+    const int rs = ATT_NW / ks / HG, rpb = 32 * rs;
+    const long long blocks = (long long)Hkv * (G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
+    // The causal part: a workgroup's last row is anywhere in the chunk (one sub-tile of 32 rows each, the last ones start
+    // first) or in its upper half (sub-tiles paired from both ends), and the longest walks set the pace.
+    const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * (rs == 1 ? 0.75f : 0.85f);
+    for (int ns = 1; ns <= ATT_MAX_SPLITS; ++ns) {
+      const size_t rows = (size_t)seq_count * Hq * n_q * ns;
+      if (ns > 1 && (rows > part_rows || ns * ks > tiles)) break;
+      const long long rounds = (blocks * ns + n_cus - 1) / n_cus;
+      const float fill = (float)(blocks * ns) / (float)(rounds * n_cus);
+      const float stages = ceilf(tiles / (float)(ks * ns));
+      const float cost = (float)rounds * (stages * (1.5f + 0.35f * fill) * (ks == 2 ? 1.07f : 1.f) + 4.f) +
+                         (ns > 1 ? 5.f + 1.7e-4f * (float)rows : 0.f);
+      if ((ks == 1 && ns == 1) || cost < best_cost) { best_cost = cost; best = AttShape{ks, ns}; }
+    }
+  }
+  return best;
+}
+
+}  // namespace ltri

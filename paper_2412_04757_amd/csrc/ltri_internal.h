@@ -4,6 +4,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include "ltri.h"
+#include "attend_shape.h"
 
 namespace ltri {
 
@@ -31,8 +32,6 @@ constexpr int QUANT_STATE_WORDS = 8 + QUANT_LISTS;   // per problem: key prefix,
 constexpr int QUANT_LIST_CAP = 1 << 14;      // cells collected for the final exact selection, at most
 constexpr int IDX_MASK_WORDS = SEG_MAX_L / 32;   // one bit per token of a chunk
 constexpr int ATT_BN = 64;               // keys per attention tile; token lists are padded to it
-constexpr int ATT_MAX_SPLITS = 16;       // key-range splits of an attention launch, at most
-constexpr int ATT_SPLIT_MAX_ROWS = 4;    // longest query block whose split does not depend on the context (decoding)
 constexpr size_t ATT_STATIC_SCRATCH_BYTES = 2u << 20;   // the library's own buffer for such partial results (ltri_attend_static)
 
 // Byte offsets of the arrays inside the caller's `state` buffer.
