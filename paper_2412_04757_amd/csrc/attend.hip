@@ -15,6 +15,7 @@
 #include <hip/hip_ext.h>
 #include "device_common.h"
 #include "attend_args.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace ltri {
@@ -876,12 +877,21 @@ static int attend_split_count(const Dims& D, int seq_count, int n_q, int n_cus, 
   return ns > ATT_MAX_SPLITS ? ATT_MAX_SPLITS : ns;
 }
 
-// Rows of partial results a context's scratch has room for: short query blocks at any batch, and longer ones.
+// Context tokens that a chunk behind c0 tokens is expected to attend (the lists themselves are on the device): initial and
+// window tokens, and retrieved ones.
+static long long near_tokens(const Dims& D, long long c0) { return std::min<long long>(c0, (long long)D.n_sink + D.window); }
+static long long far_tokens(const Dims& D, long long c0) {
+  const long long far = D.budget ? D.budget : D.k_max ? (long long)D.k_max * 256 : c0;
+  return std::min(far, c0);
+}
+
+// Rows of partial results a context's scratch has room for: short query blocks at any batch, and as many as a launch of
+// longer ones takes within the context's limits (on 256 compute units).
 size_t attend_part_rows(const Dims& D) {
+  if (!attend_on_matrix_cores(D)) return 0;
+  const long long max_ctx = std::min(D.max_tokens, near_tokens(D, D.max_tokens) + far_tokens(D, D.max_tokens));
   const size_t short_rows = (size_t)D.n_seqs * D.Hq * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS;
-  const size_t all = (size_t)D.n_seqs * D.Hq * D.chunk_max * ATT_MAX_SPLITS;
-  const size_t long_rows = all < ATT_PART_MAX_ROWS ? all : ATT_PART_MAX_ROWS;
-  return attend_on_matrix_cores(D) ? (short_rows > long_rows ? short_rows : long_rows) : 0;
+  return std::max(short_rows, attend_most_part_rows(D.Hq, D.Hkv, std::min(D.n_seqs, LTRI_MAX_BATCH), D.chunk_max, max_ctx, 256));
 }
 
 static hipError_t device_cus(int* n_cus) {
@@ -955,16 +965,13 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     return hipGetLastError();
   }
   if (mfma_ok) {
-    // expected context of the launch (the lists themselves are on the device): only the shape depends on it
     long long c0 = 0;
     for (int i = 0; i < seq_count; ++i) c0 = bp.c0[i] > c0 ? bp.c0[i] : c0;
-    const long long near = (long long)D.n_sink + D.window;
-    const long long far = D.budget ? D.budget : D.k_max ? (long long)D.k_max * 256 : c0;
-    long long n_ctx = part_mode == ATT_LOCAL ? near : part_mode == ATT_RETRIEVED ? far : near + far;
-    if (n_ctx > c0) n_ctx = c0;
-    const size_t part_rows = attend_part_rows(D) < ATT_PART_MAX_ROWS ? attend_part_rows(D) : ATT_PART_MAX_ROWS;
+    const long long near = near_tokens(D, c0), far = far_tokens(D, c0);
+    const long long n_ctx = part_mode == ATT_LOCAL ? near : part_mode == ATT_RETRIEVED ? far : std::min(near + far, c0);
+    const size_t room = std::min((size_t)D.att_part_rows, ATT_PART_MAX_ROWS);
     AttShape shape = attend_shape(D.Hq, D.Hkv, seq_count, n_q, (int)n_ctx, part_mode == ATT_RETRIEVED ? 0 : n_q,
-                                  part && part_mode == ATT_ALL ? part_rows : 0, n_cus);
+                                  part && part_mode == ATT_ALL ? room : 0, n_cus);
     if (n_q <= ATT_SPLIT_MAX_ROWS) shape = AttShape{2, ns_short};
     const int ks = shape.ks, ns = shape.ns;
     const int HG = D.G < 4 ? D.G : 4;

@@ -54,4 +54,26 @@ inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx,
   return best;
 }
 
+// The most partial rows that attend_shape takes for the blocks of more than ATT_SPLIT_MAX_ROWS rows of a context: up to
+// n_seqs sequences, chunk_max rows and max_ctx context tokens. Row counts are walked by whole workgroups, contexts by
+// eighths of their size; a launch between them that wants more takes the best shape there is room for.
+inline size_t attend_most_part_rows(int Hq, int Hkv, int n_seqs, int chunk_max, long long max_ctx, int n_cus) {
+  const int G = Hq / Hkv, step = 32 * (ATT_NW / 2 / (G < 4 ? G : 4));
+  size_t most = 0;
+  for (int seqs = 1; seqs <= n_seqs; ++seqs)
+    for (int rows = step; rows < chunk_max + step; rows += step) {
+      const int n_q = rows < chunk_max ? rows : chunk_max;
+      if (n_q <= ATT_SPLIT_MAX_ROWS) continue;
+      if ((size_t)2 * seqs * Hq * n_q > ATT_PART_MAX_ROWS) break;
+      for (long long ctx = 0;; ctx = ctx + (ctx / 8 > 64 ? ctx / 8 : 64)) {
+        const AttShape s = attend_shape(Hq, Hkv, seqs, n_q, (int)(ctx < max_ctx ? ctx : max_ctx), n_q, ATT_PART_MAX_ROWS, n_cus);
+        const size_t need = s.ns > 1 ? (size_t)seqs * Hq * n_q * s.ns : 0;
+        if (need > most) most = need;
+        if (ctx >= max_ctx) break;
+      }
+      if (most > ATT_PART_MAX_ROWS - ATT_PART_MAX_ROWS / 16) return ATT_PART_MAX_ROWS;
+    }
+  return most;
+}
+
 }  // namespace ltri

@@ -166,7 +166,8 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   CL.qpart = o;  o = align_up(o + (size_t)2 * P * (Lp / 128 + Lp) * D.d * 8, 256);
   CL.bounds = o; o = align_up(o + (size_t)c.n_kv_heads * (c.chunk_max + 2) * 4, 256);
   CL.selflag = o; o = align_up(o + (size_t)c.n_seqs * c.n_kv_heads * D.max_spans, 256);
-  CL.att_part = o; o = align_up(o + attend_part_rows(D) * (D.d + 2) * 4, 256);
+  D.att_part_rows = (long long)attend_part_rows(D);
+  CL.att_part = o; o = align_up(o + (size_t)D.att_part_rows * (D.d + 2) * 4, 256);
   CL.tokspan = o; o = align_up(o + (size_t)P * Lp * 4, 256);
   CL.dyn = o;     o = align_up(o + (size_t)P * 3 * Lp * 8, 256);
   CL.qhist = o;   o = align_up(o + (size_t)P * QUANT_BINS * 4, 256);

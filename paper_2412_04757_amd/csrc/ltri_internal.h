@@ -69,7 +69,7 @@ struct ScratchLayout {
                    //        chunk's query rows [0] and key rows [1]
   size_t bounds;   // int32  [Hkv][chunk_max + 1] + int32 [Hkv]  (append_with_spans)
   size_t selflag;  // uint8  [n_seqs * Hkv][max_spans]  1 = span selected (between the two selection kernels)
-  size_t att_part; // float  [attend_part_rows][d + 2]  partial results of an attention whose key range is split
+  size_t att_part; // float  [att_part_rows][d + 2]  partial results of an attention whose key range is split
   size_t tokspan;  // int32  [P][Lp]      span (within the chunk) of every token (dynamic index vectors)
   size_t dyn;      // double [P][3][Lp]   votes, in-span row sums, whole row sums of the softmax map
   size_t qhist;    // uint32 [P][QUANT_BINS]  histogram of one digit of the map cells' order keys (percentile theta)
@@ -108,6 +108,7 @@ struct Dims {
   int offload;
   long long arena_rows;
   int ring0, ring_mask, stage0;
+  long long att_part_rows;     // rows of partial attention results in the scratch (attend_part_rows)
 };
 
 struct BatchPos {            // per-sequence values of one batched call
@@ -210,7 +211,7 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
 // marker is queued that the neighbouring launches would wait behind); other shapes record them around the launches.
 // bytes of partial results a launch over seq_count sequences with n_q query rows needs (0: the key range is not split)
 size_t attend_partial_bytes(const Dims& D, int seq_count, int n_q, int n_cus);
-size_t attend_part_rows(const Dims& D);          // rows of (head_dim + 2) floats in a context's buffer of partial results
+size_t attend_part_rows(const Dims& D);          // Dims::att_part_rows: rows of (head_dim + 2) floats
 // device address, on the current device, of the library's own buffer of ATT_STATIC_SCRATCH_BYTES for partial results
 hipError_t attend_static_scratch(float** ptr);
 bool attend_on_matrix_cores(const Dims& D);      // the bf16 kernel takes this shape (else attend_f32.hip)
