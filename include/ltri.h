@@ -136,7 +136,9 @@ typedef struct {
 /* Sizes (bytes) of the two device buffers a context needs: `state` holds the index
  * memory (span table, representative keys, selections, token lists; lives as long as
  * the context; ltri_create enqueues a kernel that zero-fills it), `scratch` holds per-call
- * temporaries. EINVAL on an unsupported configuration. */
+ * temporaries, among them the partial results of attention launches whose key range is split
+ * (bf16: up to 34 MB, by the context's heads, sequences, chunk length, window and budget).
+ * EINVAL on an unsupported configuration. */
 int32_t ltri_workspace_bytes(const ltri_config* cfg, size_t* state_bytes, size_t* scratch_bytes);
 
 /* Creates a context. k_arena / v_arena / state / scratch are device pointers owned by the
@@ -151,8 +153,10 @@ int32_t ltri_reset(ltri_ctx* ctx, int32_t seq);
  * Ordering between work on different streams is the caller's business (events). */
 int32_t ltri_set_stream(ltri_ctx* ctx, void* hip_stream);
 /* LDS ring depth of the bf16 attention kernel: 4 (default, 130 KB of LDS per compute unit, fastest
- * on its own) or 3 (98 KB, leaves room for the segmentation kernels of the next chunk to run next
- * to it). EINVAL otherwise. */
+ * on its own) or 3 (98 KB). Launches shaped as two key groups per workgroup hold 132 KB whatever the
+ * depth. Results do not depend on it. A workgroup's registers fill its compute unit either way, so
+ * kernels of another stream run beside the attention only on compute units that its launch leaves
+ * idle. EINVAL otherwise. */
 int32_t ltri_set_attend_stages(ltri_ctx* ctx, int32_t stages);
 /* A context without device buffers: every call validates its arguments and advances the
  * host-side state exactly as a real context would, but enqueues nothing; introspection calls
@@ -247,17 +251,21 @@ int32_t ltri_force_selection(ltri_ctx* ctx, int32_t layer, int32_t seq, int32_t 
  * the scaled scores) or NULL. Query row i of the chunk attends the initial tokens, the
  * selected spans' evicted parts, the window and the chunk's tokens 0..i, with weights
  * softmax(q.k / sqrt(head_dim)). ESTATE unless ltri_retrieve (or ltri_force_selection for
- * every head) ran for this chunk. */
+ * every head) ran for this chunk.
+ * Rounding: fp32 sums; in bf16 (blocks of more than one row) the probabilities are rounded to bf16
+ * relative to the largest score met so far. How the keys are grouped follows the size of the launch
+ * (sequences, rows, the longest context in the call), so a sequence's rows can differ by the rounding
+ * of the dtype between calls with other sequences beside it. The same call on the same contexts
+ * repeats itself bit for bit. */
 int32_t ltri_attend(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int32_t seq_count,
                     const void* q, int32_t n_q, void* out, float* lse);
 
-/* ltri_attend for callers that cannot allocate device memory and bring no scratch for this call: code
- * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, same
- * results. Where ltri_attend keeps the partial results of a split key range (query blocks of 1 to 4 rows:
- * decoding) in the context's scratch buffer, this call keeps them in a buffer of 2 MiB that the library
- * itself holds on every GPU it runs on, from load until the process ends (longer blocks use the context's scratch
- * buffer like ltri_attend). The call allocates and frees
- * nothing. LTRI_ECAPACITY if the partial results of this call need more than 2 MiB (they take
+/* ltri_attend whose decoding blocks (1 to 4 query rows) leave the context's scratch buffer alone: code under
+ * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, same results. Where
+ * ltri_attend keeps the partial results of a split key range of such a block in the context's scratch, this call
+ * keeps them in a buffer of 2 MiB that the library itself holds on every GPU it runs on, from load until the
+ * process ends. Blocks of more than 4 rows are ltri_attend's launch, partial results in the context's scratch
+ * included. The call allocates and frees nothing. LTRI_ECAPACITY if the partial results of this call need more than 2 MiB (they take
  * seq_count * n_q_heads * splits * n_q * (head_dim + 2) * 4 bytes; 16 sequences of one token at 32 query
  * heads take 1.1 MB); other errors as ltri_attend. All contexts on one GPU share the buffer: calls that
  * overlap on one GPU (different streams or contexts) race; on one stream they are ordered. Nothing in the
@@ -276,7 +284,7 @@ int32_t ltri_attend_static(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int3
  * of step 1's last launch, and step 2 forms Q^R of every query span and the mean keys of the chunk's spans as
  * differences of two of their rows before it scores, selects and writes the lists. Other configurations sum the
  * rows per span in a launch of their own. The attention is one launch over initial | retrieved | window |
- * chunk; results identical to the three calls.
+ * chunk, and one that merges partial results where the key range is split; results identical to the three calls.
  * In host memory (kv_offload = 1): the fetch of the retrieved rows over the host link is the longest part of the
  * step. It is queued on a second stream the context owns, behind step 2; the attention over initial tokens,
  * window and the chunk itself, which needs none of those rows, follows step 2 on the context's stream and runs
@@ -298,8 +306,8 @@ int32_t ltri_step(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int32_t seq_c
  * launches, on the context's stream. ltri_read_step_timing synchronises that stream,
  * writes two durations (milliseconds) per step for up to `cap` steps since the last read, oldest first, to the
  * host arrays, sets *n to the count and forgets the records. With resident keys and values the first array
- * holds the one attention launch (two events per step, carried by the launch's own dispatch: they take the
- * kernel's start and end) and the second 0; with kv_offload = 1 the first holds the launch over initial | window
+ * holds the attention launch (two events per step, carried by the launch's own dispatch: they take the
+ * kernel's start and end; with a merge behind it the second event follows the merge) and the second 0; with kv_offload = 1 the first holds the launch over initial | window
  * | chunk (which shares the chip with the fetch) and the second the launch over the retrieved rows. Steps that run the plain calls (one-token chunks, fp32) leave no record. Turning timing on or off also
  * forgets pending records. */
 int32_t ltri_set_step_timing(ltri_ctx* ctx, int32_t on);
