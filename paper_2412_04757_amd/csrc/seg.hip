@@ -482,9 +482,12 @@ __global__ __launch_bounds__(1024) void quant_pick_kernel(SegArgs a) {
 // Whatever the three launched pairs left undone, one workgroup per problem walking all tiles itself.
 template <int DT, int KIND>
 __global__ __launch_bounds__(256) void quant_finish_kernel(SegArgs a) {
-  __shared__ double Ms[64 * 65];
-  __shared__ QuantShared S;
-  __shared__ __attribute__((aligned(16))) QuantPickShared SP;
+  struct TileShared { double Ms[64 * 65]; QuantShared S; };
+  constexpr size_t LDS = sizeof(TileShared) > sizeof(QuantPickShared) ? sizeof(TileShared) : sizeof(QuantPickShared);
+  __shared__ __attribute__((aligned(16))) unsigned char lds[LDS];      // the tiles', then the pick's (barriers lie between)
+  double* Ms = reinterpret_cast<TileShared*>(lds)->Ms;
+  QuantShared& S = reinterpret_cast<TileShared*>(lds)->S;
+  QuantPickShared& SP = *reinterpret_cast<QuantPickShared*>(lds);
   const int p = blockIdx.x;
   for (int it = 0; it < QUANT_PASSES; ++it) {
     const unsigned long long status = qload(a.sc.qstate + (size_t)p * QUANT_STATE_WORDS + 3);

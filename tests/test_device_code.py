@@ -49,3 +49,19 @@ def test_stores_are_complete_before_a_ticket_is_taken(tmp_path):
         assert any(re.match(r"s_waitcnt .*vmcnt\(0\)", x) for x in block), f"{name}: {block[:8]}"
         seen += 1
     assert seen == 4                                 # both kernels, both element types
+
+
+def resources(source, tmp_path):
+    """Bytes of private memory and of LDS of every kernel of a source file, from the metadata the compiler writes."""
+    kernels(source, tmp_path)
+    found = {}
+    for part in (tmp_path / "device.s").read_text().split(".amdhsa_kernel ")[1:]:
+        value = lambda key: int(re.search(rf"\.amdhsa_{key} (\d+)", part).group(1))
+        found[part.split()[0]] = (value("private_segment_fixed_size"), value("group_segment_fixed_size"))
+    return found
+
+
+def test_finishing_kernel_of_the_percentile_shares_its_lds(tmp_path):
+    """Its tile passes and its picks take turns: it needs the larger of the two (66 KB), not their sum (107 KB)."""
+    got = {k: v for k, v in resources("seg.hip", tmp_path).items() if "quant_finish_kernel" in k}
+    assert len(got) == 4 and all(lds <= 68 << 10 for _, lds in got.values()), got
