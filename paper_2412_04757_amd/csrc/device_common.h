@@ -14,13 +14,6 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);
 }
 
-// fp32 -> bf16, round to nearest even (finite inputs).
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
 // fp64 -> bf16 in ONE rounding (nearest even); avoids the double rounding of going
 // through fp32. Finite inputs in the normal bf16 range; tiny values flush to +-0.
 __device__ __forceinline__ uint16_t f64_to_bf16(double x) {
@@ -44,14 +37,12 @@ template <> struct Elt<LTRI_F32> {
   __device__ static __forceinline__ double to_f64(float v) { return (double)v; }
   __device__ static __forceinline__ float to_f32(float v) { return v; }
   __device__ static __forceinline__ float from_f64(double v) { return (float)v; }
-  __device__ static __forceinline__ float from_f32(float v) { return v; }
 };
 template <> struct Elt<LTRI_BF16> {
   typedef uint16_t type;
   __device__ static __forceinline__ double to_f64(uint16_t v) { return (double)bf16_to_f32(v); }
   __device__ static __forceinline__ float to_f32(uint16_t v) { return bf16_to_f32(v); }
   __device__ static __forceinline__ uint16_t from_f64(double v) { return f64_to_bf16(v); }
-  __device__ static __forceinline__ uint16_t from_f32(float v) { return f32_to_bf16(v); }
 };
 
 __device__ __forceinline__ int slot_of(const Dims& D, int layer, int seq, int h) {

@@ -561,9 +561,8 @@ __global__ __launch_bounds__(1024) void select_emit_kernel(RetArgs a) {
 // ---- step 2 for a one-token chunk (decode) in one launch: one workgroup per (sequence, KV head) ----
 // The chunk is its own single query span, so Q^R is the group-summed query row rounded to the
 // stored precision. Scores as in score_kernel. The selection rule is the one of select_rank_kernel,
-// reached by sorting: eligible spans are sorted by (key, id) in LDS (bitonic network over the next
-// power of two), their clipped lengths are scanned in that order, and the selected set is the
-// prefix that fits. Spans: at most RT1_MAX_SPANS (the launcher checks its bound).
+// reached by comparing or counting the items (select_prefix). Spans: at most RT1_MAX_SPANS (the
+// launcher checks its bound).
 constexpr int RT1_MAX_SPANS = 8192;
 constexpr uint32_t RT1_PAD = 0xffffffffu;
 __host__ __device__ constexpr int rt1_pow2(int n) { int m = 64; while (m < n) m <<= 1; return m; }
@@ -875,7 +874,10 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   auto score_batch = [&](auto uc, int i00) {
     constexpr int U = decltype(uc)::value;
     // the query's elements are read from LDS once for all spans of the thread (when every span had its own reads, in
-    // fp64, they bounded this loop: launch over 81 spans 13.9 us, now 12.2; 604 spans, 16 sequences 21.7 and 21.1)
+    // fp64, they bounded this loop: launch over 81 spans 13.9 us, now 12.2; 604 spans, 16 sequences 21.7 and 21.1).
+    // Spans past 256 * PASSES are requested after the first ones are used. With the vectors out of the caches, 16
+    // sequences, the launch with three spans in flight and the sorted selection against this one (us, with the events
+    // around it): 500 spans 27.7 and 24.2, 604 34.1 and 26.5, 760 35.7 and 27.4, 1200 59.3 and 34.8.
     double accs[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) accs[u] = 0.0;
@@ -931,10 +933,10 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
 }
 
 // ---- step 2 of a long chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
-//      in Eq. 9), the budgeted selection by sorting and the lists. gridDim.x = (sequence, KV head) problems;
+//      in Eq. 9), the budgeted selection and the lists. gridDim.x = (sequence, KV head) problems;
 //      the gridDim.y workgroups of a problem share its scoring in tiles of 16 spans, so that the stored vectors
 //      stream in and are multiplied on many compute units, and the one that finishes last (a ticket counter, left at zero again)
-//      sorts and writes the lists. Q^R is either in place (qrep_partial_kernel) or, with qrep_from_sums, built
+//      selects (select_prefix) and writes the lists. Q^R is either in place (qrep_partial_kernel) or, with qrep_from_sums, built
 //      here from the running sums of the chunk's query rows, two rows per query span, and so are, with rs.k_arena, the
 //      mean keys of the chunk's own spans (Sec. 3.3.1): every workgroup of a problem writes the same values to
 //      the same places and reads its own copy back after a barrier. head_dim 128, spans retrieved (not units), at
@@ -1261,7 +1263,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   a.units_cap = n_q / QREP_PIECE + n_q;                  // pieces of all spans of a chunk, at most
   // Long chunks of 128-wide heads with spans as the retrieval unit: after the pieces' sums everything else of the
   // step is one launch per batch of sequences (retrieve_chunk_kernel).
-  // (its sort arrays share the 160 KB of LDS with 42 KB of staging and list scratch)
+  // (its arrays of keys, ids and lengths share the 160 KB of LDS with 26 KB of masks and list scratch)
   const bool one_tail = n_q > QREP_PIECE && D.d == 128 && D.unit == 0 && !votes && span_bound >= 1 &&
                         span_bound <= RT1_MAX_SPANS && rt1_lds_bytes(span_bound) <= 116 * 1024;
   if (one_tail) {
