@@ -7,12 +7,12 @@
 // over both KS and 1 .. 16 splits is taken. Its constants (us): a stage 1.5 on a nearly empty chip .. 1.85 on a full one
 // (the clock falls), 7 % more with KS = 2, 4 to start and drain a workgroup, 5 + 1.7e-4 per partial row for the merge (with
 // the write-back of the rows at the end of the kernel).
-// Measured at 77 launches (32, 64, 16 and 8 query heads on 8 or 2 KV heads, 1 to 8 sequences, 64 to 2048 rows behind 1500 to
-// 12300 context tokens) in every shape: the model is 4 % low with 8 % of scatter, what it takes is 1.6 % above the best
-// shape in the geometric mean, and never slower than one group without splits, which all launches were before. That one
-// against what is taken, context + rows, 32 heads: 12292 + 1024 337 -> 230 (two groups), 2052 + 700 77 -> 50, four
-// sequences of 2052 + 256 74 -> 51, 12292 + 512 316 -> 126 (two groups, two splits), 2052 + 128 63 -> 24. A full chip keeps
-// one group (12292 + 2048: 438 against 463 with two, 2052 + 2048: 119 against 125).
+// Measured at 173 launches (64, 32, 16 and 8 query heads on 8 or 2 KV heads, 1 to 16 sequences, 64 to 2048 rows behind up to
+// 12300 context tokens; profiles/attend_shapes.txt) in every shape: the model is 8 % low with 11 % of scatter, what it takes is
+// 1.1 % above the best shape in the geometric mean, and never slower than one group without splits, which all launches were
+// before. That one against what is taken, context + rows, 32 heads: 12292 + 1024 337 -> 230 (two groups), 2052 + 700
+// 77 -> 50, four sequences of 2052 + 256 74 -> 51, 12292 + 512 316 -> 126 (two groups, two splits), 2052 + 128 63 -> 24,
+// 0 + 700 23 -> 20. A full chip keeps one group (12292 + 2048: 438 against 463 with two, 2052 + 2048: 119 against 125).
 #pragma once
 #include <math.h>
 #include <stddef.h>
@@ -37,10 +37,10 @@ inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx,
   for (int ks = 1; ks <= 2; ++ks) {
     const int rs = ATT_NW / ks / HG, rpb = 32 * rs;
     const long long blocks = (long long)Hkv * (G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
-    // The causal part: a workgroup's last row is anywhere in the chunk (one sub-tile of 32 rows each, the last ones start
-    // first) or in its upper half (sub-tiles paired from both ends), and the longest walks set the pace.
-    const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * (rs == 1 ? 0.75f : 0.85f);
     for (int ns = 1; ns <= ATT_MAX_SPLITS; ++ns) {
+      // The causal part: workgroups end at rows all over the chunk or its upper half. In a single round the longest walks
+      // set the pace, in several they average out.
+      const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * (blocks * ns > n_cus ? 0.75f : 0.85f);
       const size_t rows = (size_t)seq_count * Hq * n_q * ns;
       if (ns > 1 && (rows > part_rows || ns * ks > tiles)) break;
       const long long rounds = (blocks * ns + n_cus - 1) / n_cus;

@@ -47,10 +47,11 @@ def shapes(tmp_path_factory):
 
 
 def test_launches_that_one_group_serves_best_keep_it(shapes):
-    """Measured at 32 query and 8 KV heads: two groups (2052 context tokens) or two groups and two splits (12292) took 1 to
-    5 % longer here than one group without splits. (The last number: room as in a context of long chunks.)"""
+    """Measured at 32 and 64 query and 8 KV heads: two groups (2052 context tokens, none) or two groups and two splits (12292)
+    took 1 to 7 % longer here than one group without splits. (The last number: room as in a context of long chunks.)"""
     launches = [(32, 8, 1, rows, ctx, -1) for rows, ctx in
                 [(1900, 2052), (2048, 2052), (1100, 12292), (1200, 12292), (1400, 12292), (1536, 12292), (2048, 12292)]]
+    launches.append((64, 8, 1, 2048, 0, -1))
     assert shapes(launches) == [(1, 1)] * len(launches)
 
 
