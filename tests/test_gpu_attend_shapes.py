@@ -147,6 +147,24 @@ def test_every_key_counts_once(gpu_device, hq, hkv, seqs, window, budget, histor
     assert ctx.sync_status() == 0
 
 
+def test_step_timing_covers_the_merge(gpu_device):
+    """Steps whose attention is split: a record each, from the start of the attention to the end of the merge behind it."""
+    w = Workload("timing", 32, 8, 128, "bf16", 8192, 1024, 4, 1024, 0, 1024, "uniform", 16, 96)
+    ctx = LtriContext(config_from_workload(w, theta=theta_default(128), n_layers=1, n_seqs=1), gpu_device)
+    K, V, Q, _ = planted_stream(w, 3, device=str(gpu_device), context=8192)
+    ka, va = ctx.arena_views()
+    ka[0, 0], va[0, 0] = K, V
+    ctx.set_step_timing(True)
+    sizes, at = [1024] * 4 + [128] * 8, 0
+    for n in sizes:
+        ctx.step(0, 0, 1, None, None, Q[at:at + n].contiguous())
+        at += n
+    ms, rest = ctx.read_step_timing()
+    assert len(ms) == len(sizes) and not rest.any()
+    # between a launch over one tile and a millisecond, which is ten times what any of them takes
+    assert bool((ms > 2e-3).all()) and bool((ms[1:] < 1.0).all()), ms
+
+
 def test_rounding_of_a_batch(gpu_device):
     """A launch is shaped by all of its sequences, so the same chunk rounds differently alone, in a batch and beside a longer
     neighbour; each time it is within the rounding of bf16 of the exact result, and the same tokens are attended."""
