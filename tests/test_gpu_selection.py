@@ -88,3 +88,37 @@ def test_selection_around_its_method_changes(gpu_device, dtype, kind, n_spans):
             listed = list(range(min(SINK, here))) + tokens + list(range(max(SINK, here - WINDOW), here))
             assert list(ctx.get_token_list(0, 0, 0)) == listed
         assert ctx.sync_status() == 0
+
+
+@pytest.mark.parametrize("kind", ["spread", "tied", "outlier"])
+@pytest.mark.parametrize("n_units", [63, 256, 257, 1025, 2300])
+def test_selection_of_memory_units(gpu_device, kind, n_units):
+    """The same with units (of one token, so that a unit's score is its token's): the selection runs over unit ids."""
+    rng = np.random.default_rng(n_units)
+    T = n_units + WINDOW + CHUNK + 8
+    sign = torch.from_numpy(rng.choice([-1.0, 1.0], 128))
+    val = span_values(kind, n_units, rng)
+    rows = torch.from_numpy(val)[:, None] * sign[None, :]
+    one_each = lambda n: [np.arange(n + 1)]
+    for k_max, budget in ((7, 0), (0, n_units // 3 + 1), (n_units // 2 + 1, n_units // 4 + 2), (0, T)):
+        w = Workload("mini-units", 4, 1, 128, "bf16", T, CHUNK, SINK, WINDOW, k_max, budget, "uniform", 16, 128)
+        ctx = LtriContext(config_from_workload(w, n_layers=1, max_tokens=T, theta=1e30, max_spans=T, unit_tokens=1), gpu_device)
+        ka, va = ctx.arena_views()
+        ka.zero_(), va.zero_()
+        ka[0, 0, 0, :n_units].copy_(rows.to(torch.bfloat16))
+        for n in (1, CHUNK):
+            ctx.reset(0)
+            for at in range(0, n_units, CHUNK):
+                m = min(CHUNK, n_units - at)
+                ctx.append_chunk_with_spans(0, 0, m, one_each(m))
+            ctx.append_chunk_with_spans(0, 0, WINDOW, one_each(WINDOW))
+            ctx.append_chunk_with_spans(0, 0, n, one_each(n))
+            q = sign.to(torch.bfloat16).to(gpu_device).expand(1, n, 4, 128).contiguous()
+            ctx.retrieve(0, 0, 1, q)
+            clip = (np.arange(n_units) >= SINK).astype(int)
+            want = select_reference(val, clip, k_max, budget)
+            ids, _ = ctx.get_selection(0, 0, 0)
+            assert list(ids) == want, (k_max, budget, n)
+            here = n_units + WINDOW
+            assert list(ctx.get_token_list(0, 0, 0)) == list(range(SINK)) + want + list(range(here - WINDOW, here))
+        assert ctx.sync_status() == 0
