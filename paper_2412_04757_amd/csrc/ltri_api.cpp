@@ -157,7 +157,7 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   CL.rcar = o;   o = align_up(o + (size_t)P * nb * Lp * 8, 256);
   CL.ccar = o;   o = align_up(o + (size_t)P * nb * Lp * 8, 256);
   CL.pscore = o; o = align_up(o + (size_t)P * nt * 128 * 8, 256);
-  CL.px = o;     o = align_up(o + (size_t)P * nt * 128 * 4, 256);
+  CL.px = o;     o = align_up(o + (size_t)P * nt * 128, 256);
   CL.ckey = o;   o = align_up(o + (size_t)P * SEG_MAX_DIAG * 8, 256);
   CL.cxy = o;    o = align_up(o + (size_t)P * SEG_MAX_DIAG * 4, 256);
   CL.lse = o;    o = align_up(o + (size_t)P * G * Lp * 8, 256);
@@ -261,7 +261,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   char* t = c->scratch;
   c->dc = DevScratch{(double*)(t + CL.rowsum), (double*)(t + CL.csuf), (double*)(t + CL.tsum),
                      (double*)(t + CL.rcar), (double*)(t + CL.ccar), (double*)(t + CL.pscore),
-                     (int32_t*)(t + CL.px), (uint64_t*)(t + CL.ckey), (uint32_t*)(t + CL.cxy), (double*)(t + CL.lse), (void*)(t + CL.qrep),
+                     (int8_t*)(t + CL.px), (uint64_t*)(t + CL.ckey), (uint32_t*)(t + CL.cxy), (double*)(t + CL.lse), (void*)(t + CL.qrep),
                      (double*)(t + CL.qpart), (int32_t*)(t + CL.bounds), (uint8_t*)(t + CL.selflag), (float*)(t + CL.att_part),
                      (int32_t*)(t + CL.tokspan), (double*)(t + CL.dyn), (double*)(t + CL.lpart),
                      (uint32_t*)(t + CL.qhist), (unsigned long long*)(t + CL.qstate),
@@ -376,9 +376,9 @@ int32_t ltri_reset(ltri_ctx* c, int32_t seq) {
   return LTRI_OK;
 }
 
-// host_rows_later: the caller has the chunk's rows written to the host arenas itself (host-offloaded KV).
+// Checks of an append; positions of the sequences to bp.
 static int32_t append_common(ltri_ctx* c, int layer, int seq_begin, int seq_count, const void* k_chunk,
-                             const void* v_chunk, int n_new, BatchPos& bp, bool host_rows_later = false) {
+                             const void* v_chunk, int n_new, BatchPos& bp) {
   int32_t r = check_range(c, layer, seq_begin, seq_count);
   if (r != LTRI_OK) return r;
   if (n_new < 1 || n_new > c->D.chunk_max)
@@ -395,13 +395,23 @@ static int32_t append_common(ltri_ctx* c, int layer, int seq_begin, int seq_coun
     bp.seq[s] = seq_begin + s;
     bp.c0[s] = (int32_t)c->n_tokens[i];
   }
-  if (k_chunk && !c->dry) {
-    r = check_hip(c, launch_copy_chunk(c->D, c->k_arena, c->v_arena, k_chunk, v_chunk, layer, bp, seq_count,
-                                       n_new, host_rows_later ? nullptr : c->k_host, host_rows_later ? nullptr : c->v_host,
-                                       c->stream), "copy chunk");
-    if (r != LTRI_OK) return r;
-  }
   return LTRI_OK;
+}
+
+// The caller's rows and the device's places for them; host_rows: the host arenas as well (host-offloaded KV).
+static ChunkRows chunk_rows(const ltri_ctx* c, const void* k_chunk, const void* v_chunk, bool host_rows) {
+  ChunkRows r;
+  r.k_chunk = k_chunk; r.v_chunk = v_chunk;
+  r.k_arena = c->k_arena; r.v_arena = c->v_arena;
+  if (host_rows) { r.k_host = c->k_host; r.v_host = c->v_host; }
+  return r;
+}
+
+static int32_t copy_chunk(ltri_ctx* c, int layer, const BatchPos& bp, int seq_count, const void* k_chunk, const void* v_chunk,
+                          int n_new, bool host_rows) {
+  if (!k_chunk || c->dry) return LTRI_OK;
+  return check_hip(c, launch_copy_chunk(c->D, chunk_rows(c, k_chunk, v_chunk, host_rows), layer, bp, seq_count, n_new, c->stream),
+                   "copy chunk");
 }
 
 static void append_commit(ltri_ctx* c, int layer, int seq_begin, int seq_count, int n_new) {
@@ -414,17 +424,23 @@ static void append_commit(ltri_ctx* c, int layer, int seq_begin, int seq_count, 
   }
 }
 
-// Step 1 of a chunk whose rows are already in the arenas: segmentation and index vectors. `fork` (or NULL)
+// Step 1 of a chunk: segmentation and index vectors. Its rows are in the arenas already, or (src) a launch of the segmentation
+// copies them there. `fork` (or NULL)
 // is recorded on the context's stream behind the last kernel that fills the chip; what follows it there
 // are kernels of a few workgroups each.
 // q_step2 (or NULL): the query rows that step 2 will be called with right after; *sums_ready then says whether the
 // running sums it reads were taken along by the segmentation's first launch.
 static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_count, const void* q_seg, int n_new,
-                            hipEvent_t fork, bool rep_keys_later = false, const void* q_step2 = nullptr,
+                            hipEvent_t fork, const ChunkRows* src, bool rep_keys_later = false, const void* q_step2 = nullptr,
                             bool* sums_ready = nullptr) {
   int32_t r;
+  if (src && !src->k_chunk) src = nullptr;
   if (sums_ready) *sums_ready = false;
   if (n_new == 1) {
+    if (src) {
+      r = check_hip(c, launch_copy_chunk(c->D, *src, layer, bp, seq_count, 1, c->stream), "copy chunk");
+      if (r != LTRI_OK) return r;
+    }
     r = check_hip(c, launch_append_single(c->D, c->ds, c->k_arena, layer, bp, seq_count, c->stream),
                   "append (single token)");
     if (r == LTRI_OK && fork) r = check_hip(c, hipEventRecord(fork, c->stream), "fork");
@@ -441,7 +457,7 @@ static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_
     const int cnt = std::min(per, seq_count - off);
     const bool last = off + per >= seq_count;
     r = check_hip(c, launch_segment(c->D, c->ds, c->dc, c->k_arena, q_seg, layer, bp, off, cnt, n_new,
-                                    last && !dynamic ? fork : nullptr, with_sums ? &sums : nullptr, c->stream), "segment");
+                                    last && !dynamic ? fork : nullptr, with_sums ? &sums : nullptr, src, c->stream), "segment");
     if (r != LTRI_OK) return r;
     if (dynamic) {
       r = check_hip(c, launch_dynamic_reps(c->D, c->ds, c->dc, c->k_arena, q_seg, layer, bp, off, cnt, n_new,
@@ -467,7 +483,12 @@ int32_t ltri_append_chunk(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t
   int32_t r = append_common(c, layer, seq_begin, seq_count, k_chunk, v_chunk, n_new, bp);
   if (r != LTRI_OK) return r;
   if (!c->dry) {
-    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr);
+    // rows for host arenas leave in a launch of their own: writes over the host link would hold up the others
+    const bool own_copy = c->D.offload != 0;
+    if (own_copy) r = copy_chunk(c, layer, bp, seq_count, k_chunk, v_chunk, n_new, true);
+    if (r != LTRI_OK) return r;
+    const ChunkRows src = chunk_rows(c, k_chunk, v_chunk, false);
+    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, own_copy ? nullptr : &src);
     if (r != LTRI_OK) return r;
   }
   append_commit(c, layer, seq_begin, seq_count, n_new);
@@ -500,6 +521,8 @@ int32_t ltri_append_chunk_with_spans(ltri_ctx* c, int32_t layer, int32_t seq, co
   int32_t r = append_common(c, layer, seq, 1, k_chunk, v_chunk, n_new, bp);
   if (r != LTRI_OK) return r;
   if (!c->dry) {
+    r = copy_chunk(c, layer, bp, 1, k_chunk, v_chunk, n_new, true);
+    if (r != LTRI_OK) return r;
     r = check_hip(c, hipMemcpyAsync(c->dc.bounds, staged.data(), staged.size() * 4, hipMemcpyHostToDevice,
                                     c->stream), "copy boundaries");
     if (r != LTRI_OK) return r;
@@ -551,7 +574,7 @@ static int32_t retrieve_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int3
     long long bound = 0;
     for (int s = 0; s < seq_count; ++s) bound = std::max(bound, c->span_bound[ls_index(c, layer, seq_begin + s)]);
     r = check_hip(c, launch_retrieve(c->D, c->ds, c->dc, c->CL.max_problems, q, layer, bp, seq_count, n_q, (int)bound, sel_ids,
-                                     sel_cnt, nullptr, nullptr, store_rep_keys ? c->k_arena : nullptr, sums_ready, c->stream),
+                                     sel_cnt, nullptr, nullptr, nullptr, store_rep_keys ? c->k_arena : nullptr, sums_ready, c->stream),
                   "retrieve");
     if (r != LTRI_OK) return r;
     if (fork) {
@@ -606,7 +629,7 @@ int32_t ltri_retrieve_collaborative(ltri_ctx* c, int32_t layer, int32_t seq_begi
     long long bound = 0;
     for (int s = 0; s < seq_count; ++s) bound = std::max(bound, c->span_bound[ls_index(c, layer, seq_begin + s)]);
     r = check_hip(c, launch_retrieve(c->D, c->ds, c->dc, c->CL.max_problems, q, layer, bp, seq_count, n_q, (int)bound,
-                                     sel_ids, sel_cnt, &v, nullptr, nullptr, false, c->stream), "collaborative retrieve");
+                                     sel_ids, sel_cnt, &v, nullptr, nullptr, nullptr, false, c->stream), "collaborative retrieve");
     if (r != LTRI_OK) return r;
     r = fetch_retrieved(c, layer, bp, seq_count);
     if (r != LTRI_OK) return r;
@@ -805,10 +828,16 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     long long bound = 0;
     for (int s = 0; s < seq_count; ++s)
       bound = std::max(bound, std::min<long long>(c->span_bound[ls_index(c, layer, seq_begin + s)] + 1, c->D.max_spans));
+    // Resident rows are copied by the launch of steps 1 and 2 (a launch of its own for 512 bytes a head took 4 us and a gap).
+    const ChunkRows src = chunk_rows(c, k_chunk, v_chunk, false);
+    const bool own_copy = c->D.offload != 0;
+    if (own_copy) r = copy_chunk(c, layer, bp, seq_count, k_chunk, v_chunk, 1, true);
+    if (r != LTRI_OK) return r;
     if (retrieve_is_one_launch(c->D, 1, (int)bound)) {
       append_commit(c, layer, seq_begin, seq_count, 1);
       r = check_hip(c, launch_retrieve(c->D, c->ds, c->dc, c->CL.max_problems, q, layer, bp, seq_count, 1, (int)bound,
-                                       nullptr, nullptr, nullptr, c->k_arena, nullptr, false, c->stream), "append and retrieve (one token)");
+                                       nullptr, nullptr, nullptr, c->k_arena, k_chunk && !own_copy ? &src : nullptr, nullptr, false, c->stream),
+                    "append and retrieve (one token)");
       if (r != LTRI_OK) return r;
       r = fetch_retrieved(c, layer, bp, seq_count);
       if (r != LTRI_OK) return r;
@@ -817,7 +846,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
         c->ever_sel[ls_index(c, layer, seq_begin + s)] = 0xFFFFFFFFu;
       }
     } else {
-      r = append_spans(c, layer, bp, seq_count, q_seg, 1, nullptr);
+      r = append_spans(c, layer, bp, seq_count, q_seg, 1, nullptr, own_copy ? nullptr : &src);
       if (r != LTRI_OK) return r;
       append_commit(c, layer, seq_begin, seq_count, 1);
       r = ltri_retrieve(c, layer, seq_begin, seq_count, q, 1, nullptr, nullptr);
@@ -834,9 +863,10 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   }
   BatchPos bp;
   memset(&bp, 0, sizeof bp);
-  int32_t r = append_common(c, layer, seq_begin, seq_count, k_chunk, v_chunk, n_new, bp, c->D.offload != 0);
+  int32_t r = append_common(c, layer, seq_begin, seq_count, k_chunk, v_chunk, n_new, bp);
   if (r != LTRI_OK) return r;
   const bool keys_with_step2 = retrieve_stores_rep_keys(c->D, n_new);
+  const ChunkRows src = chunk_rows(c, k_chunk, v_chunk, false);        // (offloaded: the fetch's launch writes the host rows)
   StepTiming timing(c);
   bool sums_ready = false;               // step 2's running sums of the query and key rows ride in step 1's first launch
   if (!c->D.offload) {
@@ -844,7 +874,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     // attention is one launch over initial | retrieved | window | chunk. Its workgroups are equal in work (row
     // sub-tiles paired from both ends of the chunk) and fill every compute unit, so a split that runs the first
     // part beside the small kernels of steps 1 and 2 only makes those wait for a free compute unit.
-    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, keys_with_step2, q, &sums_ready);
+    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, &src, keys_with_step2, q, &sums_ready);
     if (r != LTRI_OK) return r;
     append_commit(c, layer, seq_begin, seq_count, n_new);
     r = retrieve_impl(c, layer, seq_begin, seq_count, q, n_new, nullptr, nullptr, keys_with_step2, sums_ready);
@@ -873,15 +903,14 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   auto both_streams = [&]() -> int32_t {
     int32_t e = check_hip(c, launch_local_list(c->D, bp, seq_count, c->dc.loclist, c->CL.loc_cap, c->stream), "local list");
     if (e != LTRI_OK) return e;
-    e = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, keys_with_step2, q, &sums_ready);
+    e = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, &src, keys_with_step2, q, &sums_ready);
     if (e != LTRI_OK) return e;
     append_commit(c, layer, seq_begin, seq_count, n_new);
     side_queued = true;                  // (from here on the second stream may hold work of this step)
     e = retrieve_impl(c, layer, seq_begin, seq_count, q, n_new, nullptr, nullptr, keys_with_step2, sums_ready, c->ev_fork,
                       c->side, k_chunk, v_chunk);
     if (e != LTRI_OK) {                  // the tokens count already: their host rows must not be missing
-      (void)launch_copy_chunk(c->D, c->k_arena, c->v_arena, k_chunk, v_chunk, layer, bp, seq_count, n_new, c->k_host,
-                              c->v_host, c->stream);
+      (void)copy_chunk(c, layer, bp, seq_count, k_chunk, v_chunk, n_new, true);
       return e;
     }
     e = timing_mark(c, c->stream);

@@ -60,7 +60,7 @@ struct ScratchLayout {
   size_t rcar;     // double [P][nb][Lp]   row carry  RC[J][i]
   size_t ccar;     // double [P][nb][Lp]   column carry A[I][x]
   size_t pscore;   // double [P][ntiles][128]
-  size_t px;       // int32  [P][ntiles][128]
+  size_t px;       // int8   [P][ntiles][128]  column inside the tile, -1: none
   size_t ckey;     // uint64 [P][SEG_MAX_DIAG]  merged candidates: order key per anti-diagonal
   size_t cxy;      // uint32 [P][SEG_MAX_DIAG]  x << 16 | y
   size_t lse;      // double [P][G][Lp]    (SOFTMAX map only)
@@ -134,7 +134,7 @@ struct DevState {
 };
 struct DevScratch {
   double* rowsum; double* csuf; double* tsum; double* rcar; double* ccar;
-  double* pscore; int32_t* px; uint64_t* ckey; uint32_t* cxy; double* lse; void* qrep; double* qpart; int32_t* bounds; uint8_t* selflag; float* att_part;
+  double* pscore; int8_t* px; uint64_t* ckey; uint32_t* cxy; double* lse; void* qrep; double* qpart; int32_t* bounds; uint8_t* selflag; float* att_part;
   int32_t* tokspan; double* dyn; double* lpart; uint32_t* qhist; unsigned long long* qstate;
   float* att_lse2; int32_t* loclist;
   unsigned long long* qlist;
@@ -145,7 +145,8 @@ struct DevScratch {
 // representatives reads instead of summing the rows of every span.
 struct RunSums {
   const void* q;         // [seq][n_q][Hq][128] query rows of the chunk
-  const void* k_arena;   // key rows (the chunk's are in place), or NULL: no running sums of keys
+  const void* k_arena;   // key rows, or NULL: no running sums of keys
+  const void* k_chunk;   // the chunk's key rows as the caller passed them (not in the arena yet), or NULL: they are in place
   double* out;           // [problem][rows][128]
   size_t keys_off;       // elements from the query rows' sums to the key rows'
   int n_q;
@@ -157,18 +158,24 @@ bool retrieve_reads_running_sums(const Dims& D, int n_q);
 inline RunSums running_sums_of(const Dims& D, const DevScratch& sc, int sc_max_problems, const void* q,
                                const void* k_arena, int n_q) {
   RunSums r;
-  r.q = q; r.k_arena = k_arena; r.out = sc.qpart; r.n_q = n_q;
+  r.q = q; r.k_arena = k_arena; r.k_chunk = nullptr; r.out = sc.qpart; r.n_q = n_q;
   r.rows = n_q / 128 + n_q;
   r.keys_off = (size_t)sc_max_problems * r.rows * D.d;
   return r;
 }
 
+// A chunk's rows as the caller passes them, [sequence][KV head][token][d], and where they go: the arenas (offloaded KV: the
+// device pools) and, unless NULL, the host arenas of an offloaded context.
+struct ChunkRows {
+  const void* k_chunk = nullptr; const void* v_chunk = nullptr;
+  void* k_arena = nullptr; void* v_arena = nullptr;
+  void* k_host = nullptr; void* v_host = nullptr;
+};
+
 // ---- launchers (each returns the hipError_t of the launch) ----
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
-// k_host / v_host: the host arenas of an offloaded context, which get the rows as well, or NULL
-hipError_t launch_copy_chunk(const Dims& D, void* k_arena, void* v_arena, const void* k_chunk,
-                             const void* v_chunk, int layer, const BatchPos& bp, int seq_count,
-                             int n_new, void* k_host, void* v_host, hipStream_t s);
+hipError_t launch_copy_chunk(const Dims& D, const ChunkRows& src, int layer, const BatchPos& bp, int seq_count, int n_new,
+                             hipStream_t s);
 // host-offloaded KV: rows of the retrieved tokens of the current list, host arenas -> device pool; with k_chunk / v_chunk
 // (both or neither) the same launch writes the n_new rows of the chunk at bp out to the host arenas
 hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_pool, void* v_pool, void* k_host,
@@ -176,9 +183,9 @@ hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_poo
                                   const void* v_chunk, int n_new, hipStream_t s);
 hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                           const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                          int n_new, hipEvent_t after_tiles, const RunSums* sums, hipStream_t s);
+                          int n_new, hipEvent_t after_tiles, const RunSums* sums, const ChunkRows* src, hipStream_t s);
 // event (or NULL): recorded behind the last kernel that fills the chip; sums (or NULL): further workgroups of the
-// first tile launch take these running sums
+// selections' launch take these running sums; src (or NULL): rows of the chunk that the selections' launch copies
 hipError_t launch_append_single(const Dims& D, const DevState& st, const void* k_arena, int layer,
                                 const BatchPos& bp, int seq_count, hipStream_t s);
 hipError_t launch_append_bounds(const Dims& D, const DevState& st, const DevScratch& sc, int layer,
@@ -191,8 +198,9 @@ hipError_t launch_rep_keys(const Dims& D, const DevState& st, const void* k_aren
 hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& sc, int sc_max_problems,
                            const void* q, int layer, const BatchPos& bp, int seq_count, int n_q, int span_bound,
                            int32_t* sel_ids_out, int32_t* sel_cnt_out, const VoteArgs* votes, const void* append_k_arena,
-                           const void* rep_k_arena, bool sums_ready, hipStream_t s);
-// append_k_arena (or NULL): a one-token chunk's step 1 runs in the same launch; rep_k_arena (or NULL): the step
+                           const ChunkRows* src, const void* rep_k_arena, bool sums_ready, hipStream_t s);
+// append_k_arena (or NULL): a one-token chunk's step 1 runs in the same launch, which copies the rows of src (or NULL) as
+// well; rep_k_arena (or NULL): the step
 // also stores the chunk's mean keys (only where retrieve_stores_rep_keys says so); sums_ready: the running sums of
 // running_sums_of(D, sc, sc_max_problems, q, rep_k_arena, n_q) are in place (one batch of sequences only)
 bool retrieve_stores_rep_keys(const Dims& D, int n_q);

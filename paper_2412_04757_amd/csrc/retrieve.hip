@@ -18,7 +18,8 @@ struct RetArgs {
   int layer; int seq_count; int n_q; int Lp;
   int batch_off; int units_cap;          // two-stage query representatives (long chunks)
   int32_t* sel_ids_out; int32_t* sel_cnt_out;
-  const void* k_arena; int append_first;  // one-token chunk: step 1 (the token becomes a span of its own) in the same launch
+  const void* k_arena; int append_first;  // one-token chunk: step 1 (the token becomes a span of its own) in the same launch,
+  ChunkRows src;                          // after the caller's rows (or NULL) are copied into the arenas (resident KV)
   const void* rep_k_arena;                // not NULL: the launch of the query-span pieces also stores the chunk's mean keys
   int qrep_by_last;                       // the last workgroup of the pieces' launch adds them up into Q^R
   int ticket_base;                        // first ticket counter of retrieve_chunk_kernel's problems
@@ -808,9 +809,15 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
     c0 = a.bp.c0[bi];
     const bool fits = base + 1 <= D.max_spans;
     __syncthreads();                                    // every thread has read the old count
-    if (fits && tid < d) {
-      const T* row = reinterpret_cast<const T*>(a.k_arena) + arena_off(D, slot) + (size_t)chunk_tok_row(D, c0, c0) * d;
-      (reinterpret_cast<T*>(a.st.krep) + ((size_t)slot * D.max_spans + base) * d)[tid] = row[tid];
+    const size_t row_off = arena_off(D, slot) + (size_t)chunk_tok_row(D, c0, c0) * d;
+    if (tid < d) {
+      const T* row = a.src.k_chunk ? reinterpret_cast<const T*>(a.src.k_chunk) + (size_t)p * d
+                                   : reinterpret_cast<const T*>(a.k_arena) + row_off;
+      const T key = row[tid];
+      if (fits) (reinterpret_cast<T*>(a.st.krep) + ((size_t)slot * D.max_spans + base) * d)[tid] = key;
+      if (a.src.k_chunk) (reinterpret_cast<T*>(a.src.k_arena) + row_off)[tid] = key;
+    } else if (tid < 2 * d && a.src.k_chunk) {
+      (reinterpret_cast<T*>(a.src.v_arena) + row_off)[tid - d] = (reinterpret_cast<const T*>(a.src.v_chunk) + (size_t)p * d)[tid - d];
     }
     if (tid == 0) {
       if (fits) {
@@ -1229,10 +1236,12 @@ bool retrieve_stores_rep_keys(const Dims& D, int n_q) {
 hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& sc, int sc_max_problems,
                            const void* q, int layer, const BatchPos& bp, int seq_count, int n_q, int span_bound,
                            int32_t* sel_ids_out, int32_t* sel_cnt_out, const VoteArgs* votes, const void* append_k_arena,
-                           const void* rep_k_arena, bool sums_ready, hipStream_t s) {
+                           const ChunkRows* src, const void* rep_k_arena, bool sums_ready, hipStream_t s) {
   RetArgs a;
   a.D = D; a.st = st; a.sc = sc; a.q = q; a.layer = layer; a.seq_count = seq_count; a.n_q = n_q;
   a.k_arena = append_k_arena; a.append_first = append_k_arena != nullptr;
+  if (src && (!a.append_first || D.offload)) return hipErrorInvalidValue;
+  if (src) a.src = *src;
   a.rep_k_arena = rep_k_arena;
   a.qrep_by_last = false; a.ticket_base = 0; a.qrep_from_sums = 0;
   a.rs = RunSums{};
@@ -1386,8 +1395,7 @@ __global__ __launch_bounds__(1024) void persist_list_kernel(RetArgs a) {
 
 hipError_t launch_persist_list(const Dims& D, const DevState& st, int layer, const BatchPos& bp, int seq_count,
                                hipStream_t s) {
-  RetArgs a;
-  memset(&a, 0, sizeof a);
+  RetArgs a{};
   a.D = D; a.st = st; a.layer = layer; a.seq_count = seq_count; a.bp = bp;
   persist_list_kernel<<<seq_count * D.Hkv, 1024, 0, s>>>(a);
   return hipGetLastError();

@@ -37,7 +37,9 @@ __device__ __forceinline__ void running_sums_one(const Dims& D, const BatchPos& 
   const int inner = keys ? 1 : D.G;                     // rows per token
   const size_t tok_stride = keys ? (size_t)d : (size_t)D.Hq * d;
   const uint16_t* base;
-  if (keys) {
+  if (keys && r.k_chunk) {
+    base = reinterpret_cast<const uint16_t*>(r.k_chunk) + (size_t)(bi * D.Hkv + h) * r.n_q * d + col;
+  } else if (keys) {
     const int c0 = bp.c0[bi];
     base = reinterpret_cast<const uint16_t*>(r.k_arena) + arena_off(D, slot_of(D, layer, bp.seq[bi], h)) +
            (size_t)chunk_tok_row(D, c0, c0) * d + col;

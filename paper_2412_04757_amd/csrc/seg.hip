@@ -22,6 +22,69 @@
 
 namespace ltri {
 
+// ---- copies of a caller's chunk into the arenas ----
+// Resident KV: the rows go to their tokens' places. Host-offloaded KV (Sec. 3.4 first step): the device keeps
+// only the initial tokens and a ring of the latest tokens; every row is also written to the host arenas
+// (device-visible pinned memory), from which step 3 fetches the rows it retrieves.
+struct CopyArgs { Dims D; ChunkRows src; int layer; int n_new; BatchPos bp; };
+
+constexpr int COPY_UNROLL = 4;         // 16-byte pieces of K and of V per thread in flight
+// Workgroups of `threads` threads per (sequence, KV head) that copy a chunk.
+inline int copy_chunk_wgs(const Dims& D, int n_new, int threads) {
+  const size_t n16 = (size_t)n_new * D.d * D.elt / 16, per = (size_t)threads * COPY_UNROLL;
+  const size_t w = (n16 + per - 1) / per;
+  return w < 1 ? 1 : w > 64 ? 64 : (int)w;
+}
+
+// Workgroup wg of n_wgs of sequence bi of the batch and KV head h.
+__device__ __forceinline__ void copy_chunk_rows(const Dims& D, const ChunkRows& src, int layer, const BatchPos& bp, int bi, int h,
+                                                int n_new, int wg, int n_wgs) {
+  const int slot = slot_of(D, layer, bp.seq[bi], h);
+  const int c0 = bp.c0[bi];
+  const size_t row_bytes = (size_t)D.d * D.elt;
+  const int r16 = (int)(row_bytes / 16);                     // 16-byte pieces per row
+  const size_t n16 = (size_t)n_new * r16;
+  const size_t dst_off = (arena_off(D, slot) + (size_t)chunk_tok_row(D, c0, c0) * D.d) * D.elt;
+  const size_t src_off = (size_t)(bi * D.Hkv + h) * n_new * row_bytes;
+  const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(src.k_chunk) + src_off);
+  const uint4* vs = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(src.v_chunk) + src_off);
+  uint4* kd = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.k_arena) + dst_off);
+  uint4* vd = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.v_arena) + dst_off);
+  const size_t slot_bytes = arena_off(D, slot) * D.elt;
+  uint4* kp = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.k_arena) + slot_bytes);     // row 0 of the slot's pool
+  uint4* vp = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.v_arena) + slot_bytes);
+  const size_t host_off = ((size_t)slot * (size_t)D.max_tokens + (size_t)c0) * row_bytes;
+  uint4* kh = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.k_host) + host_off);
+  uint4* vh = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.v_host) + host_off);
+  const int ring = D.ring_mask + 1, pos0 = c0 & D.ring_mask;
+  const size_t stride = (size_t)n_wgs * blockDim.x;
+  for (size_t i0 = (size_t)wg * blockDim.x + threadIdx.x; i0 < n16; i0 += COPY_UNROLL * stride) {
+    uint4 kv[COPY_UNROLL], vv[COPY_UNROLL];
+#pragma unroll
+    for (int u = 0; u < COPY_UNROLL; ++u) {
+      const size_t i = i0 + u * stride;
+      if (i < n16) { kv[u] = ks[i]; vv[u] = vs[i]; }
+    }
+#pragma unroll
+    for (int u = 0; u < COPY_UNROLL; ++u) {
+      const size_t i = i0 + u * stride;
+      if (i >= n16) continue;
+      kd[i] = kv[u]; vd[i] = vv[u];                          // in place, or the ring (running on into its mirror rows)
+      if (!D.offload) continue;
+      const int r = (int)(i / r16), piece = (int)(i - (size_t)r * r16);
+      if (pos0 + r >= ring) {                                // the part past the ring's end, again at its start
+        const size_t w = (size_t)(D.ring0 + pos0 + r - ring) * r16 + piece;
+        kp[w] = kv[u]; vp[w] = vv[u];
+      }
+      if (c0 + r < D.n_sink) {                               // initial tokens keep rows of their own
+        const size_t w = (size_t)(c0 + r) * r16 + piece;
+        kp[w] = kv[u]; vp[w] = vv[u];
+      }
+      if (src.k_host) { kh[i] = kv[u]; vh[i] = vv[u]; }      // host arenas: every token, in place
+    }
+  }
+}
+
 struct SegArgs {
   Dims D; DevState st; DevScratch sc;
   const void* k_arena; const void* q_seg;
@@ -30,7 +93,22 @@ struct SegArgs {
   int sum_wgs;     // further workgroups per problem of seg_select_kernel's launch that take running sums for step 2
   RunSums rs;
   unsigned long long quant_rank, quant_cells;   // percentile theta: rank of the cell and number of cells; cells 0: nothing to set up
+  // The caller's chunk, if any: everything up to the selection reads the key rows there, and copy_wgs further workgroups per
+  // problem of the selections' launch, which leaves most compute units idle, copy it into the arenas. As a launch of its own
+  // the copy took 5 us in front of everything else (256 to 1024 tokens); on workgroups of the first tile launch it made that
+  // 3 us longer.
+  ChunkRows src; int copy_wgs;
 };
+
+// The chunk's key rows of sequence bi of the batch, KV head h.
+template <typename T>
+__device__ __forceinline__ const T* chunk_keys(const SegArgs& a, int bi, int h) {
+  const Dims& D = a.D;
+  if (a.src.k_chunk) return reinterpret_cast<const T*>(a.src.k_chunk) + (size_t)(bi * D.Hkv + h) * a.n_new * D.d;
+  return reinterpret_cast<const T*>(a.k_arena) + arena_off(D, slot_of(D, a.layer, a.bp.seq[bi], h)) +
+         (size_t)chunk_tok_row(D, a.bp.c0[bi], a.bp.c0[bi]) * D.d;
+}
+
 
 __device__ __forceinline__ void tile_decode(int t, int& I, int& J) {
   int i = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
@@ -104,12 +182,10 @@ __device__ __forceinline__ void compute_tile(const SegArgs& a, int p, int I, int
   typedef typename Elt<DT>::type T;
   const Dims& D = a.D;
   const int sl = p / D.Hkv, h = p - sl * D.Hkv, bi = a.batch_off + sl;
-  const int seq = a.bp.seq[bi], c0 = a.bp.c0[bi];
   const int L = a.n_new, d = D.d;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wi = wave >> 1, wj = wave & 1, hf = lane >> 5, l32 = lane & 31;
-  const int slot = slot_of(D, a.layer, seq, h);
-  const T* Kc = reinterpret_cast<const T*>(a.k_arena) + arena_off(D, slot) + (size_t)chunk_tok_row(D, c0, c0) * d;
+  const T* Kc = chunk_keys<T>(a, bi, h);
   const T* Qb = a.q_seg ? reinterpret_cast<const T*>(a.q_seg) + (size_t)bi * L * D.Hq * d + (size_t)h * D.G * d : nullptr;
   const int n_h = a.q_seg ? D.G : 1;
   const int nkc = d * (int)sizeof(T) / 256;                  // 256-byte pieces per row
@@ -713,7 +789,7 @@ __global__ __launch_bounds__(256) void seg_tile_scan_kernel(SegArgs a) {
         if (ox >= 0 && (bx < 0 || ob >= best)) { best = ob; bx = ox; }
       }
       a.sc.pscore[((size_t)p * a.ntiles + blockIdx.x) * 128 + tid] = best;
-      a.sc.px[((size_t)p * a.ntiles + blockIdx.x) * 128 + tid] = bx >= 0 ? J * 64 + bx : -1;
+      a.sc.px[((size_t)p * a.ntiles + blockIdx.x) * 128 + tid] = (int8_t)bx;
     }
   }
 }
@@ -748,47 +824,64 @@ __device__ void append_spans(const Dims& D, const DevState& st, int slot, int c0
 }
 
 // Pass 3a: per anti-diagonal s = x + y, merge the tiles' partial results (ties: larger x =
-// shorter span) and keep the span if S > 0 (appendix "NMS Input Filtration"). One thread per
-// anti-diagonal, many workgroups per problem: the partial results are ~100 bytes per
-// anti-diagonal and tile, far more than one CU reads quickly. Output: an order key (ascending
-// key = descending score: positive doubles order like their bit patterns) and x << 16 | y.
-__global__ __launch_bounds__(256) void seg_merge_kernel(SegArgs a) {
-  const int p = blockIdx.y, nb = a.nb, L = a.n_new;
-  const int n_diag = 2 * L - 1;
-  const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s >= n_diag) return;
+// shorter span) and keep the span if S > 0 (appendix "NMS Input Filtration"). Result: an order key (ascending
+// key = descending score: positive doubles order like their bit patterns) and x << 16 | y. N consecutive anti-diagonals
+// s0 .. s0 + N - 1 (s0 a multiple of N) of problem p; at most MT tiles lie on one block anti-diagonal, and all
+// their entries are loaded before the comparison chain so that the loads are in flight together.
+template <int N, int MT>
+__device__ __forceinline__ void merge_diagonals(const SegArgs& a, int p, int s0, uint64_t (&key)[N], uint32_t (&xy)[N]) {
+  typedef double dN_t __attribute__((ext_vector_type(N)));
+  typedef int8_t cN_t __attribute__((ext_vector_type(N)));
+  const int nb = a.nb, n_diag = 2 * a.n_new - 1;
   const double* pscore = a.sc.pscore + (size_t)p * a.ntiles * 128;
-  const int32_t* px = a.sc.px + (size_t)p * a.ntiles * 128;
-  double best = -INFINITY;
-  int bx = -1;
-  const int b = s >> 6;
-  for (int bb = b; bb >= b - 1 && bb >= 0; --bb) {
-    const int sloc = s - 64 * bb;
-    if (sloc > 126 || bb > 2 * (nb - 1)) continue;          // (no tile has I + J > 2 (nb - 1))
-    // at most 16 tiles lie on one block anti-diagonal; all their entries are loaded before
-    // the comparison chain so that the loads are in flight together
-    const int J0 = max(0, bb - (nb - 1));
-    double vs[SEG_MAX_NB / 2];
-    int xs[SEG_MAX_NB / 2];
+  const int8_t* px = a.sc.px + (size_t)p * a.ntiles * 128;
+  double best[N];
+  int bx[N];
 #pragma unroll
-    for (int q = 0; q < SEG_MAX_NB / 2; ++q) {
-      const int J = J0 + q;
-      const bool ok = 2 * J <= bb;
-      const int Jc = ok ? J : J0, I = bb - Jc;
+  for (int e = 0; e < N; ++e) { best[e] = -INFINITY; bx[e] = -1; }
+  const int b = s0 >> 6;
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {                              // the block's own tiles, then those one block before
+    const int bb = b - w, sloc = s0 - 64 * bb;
+    if (s0 >= n_diag || bb < 0 || bb > 2 * (nb - 1)) continue;      // (no tile has I + J > 2 (nb - 1))
+    const int J0 = max(0, bb - (nb - 1));
+    dN_t vs[MT];
+    cN_t xs[MT];
+#pragma unroll
+    for (int q = 0; q < MT; ++q) {
+      const int J = J0 + q, Jc = 2 * J <= bb ? J : J0, I = bb - Jc;
       const size_t idx = (size_t)(I * (I + 1) / 2 + Jc) * 128 + sloc;
-      vs[q] = pscore[idx];
-      xs[q] = ok ? px[idx] : -1;
+      vs[q] = *reinterpret_cast<const dN_t*>(pscore + idx);
+      xs[q] = *reinterpret_cast<const cN_t*>(px + idx);
     }
 #pragma unroll
-    for (int q = 0; q < SEG_MAX_NB / 2; ++q) {
-      const double v = vs[q];
-      const int x = xs[q];
-      if (x >= 0 && (v > best || (v == best && x > bx))) { best = v; bx = x; }
+    for (int q = 0; q < MT; ++q) {
+      const int J = J0 + q;
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        const int xl = xs[q][e], x = 64 * J + xl;            // xl < 0: the tile has no cell there (nor at sloc = 127)
+        if (2 * J <= bb && xl >= 0 && (vs[q][e] > best[e] || (vs[q][e] == best[e] && x > bx[e]))) { best[e] = vs[q][e]; bx[e] = x; }
+      }
     }
   }
-  const bool is_cand = bx >= 0 && best > 0.0;
-  a.sc.ckey[(size_t)p * SEG_MAX_DIAG + s] = is_cand ? ~(uint64_t)__double_as_longlong(best) : ~0ull;
-  a.sc.cxy[(size_t)p * SEG_MAX_DIAG + s] = is_cand ? (((uint32_t)bx << 16) | (uint32_t)(s - bx)) : 0xFFFFFFFFu;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const bool is_cand = bx[e] >= 0 && best[e] > 0.0 && s0 + e < n_diag;
+    key[e] = is_cand ? ~(uint64_t)__double_as_longlong(best[e]) : ~0ull;
+    xy[e] = is_cand ? (((uint32_t)bx[e] << 16) | (uint32_t)(s0 + e - bx[e])) : 0xFFFFFFFFu;
+  }
+}
+
+// Chunks of more than MERGE_INLINE_NB tiles a side: one thread per anti-diagonal, many workgroups per problem (2048 rows:
+// 1.2 MB of partial results per problem, far more than one CU reads quickly).
+__global__ __launch_bounds__(256) void seg_merge_kernel(SegArgs a) {
+  const int p = blockIdx.y, s = blockIdx.x * 256 + threadIdx.x;
+  if (s >= 2 * a.n_new - 1) return;
+  uint64_t key[1];
+  uint32_t xy[1];
+  merge_diagonals<1, SEG_MAX_NB / 2>(a, p, s, key, xy);
+  a.sc.ckey[(size_t)p * SEG_MAX_DIAG + s] = key[0];
+  a.sc.cxy[(size_t)p * SEG_MAX_DIAG + s] = xy[0];
 }
 
 // Pass 3b: greedy NMS (Sec. 3.2) over the candidates in the order (score descending, x ascending,
@@ -797,14 +890,22 @@ __global__ __launch_bounds__(256) void seg_merge_kernel(SegArgs a) {
 // of kept spans is small, so no sort is done: every thread holds four candidates in registers;
 // one round = a workgroup-wide minimum of the order key over the live candidates, the winner is
 // kept, every candidate it suppresses (and the winner itself) dies. One workgroup per problem.
+// MT > 0: chunks of at most 2 MT tiles a side, whose partial results the threads merge themselves (pass 3a); else the
+// merged candidates are in place.
+constexpr int MERGE_INLINE_NB = 16;
+template <int MT>
 __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t kept[SEG_MAX_DIAG + 1];
   if (blockIdx.y > 0) {
     // Not a selection: running sums of the chunk's query and key rows (bf16, head_dim 128), which step 2 reads once
-    // the spans are known. They need nothing of the segmentation, and this launch leaves all but a few compute
-    // units idle, so they ride along here (gridDim.y - 1 workgroups per problem, dispatched after the selections).
+    // the spans are known, or the copy of the caller's chunk. They need nothing of the segmentation, and this launch leaves
+    // all but a few compute units idle, so they ride along here (gridDim.y - 1 workgroups per problem, dispatched after
+    // the selections).
     static_assert(sizeof(kept) >= 16 * 128 * sizeof(double), "staging of the running sums");
-    running_sums_block(a.D, a.bp, a.layer, a.batch_off, a.rs, (int)blockIdx.y - 1, blockIdx.x, reinterpret_cast<double*>(kept));
+    // (The key rows' sums read the caller's chunk where there is one: the arena is being written.)
+    const int w = (int)blockIdx.y - 1, p = blockIdx.x;
+    if (w < a.sum_wgs) running_sums_block(a.D, a.bp, a.layer, a.batch_off, a.rs, w, p, reinterpret_cast<double*>(kept));
+    else copy_chunk_rows(a.D, a.src, a.layer, a.bp, a.batch_off + p / a.D.Hkv, p % a.D.Hkv, a.n_new, w - a.sum_wgs, a.copy_wgs);
     return;
   }
   __shared__ uint64_t s_w1[2][16];
@@ -820,13 +921,17 @@ __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
   const int n_diag = 2 * L - 1;
   uint64_t e1[4];
   uint32_t e2[4];
+  // consecutive anti-diagonals per thread and wavefront: spans that are kept cover the chunk region by region,
+  // so whole wavefronts run out of live candidates and skip most of a round
+  if constexpr (MT > 0) {
+    merge_diagonals<4, MT>(a, p, 4 * tid, e1, e2);
+  } else {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    // consecutive anti-diagonals per thread and wavefront: spans that are kept cover the chunk region by region,
-    // so whole wavefronts run out of live candidates and skip most of a round
-    const int sd = 4 * tid + r;
-    e1[r] = sd < n_diag ? a.sc.ckey[(size_t)p * SEG_MAX_DIAG + sd] : ~0ull;
-    e2[r] = sd < n_diag ? a.sc.cxy[(size_t)p * SEG_MAX_DIAG + sd] : 0xFFFFFFFFu;
+    for (int r = 0; r < 4; ++r) {
+      const int sd = 4 * tid + r;
+      e1[r] = sd < n_diag ? a.sc.ckey[(size_t)p * SEG_MAX_DIAG + sd] : ~0ull;
+      e2[r] = sd < n_diag ? a.sc.cxy[(size_t)p * SEG_MAX_DIAG + sd] : 0xFFFFFFFFu;
+    }
   }
   const int max_keep = D.max_keep;
   const float phi = D.phi;
@@ -885,6 +990,12 @@ __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
     // the best of the 16 wavefronts: one entry per lane of every row of 16 lanes
     uint64_t w1 = s_w1[buf][lane & 15];
     uint32_t w2 = s_w2[buf][lane & 15];
+    if (!wave_alive) {                           // nothing left to suppress here: only whether this was the last round
+      if (__ballot(w1 != ~0ull) == 0ull) break;  // (uniform over the workgroup, as below)
+      ++nkept;
+      if (max_keep > 0 && nkept >= max_keep) break;
+      continue;
+    }
     {
       const uint32_t hi = (uint32_t)(w1 >> 32);
       const uint32_t m = hi_min(std::integral_constant<int, 4>{}, hi);
@@ -901,12 +1012,18 @@ __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
         step(std::integral_constant<int, 8>{}, w1, w2);
       }
     }
-    if (w1 == ~0ull) break;                      // nothing alive (uniform)
-    if (tid == 0) kept[nkept] = w2;
+    if (lane == 0) kept[nkept] = w2;             // (every live wavefront writes the same value)
     ++nkept;
     if (max_keep > 0 && nkept >= max_keep) break;
     const int kx = (int)(w2 >> 16), ky = (int)(w2 & 0xFFFFu);
-    if (!wave_alive) continue;                   // nothing left to suppress in this wavefront
+    if (phi == 0.0f) {                           // any overlap suppresses (uniform)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int x = (int)(e2[r] >> 16), y = (int)(e2[r] & 0xFFFFu);
+        e1[r] = ((y >= kx) & (x <= ky)) ? ~0ull : e1[r];
+      }
+      continue;
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int x = (int)(e2[r] >> 16), y = (int)(e2[r] & 0xFFFFu);
@@ -918,6 +1035,7 @@ __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
       e1[r] = kill ? ~0ull : e1[r];
     }
   }
+  __syncthreads();                               // kept[] is read below
   // cuts: 0, L, both ends of every kept interval, and (retrieval by memory units) every unit edge
   for (int i = tid; i <= L; i += blockDim.x)
     flags[i] = (i == 0 || i == L || (D.unit > 0 && (c0 + i) % D.unit == 0)) ? 1 : 0;
@@ -978,12 +1096,10 @@ __global__ __launch_bounds__(256) void lse_tile_kernel(SegArgs a) {
   int I, J;
   tile_decode(blockIdx.x, I, J);
   const int sl = p / D.Hkv, h = p - sl * D.Hkv, bi = a.batch_off + sl;
-  const int seq = a.bp.seq[bi], c0 = a.bp.c0[bi];
   const int L = a.n_new, d = D.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wi = wave >> 1, wj = wave & 1, hf = lane >> 5, l32 = lane & 31;
-  const int slot = slot_of(D, a.layer, seq, h);
-  const T* Kc = reinterpret_cast<const T*>(a.k_arena) + arena_off(D, slot) + (size_t)chunk_tok_row(D, c0, c0) * d;
+  const T* Kc = chunk_keys<T>(a, bi, h);
   const T* Qb = a.q_seg ? reinterpret_cast<const T*>(a.q_seg) + (size_t)bi * L * D.Hq * d + (size_t)h * D.G * d : nullptr;
   const int n_h = a.q_seg ? D.G : 1;
   const int nkc = d * (int)sizeof(T) / 256;
@@ -1385,55 +1501,8 @@ __global__ __launch_bounds__(1024) void rep_keys_kernel(RepArgs a) {
   }
 }
 
-// ---- copies of a caller's chunk into the arenas ----
-// Resident KV: the rows go to their tokens' places. Host-offloaded KV (Sec. 3.4 first step): the device keeps
-// only the initial tokens and a ring of the latest tokens; every row is also written to the host arenas
-// (device-visible pinned memory), from which step 3 fetches the rows it retrieves.
-struct CopyArgs { Dims D; void* k_arena; void* v_arena; const void* k_chunk; const void* v_chunk;
-                  int layer; int seq_count; int n_new; BatchPos bp; void* k_host; void* v_host; };
-
 __global__ __launch_bounds__(256) void copy_chunk_kernel(CopyArgs a) {
-  const Dims& D = a.D;
-  const int p = blockIdx.y, bi = p / D.Hkv, h = p - bi * D.Hkv;
-  const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
-  const int c0 = a.bp.c0[bi];
-  const size_t row_bytes = (size_t)D.d * D.elt;
-  const int r16 = (int)(row_bytes / 16);                     // 16-byte pieces per row
-  const size_t n16 = (size_t)a.n_new * r16;
-  const size_t dst_off = (arena_off(D, slot) + (size_t)chunk_tok_row(D, c0, c0) * D.d) * D.elt;
-  const size_t src_off = (size_t)p * a.n_new * row_bytes;
-  const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.k_chunk) + src_off);
-  const uint4* vs = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.v_chunk) + src_off);
-  uint4* kd = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.k_arena) + dst_off);
-  uint4* vd = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.v_arena) + dst_off);
-  if (!D.offload) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x) {
-      kd[i] = ks[i];
-      vd[i] = vs[i];
-    }
-    return;
-  }
-  const size_t slot_bytes = arena_off(D, slot) * D.elt;
-  uint4* kp = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.k_arena) + slot_bytes);     // row 0 of the slot's pool
-  uint4* vp = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.v_arena) + slot_bytes);
-  const size_t host_off = ((size_t)slot * (size_t)D.max_tokens + (size_t)c0) * row_bytes;
-  uint4* kh = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.k_host) + host_off);
-  uint4* vh = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.v_host) + host_off);
-  const int ring = D.ring_mask + 1, pos0 = c0 & D.ring_mask;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x) {
-    const uint4 kv = ks[i], vv = vs[i];
-    const int r = (int)(i / r16), piece = (int)(i - (size_t)r * r16);
-    kd[i] = kv; vd[i] = vv;                                  // ring (running on into its mirror rows)
-    if (pos0 + r >= ring) {                                  // the part past the ring's end, again at its start
-      const size_t w = (size_t)(D.ring0 + pos0 + r - ring) * r16 + piece;
-      kp[w] = kv; vp[w] = vv;
-    }
-    if (c0 + r < D.n_sink) {                                 // initial tokens keep rows of their own
-      const size_t w = (size_t)(c0 + r) * r16 + piece;
-      kp[w] = kv; vp[w] = vv;
-    }
-    if (a.k_host) { kh[i] = kv; vh[i] = vv; }                // host arenas: every token, in place
-  }
+  copy_chunk_rows(a.D, a.src, a.layer, a.bp, blockIdx.y / a.D.Hkv, blockIdx.y % a.D.Hkv, a.n_new, blockIdx.x, gridDim.x);
 }
 
 // ---- host-offloaded KV: rows of the retrieved tokens, host arenas -> the staging rows of the device pool ----
@@ -1500,14 +1569,11 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_copy_chunk(const Dims& D, void* k_arena, void* v_arena, const void* k_chunk,
-                             const void* v_chunk, int layer, const BatchPos& bp, int seq_count,
-                             int n_new, void* k_host, void* v_host, hipStream_t s) {
-  if (!k_host != !v_host) return hipErrorInvalidValue;
-  CopyArgs a{D, k_arena, v_arena, k_chunk, v_chunk, layer, seq_count, n_new, bp, k_host, v_host};
-  const size_t n16 = (size_t)n_new * D.d * D.elt / 16;
-  const int bx = (int)((n16 + 255) / 256 < 64 ? (n16 + 255) / 256 : 64);
-  copy_chunk_kernel<<<dim3(bx > 0 ? bx : 1, seq_count * D.Hkv), 256, 0, s>>>(a);
+hipError_t launch_copy_chunk(const Dims& D, const ChunkRows& src, int layer, const BatchPos& bp, int seq_count, int n_new,
+                             hipStream_t s) {
+  if (!src.k_host != !src.v_host) return hipErrorInvalidValue;
+  CopyArgs a{D, src, layer, n_new, bp};
+  copy_chunk_kernel<<<dim3(copy_chunk_wgs(D, n_new, 256), seq_count * D.Hkv), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -1531,6 +1597,8 @@ hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScrat
   a.sum_wgs = 0;
   a.rs = RunSums{};
   a.quant_rank = a.quant_cells = 0;
+  a.src = ChunkRows{};
+  a.copy_wgs = 0;
   const int P = seq_count * D.Hkv;
   const bool bf = D.dtype == LTRI_BF16;
   dim3 gl((a.Lp + 255) / 256, P), gt(a.ntiles, P);
@@ -1556,7 +1624,7 @@ hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScrat
 
 hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                           const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                          int n_new, hipEvent_t after_tiles, const RunSums* sums, hipStream_t s) {
+                          int n_new, hipEvent_t after_tiles, const RunSums* sums, const ChunkRows* src, hipStream_t s) {
   SegArgs a;
   a.D = D; a.st = st; a.sc = sc; a.k_arena = k_arena; a.q_seg = q_seg; a.layer = layer;
   a.batch_off = batch_off; a.n_new = n_new;
@@ -1567,12 +1635,19 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
   if (sums) {
     if (D.d != 128 || D.dtype != LTRI_BF16 || sums->n_q != n_new) return hipErrorInvalidValue;
     a.rs = *sums;
+    if (src) a.rs.k_chunk = src->k_chunk;
     a.sum_wgs = running_sums_blocks(a.rs);
   }
   const int P = seq_count * D.Hkv;
   const bool bf = D.dtype == LTRI_BF16;
   dim3 gt(a.ntiles, P);
   a.quant_rank = a.quant_cells = 0;
+  a.src = ChunkRows{};
+  a.copy_wgs = 0;
+  if (src) {
+    a.src = *src;
+    a.copy_wgs = copy_chunk_wgs(D, n_new, 1024 / COPY_UNROLL);      // (one piece per thread: as many compute units as there are)
+  }
   if (D.theta_quantile > 0.0) {
     a.quant_cells = (unsigned long long)n_new * (unsigned long long)(n_new + 1) / 2;
     a.quant_rank = (unsigned long long)floor(D.theta_quantile * ((double)a.quant_cells - 1.0));
@@ -1589,7 +1664,7 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
     if (D.theta_quantile > 0.0) {
       if (KIND == LTRI_MAP_LOGIT) quant_init_kernel<<<P, 256, 0, s>>>(a);
       seg_tile_sums_kernel<DT, KIND, true><<<gt, 256, 0, s>>>(a);      // pass 1 and the selection's first tile pass
-      quant_pick_kernel<<<P, 1024, 0, s>>>(a);
+        quant_pick_kernel<<<P, 1024, 0, s>>>(a);
       // a map whose cells all fit the list (chunks of up to 180 tokens) was collected whole by the first pass, and
       // the pick has finished the selection: the other kernels would only find that out (4.5 us each)
       if (a.quant_cells > (unsigned long long)QUANT_LIST_CAP) {
@@ -1601,7 +1676,7 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
       }
     } else {
       seg_tile_sums_kernel<DT, KIND, false><<<gt, 256, 0, s>>>(a);
-    }
+      }
     seg_tile_scan_kernel<DT, KIND><<<gt, 256, 0, s>>>(a);
   };
   using std::integral_constant;
@@ -1615,9 +1690,15 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
     const hipError_t e = hipEventRecord(after_tiles, s);
     if (e != hipSuccess) return e;
   }
-  dim3 gm((2 * n_new - 1 + 255) / 256, P);
-  seg_merge_kernel<<<gm, 256, 0, s>>>(a);
-  seg_select_kernel<<<dim3(P, 1 + a.sum_wgs), 1024, 0, s>>>(a);
+  const dim3 gsel(P, 1 + a.sum_wgs + a.copy_wgs);
+  if (a.nb <= 4) {
+    seg_select_kernel<2><<<gsel, 1024, 0, s>>>(a);
+  } else if (a.nb <= MERGE_INLINE_NB) {
+    seg_select_kernel<MERGE_INLINE_NB / 2><<<gsel, 1024, 0, s>>>(a);
+  } else {
+    seg_merge_kernel<<<dim3((2 * n_new - 1 + 255) / 256, P), 256, 0, s>>>(a);
+    seg_select_kernel<0><<<gsel, 1024, 0, s>>>(a);
+  }
   return hipGetLastError();
 }
 

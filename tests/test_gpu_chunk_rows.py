@@ -1,0 +1,58 @@
+"""Rows that come with a call against rows that are in the arenas already, at chunk lengths around the tile, the sizes where
+the merge of the tiles' results moves into the selection, and the copy's whole workgroups."""
+import pytest
+import torch
+
+from paper_2412_04757_amd import LtriContext, config_from_workload
+from tests.test_gpu_parity import _stream_parity
+from workloads import Workload, theta_default
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("sizes", [[256, 257, 64, 65], [1024, 1025], [1025, 960, 961]])
+def test_merge_of_tiles_at_its_limits(gpu_device, sizes):
+    w = Workload("mini-merge", 4, 1, 128, "bf16", sum(sizes), max(sizes), 4, 96, 0, 300, "uniform", 16, 200)
+    _stream_parity(w, 31, sum(sizes), gpu_device, chunk_sizes=sizes, whole_step=True)
+
+
+@pytest.mark.parametrize("whole_step", [True, False])
+@pytest.mark.parametrize("dtype,dim,seqs", [("bf16", 128, 1), ("bf16", 128, 5), ("f32", 64, 2)])
+def test_rows_passed_equal_rows_in_place(gpu_device, dtype, dim, seqs, whole_step):
+    sizes = [2, 65, 256, 700, 1, 3, 1025, 1]
+    T = sum(sizes)
+    w = Workload("mini-rows", 4, 2, dim, dtype, T, max(sizes), 4, 100, 0, 300, "uniform", 16, 200)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device=gpu_device).manual_seed(5)
+    mean = torch.randn(seqs, 2, T // 50 + 1, dim, generator=gen, device=gpu_device).repeat_interleave(50, 2)[:, :, :T]
+    K = (mean + 0.3 * torch.randn(seqs, 2, T, dim, generator=gen, device=gpu_device)).to(dt)
+    V = torch.randn(seqs, 2, T, dim, generator=gen, device=gpu_device).to(dt)
+    Q = torch.randn(seqs, T, 4, dim, generator=gen, device=gpu_device).to(dt)
+    got = []
+    for passed in (True, False):
+        ctx = LtriContext(config_from_workload(w, n_layers=1, n_seqs=seqs, max_tokens=T, theta=theta_default(dim)), gpu_device)
+        ka, va = ctx.arena_views()
+        ka.zero_(), va.zero_()
+        outs, at = [], 0
+        for n in sizes:
+            k, v = K[:, :, at:at + n].contiguous(), V[:, :, at:at + n].contiguous()
+            if not passed:
+                ka[0, :, :, at:at + n].copy_(k), va[0, :, :, at:at + n].copy_(v)
+                k = v = None
+            q = Q[:, at:at + n].contiguous()
+            if whole_step:
+                outs.append(ctx.step(0, 0, seqs, k, v, q))
+            else:
+                ctx.append_chunk(0, 0, seqs, n, k_chunk=k, v_chunk=v)
+                ctx.retrieve(0, 0, seqs, q)
+                outs.append(ctx.attend(0, 0, seqs, q))
+            at += n
+        assert ctx.sync_status() == 0
+        spans = [[list(x) for x in ctx.get_spans(0, s, h)] + [ctx.get_rep_keys(0, s, h)] for s in range(seqs) for h in range(2)]
+        got.append((outs, spans, ka.clone(), va.clone()))
+    (oa, sa, ka, va), (ob, sb, kb, vb) = got
+    assert torch.equal(ka, kb) and torch.equal(va, vb) and torch.equal(ka[0, :, :, :T], K)
+    for a, b in zip(sa, sb):
+        assert a[:2] == b[:2] and torch.equal(a[2], b[2])
+    for a, b in zip(oa, ob):
+        assert torch.equal(a, b)
