@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "ltri_internal.h"
 
 namespace ltri {
@@ -67,12 +68,6 @@ __device__ __forceinline__ int window_tok_row(const Dims& D, int tok) {
 // are then visible to loads at device scope on the whole chip.
 __device__ __forceinline__ void wait_for_own_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // Value of lane (lane ^ M) for M = 1 .. 32, on the vector ALU (DPP / lane-swap instructions)
 // instead of the LDS crossbar that __shfl_xor goes through.
 template <int M>
@@ -94,6 +89,60 @@ __device__ __forceinline__ uint32_t lane_xor_c(uint32_t v) {
     const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
     return (threadIdx.x & 32) ? r[0] : r[1];
   }
+}
+template <int M>
+__device__ __forceinline__ double lane_xor_f64(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  return __longlong_as_double((long long)(((uint64_t)lane_xor_c<M>((uint32_t)(u >> 32)) << 32) | lane_xor_c<M>((uint32_t)u)));
+}
+__device__ __forceinline__ double wave_sum_f64(double v) {
+  v += lane_xor_f64<32>(v);
+  v += lane_xor_f64<16>(v);
+  v += lane_xor_f64<8>(v);
+  v += lane_xor_f64<4>(v);
+  v += lane_xor_f64<2>(v);
+  v += lane_xor_f64<1>(v);
+  return v;
+}
+
+// Inclusive scan over the wavefront's lanes (DPP row shifts and broadcasts; a __shfl_up goes through the LDS crossbar, and six
+// of them one after the other are 0.3 us).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_scan_i32(int x) {
+  uint32_t v = (uint32_t)x;
+  v += dpp_or_zero<0x111, 0xF>(v);         // row_shr:1, 2, 4, 8
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  v += dpp_or_zero<0x142, 0xA>(v);         // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xC>(v);         // row_bcast:31 into rows 2 and 3
+  return (int)v;
+}
+__device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {
+  auto add = [&](auto c, auto rows) {
+    constexpr int C = decltype(c)::value, R = decltype(rows)::value;
+    v += ((uint64_t)dpp_or_zero<C, R>((uint32_t)(v >> 32)) << 32) | dpp_or_zero<C, R>((uint32_t)v);
+  };
+  using std::integral_constant;
+  add(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});
+  add(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+  add(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+  add(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+  add(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});
+  add(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
+  return v;
+}
+// Maximum over the lanes of groups of N (16 or 64).
+template <int N>
+__device__ __forceinline__ float lanes_max(float v) {
+  auto x = [&](auto m) { v = fmaxf(v, __uint_as_float(lane_xor_c<decltype(m)::value>(__float_as_uint(v)))); };
+  using std::integral_constant;
+  x(integral_constant<int, 1>{}); x(integral_constant<int, 2>{}); x(integral_constant<int, 4>{}); x(integral_constant<int, 8>{});
+  if constexpr (N == 64) { x(integral_constant<int, 16>{}); x(integral_constant<int, 32>{}); }
+  return v;
 }
 __device__ __forceinline__ bool key_less(uint64_t a1, uint32_t a2, uint64_t b1, uint32_t b2) {
   return (a1 < b1) || (a1 == b1 && a2 < b2);

@@ -284,52 +284,65 @@ __global__ __launch_bounds__(256) void score_kernel(RetArgs a) {
 // 1e-12). A lane (r = lane % 16, g = lane / 16) feeds row r of A (span i0 + r) and column r of B (query span
 // j0 + r): both fetch the 16-byte pieces g, g + 4, ... of their row, and product step (t, e) takes element e of
 // piece g + 4 t from either side, i.e. the same k on both sides in a permuted order. Rows past n and columns
-// past nqs read a valid row and are masked. All 64 lanes must call it together.
+// past nqs read a valid row and are masked. All 64 lanes must call it together. load() may run ahead of score().
+// qlds (or NULL): the query representatives in LDS, 256-byte rows whose 16-byte pieces are permuted by the row (score_q_piece).
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 template <int DT>
-__device__ __forceinline__ void score_tile_f64(const typename Elt<DT>::type* krep, int n, int i0,
-                                               const typename Elt<DT>::type* qrep, int nqs, int d, double (&best)[4]) {
+struct ScoreTile {
   typedef typename Elt<DT>::type T;
-  constexpr int N = 16 / (int)sizeof(T);                // elements per 16-byte piece
-  constexpr int TMAX = 128 * (int)sizeof(T) / 16 / 4;   // pieces per lane at d = 128
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int nt = d / N / 4;                             // pieces per lane
-  const uint4* arow = reinterpret_cast<const uint4*>(krep + (size_t)max(min(i0 + r, n - 1), 0) * d);
+  static constexpr int N = 16 / (int)sizeof(T);                // elements per 16-byte piece
+  static constexpr int TMAX = 128 * (int)sizeof(T) / 16 / 4;   // pieces per lane at d = 128
   uint4 av[TMAX];
+  __device__ __forceinline__ void load(const T* krep, int n, int i0, int d) {
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, nt = d / N / 4;
+    const uint4* arow = reinterpret_cast<const uint4*>(krep + (size_t)max(min(i0 + r, n - 1), 0) * d);
 #pragma unroll
-  for (int t = 0; t < TMAX; ++t) av[t] = t < nt ? arow[g + 4 * t] : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) best[v] = -INFINITY;
-  auto elem = [](const uint4& u, int e) -> double {
+    for (int t = 0; t < TMAX; ++t) av[t] = t < nt ? arow[g + 4 * t] : make_uint4(0u, 0u, 0u, 0u);
+  }
+  __device__ static __forceinline__ double elem(const uint4& u, int e) {
     const uint32_t w[4] = {u.x, u.y, u.z, u.w};
     if constexpr (DT == LTRI_BF16) return (double)__uint_as_float((e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
     else return (double)__uint_as_float(w[e]);
-  };
-  for (int j0 = 0; j0 < nqs; j0 += 16) {
-    const uint4* brow = reinterpret_cast<const uint4*>(qrep + (size_t)min(j0 + r, nqs - 1) * d);
-    uint4 bv[TMAX];
+  }
+  __device__ __forceinline__ void score(const T* qrep, const unsigned char* qlds, int nqs, int d, double (&best)[4]) const {
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, nt = d / N / 4;
 #pragma unroll
-    for (int t = 0; t < TMAX; ++t) bv[t] = t < nt ? brow[g + 4 * t] : make_uint4(0u, 0u, 0u, 0u);
-    f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+    for (int v = 0; v < 4; ++v) best[v] = -INFINITY;
+    for (int j0 = 0; j0 < nqs; j0 += 16) {
+      const int row = min(j0 + r, nqs - 1);
+      uint4 bv[TMAX];
+      if (qlds) {
 #pragma unroll
-    for (int t = 0; t < TMAX; ++t) {
-      if (t < nt) {
+        for (int t = 0; t < TMAX; ++t) bv[t] = *reinterpret_cast<const uint4*>(qlds + row * 256 + ((((g + 4 * t) ^ row) & 15) << 4));
+      } else {
+        const uint4* brow = reinterpret_cast<const uint4*>(qrep + (size_t)row * d);
 #pragma unroll
-        for (int e = 0; e < N; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(elem(av[t], e), elem(bv[t], e), acc, 0, 0, 0);
+        for (int t = 0; t < TMAX; ++t) bv[t] = t < nt ? brow[g + 4 * t] : make_uint4(0u, 0u, 0u, 0u);
       }
+      f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int t = 0; t < TMAX; ++t) {
+        if (t < nt) {
+          uint4 at = av[t];
+          asm volatile("" : "+v"(at.x), "+v"(at.y), "+v"(at.z), "+v"(at.w));   // (converted ahead of the loop, a tile is 64 registers)
+#pragma unroll
+          for (int e = 0; e < N; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(elem(at, e), elem(bv[t], e), acc, 0, 0, 0);
+        }
+      }
+      // acc[v] = score of span i0 + 4 v + g against query span j0 + r
+#pragma unroll
+      for (int v = 0; v < 4; ++v) best[v] = fmax(best[v], (j0 + r < nqs) ? acc[v] : -INFINITY);
     }
-    // acc[v] = score of span i0 + 4 v + g against query span j0 + r: maximum over the 16 lanes of a group
+    // maximum over the 16 lanes of a group
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      double m = (j0 + r < nqs) ? acc[v] : -INFINITY;
-      m = fmax(m, __shfl_xor(m, 1, 64));
-      m = fmax(m, __shfl_xor(m, 2, 64));
-      m = fmax(m, __shfl_xor(m, 4, 64));
-      m = fmax(m, __shfl_xor(m, 8, 64));
-      best[v] = fmax(best[v], m);
+      best[v] = fmax(best[v], lane_xor_f64<1>(best[v]));
+      best[v] = fmax(best[v], lane_xor_f64<2>(best[v]));
+      best[v] = fmax(best[v], lane_xor_f64<4>(best[v]));
+      best[v] = fmax(best[v], lane_xor_f64<8>(best[v]));
     }
   }
-}
+};
 
 // Evicted part [a, b) of a stored span for a chunk starting at c0.
 __device__ __forceinline__ void clip_span(const Dims& D, int c0, int start, int len, int& a, int& b) {
@@ -366,15 +379,16 @@ constexpr int EMIT_CAP = 2048;     // selected spans whose tokens are written co
 struct EmitShared {
   __attribute__((aligned(16))) int a[EMIT_CAP];
   int len[EMIT_CAP], off[EMIT_CAP];
-  int wcnt[16], wtok[16], base_cnt, base_tok;
+  int wcnt[16], wtok[16];
 };
 
-__device__ __forceinline__ void emit_selection(const Dims& D, const DevState& st, int slot, const uint32_t* selmask,
-                               int n, int32_t* ids_out, int32_t* cnt_out, EmitShared& E) {
-  int (&s_wcnt)[16] = E.wcnt, (&s_wtok)[16] = E.wtok, &s_base_cnt = E.base_cnt, &s_base_tok = E.base_tok;
+// c0, n_new: the chunk's start and length, as the caller has read them. own (or NULL): evicted part [own[0], own[1]) of item
+// threadIdx.x, which the caller holds in registers (the loads it saves are 0.7 us of the chain).
+__device__ __forceinline__ void emit_selection(const Dims& D, const DevState& st, int slot, int c0, int n_new,
+                               const uint32_t* selmask, int n, const int* own, int32_t* ids_out, int32_t* cnt_out, EmitShared& E) {
+  int (&s_wcnt)[16] = E.wcnt, (&s_wtok)[16] = E.wtok;
   int (&e_a)[EMIT_CAP] = E.a, (&e_len)[EMIT_CAP] = E.len, (&e_off)[EMIT_CAP] = E.off;
   int32_t* meta = st.meta + (size_t)slot * META_WORDS;
-  const int c0 = meta[META_CHUNK_START];
   const int ns = min(D.n_sink, c0), ws = max(ns, c0 - D.window);
   const int32_t* sstart = st.span_start + (size_t)slot * D.max_spans;
   const int32_t* slen = st.span_len + (size_t)slot * D.max_spans;
@@ -383,31 +397,30 @@ __device__ __forceinline__ void emit_selection(const Dims& D, const DevState& st
   // host-offloaded KV: the same list as rows of the device pool (initial tokens in place, retrieved token j at
   // stage0 + j, window tokens in the ring), which is what the attention walks
   int32_t* rows = D.offload ? st.row_list + (size_t)slot * D.list_cap : nullptr;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) { s_base_cnt = 0; s_base_tok = 0; }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (int t = tid; t < ns; t += blockDim.x) { list[t] = t; if (rows) rows[t] = t; }
-  __syncthreads();
+  int base_cnt = 0, base_tok = 0;                          // of the items before this pass (uniform)
   for (int i0 = 0; i0 < n; i0 += blockDim.x) {
     const int i = i0 + tid;
     const bool f = i < n && ((selmask[i >> 5] >> (i & 31)) & 1u);
     int a = 0, b = 0;
-    if (f) {
+    if (f && own && i0 == 0) {
+      a = own[0]; b = own[1];
+    } else if (f) {
       int start, len;
-      item_range(D, sstart, slen, c0 + meta[META_CHUNK_LEN], i, start, len);
+      item_range(D, sstart, slen, c0 + n_new, i, start, len);
       clip_span(D, c0, start, len, a, b);
     }
     const int w = f ? max(b - a, 0) : 0;
-    // wave-level inclusive scans of (flag, tokens)
-    int cs = f ? 1 : 0, ts = w;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int c2 = __shfl_up(cs, o, 64), t2 = __shfl_up(ts, o, 64);
-      if (lane >= o) { cs += c2; ts += t2; }
-    }
+    const uint64_t fm = __ballot(f);
+    const int cs = __popcll(fm & ((2ull << lane) - 1ull)), ts = wave_scan_i32(w);      // inclusive, over the wavefront
+    if (i0 > 0) __syncthreads();                            // the totals of the pass before are read
     if (lane == 63) { s_wcnt[wave] = cs; s_wtok[wave] = ts; }
     __syncthreads();
-    int coff = s_base_cnt, toff = s_base_tok;
-    for (int w2 = 0; w2 < wave; ++w2) { coff += s_wcnt[w2]; toff += s_wtok[w2]; }
+    // totals of all wavefronts, scanned by every row of 16 lanes: the sums up to each wavefront in lanes 0 .. 15
+    const int wc = wave_scan_i32(lane < 16 ? s_wcnt[lane] : 0), wt = wave_scan_i32(lane < 16 ? s_wtok[lane] : 0);
+    const int coff = base_cnt + (wave ? __builtin_amdgcn_readlane(wc, wave - 1) : 0);
+    const int toff = base_tok + (wave ? __builtin_amdgcn_readlane(wt, wave - 1) : 0);
     if (f) {
       const int pos = coff + cs - 1;
       if (pos < D.sel_cap) {
@@ -422,15 +435,11 @@ __device__ __forceinline__ void emit_selection(const Dims& D, const DevState& st
           if (o + t < D.list_cap) list[o + t] = a + t;
       }
     }
-    __syncthreads();
-    if (tid == 0) {
-      int c = 0, t = 0;
-      for (int w2 = 0; w2 < 16; ++w2) { c += s_wcnt[w2]; t += s_wtok[w2]; }
-      s_base_cnt += c; s_base_tok += t;
-    }
-    __syncthreads();
+    base_cnt += __builtin_amdgcn_readlane(wc, 15);
+    base_tok += __builtin_amdgcn_readlane(wt, 15);
   }
-  const int n_sel = s_base_cnt, n_ret = s_base_tok;
+  __syncthreads();
+  const int n_sel = base_cnt, n_ret = base_tok;
   const int n_win = c0 - ws;
   const int len = ns + n_ret + n_win;
   const bool fits = n_sel <= D.sel_cap && len <= D.list_cap;
@@ -543,7 +552,7 @@ __global__ __launch_bounds__(1024) void select_emit_kernel(RetArgs a) {
   const int p = blockIdx.x, bi = p / D.Hkv, h = p - bi * D.Hkv;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
   const int32_t* meta = a.st.meta + (size_t)slot * META_WORDS;
-  const int n = meta[META_N_SPANS];
+  const int n = meta[META_N_SPANS], c0 = meta[META_CHUNK_START];
   const uint8_t* flag = a.sc.selflag + (size_t)p * D.max_spans;
   for (int i0 = 0; i0 < n; i0 += blockDim.x) {
     const int i = i0 + threadIdx.x;
@@ -556,7 +565,7 @@ __global__ __launch_bounds__(1024) void select_emit_kernel(RetArgs a) {
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
+  emit_selection(D, a.st, slot, c0, meta[META_CHUNK_LEN], selmask, n, nullptr, ids_out, cnt_out, E);
 }
 
 // ---- step 2 for a one-token chunk (decode) in one launch: one workgroup per (sequence, KV head) ----
@@ -664,17 +673,19 @@ __device__ __forceinline__ void select_sorted_prefix(const Dims& D, uint64_t* sk
 // The same rule without the sort (the order of the items is not left behind): item i is selected iff the eligible
 // items up to and including it in the order are at most k_max and their clipped tokens fit the budget, and both
 // sums are monotone in the order, so only the items near the limit need their exact place.
-// Up to SEL_DIRECT items: every item is compared with all others (1024 / npow lanes share an item).
+// Up to SEL_DIRECT items: every item is compared with all others (1024 / npow lanes share an item). The comparisons grow with
+// the square: 2.4 us at 108 items, 7.0 at 209, where the other way takes 3.7.
 // More: the scores (in fp32, a monotone coarsening) are cut into 1024 equal pieces of their range, from the largest
 // down; counts and tokens of the pieces are scanned; pieces that fit whole are selected, the first that does not is
-// resolved by comparing its items with each other. Where that piece holds more than SEL_DIRECT items (most scores
+// resolved by comparing its items with each other. Where that piece holds more than SEL_EDGE items (most scores
 // are about equal) or a score is not finite in fp32, the items are sorted after all.
 // The sort is a chain of 28 (81 items) to 55 (604) dependent exchanges; the sort and the scan behind it took 5.0 and
 // 9.6 us of a one-token retrieve of one sequence and of 16, this takes 2.0 and 3.7 (launches 16.9 -> 13.9, 27.6 -> 21.7).
 // skey, sidx, clip, npow, selmask and wave_tot as above; n: items; E: LDS scratch. A barrier has to follow.
-constexpr int SEL_DIRECT = 256;
+constexpr int SEL_DIRECT = 128;
+constexpr int SEL_EDGE = 256;
 constexpr int SEL_BINS = 1024;
-// Items ids[0..m) (ids NULL: items 0..m), m <= SEL_DIRECT, npow = rt1_pow2(m): cnt0 items with tok0 tokens come
+// Items ids[0..m) (ids NULL: items 0..m), m <= SEL_EDGE, npow = rt1_pow2(m): cnt0 items with tok0 tokens come
 // before all of them.
 __device__ __forceinline__ void select_direct(const Dims& D, const uint64_t* skey, const int* clip, const int* ids, int m,
                                               int npow, int cnt0, int tok0, uint32_t* selmask) {
@@ -683,15 +694,34 @@ __device__ __forceinline__ void select_direct(const Dims& D, const uint64_t* ske
   const int tc = min(t, m - 1), i = ids ? ids[tc] : tc;
   const uint64_t ki = skey[i];
   int cnt = 0, tok = 0;
-  for (int u = part; u < m; u += parts) {
-    const int j = ids ? ids[u] : u;
-    const uint64_t kj = skey[j];
-    const int cj = clip[j];
-    const bool upto = cj > 0 && (kj < ki || (kj == ki && j <= i));
-    cnt += upto ? 1 : 0;
-    tok += upto ? cj : 0;
+  constexpr int U = 4;                                     // items whose LDS reads are in flight together
+  for (int u0 = part; u0 < m; u0 += U * parts) {
+    int jj[U], cj[U];
+    uint64_t kj[U];
+#pragma unroll
+    for (int e = 0; e < U; ++e) {
+      const int u = min(u0 + e * parts, m - 1);
+      jj[e] = ids ? ids[u] : u;
+    }
+#pragma unroll
+    for (int e = 0; e < U; ++e) { kj[e] = skey[jj[e]]; cj[e] = clip[jj[e]]; }
+#pragma unroll
+    for (int e = 0; e < U; ++e) {
+      const bool upto = (u0 + e * parts < m) & (cj[e] > 0) & ((kj[e] < ki) | ((kj[e] == ki) & (jj[e] <= i)));
+      cnt += upto ? 1 : 0;
+      tok += upto ? cj[e] : 0;
+    }
   }
-  for (int o = 1; o < parts; o <<= 1) { cnt += __shfl_xor(cnt, o, 64); tok += __shfl_xor(tok, o, 64); }
+  // over the lanes of an item: 4 (npow 256), 8 or 16 neighbours
+  auto add = [&](auto m) {
+    cnt += (int)lane_xor_c<decltype(m)::value>((uint32_t)cnt);
+    tok += (int)lane_xor_c<decltype(m)::value>((uint32_t)tok);
+  };
+  add(std::integral_constant<int, 1>{});
+  add(std::integral_constant<int, 2>{});
+  if (parts >= 8) add(std::integral_constant<int, 4>{});
+  if (parts >= 16) add(std::integral_constant<int, 8>{});
+  static_assert(1024 / rt1_pow2(SEL_EDGE) == 4, "lanes per item");
   const bool sel = part == 0 && t < m && clip[i] > 0 && (D.k_max == 0 || cnt0 + cnt <= D.k_max) &&
                    (D.budget == 0 || (long long)tok0 + tok <= D.budget);
   if (sel) atomicOr(&selmask[i >> 5], 1u << (i & 31));
@@ -709,7 +739,7 @@ __device__ __forceinline__ void select_prefix(const Dims& D, uint64_t* skey, uin
     if (n > 0) select_direct(D, skey, clip, nullptr, n, npow, 0, 0, selmask);
     return;
   }
-  static_assert(sizeof(E.a) == SEL_BINS * sizeof(unsigned long long) && EMIT_CAP >= SEL_DIRECT, "LDS of the selection");
+  static_assert(sizeof(E.a) == SEL_BINS * sizeof(unsigned long long) && EMIT_CAP >= SEL_EDGE && SEL_EDGE >= SEL_DIRECT, "LDS of the selection");
   unsigned long long* bins = reinterpret_cast<unsigned long long*>(E.a);   // items << 32 | tokens of a piece
   int* edge = E.len;                                                       // items of the piece that does not fit whole
   int* edge_n = E.off, *edge_bin = E.off + 1, *edge_cnt = E.off + 2, *edge_tok = E.off + 3;
@@ -725,11 +755,12 @@ __device__ __forceinline__ void select_prefix(const Dims& D, uint64_t* skey, uin
     hi = fmaxf(hi, ok ? v : INFINITY);
     lo = fminf(lo, ok ? v : -INFINITY);
   }
-  for (int o = 1; o < 64; o <<= 1) { hi = fmaxf(hi, __shfl_xor(hi, o, 64)); lo = fminf(lo, __shfl_xor(lo, o, 64)); }
+  hi = lanes_max<64>(hi);
+  lo = -lanes_max<64>(-lo);
   if (lane == 0) { wmax[wave] = hi; wmin[wave] = lo; }
   __syncthreads();
-  hi = wmax[lane & 15]; lo = wmin[lane & 15];
-  for (int o = 1; o < 16; o <<= 1) { hi = fmaxf(hi, __shfl_xor(hi, o, 64)); lo = fminf(lo, __shfl_xor(lo, o, 64)); }
+  hi = lanes_max<16>(wmax[lane & 15]);
+  lo = -lanes_max<16>(-wmin[lane & 15]);
   if (hi < lo) return;                                                     // no eligible item (uniform)
   const float range = hi - lo, scale = range > 0.f ? (float)(SEL_BINS - 1) / range : 0.f;
   const bool sorted = !(range < INFINITY && scale < INFINITY);             // uniform, as hi and lo are
@@ -743,15 +774,14 @@ __device__ __forceinline__ void select_prefix(const Dims& D, uint64_t* skey, uin
     }
     __syncthreads();
     const unsigned long long own = bins[tid];
-    unsigned long long incl = own;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
-    }
+    unsigned long long incl = wave_scan_u64(own);
     if (lane == 63) wave_tot[wave] = (long long)incl;
     __syncthreads();
-    for (int w = 0; w < wave; ++w) incl += (unsigned long long)wave_tot[w];
+    const unsigned long long wt = wave_scan_u64(lane < 16 ? (unsigned long long)wave_tot[lane] : 0ull);
+    const int before = max(__builtin_amdgcn_readfirstlane(wave) - 1, 0);
+    const unsigned long long prev = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(wt >> 32), before) << 32) |
+                                    (uint32_t)__builtin_amdgcn_readlane((int)wt, before);
+    incl += wave ? prev : 0ull;
     auto fits = [&](unsigned long long v) {
       return (D.k_max == 0 || (int)(v >> 32) <= D.k_max) && (D.budget == 0 || (long long)(uint32_t)v <= D.budget);
     };
@@ -769,13 +799,13 @@ __device__ __forceinline__ void select_prefix(const Dims& D, uint64_t* skey, uin
         atomicOr(&selmask[i >> 5], 1u << (i & 31));
       } else if (b == eb) {
         const int at = atomicAdd(edge_n, 1);
-        if (at < SEL_DIRECT) edge[at] = i;
+        if (at < SEL_EDGE) edge[at] = i;
       }
     }
     __syncthreads();
     const int m = *edge_n;
     if (m == 0) return;
-    if (m <= SEL_DIRECT) {
+    if (m <= SEL_EDGE) {
       select_direct(D, skey, clip, edge, m, rt1_pow2(m), *edge_cnt, *edge_tok, selmask);
       return;
     }
@@ -801,6 +831,35 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   int32_t* meta = a.st.meta + (size_t)slot * META_WORDS;
   const int d = D.d, tid = threadIdx.x;
   int n = meta[META_N_SPANS], c0 = meta[META_CHUNK_START];
+  const T* krep = reinterpret_cast<const T*>(a.st.krep) + (size_t)slot * D.max_spans * d;
+  double* scores = a.st.scores + (size_t)slot * D.max_spans;
+  const int32_t* sstart = a.st.span_start + (size_t)slot * D.max_spans;
+  const int32_t* slen = a.st.span_len + (size_t)slot * D.max_spans;
+  constexpr int PPL = 128 / N / 4;                      // 16-byte pieces per lane (d = 128)
+  constexpr int PASSES = DT == LTRI_BF16 ? 2 : 1;       // spans per thread whose loads are in flight together (3 spill)
+  const int part = tid & 3;
+  uint4 kv[PASSES][PPL];
+  int ss[PASSES], sl[PASSES];                           // the spans' extents travel with their keys
+  auto load_batch = [&](auto u0, auto u1, int i00, int last) {
+#pragma unroll
+    for (int u = decltype(u0)::value; u < decltype(u1)::value; ++u) {
+      const int ic = min(i00 + 256 * u + (tid >> 2), last);
+      const uint4* krow = reinterpret_cast<const uint4*>(krep + (size_t)ic * d);
+#pragma unroll
+      for (int q = 0; q < PPL; ++q) kv[u][q] = krow[part + 4 * q];
+      ss[u] = sstart[ic];
+      sl[u] = slen[ic];
+    }
+  };
+  // up to 256 spans go by one span per thread, more by PASSES of them. The first 128 are requested without waiting for the
+  // count (the table has room for `bound` spans; what lies past the count is not used), and so is the extent of
+  // the thread's own item for the list.
+  using None = std::integral_constant<int, 0>;
+  using One = std::integral_constant<int, 1>;
+  using All = std::integral_constant<int, PASSES>;
+  const bool ahead = tid < 512;                         // (uniform over a wavefront)
+  if (ahead) load_batch(None{}, One{}, 0, bound - 1);
+  int own_start = sstart[min(tid, bound - 1)], own_len = slen[min(tid, bound - 1)];
   // Step 1 of a one-token chunk, if asked for: the token is appended as a span of one, its key is the
   // stored vector (what append_single_kernel does). The table entry written here is read back below by
   // other threads of this workgroup, so a barrier stands on either side of the writes.
@@ -809,6 +868,7 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
     c0 = a.bp.c0[bi];
     const bool fits = base + 1 <= D.max_spans;
     __syncthreads();                                    // every thread has read the old count
+    // (the loads above may or may not see the new span: its entry is taken from here)
     const size_t row_off = arena_off(D, slot) + (size_t)chunk_tok_row(D, c0, c0) * d;
     if (tid < d) {
       const T* row = a.src.k_chunk ? reinterpret_cast<const T*>(a.src.k_chunk) + (size_t)p * d
@@ -835,37 +895,22 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
     n = fits ? base + 1 : base;
     __threadfence_block();
     __syncthreads();
+    if (fits && ahead && (tid >> 2) == base) {          // (four lanes)
+      const uint4* krow = reinterpret_cast<const uint4*>(krep + (size_t)base * d);
+#pragma unroll
+      for (int q = 0; q < PPL; ++q) kv[0][q] = krow[part + 4 * q];
+      ss[0] = c0; sl[0] = 1;
+    }
+    if (fits && tid == base) { own_start = c0; own_len = 1; }
   }
   n = min(n, bound);
+  if (!ahead) load_batch(None{}, One{}, 0, max(n - 1, 0));
+  if (n > 256) load_batch(One{}, All{}, 0, n - 1);
   const int npow = rt1_pow2(n);
   uint64_t* skey = reinterpret_cast<uint64_t*>(rt1_lds);
   uint32_t* sidx = reinterpret_cast<uint32_t*>(rt1_lds + (size_t)rt1_pow2(bound) * 8);
   int* clip = reinterpret_cast<int*>(rt1_lds + (size_t)rt1_pow2(bound) * 12);
   // scores, order keys and clipped lengths: four lanes per span
-  const T* krep = reinterpret_cast<const T*>(a.st.krep) + (size_t)slot * D.max_spans * d;
-  double* scores = a.st.scores + (size_t)slot * D.max_spans;
-  const int32_t* sstart = a.st.span_start + (size_t)slot * D.max_spans;
-  const int32_t* slen = a.st.span_len + (size_t)slot * D.max_spans;
-  constexpr int PPL = 128 / N / 4;                      // 16-byte pieces per lane (d = 128)
-  constexpr int PASSES = DT == LTRI_BF16 ? 2 : 1;       // spans per thread whose loads are in flight together (3 spill)
-  const int part = tid & 3;
-  uint4 kv[PASSES][PPL];
-  int ss[PASSES], sl[PASSES];                           // the spans' extents travel with their keys
-  auto load_batch = [&](auto uc, int i00) {
-#pragma unroll
-    for (int u = 0; u < decltype(uc)::value; ++u) {
-      const int ic = max(min(i00 + 256 * u + (tid >> 2), n - 1), 0);
-      const uint4* krow = reinterpret_cast<const uint4*>(krep + (size_t)ic * d);
-#pragma unroll
-      for (int q = 0; q < PPL; ++q) kv[u][q] = krow[part + 4 * q];
-      ss[u] = sstart[ic];
-      sl[u] = slen[ic];
-    }
-  };
-  // up to 256 spans go by one span per thread, more by PASSES of them
-  using One = std::integral_constant<int, 1>;
-  using All = std::integral_constant<int, PASSES>;
-  if (n <= 256) load_batch(One{}, 0); else load_batch(All{}, 0);      // in flight while the query row is fetched
   // Q^R of the chunk's one span
   if (tid < d) {
     const T* Qb = reinterpret_cast<const T*>(a.q) + (size_t)bi * D.Hq * d + (size_t)h * D.G * d;
@@ -927,7 +972,7 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
     score_batch(One{}, 0);
   } else {
     for (int i00 = 0; i00 < n; i00 += 256 * PASSES) {
-      if (i00 > 0) load_batch(All{}, i00);
+      if (i00 > 0) load_batch(None{}, All{}, i00, n - 1);
       score_batch(All{}, i00);
     }
   }
@@ -936,7 +981,9 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
+  int own[2];
+  clip_span(D, c0, own_start, own_len, own[0], own[1]);
+  emit_selection(D, a.st, slot, c0, 1, selmask, n, own, ids_out, cnt_out, E);
 }
 
 // ---- step 2 of a long chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
@@ -945,8 +992,8 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
 //      stream in and are multiplied on many compute units, and the one that finishes last (a ticket counter, left at zero again)
 //      selects (select_prefix) and writes the lists. Q^R is either in place (qrep_partial_kernel) or, with qrep_from_sums, built
 //      here from the running sums of the chunk's query rows, two rows per query span, and so are, with rs.k_arena, the
-//      mean keys of the chunk's own spans (Sec. 3.3.1): every workgroup of a problem writes the same values to
-//      the same places and reads its own copy back after a barrier. head_dim 128, spans retrieved (not units), at
+//      mean keys of the chunk's own spans (Sec. 3.3.1), which every workgroup of a problem writes to the same places (the
+//      same values) and reads its own copy back after a barrier. head_dim 128, spans retrieved (not units), at
 //      most RT1_MAX_SPANS stored spans (the launcher checks). ----
 template <int DT>
 __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bound) {
@@ -967,6 +1014,15 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   const int32_t* slen = a.st.span_len + (size_t)slot * D.max_spans;
   T* qrep = reinterpret_cast<T*>(a.sc.qrep) + (size_t)pg * a.Lp * d;
   T* krep_w = reinterpret_cast<T*>(a.st.krep) + (size_t)slot * D.max_spans * d;
+  const int n_score = (int)gridDim.y;
+  const T* krep = krep_w;
+  double* scores = a.st.scores + (size_t)slot * D.max_spans;
+  // a tile of 16 spans per wavefront, dealt out over the workgroups first: a compute unit takes 0.9 us of fp64 matrix
+  // products per tile and SIMD, so the tiles of a problem belong on as many of them as there are workgroups
+  const int i_first = 16 * (wave * n_score + (int)blockIdx.y);
+  ScoreTile<DT> tile;
+  if (i_first < n) tile.load(krep, n, i_first, d);        // in flight while Q^R is built
+  unsigned char* qlds = nullptr;
   if (a.qrep_from_sums && 16 * (int)blockIdx.y < n) {      // (a workgroup without spans to score needs none of it)
     // representative = (running sum at the span's end - running sum at its start) / length, rounded to the dtype
     const int n_q = a.rs.n_q, nblk = (n_q + RUNSUM_BLOCK - 1) / RUNSUM_BLOCK;
@@ -974,8 +1030,27 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
     const double* qpre = a.rs.out + (size_t)pl * a.rs.rows * d;
     const double* kpre = qpre + a.rs.keys_off;
     const bool with_keys = a.rs.k_arena != nullptr;
+    // The list writer's LDS is free until then: it holds Q^R of the chunk's spans where they fit (96 of them), else Q^R goes
+    // through memory, written and read back by the same workgroup.
+    if ((size_t)nqs * 256 <= sizeof(EmitShared)) qlds = reinterpret_cast<unsigned char*>(&E);
+    const int c = tid & 127;
+    // The two rows of a span, requested for the first eight spans together with the block sums (everything up to the
+    // scores took 5.6 us when the block sums, the rows, Q^R out of memory and the stored vectors followed each other)
+    struct Rows { double q0, q1, k0, k1; int x0, x1, len; };
+    auto rows_of = [&](int q) {
+      Rows w;
+      w.len = slen[first + q];
+      w.x0 = min(max(sstart[first + q] - c0, 0), n_q);
+      w.x1 = min(w.x0 + w.len, n_q);
+      const size_t o0 = (size_t)(max(w.x0, 1) - 1) * d + c, o1 = (size_t)(max(w.x1, 1) - 1) * d + c;
+      w.q0 = qpre[o0]; w.q1 = qpre[o1];
+      w.k0 = with_keys ? kpre[o0] : 0.0; w.k1 = with_keys ? kpre[o1] : 0.0;
+      return w;
+    };
+    int q = tid >> 7;
+    Rows w{};
+    if (q < nqs) w = rows_of(q);
     if (tid < 2 * d && (tid < d || with_keys)) {
-      const int c = tid & 127;
       const double* src = tid < d ? qpre : kpre;
       double* dst = carry + (tid < d ? 0 : nblk * d);
       double run = 0.0;
@@ -992,31 +1067,28 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
       }
     }
     __syncthreads();
-    const int c = tid & 127;
-    for (int q = tid >> 7; q < nqs; q += 8) {
-      const int len = slen[first + q];
-      const int x0 = min(max(sstart[first + q] - c0, 0), n_q), x1 = min(x0 + len, n_q);
-      const int b0 = (max(x0, 1) - 1) / RUNSUM_BLOCK, b1 = (max(x1, 1) - 1) / RUNSUM_BLOCK;
-      const size_t o0 = (size_t)(max(x0, 1) - 1) * d + c, o1 = (size_t)(max(x1, 1) - 1) * d + c;
-      const double q0 = x0 > 0 ? carry[b0 * d + c] + qpre[o0] : 0.0;
-      const double q1 = x1 > 0 ? carry[b1 * d + c] + qpre[o1] : 0.0;
-      qrep[(size_t)q * d + c] = Elt<DT>::from_f64((q1 - q0) / (double)len);
+    for (; q < nqs; q += 8) {
+      const int b0 = (max(w.x0, 1) - 1) / RUNSUM_BLOCK, b1 = (max(w.x1, 1) - 1) / RUNSUM_BLOCK;
+      const double q0 = w.x0 > 0 ? carry[b0 * d + c] + w.q0 : 0.0;
+      const double q1 = w.x1 > 0 ? carry[b1 * d + c] + w.q1 : 0.0;
+      const T qv = Elt<DT>::from_f64((q1 - q0) / (double)w.len);
+      if (qlds) *reinterpret_cast<T*>(qlds + q * 256 + (((((c * (int)sizeof(T)) >> 4) ^ q) & 15) << 4) + ((c * (int)sizeof(T)) & 15)) = qv;
+      else      qrep[(size_t)q * d + c] = qv;
       if (with_keys) {
-        const double k0 = x0 > 0 ? carry[(nblk + b0) * d + c] + kpre[o0] : 0.0;
-        const double k1 = x1 > 0 ? carry[(nblk + b1) * d + c] + kpre[o1] : 0.0;
-        krep_w[(size_t)(first + q) * d + c] = Elt<DT>::from_f64((k1 - k0) / (double)len);
+        const double k0 = w.x0 > 0 ? carry[(nblk + b0) * d + c] + w.k0 : 0.0;
+        const double k1 = w.x1 > 0 ? carry[(nblk + b1) * d + c] + w.k1 : 0.0;
+        krep_w[(size_t)(first + q) * d + c] = Elt<DT>::from_f64((k1 - k0) / (double)w.len);
       }
+      if (q + 8 < nqs) w = rows_of(q + 8);
     }
     __syncthreads();
+    // the chunk's own vectors have only now been written
+    if (with_keys && i_first < n && i_first + 16 > first) tile.load(krep, n, i_first, d);
   }
-  const int n_score = (int)gridDim.y;
-  const T* krep = reinterpret_cast<const T*>(a.st.krep) + (size_t)slot * D.max_spans * d;
-  double* scores = a.st.scores + (size_t)slot * D.max_spans;
-  // a tile of 16 spans per wavefront, dealt out over the workgroups first: a compute unit takes 0.9 us of fp64 matrix
-  // products per tile and SIMD, so the tiles of a problem belong on as many of them as there are workgroups
-  for (int i0 = 16 * (wave * n_score + (int)blockIdx.y); i0 < n; i0 += 256 * n_score) {
+  for (int i0 = i_first; i0 < n; i0 += 256 * n_score) {
+    if (i0 != i_first) tile.load(krep, n, i0, d);
     double best[4];
-    score_tile_f64<DT>(krep, n, i0, qrep, nqs, d, best);
+    tile.score(qrep, qlds, nqs, d, best);
     if ((lane & 15) == 0) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
@@ -1026,6 +1098,9 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
       }
     }
   }
+  // the extent of the thread's first item, for the workgroup that will select
+  int own[2] = {0, 0};
+  if (tid < n) clip_span(D, c0, sstart[tid], slen[tid], own[0], own[1]);
   wait_for_own_stores();                                  // the last workgroup reads them once every ticket is taken
   __syncthreads();
   if (n_score > 1) {
@@ -1043,8 +1118,8 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
     int c = 0;
     double sc = 0.0;
     if (i < n) {
-      int lo, hi;
-      clip_span(D, c0, sstart[i], slen[i], lo, hi);
+      int lo = own[0], hi = own[1];
+      if (i != tid) clip_span(D, c0, sstart[i], slen[i], lo, hi);
       c = max(hi - lo, 0);
       sc = __hip_atomic_load(scores + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       clip[i] = c;
@@ -1058,7 +1133,7 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)pg * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + pg : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
+  emit_selection(D, a.st, slot, c0, meta[META_CHUNK_LEN], selmask, n, own, ids_out, cnt_out, E);
 }
 
 // ---- retrieval by memory units (Eq. 9 as written): a unit scores the maximum over its spans; the
@@ -1106,7 +1181,7 @@ __global__ __launch_bounds__(1024) void unit_select_kernel(RetArgs a, int unit_b
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
+  emit_selection(D, a.st, slot, c0, meta[META_CHUNK_LEN], selmask, n, nullptr, ids_out, cnt_out, E);
 }
 
 // ---- collaborative voting over memory units (Sec. 3.5): the layer selects on its own, then the
@@ -1188,7 +1263,7 @@ __global__ __launch_bounds__(1024) void unit_vote_select_kernel(RetArgs a, int u
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)p * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + p : nullptr;
-  emit_selection(D, a.st, slot, selmask, n, ids_out, cnt_out, E);
+  emit_selection(D, a.st, slot, c0, meta[META_CHUNK_LEN], selmask, n, nullptr, ids_out, cnt_out, E);
 }
 
 // ---- caller-forced selection: ids already copied (ascending, unique) into sel_ids ----
@@ -1217,7 +1292,7 @@ __global__ __launch_bounds__(1024) void force_list_kernel(ForceArgs a) {
     }
   }
   __syncthreads();
-  emit_selection(D, a.st, slot, selmask, n, nullptr, nullptr, E);
+  emit_selection(D, a.st, slot, c0, meta[META_CHUNK_LEN], selmask, n, nullptr, nullptr, nullptr, E);
 }
 
 bool retrieve_is_one_launch(const Dims& D, int n_q, int span_bound) {
@@ -1390,7 +1465,7 @@ __global__ __launch_bounds__(1024) void persist_list_kernel(RetArgs a) {
     }
   }
   __syncthreads();
-  emit_selection(D, a.st, slot, selmask, n, nullptr, nullptr, E);
+  emit_selection(D, a.st, slot, c0, meta[META_CHUNK_LEN], selmask, n, nullptr, nullptr, nullptr, E);
 }
 
 hipError_t launch_persist_list(const Dims& D, const DevState& st, int layer, const BatchPos& bp, int seq_count,
