@@ -177,7 +177,7 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   CL.loc_cap = (int)align_up((size_t)c.n_sink + c.window, ATT_BN) + ATT_BN;
   CL.att_lse2 = o;  o = align_up(o + (size_t)c.n_seqs * c.chunk_max * c.n_q_heads * 4, 256);
   CL.loclist = o;   o = align_up(o + (size_t)c.n_seqs * CL.loc_cap * 4, 256);
-  CL.tickets = o;   o = align_up(o + (size_t)2 * P * 4, 256);
+  CL.tickets = o;   o = align_up(o + ((size_t)P + (size_t)c.n_seqs * c.n_kv_heads) * 4, 256);
   CL.total = o;
   CL.max_problems = P;
   return LTRI_OK;
@@ -275,7 +275,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   c->ever_sel.assign(n, 0u);
   if (!dry) {
     hipError_t e = launch_fill_zero(c->state, SL.total, c->stream);
-    if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.tickets, align_up((size_t)2 * CL.max_problems * 4, 256), c->stream);
+    if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.tickets, align_up(((size_t)CL.max_problems + (size_t)D.n_seqs * D.Hkv) * 4, 256), c->stream);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
     // the two events order streams of this device only: no timing, and a device-scope release when they are recorded
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming | hipEventReleaseToDevice);

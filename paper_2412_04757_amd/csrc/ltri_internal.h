@@ -78,7 +78,7 @@ struct ScratchLayout {
   size_t lpart;    // double [P][G][nb][Lp][2]  per tile: row maximum and sum of exponentials (row log-sum-exp in pieces)
   size_t att_lse2; // float  [n_seqs][chunk_max][Hq]  log-sum-exp of the first part of a two-part step
   size_t loclist;  // int32  [n_seqs][loc_cap]  initial | window tokens (two-part step)
-  size_t tickets;  // int32  [2][P]  finished workgroups per problem (step 2 of long chunks); zero between launches
+  size_t tickets;  // int32  [P] + [n_seqs * Hkv]  finished workgroups per problem (the two launches of step 2); zero between launches
   size_t total;
   int    loc_cap;       // entries of one sequence's initial | window list, whole tiles plus one
   int    max_problems;  // P the buffer was sized for
@@ -138,7 +138,7 @@ struct DevScratch {
   int32_t* tokspan; double* dyn; double* lpart; uint32_t* qhist; unsigned long long* qstate;
   float* att_lse2; int32_t* loclist;
   unsigned long long* qlist;
-  int32_t* tickets;   // [2][max_problems] counters of finished workgroups; zero between launches
+  int32_t* tickets;   // [max_problems] and [n_seqs * Hkv] counters of finished workgroups; zero between launches
 };
 
 // Running sums of a chunk's query and key rows (running_sums.h), which step 2 of long chunks with mean

@@ -23,8 +23,8 @@ struct RetArgs {
   const void* rep_k_arena;                // not NULL: the launch of the query-span pieces also stores the chunk's mean keys
   int qrep_by_last;                       // the last workgroup of the pieces' launch adds them up into Q^R
   int ticket_base;                        // first ticket counter of retrieve_chunk_kernel's problems
-  int qrep_from_sums;                     // retrieve_chunk_kernel builds Q^R (and, with rs.k_arena, the chunk's mean keys)
-  RunSums rs;                             // itself from these running sums
+  int qrep_mode;                          // where retrieve_chunk_kernel has Q^R from (QREP_*)
+  RunSums rs;                             // QREP_SUMS: the running sums
   BatchPos bp;
 };
 
@@ -285,7 +285,10 @@ __global__ __launch_bounds__(256) void score_kernel(RetArgs a) {
 // j0 + r): both fetch the 16-byte pieces g, g + 4, ... of their row, and product step (t, e) takes element e of
 // piece g + 4 t from either side, i.e. the same k on both sides in a permuted order. Rows past n and columns
 // past nqs read a valid row and are masked. All 64 lanes must call it together. load() may run ahead of score().
-// qlds (or NULL): the query representatives in LDS, 256-byte rows whose 16-byte pieces are permuted by the row (score_q_piece).
+// qlds (or NULL): the query representatives in LDS, whole rows whose 16-byte pieces are permuted by the row (qlds_off).
+__device__ __forceinline__ int qlds_off(int row, int byte, int row_bytes) {
+  return row * row_bytes + ((((byte >> 4) ^ (row & min(15, (row_bytes >> 4) - 1))) << 4) | (byte & 15));
+}
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 template <int DT>
 struct ScoreTile {
@@ -313,7 +316,8 @@ struct ScoreTile {
       uint4 bv[TMAX];
       if (qlds) {
 #pragma unroll
-        for (int t = 0; t < TMAX; ++t) bv[t] = *reinterpret_cast<const uint4*>(qlds + row * 256 + ((((g + 4 * t) ^ row) & 15) << 4));
+        for (int t = 0; t < TMAX; ++t)
+          bv[t] = t < nt ? *reinterpret_cast<const uint4*>(qlds + qlds_off(row, 16 * (g + 4 * t), d * (int)sizeof(T))) : make_uint4(0u, 0u, 0u, 0u);
       } else {
         const uint4* brow = reinterpret_cast<const uint4*>(qrep + (size_t)row * d);
 #pragma unroll
@@ -986,17 +990,21 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   emit_selection(D, a.st, slot, c0, 1, selmask, n, own, ids_out, cnt_out, E);
 }
 
-// ---- step 2 of a long chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
+constexpr int QREP_SHORT = SHORT_SUMS_TOKENS;      // longest chunk whose query rows every scoring workgroup sums itself
+
+// ---- step 2 of a chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
 //      in Eq. 9), the budgeted selection and the lists. gridDim.x = (sequence, KV head) problems;
 //      the gridDim.y workgroups of a problem share its scoring in tiles of 16 spans, so that the stored vectors
 //      stream in and are multiplied on many compute units, and the one that finishes last (a ticket counter, left at zero again)
-//      selects (select_prefix) and writes the lists. Q^R is either in place (qrep_partial_kernel) or, with qrep_from_sums, built
-//      here from the running sums of the chunk's query rows, two rows per query span, and so are, with rs.k_arena, the
-//      mean keys of the chunk's own spans (Sec. 3.3.1), which every workgroup of a problem writes to the same places (the
-//      same values) and reads its own copy back after a barrier. head_dim 128, spans retrieved (not units), at
-//      most RT1_MAX_SPANS stored spans (the launcher checks). ----
+//      selects (select_prefix; spans, or memory units by their spans' largest scores) and writes the lists. Q^R is in place
+//      (QREP_STORED, qrep_partial_kernel), or built here by every workgroup for itself: from the running sums of the chunk's
+//      query rows, two rows per query span (QREP_SUMS), or from the query rows (QREP_ROWS, up to QREP_SHORT of them). With the
+//      running sums come the mean keys of the chunk's own spans (Sec. 3.3.1) where the step stores them: every workgroup of a
+//      problem writes the same values to the same places and reads its own copy back after a barrier. head_dim 64 or 128 (QREP_SUMS: 128),
+//      at most RT1_MAX_SPANS stored spans (the launcher checks). ----
+enum : int { QREP_STORED = 0, QREP_SUMS = 1, QREP_ROWS = 2 };
 template <int DT>
-__global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bound) {
+__global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bound, int item_bound) {
   typedef typename Elt<DT>::type T;
   extern __shared__ __attribute__((aligned(16))) unsigned char rt1_lds[];
   __shared__ uint32_t selmask[RT1_MAX_SPANS / 32 + 2];
@@ -1007,7 +1015,7 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   const int pl = blockIdx.x, bi = a.batch_off + pl / D.Hkv, h = pl % D.Hkv, pg = bi * D.Hkv + h;
   const int slot = slot_of(D, a.layer, a.bp.seq[bi], h);
   const int32_t* meta = a.st.meta + (size_t)slot * META_WORDS;
-  const int d = 128, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int d = D.d, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = min(meta[META_N_SPANS], bound), c0 = meta[META_CHUNK_START];
   const int nqs = meta[META_CHUNK_NSP], first = meta[META_CHUNK_FIRST];
   const int32_t* sstart = a.st.span_start + (size_t)slot * D.max_spans;
@@ -1023,16 +1031,29 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   ScoreTile<DT> tile;
   if (i_first < n) tile.load(krep, n, i_first, d);        // in flight while Q^R is built
   unsigned char* qlds = nullptr;
-  if (a.qrep_from_sums && 16 * (int)blockIdx.y < n) {      // (a workgroup without spans to score needs none of it)
+  const int row_bytes = d * (int)sizeof(T);
+  // The list writer's LDS is free until then: it holds Q^R of the chunk's spans where they fit (96 of 256 bytes), else Q^R goes
+  // through memory, written and read back by the same workgroup.
+  if (a.qrep_mode != QREP_STORED && (size_t)nqs * row_bytes <= sizeof(EmitShared)) qlds = reinterpret_cast<unsigned char*>(&E);
+  auto put_qrep = [&](int q, int c, T v) {
+    if (qlds) *reinterpret_cast<T*>(qlds + qlds_off(q, c * (int)sizeof(T), row_bytes)) = v;
+    else      qrep[(size_t)q * d + c] = v;
+  };
+  if (a.qrep_mode == QREP_ROWS && 16 * (int)blockIdx.y < n) {
+    const T* Qb = reinterpret_cast<const T*>(a.q) + (size_t)bi * a.n_q * D.Hq * d + (size_t)h * D.G * d;
+    const uint32_t* mask = index_mask(D, a.st, slot, meta);
+    short_span_sums<DT, 16>(Qb, (size_t)D.Hq * d, D.G, a.n_q, d, nqs,
+                            [&](int q) { return q < nqs ? sstart[first + q] - c0 : sstart[first + nqs - 1] - c0 + slen[first + nqs - 1]; },
+                            mask, rt1_lds, [&](int q, int c, double v, int n_rows) { put_qrep(q, c, Elt<DT>::from_f64(mask ? v : v / (double)n_rows)); });
+    __syncthreads();
+  }
+  if (a.qrep_mode == QREP_SUMS && 16 * (int)blockIdx.y < n) {      // (a workgroup without spans to score needs none of it)
     // representative = (running sum at the span's end - running sum at its start) / length, rounded to the dtype
     const int n_q = a.rs.n_q, nblk = (n_q + RUNSUM_BLOCK - 1) / RUNSUM_BLOCK;
     double* carry = reinterpret_cast<double*>(rt1_lds);   // [2][blocks][128]: sum of the rows of all earlier blocks
     const double* qpre = a.rs.out + (size_t)pl * a.rs.rows * d;
     const double* kpre = qpre + a.rs.keys_off;
     const bool with_keys = a.rs.k_arena != nullptr;
-    // The list writer's LDS is free until then: it holds Q^R of the chunk's spans where they fit (96 of them), else Q^R goes
-    // through memory, written and read back by the same workgroup.
-    if ((size_t)nqs * 256 <= sizeof(EmitShared)) qlds = reinterpret_cast<unsigned char*>(&E);
     const int c = tid & 127;
     // The two rows of a span, requested for the first eight spans together with the block sums (everything up to the
     // scores took 5.6 us when the block sums, the rows, Q^R out of memory and the stored vectors followed each other)
@@ -1071,9 +1092,7 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
       const int b0 = (max(w.x0, 1) - 1) / RUNSUM_BLOCK, b1 = (max(w.x1, 1) - 1) / RUNSUM_BLOCK;
       const double q0 = w.x0 > 0 ? carry[b0 * d + c] + w.q0 : 0.0;
       const double q1 = w.x1 > 0 ? carry[b1 * d + c] + w.q1 : 0.0;
-      const T qv = Elt<DT>::from_f64((q1 - q0) / (double)w.len);
-      if (qlds) *reinterpret_cast<T*>(qlds + q * 256 + (((((c * (int)sizeof(T)) >> 4) ^ q) & 15) << 4) + ((c * (int)sizeof(T)) & 15)) = qv;
-      else      qrep[(size_t)q * d + c] = qv;
+      put_qrep(q, c, Elt<DT>::from_f64((q1 - q0) / (double)w.len));
       if (with_keys) {
         const double k0 = w.x0 > 0 ? carry[(nblk + b0) * d + c] + w.k0 : 0.0;
         const double k1 = w.x1 > 0 ? carry[(nblk + b1) * d + c] + w.k1 : 0.0;
@@ -1098,9 +1117,8 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
       }
     }
   }
-  // the extent of the thread's first item, for the workgroup that will select
-  int own[2] = {0, 0};
-  if (tid < n) clip_span(D, c0, sstart[tid], slen[tid], own[0], own[1]);
+  // the extent of the thread's first span, for the workgroup that will select
+  const int own_start = sstart[min(tid, max(n - 1, 0))], own_len = slen[min(tid, max(n - 1, 0))];
   wait_for_own_stores();                                  // the last workgroup reads them once every ticket is taken
   __syncthreads();
   if (n_score > 1) {
@@ -1109,31 +1127,47 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
     if (!s_last) return;
     if (tid == 0) a.sc.tickets[a.ticket_base + pl] = 0;
   }
-  const int npow = rt1_pow2(n);
+  const int n_new = meta[META_CHUNK_LEN];
+  const int ni = D.unit > 0 ? min(item_count(D, meta), item_bound) : n;      // items: units, or spans
+  const int npow = rt1_pow2(ni);
   uint64_t* skey = reinterpret_cast<uint64_t*>(rt1_lds);
-  uint32_t* sidx = reinterpret_cast<uint32_t*>(rt1_lds + (size_t)rt1_pow2(bound) * 8);
-  int* clip = reinterpret_cast<int*>(rt1_lds + (size_t)rt1_pow2(bound) * 12);
-  for (int w = tid; w < (n + 31) / 32 + 2; w += blockDim.x) selmask[w] = 0u;
-  for (int i = tid; i < npow; i += blockDim.x) {
-    int c = 0;
-    double sc = 0.0;
-    if (i < n) {
-      int lo = own[0], hi = own[1];
-      if (i != tid) clip_span(D, c0, sstart[i], slen[i], lo, hi);
-      c = max(hi - lo, 0);
-      sc = __hip_atomic_load(scores + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      clip[i] = c;
+  uint32_t* sidx = reinterpret_cast<uint32_t*>(rt1_lds + (size_t)rt1_pow2(item_bound) * 8);
+  int* clip = reinterpret_cast<int*>(rt1_lds + (size_t)rt1_pow2(item_bound) * 12);
+  for (int w = tid; w < (ni + 31) / 32 + 2; w += blockDim.x) selmask[w] = 0u;
+  auto span_score = [&](int i) { return __hip_atomic_load(scores + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  if (D.unit > 0) {
+    // a unit's score is the largest of the spans that start in it: the smallest order key
+    for (int u = tid; u < npow; u += blockDim.x) skey[u] = score_key(-INFINITY);
+    __syncthreads();
+    for (int i = tid; i < n; i += blockDim.x) {
+      const int u = (i == tid ? own_start : sstart[i]) / D.unit;
+      if (u < ni) atomicMin(reinterpret_cast<unsigned long long*>(skey + u), (unsigned long long)score_key(span_score(i)));
     }
-    // spans that cannot be retrieved go to the end of the order with the padding
-    skey[i] = c > 0 ? score_key(sc) : ~0ull;
+    __syncthreads();
+  }
+  int own[2] = {0, 0};
+  for (int i = tid; i < npow; i += blockDim.x) {
+    int c = 0, lo = 0, hi = 0;
+    uint64_t key = 0;
+    if (i < ni) {
+      int start = own_start, len = own_len;
+      if (D.unit > 0 || i != tid) item_range(D, sstart, slen, c0 + n_new, i, start, len);
+      clip_span(D, c0, start, len, lo, hi);
+      c = max(hi - lo, 0);
+      clip[i] = c;
+      key = D.unit > 0 ? skey[i] : score_key(span_score(i));
+      if (i == tid) { own[0] = lo; own[1] = hi; }
+    }
+    // items that cannot be retrieved go to the end of the order with the padding
+    skey[i] = c > 0 ? key : ~0ull;
     sidx[i] = c > 0 ? (uint32_t)i : RT1_PAD;
   }
   __syncthreads();
-  select_prefix(D, skey, sidx, clip, n, npow, selmask, wave_tot, E);
+  select_prefix(D, skey, sidx, clip, ni, npow, selmask, wave_tot, E);
   __syncthreads();
   int32_t* ids_out = a.sel_ids_out ? a.sel_ids_out + (size_t)pg * D.sel_cap : nullptr;
   int32_t* cnt_out = a.sel_cnt_out ? a.sel_cnt_out + pg : nullptr;
-  emit_selection(D, a.st, slot, c0, meta[META_CHUNK_LEN], selmask, n, own, ids_out, cnt_out, E);
+  emit_selection(D, a.st, slot, c0, n_new, selmask, ni, own, ids_out, cnt_out, E);
 }
 
 // ---- retrieval by memory units (Eq. 9 as written): a unit scores the maximum over its spans; the
@@ -1318,7 +1352,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   if (src && (!a.append_first || D.offload)) return hipErrorInvalidValue;
   if (src) a.src = *src;
   a.rep_k_arena = rep_k_arena;
-  a.qrep_by_last = false; a.ticket_base = 0; a.qrep_from_sums = 0;
+  a.qrep_by_last = false; a.ticket_base = 0; a.qrep_mode = QREP_STORED;
   a.rs = RunSums{};
   if (rep_k_arena && !retrieve_stores_rep_keys(D, n_q)) return hipErrorInvalidValue;
   if (a.append_first && !retrieve_is_one_launch(D, n_q, span_bound)) return hipErrorInvalidValue;
@@ -1345,11 +1379,15 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
     return hipGetLastError();
   }
   a.units_cap = n_q / QREP_PIECE + n_q;                  // pieces of all spans of a chunk, at most
-  // Long chunks of 128-wide heads with spans as the retrieval unit: after the pieces' sums everything else of the
-  // step is one launch per batch of sequences (retrieve_chunk_kernel).
-  // (its arrays of keys, ids and lengths share the 160 KB of LDS with 26 KB of masks and list scratch)
-  const bool one_tail = n_q > QREP_PIECE && D.d == 128 && D.unit == 0 && !votes && span_bound >= 1 &&
-                        span_bound <= RT1_MAX_SPANS && rt1_lds_bytes(span_bound) <= 116 * 1024;
+  // One launch per batch of sequences for everything, or everything but the sums of the query rows (retrieve_chunk_kernel):
+  // all but collaborative retrieval and very long tables (its arrays of keys, ids and lengths share the 160 KB of LDS with
+  // 26 KB of masks and list scratch). The launches it replaces on other than 128-wide heads, chunks of up to 128 tokens and
+  // retrieval by units (Q^R, scores, ranks or units, lists: 3 to 5 of them): 256 fp32 tokens, 64 wide, 25.6 us -> 17.2; 128
+  // tokens by units with index vectors 27 -> 14.6; 2048 tokens 62 -> 41.
+  const int unit_bound = D.unit > 0 ? (int)(D.max_tokens / D.unit) + 1 : 0;    // units a full stream has, at most
+  const int item_bound = D.unit > 0 ? unit_bound : span_bound;
+  const bool one_tail = !votes && span_bound >= 1 && span_bound <= RT1_MAX_SPANS && item_bound <= RT1_MAX_SPANS &&
+                        rt1_lds_bytes(item_bound) <= 116 * 1024;
   if (one_tail) {
     static bool attr_set = false;
     if (!attr_set) {
@@ -1362,29 +1400,32 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
       attr_set = true;
     }
   }
-  if (n_q > QREP_PIECE) {
-    const int per = sc_max_problems / D.Hkv;               // sequences the piece buffer holds
+  if (one_tail || n_q > QREP_PIECE) {
+    const int piece_seqs = sc_max_problems / D.Hkv;        // sequences the buffer of pieces or running sums is for
     const int gx = QREP_GRID_X + (rep_k_arena ? QREP_GRID_X : 0);
     // Mean representatives in bf16 (whose sums are exact in fp64): Q^R and the chunk's mean keys come from running
     // sums of the query and key rows, which need no span boundaries (no piece sums, no ticket).
     const bool from_sums = one_tail && retrieve_reads_running_sums(D, n_q);
-    size_t lds = rt1_lds_bytes(span_bound);
+    if (sums_ready && (!from_sums || seq_count > piece_seqs)) sums_ready = false;     // not usable: taken here
+    const bool from_rows = one_tail && !from_sums && n_q <= QREP_SHORT;
+    size_t lds = rt1_lds_bytes(item_bound);
     if (from_sums) {
       const size_t carry_bytes = (size_t)((n_q + RUNSUM_BLOCK - 1) / RUNSUM_BLOCK) * 2 * 128 * 8;
       if (lds < carry_bytes) lds = carry_bytes;
       a.rs = running_sums_of(D, sc, sc_max_problems, q, rep_k_arena, n_q);
     }
-    if (sums_ready && (!from_sums || seq_count > per)) sums_ready = false;     // not usable: taken here
+    if (from_rows && lds < short_sums_lds(D.d)) lds = short_sums_lds(D.d);
+    a.qrep_mode = from_sums ? QREP_SUMS : from_rows ? QREP_ROWS : QREP_STORED;
+    a.ticket_base = sc_max_problems;                        // the second part of the counters
+    const int per = from_rows ? seq_count : piece_seqs;
     for (int off = 0; off < seq_count; off += per) {
       const int cnt = seq_count - off < per ? seq_count - off : per;
       a.batch_off = off;
       dim3 gp(gx, cnt * D.Hkv), gf(n_q < 64 ? n_q : 64, cnt * D.Hkv);
       a.qrep_by_last = one_tail;
-      a.ticket_base = sc_max_problems;                      // the second half of the counters
       if (from_sums) {
         if (!sums_ready) running_sums_kernel<<<dim3(running_sums_blocks(a.rs), cnt * D.Hkv), 1024, 0, s>>>(a);
-        a.qrep_from_sums = 1;
-      } else {
+      } else if (!from_rows) {
         if (bf) qrep_partial_kernel<LTRI_BF16><<<gp, 1024, 0, s>>>(a);
         else    qrep_partial_kernel<LTRI_F32><<<gp, 1024, 0, s>>>(a);
       }
@@ -1393,8 +1434,8 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
         // one tile per SIMD (with 256 spans per workgroup, held together, a launch over 100 to 300 spans took 18.7 us,
         // now 16.6)
         const dim3 gt(cnt * D.Hkv, (span_bound + 127) / 128);
-        if (bf) retrieve_chunk_kernel<LTRI_BF16><<<gt, 1024, lds, s>>>(a, span_bound);
-        else    retrieve_chunk_kernel<LTRI_F32><<<gt, 1024, lds, s>>>(a, span_bound);
+        if (bf) retrieve_chunk_kernel<LTRI_BF16><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
+        else    retrieve_chunk_kernel<LTRI_F32><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
       } else {
         if (bf) qrep_final_kernel<LTRI_BF16><<<gf, 128, 0, s>>>(a);
         else    qrep_final_kernel<LTRI_F32><<<gf, 128, 0, s>>>(a);
@@ -1414,7 +1455,6 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   if (bf) score_kernel<LTRI_BF16><<<gs, 256, qs_bytes, s>>>(a);
   else    score_kernel<LTRI_F32><<<gs, 256, qs_bytes, s>>>(a);
   if (D.unit > 0) {
-    const int unit_bound = (int)(D.max_tokens / D.unit) + 1;           // units a full stream has, at most
     static bool attr_set = false;
     if (!attr_set) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&unit_select_kernel),

@@ -73,4 +73,107 @@ __device__ __forceinline__ void span_mean_block(const typename Elt<DT>::type* ba
   __syncthreads();
 }
 
+// ---- the same for all spans of a short chunk, by one workgroup ----
+// put(q, c, sum, n): column c of the sum over the tokens of span q (with a mask: its marked ones; n of them), q < nq, of the
+// `inner` rows of every token (tok_stride elements apart). start(q): chunk-local start of span q, start(nq) the last one's
+// end. Chunks of up to SHORT_SUMS_TOKENS tokens; called by all 64 NW threads; lds: short_sums_lds() bytes. Wavefront w takes
+// the w-th share of the tokens (with a mask, of a list of the marked ones, so that only their rows are read), eight loads in
+// flight, and leaves one partial sum per span it meets (spans and shares both ascend, so the places differ), which are added
+// up in ascending order. It takes the place of a launch with a workgroup per span. What bounds it: one compute unit reads
+// about 25 GB/s of rows that are in no cache (128 bf16 tokens of four heads 5 us, 256 fp32 ones, 64 wide, 9.3: longer chunks
+// keep a workgroup per span or piece, also for the 64 KB of keys, where this took 5 us behind the selection and the launch 4).
+constexpr int SHORT_SUMS_TOKENS = 128;
+constexpr int SHORT_SUMS_SPANS = 32;                       // spans at a time
+__host__ __device__ constexpr size_t short_sums_lds(int d) {
+  return (size_t)(SHORT_SUMS_SPANS + 15) * d * 8 + (SHORT_SUMS_SPANS + 1 + SHORT_SUMS_TOKENS) * 4;
+}
+template <int DT, int NW, class Start, class Put>
+__device__ __forceinline__ void short_span_sums(const typename Elt<DT>::type* base, size_t tok_stride, int inner, int n_tok,
+                                                int d, int nq, Start start_of, const uint32_t* mask, unsigned char* lds, Put put) {
+  typedef typename Elt<DT>::type T;
+  static_assert(NW <= 16, "places of the partial sums");
+  constexpr int EPP = 16 / (int)sizeof(T), MW = SHORT_SUMS_TOKENS / 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = d / EPP, rpw = 64 / R;                     // lanes per row, rows per load
+  const int sub = lane / R, piece = lane - sub * R;
+  const int GL = (inner + rpw - 1) / rpw;                  // loads per token
+  double* part = reinterpret_cast<double*>(lds);
+  int* start = reinterpret_cast<int*>(lds + (size_t)(SHORT_SUMS_SPANS + 15) * d * 8);      // places in the list
+  int* list = start + SHORT_SUMS_SPANS + 1;
+  uint32_t mw[MW];
+  auto place = [&](int t) {                                // marked tokens before token t
+    if (!mask) return t;
+    int c = 0;
+#pragma unroll
+    for (int w = 0; w < MW; ++w) {
+      const int bits = min(max(t - 32 * w, 0), 32);
+      c += __popc(bits == 32 ? mw[w] : mw[w] & ((1u << bits) - 1u));
+    }
+    return c;
+  };
+  if (mask) {
+#pragma unroll
+    for (int w = 0; w < MW; ++w) mw[w] = mask[w];
+    if (tid < n_tok && ((mask[tid >> 5] >> (tid & 31)) & 1u)) list[place(tid)] = tid;
+  }
+  const int n_list = place(n_tok), S = max((n_list + NW - 1) / NW, 1);
+  for (int s0 = 0; s0 < nq; s0 += SHORT_SUMS_SPANS) {
+    const int ns = min(SHORT_SUMS_SPANS, nq - s0);
+    if (s0) __syncthreads();                               // the partial sums of the spans before are read
+    if (tid <= ns) start[tid] = place(start_of(s0 + tid));
+    __syncthreads();
+    const int t_lo = max(wave * S, start[0]), t_hi = min((wave + 1) * S, start[ns]);
+    if (t_lo < t_hi) {
+      const uint64_t begun = __ballot(lane < ns && start[min(lane, ns)] <= t_lo);
+      int s = __popcll(begun) - 1, next = start[s + 1];
+      double acc[EPP];
+#pragma unroll
+      for (int e = 0; e < EPP; ++e) acc[e] = 0.0;
+      auto flush = [&]() {
+#pragma unroll
+        for (int e = 0; e < EPP; ++e) {
+          if (R <= 16) acc[e] += lane_xor_f64<16>(acc[e]);
+          acc[e] += lane_xor_f64<32>(acc[e]);
+        }
+        if (lane < R) {
+#pragma unroll
+          for (int e = 0; e < EPP; ++e) part[(s + wave) * d + piece * EPP + e] = acc[e];
+        }
+#pragma unroll
+        for (int e = 0; e < EPP; ++e) acc[e] = 0.0;
+      };
+      int lt = t_lo, lg = 0, ct = t_lo, cg = 0;            // (token, load) to request next, and to add next
+      while (ct < t_hi) {
+        uint4 v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {                      // (past the end: the last token again)
+          const int i = min(lt, t_hi - 1), tok = mask ? list[i] : i;
+          v[e] = *reinterpret_cast<const uint4*>(base + (size_t)tok * tok_stride + (size_t)min(lg * rpw + sub, inner - 1) * d + piece * EPP);
+          if (++lg == GL) { lg = 0; ++lt; }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (ct >= t_hi) break;                           // uniform
+          while (cg == 0 && ct == next) { flush(); ++s; next = start[s + 1]; }      // (a span without a marked token: 0)
+          if (cg * rpw + sub < inner) {
+            const T* pv = reinterpret_cast<const T*>(&v[e]);
+#pragma unroll
+            for (int k = 0; k < EPP; ++k) acc[k] += Elt<DT>::to_f64(pv[k]);
+          }
+          if (++cg == GL) { cg = 0; ++ct; }
+        }
+      }
+      flush();
+    }
+    __syncthreads();
+    for (int i = tid; i < ns * d; i += 64 * NW) {
+      const int q = i / d, c = i - q * d, b0 = start[q], b1 = start[q + 1];
+      double sum = 0.0;
+      if (b1 > b0)
+        for (int w = b0 / S; w <= (b1 - 1) / S; ++w) sum += part[(q + w) * d + c];
+      put(s0 + q, c, sum, b1 - b0);
+    }
+  }
+}
+
 }  // namespace ltri
