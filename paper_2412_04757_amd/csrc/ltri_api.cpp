@@ -425,13 +425,11 @@ static void append_commit(ltri_ctx* c, int layer, int seq_begin, int seq_count, 
 }
 
 // Step 1 of a chunk: segmentation and index vectors. Its rows are in the arenas already, or (src) a launch of the segmentation
-// copies them there. `fork` (or NULL)
-// is recorded on the context's stream behind the last kernel that fills the chip; what follows it there
-// are kernels of a few workgroups each.
+// copies them there. rep_keys_later: step 2 stores the mean keys.
 // q_step2 (or NULL): the query rows that step 2 will be called with right after; *sums_ready then says whether the
-// running sums it reads were taken along by the segmentation's first launch.
+// running sums it reads were taken along.
 static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_count, const void* q_seg, int n_new,
-                            hipEvent_t fork, const ChunkRows* src, bool rep_keys_later = false, const void* q_step2 = nullptr,
+                            const ChunkRows* src, bool rep_keys_later = false, const void* q_step2 = nullptr,
                             bool* sums_ready = nullptr) {
   int32_t r;
   if (src && !src->k_chunk) src = nullptr;
@@ -441,13 +439,12 @@ static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_
       r = check_hip(c, launch_copy_chunk(c->D, *src, layer, bp, seq_count, 1, c->stream), "copy chunk");
       if (r != LTRI_OK) return r;
     }
-    r = check_hip(c, launch_append_single(c->D, c->ds, c->k_arena, layer, bp, seq_count, c->stream),
-                  "append (single token)");
-    if (r == LTRI_OK && fork) r = check_hip(c, hipEventRecord(fork, c->stream), "fork");
-    return r;
+    return check_hip(c, launch_append_single(c->D, c->ds, c->k_arena, layer, bp, seq_count, c->stream),
+                     "append (single token)");
   }
   const int per = c->CL.max_problems / c->D.Hkv;     // sequences per segmentation launch
   const bool dynamic = c->D.rep_mode == LTRI_REP_DYNAMIC;
+  const bool reps = segment_stores_reps(c->D, n_new);
   // one batch of sequences only: the sums of a second batch would take the place of the first one's
   const bool with_sums = q_step2 && sums_ready && seq_count <= per && retrieve_reads_running_sums(c->D, n_new);
   RunSums sums;
@@ -455,20 +452,18 @@ static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_
     sums = running_sums_of(c->D, c->dc, c->CL.max_problems, q_step2, rep_keys_later ? c->k_arena : nullptr, n_new);
   for (int off = 0; off < seq_count; off += per) {
     const int cnt = std::min(per, seq_count - off);
-    const bool last = off + per >= seq_count;
     r = check_hip(c, launch_segment(c->D, c->ds, c->dc, c->k_arena, q_seg, layer, bp, off, cnt, n_new,
-                                    last && !dynamic ? fork : nullptr, with_sums ? &sums : nullptr, src, c->stream), "segment");
+                                    with_sums ? &sums : nullptr, src, c->stream), "segment");
     if (r != LTRI_OK) return r;
-    if (dynamic) {
+    if (dynamic && !reps) {
       r = check_hip(c, launch_dynamic_reps(c->D, c->ds, c->dc, c->k_arena, q_seg, layer, bp, off, cnt, n_new,
-                                           c->D.seg_map == LTRI_MAP_SOFTMAX, last ? fork : nullptr, c->stream),
-                    "index vectors");
+                                           c->D.seg_map == LTRI_MAP_SOFTMAX, c->stream), "index vectors");
       if (r != LTRI_OK) return r;
     }
     c->theta_layer = layer; c->theta_seq0 = bp.seq[off]; c->theta_seqs = cnt;
   }
   if (with_sums) *sums_ready = true;
-  if (c->D.rep_mode == LTRI_REP_MEAN && !rep_keys_later) {   // later: step 2's first launch stores them as well
+  if (!dynamic && !reps && !rep_keys_later) {
     r = check_hip(c, launch_rep_keys(c->D, c->ds, c->k_arena, layer, bp, seq_count, n_new, c->stream),
                   "representative keys");
     if (r != LTRI_OK) return r;
@@ -488,7 +483,7 @@ int32_t ltri_append_chunk(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t
     if (own_copy) r = copy_chunk(c, layer, bp, seq_count, k_chunk, v_chunk, n_new, true);
     if (r != LTRI_OK) return r;
     const ChunkRows src = chunk_rows(c, k_chunk, v_chunk, false);
-    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, own_copy ? nullptr : &src);
+    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, own_copy ? nullptr : &src);
     if (r != LTRI_OK) return r;
   }
   append_commit(c, layer, seq_begin, seq_count, n_new);
@@ -533,7 +528,7 @@ int32_t ltri_append_chunk_with_spans(ltri_ctx* c, int32_t layer, int32_t seq, co
     if (r != LTRI_OK) return r;
     if (c->D.rep_mode == LTRI_REP_DYNAMIC && n_new > 1)
       r = check_hip(c, launch_dynamic_reps(c->D, c->ds, c->dc, c->k_arena, nullptr, layer, bp, 0, 1, n_new, false,
-                                           nullptr, c->stream), "index vectors");
+                                           c->stream), "index vectors");
     else
       r = check_hip(c, launch_rep_keys(c->D, c->ds, c->k_arena, layer, bp, 1, n_new, c->stream),
                     "representative keys");
@@ -846,7 +841,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
         c->ever_sel[ls_index(c, layer, seq_begin + s)] = 0xFFFFFFFFu;
       }
     } else {
-      r = append_spans(c, layer, bp, seq_count, q_seg, 1, nullptr, own_copy ? nullptr : &src);
+      r = append_spans(c, layer, bp, seq_count, q_seg, 1, own_copy ? nullptr : &src);
       if (r != LTRI_OK) return r;
       append_commit(c, layer, seq_begin, seq_count, 1);
       r = ltri_retrieve(c, layer, seq_begin, seq_count, q, 1, nullptr, nullptr);
@@ -874,7 +869,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     // attention is one launch over initial | retrieved | window | chunk. Its workgroups are equal in work (row
     // sub-tiles paired from both ends of the chunk) and fill every compute unit, so a split that runs the first
     // part beside the small kernels of steps 1 and 2 only makes those wait for a free compute unit.
-    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, &src, keys_with_step2, q, &sums_ready);
+    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready);
     if (r != LTRI_OK) return r;
     append_commit(c, layer, seq_begin, seq_count, n_new);
     r = retrieve_impl(c, layer, seq_begin, seq_count, q, n_new, nullptr, nullptr, keys_with_step2, sums_ready);
@@ -903,7 +898,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   auto both_streams = [&]() -> int32_t {
     int32_t e = check_hip(c, launch_local_list(c->D, bp, seq_count, c->dc.loclist, c->CL.loc_cap, c->stream), "local list");
     if (e != LTRI_OK) return e;
-    e = append_spans(c, layer, bp, seq_count, q_seg, n_new, nullptr, &src, keys_with_step2, q, &sums_ready);
+    e = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready);
     if (e != LTRI_OK) return e;
     append_commit(c, layer, seq_begin, seq_count, n_new);
     side_queued = true;                  // (from here on the second stream may hold work of this step)

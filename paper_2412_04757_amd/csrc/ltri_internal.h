@@ -183,16 +183,17 @@ hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_poo
                                   const void* v_chunk, int n_new, hipStream_t s);
 hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                           const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                          int n_new, hipEvent_t after_tiles, const RunSums* sums, const ChunkRows* src, hipStream_t s);
-// event (or NULL): recorded behind the last kernel that fills the chip; sums (or NULL): further workgroups of the
-// selections' launch take these running sums; src (or NULL): rows of the chunk that the selections' launch copies
+                          int n_new, const RunSums* sums, const ChunkRows* src, hipStream_t s);
+// sums (or NULL): further workgroups of the selections' launch take these running sums; src (or NULL): rows of the chunk
+// that the selections' launch copies
+bool segment_stores_reps(const Dims& D, int n_new);      // the index vectors as well (chunks of up to 128 tokens, which are one launch)
 hipError_t launch_append_single(const Dims& D, const DevState& st, const void* k_arena, int layer,
                                 const BatchPos& bp, int seq_count, hipStream_t s);
 hipError_t launch_append_bounds(const Dims& D, const DevState& st, const DevScratch& sc, int layer,
                                 int seq, int c0, int n_new, hipStream_t s);
 hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                                const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                               int n_new, bool lse_ready, hipEvent_t after_tiles, hipStream_t s);   // event as in launch_segment
+                               int n_new, bool lse_ready, hipStream_t s);
 hipError_t launch_rep_keys(const Dims& D, const DevState& st, const void* k_arena, int layer,
                            const BatchPos& bp, int seq_count, int n_new, hipStream_t s);
 hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& sc, int sc_max_problems,

@@ -1270,6 +1270,40 @@ __device__ __forceinline__ int wave_sum_i32(int v) {
   return v;
 }
 
+// Eq. 7: index tokens of a span of `len` tokens with these sums of votes, in-span and whole row sums of the map. Triangle + row
+// neighbours are the span's rows, triangle + column neighbours its votes.
+__device__ __forceinline__ int index_count(const Dims& D, int len, double votes, double tri, double rows) {
+  const double den = D.ratio_mode == LTRI_RATIO_ROW ? rows : D.ratio_mode == LTRI_RATIO_COL ? votes : rows + votes - tri;
+  const double r_v = 1.0 / exp(D.lambda * (1.0 - tri / den));
+  int n = (int)rint((double)len * r_v);
+  n = max(n, D.index_min);
+  if (D.index_max > 0) n = min(n, D.index_max);
+  return max(1, min(n, len));
+}
+
+// Share of span k of a memory block's nm spans, whose counts are cnt[], under the block's budget, by one wavefront: a lane per
+// span, or several spans where there are more than 64.
+__device__ __forceinline__ int block_share(const int* cnt, int nm, int k, int budget) {
+  const int lane = threadIdx.x & 63;
+  auto levelled = [&](int level) {                        // total of the counts cut off at this level
+    int sum = 0;
+    for (int m = lane; m < nm; m += 64) sum += min(cnt[m], level);
+    return wave_sum_i32(sum);
+  };
+  const int share = cnt[k];
+  if (levelled(SEG_MAX_L) <= budget) return share;
+  int lvl_lo = 1, lvl_hi = min(SEG_MAX_L, budget);        // the largest level whose levelled total fits (1 if none does)
+  while (lvl_lo < lvl_hi) {
+    const int mid = (lvl_lo + lvl_hi + 1) >> 1;
+    if (levelled(mid) <= budget) lvl_lo = mid; else lvl_hi = mid - 1;
+  }
+  const int level = lvl_lo, left = budget - levelled(level);
+  int before = 0;                                         // spans in front of this one that are still short
+  for (int m = lane; m < k; m += 64) before += cnt[m] > level ? 1 : 0;
+  before = wave_sum_i32(before);
+  return min(share, level) + (share > level && before < left ? 1 : 0);
+}
+
 // per span: area ratio, number of index tokens (Eq. 7), the tokens, the sum of their keys. One workgroup per span, and
 // bound by the latency of its chain of steps: 18.5 us a chunk of 128 tokens and 12 index tokens per block with a sort of
 // the tokens and a block's budget levelled by one thread, 11.6 us with tokens ranked by comparing them (spans up to
@@ -1312,15 +1346,7 @@ __global__ __launch_bounds__(1024) void dyn_span_kernel(SegArgs a) {
       if (tid == 0) {
         double votes = 0.0, tri = 0.0, rows = 0.0;
         for (int w = 0; w < 16; ++w) { votes += red[0][w]; tri += red[1][w]; rows += red[2][w]; }
-        // triangle + row neighbours = the span's rows; triangle + column neighbours = its votes
-        const double den = D.ratio_mode == LTRI_RATIO_ROW ? rows
-                         : D.ratio_mode == LTRI_RATIO_COL ? votes : rows + votes - tri;
-        const double r_a = tri / den;
-        const double r_v = 1.0 / exp(D.lambda * (1.0 - r_a));
-        int n = (int)rint((double)len * r_v);
-        n = max(n, D.index_min);
-        if (D.index_max > 0) n = min(n, D.index_max);
-        s_count = max(1, min(n, len));
+        s_count = index_count(D, len, votes, tri, rows);
       }
     } else {
       // A budget of index vectors per memory block (the piece of a unit inside this chunk), shared over the
@@ -1340,36 +1366,12 @@ __global__ __launch_bounds__(1024) void dyn_span_kernel(SegArgs a) {
         double v0 = 0.0, v1 = 0.0, v2 = 0.0;
         for (int t = lane; t < ml; t += 64) { v0 += dyn[ms + t]; v1 += dyn[a.Lp + ms + t]; v2 += dyn[2 * a.Lp + ms + t]; }
         v0 = wave_sum_f64(v0); v1 = wave_sum_f64(v1); v2 = wave_sum_f64(v2);
-        if (lane == 0) {
-          const double den = D.ratio_mode == LTRI_RATIO_ROW ? v2 : D.ratio_mode == LTRI_RATIO_COL ? v0 : v2 + v0 - v1;
-          const double r_v = 1.0 / exp(D.lambda * (1.0 - v1 / den));
-          int n = (int)rint((double)ml * r_v);
-          n = max(n, D.index_min);
-          if (D.index_max > 0) n = min(n, D.index_max);
-          s_cnt[m - mlo] = max(1, min(n, ml));
-        }
+        if (lane == 0) s_cnt[m - mlo] = index_count(D, ml, v0, v1, v2);
       }
       __syncthreads();
       const int nm = mhi - mlo + 1, budget = D.index_block_max;
       if (wave == 0) {                                    // a lane per span, or several spans where there are more than 64
-        auto levelled = [&](int level) {                  // total of the counts cut off at this level
-          int sum = 0;
-          for (int m = lane; m < nm; m += 64) sum += min(s_cnt[m], level);
-          return wave_sum_i32(sum);
-        };
-        int share = s_cnt[q - mlo];
-        if (levelled(SEG_MAX_L) > budget) {
-          int lvl_lo = 1, lvl_hi = min(SEG_MAX_L, budget);   // the largest level whose levelled total fits (1 if none does)
-          while (lvl_lo < lvl_hi) {
-            const int mid = (lvl_lo + lvl_hi + 1) >> 1;
-            if (levelled(mid) <= budget) lvl_lo = mid; else lvl_hi = mid - 1;
-          }
-          const int level = lvl_lo, left = budget - levelled(level);
-          int before = 0;                                 // spans in front of this one that are still short
-          for (int m = lane; m < q - mlo; m += 64) before += s_cnt[m] > level ? 1 : 0;
-          before = wave_sum_i32(before);
-          share = min(share, level) + (share > level && before < left ? 1 : 0);
-        }
+        const int share = block_share(s_cnt, nm, q - mlo, budget);
         if (lane == 0) s_count = share;
       }
     }
@@ -1560,6 +1562,12 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint4* p, size_t n16) {
     p[i] = z;
 }
 
+}  // namespace ltri
+
+#include "seg_short.h"
+
+namespace ltri {
+
 // ============================================================================ launchers
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   const size_t n16 = bytes / 16;
@@ -1588,7 +1596,7 @@ hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_poo
 
 hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                                const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                               int n_new, bool lse_ready, hipEvent_t after_tiles, hipStream_t s) {
+                               int n_new, bool lse_ready, hipStream_t s) {
   SegArgs a;
   a.D = D; a.st = st; a.sc = sc; a.k_arena = k_arena; a.q_seg = q_seg; a.layer = layer;
   a.batch_off = batch_off; a.n_new = n_new;
@@ -1611,10 +1619,6 @@ hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScrat
   dyn_token_span_kernel<<<gl, 256, 0, s>>>(a);
   if (bf) dyn_tile_kernel<LTRI_BF16><<<gt, 256, 0, s>>>(a);
   else    dyn_tile_kernel<LTRI_F32><<<gt, 256, 0, s>>>(a);
-  if (after_tiles) {                     // the last kernel that fills the chip is queued
-    const hipError_t e = hipEventRecord(after_tiles, s);
-    if (e != hipSuccess) return e;
-  }
   dyn_reduce_kernel<<<gl, 256, 0, s>>>(a);
   dim3 gs(64, P);
   if (bf) dyn_span_kernel<LTRI_BF16><<<gs, 1024, 0, s>>>(a);
@@ -1622,9 +1626,13 @@ hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScrat
   return hipGetLastError();
 }
 
+bool segment_stores_reps(const Dims& D, int n_new) {
+  return n_new <= SEG_SHORT && (D.rep_mode == LTRI_REP_MEAN || D.seg_map == LTRI_MAP_SOFTMAX);
+}
+
 hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                           const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                          int n_new, hipEvent_t after_tiles, const RunSums* sums, const ChunkRows* src, hipStream_t s) {
+                          int n_new, const RunSums* sums, const ChunkRows* src, hipStream_t s) {
   SegArgs a;
   a.D = D; a.st = st; a.sc = sc; a.k_arena = k_arena; a.q_seg = q_seg; a.layer = layer;
   a.batch_off = batch_off; a.n_new = n_new;
@@ -1651,6 +1659,16 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
   if (D.theta_quantile > 0.0) {
     a.quant_cells = (unsigned long long)n_new * (unsigned long long)(n_new + 1) / 2;
     a.quant_rank = (unsigned long long)floor(D.theta_quantile * ((double)a.quant_cells - 1.0));
+  }
+  if (n_new <= SEG_SHORT) {
+    if (src) a.copy_wgs = copy_chunk_wgs(D, n_new, SHORT_NT / COPY_UNROLL);
+    const dim3 g(P, 1 + a.copy_wgs);
+    const bool lg = D.seg_map == LTRI_MAP_LOGIT;
+    if (bf && lg)  seg_short_kernel<LTRI_BF16, LTRI_MAP_LOGIT><<<g, SHORT_NT, 0, s>>>(a);
+    else if (bf)   seg_short_kernel<LTRI_BF16, LTRI_MAP_SOFTMAX><<<g, SHORT_NT, 0, s>>>(a);
+    else if (lg)   seg_short_kernel<LTRI_F32, LTRI_MAP_LOGIT><<<g, SHORT_NT, 0, s>>>(a);
+    else           seg_short_kernel<LTRI_F32, LTRI_MAP_SOFTMAX><<<g, SHORT_NT, 0, s>>>(a);
+    return hipGetLastError();
   }
   if (D.seg_map == LTRI_MAP_SOFTMAX) {
     const int n_h = q_seg ? D.G : 1;
@@ -1685,11 +1703,6 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
   else if (bf)        tiles(integral_constant<int, LTRI_BF16>{}, integral_constant<int, LTRI_MAP_SOFTMAX>{});
   else if (lg)        tiles(integral_constant<int, LTRI_F32>{}, integral_constant<int, LTRI_MAP_LOGIT>{});
   else                tiles(integral_constant<int, LTRI_F32>{}, integral_constant<int, LTRI_MAP_SOFTMAX>{});
-  // the kernels from here on use a few compute units each
-  if (after_tiles) {
-    const hipError_t e = hipEventRecord(after_tiles, s);
-    if (e != hipSuccess) return e;
-  }
   const dim3 gsel(P, 1 + a.sum_wgs + a.copy_wgs);
   if (a.nb <= 4) {
     seg_select_kernel<2><<<gsel, 1024, 0, s>>>(a);
