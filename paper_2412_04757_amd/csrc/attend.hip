@@ -119,9 +119,68 @@ __device__ __forceinline__ void lds_wait(u32x4_t& a, u32x4_t& b, u32x4_t& c, u32
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
 }
 
+// ---- even shares (attend_even) ----
+// The stages of all blocks (a block: the query rows and heads of one workgroup of an ordinary launch) are strung together and
+// cut into equal shares, one per compute unit, wherever the cuts fall. Workgroup ids go round the eight dies, so die x takes
+// the ids x, x + 8, ...: it gets an eighth of the blocks (whole ones, KV heads together) and its workgroups, in the order of
+// their ids, consecutive shares of it. A share that ends inside a block leaves the partial result of that piece in a place
+// of its own; the workgroup whose share holds the block's last stage folds in those of the shares before it. A workgroup takes
+// its pieces from the last to the first: the piece that others wait for is its first, the one that waits for others
+// its last, so that the wait is short; and as it waits only for lower ids, which were dispatched before it and never wait
+// before they have written, it ends whatever else runs on the chip (and is bounded besides).
+constexpr int ATT_EVEN_SPINS = 1 << 22;         // polls of a partial result that does not come (some seconds): an error is raised
+
+struct EvenShare {
+  int xcd, k, per, b0, m;                       // the die's place, this workgroup's among its `per`; first block, blocks
+  int u0, u1, lo, hi;                           // stages [u0, u1) of the die's, in its blocks lo .. hi
+};
+
+// Stages of one block: those of its context list and of the chunk tiles that its rows see (KS tiles each).
+template <int KS>
+__device__ __forceinline__ int even_stages(const AttArgs& a, int block, int n_rb) {
+  const Dims& D = a.D;
+  const int gpk = D.G / (D.G < 4 ? D.G : 4), RS = ATT_NW / KS / (D.G < 4 ? D.G : 4);
+  const int sidx = block / n_rb, yb = block - sidx * n_rb, hk = sidx / a.seq_count, bi = sidx - hk * a.seq_count;
+  const int slot = slot_of(D, a.layer, a.bp.seq[bi], hk / gpk);
+  const int list_len = a.st.meta[(size_t)slot * META_WORDS + META_LIST_LEN];
+  const int rb_end = RS == 1 ? min(a.n_q, (n_rb - yb) * 32) : min(a.n_q, (n_rb * RS - yb * (RS / 2)) * 32);
+  return ((list_len + 63) / 64 + (rb_end + 63) / 64 + KS - 1) / KS;
+}
+
+// The workgroup's share; pre[0 .. m]: first stage of each of the die's blocks, and their sum. All 512 threads.
+template <int KS>
+__device__ __forceinline__ EvenShare even_share(const AttArgs& a, int n_blocks, int n_rb, int* pre) {
+  static_assert(64 * ATT_NW >= ATT_EVEN_BLOCKS, "a block per thread");
+  __shared__ int wtot[ATT_NW], edge[2];
+  EvenShare e;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  e.xcd = (int)blockIdx.x & 7;
+  e.k = (int)blockIdx.x >> 3;
+  e.per = (int)gridDim.x >> 3;
+  e.b0 = (int)((long long)n_blocks * e.xcd / 8);
+  e.m = (int)((long long)n_blocks * (e.xcd + 1) / 8) - e.b0;
+  const int own = tid < e.m ? even_stages<KS>(a, e.b0 + tid, n_rb) : 0;
+  int incl = wave_scan_i32(own);
+  if (lane == 63) wtot[wave] = incl;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) incl += wtot[w];
+  if (tid < e.m) pre[tid + 1] = incl;
+  if (tid == 0) pre[0] = 0;
+  __syncthreads();
+  const int total = __builtin_amdgcn_readfirstlane(pre[e.m]);
+  e.u0 = (int)((long long)total * e.k / e.per);
+  e.u1 = (int)((long long)total * (e.k + 1) / e.per);
+  if (tid < e.m && pre[tid] <= e.u0 && e.u0 < pre[tid + 1]) edge[0] = tid;
+  if (tid < e.m && pre[tid] < e.u1 && e.u1 <= pre[tid + 1]) edge[1] = tid;
+  __syncthreads();
+  e.lo = e.u0 < e.u1 ? __builtin_amdgcn_readfirstlane(edge[0]) : 1;
+  e.hi = e.u0 < e.u1 ? __builtin_amdgcn_readfirstlane(edge[1]) : 0;
+  return e;
+}
+
 // KS groups of ATT_NW / KS wavefronts, each wavefront with 32 query rows of one head; a ring stage holds KS tiles of
-// 64 keys, one per group. NS ring stages.
-template <int KS, int NS>
+// 64 keys, one per group. NS ring stages. EVEN: even shares, else a block (or a split of it) per workgroup.
+template <int KS, int NS, bool EVEN>
 __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   constexpr int NW = ATT_NW, NWQ = NW / KS;         // wavefronts in all, and per group (they cover the workgroup's rows)
   constexpr int TOK_AHEAD = 2 * (NS - 1) + 1;       // token ids of stage t + TOK_AHEAD are requested in iteration t
@@ -139,23 +198,35 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   const int gpk = D.G / HG;                         // blocks per KV head
   // KV head along x: consecutive workgroup ids go to different XCDs, so all query tiles of one
   // KV head run on one XCD and share its K/V rows in that XCD's L2
-  const int bi = blockIdx.z, h = blockIdx.x / gpk, gsub = blockIdx.x - h * gpk;
-  const int seq = a.bp.seq[bi], c0 = a.bp.c0[bi];
+  // (even shares give each die consecutive blocks, and these are numbered by KV head first)
   const int L = a.n_q, d = 128;
+  const int n_rb = EVEN ? (L + RPB - 1) / RPB : (int)gridDim.y / a.n_splits;     // row blocks
+  __shared__ int pre[EVEN ? ATT_EVEN_BLOCKS + 1 : 1];
+  EvenShare share{};
+  if constexpr (EVEN) share = even_share<KS>(a, D.Hkv * gpk * a.seq_count * n_rb, n_rb, pre);
+  for (int blk = EVEN ? share.hi : 0; blk >= (EVEN ? share.lo : 0); --blk) {
+  int bi = blockIdx.z, hk = blockIdx.x, yb = (int)blockIdx.y / a.n_splits;
+  if constexpr (EVEN) {
+    const int block = share.b0 + blk, sidx = block / n_rb;
+    yb = block - sidx * n_rb;
+    hk = sidx / a.seq_count;
+    bi = sidx - hk * a.seq_count;
+    if (blk != share.hi) __syncthreads();           // the piece before is done with the ring
+  }
+  const int h = hk / gpk, gsub = hk - h * gpk;
+  const int seq = a.bp.seq[bi], c0 = a.bp.c0[bi];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave / NWQ, wq = wave % NWQ;       // the wave's key group, and its place among the group's waves
   const int l32 = lane & 31, hf = lane >> 5;
   const int head = h * D.G + gsub * HG + (wq % HG);
-  const int n_rb = (int)gridDim.y / a.n_splits;     // row blocks
-  const int split = (int)blockIdx.y % a.n_splits;
+  const int split = EVEN ? 0 : (int)blockIdx.y % a.n_splits;
   // Query rows of the workgroup. The chunk's rows are cut into sub-tiles of 32; workgroup y takes RS / 2 of them
   // from the low end and RS / 2 from the high end (sub-tiles y RS / 2 .. and their mirror images), so that under
   // the causal mask every workgroup has about the same number of (sub-tile, chunk tile) pairs to compute: the
   // low sub-tiles stop early at their diagonal, the high ones walk on alone. With one sub-tile per workgroup
   // (RS == 1) the last rows, which walk furthest, start first.
   const int nsub = n_rb * RS;                       // sub-tiles, padded to whole workgroups
-  const int yb = (int)blockIdx.y / a.n_splits;
   const int rs = wq / HG;
   const int sub = (RS == 1) ? n_rb - 1 - yb : (rs < RS / 2 ? yb * (RS / 2) + rs : nsub - (yb + 1) * (RS / 2) + (rs - RS / 2));
   const int r0 = sub * 32;                          // first row of this wave
@@ -182,8 +253,9 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   const int n_tiles = n_ctx_tiles + n_chunk_tiles;
   // stages of KS tiles; with splits, this workgroup takes the stages [st0, st1) of context and chunk
   const int n_st = (n_tiles + KS - 1) / KS;
-  const int st0 = (int)((long long)split * n_st / a.n_splits);
-  const int st1 = (int)((long long)(split + 1) * n_st / a.n_splits);
+  const int first_st = EVEN ? __builtin_amdgcn_readfirstlane(pre[blk]) : 0;       // (of the block, among the die's)
+  const int st0 = EVEN ? max(share.u0 - first_st, 0) : (int)((long long)split * n_st / a.n_splits);
+  const int st1 = EVEN ? min(share.u1 - first_st, n_st) : (int)((long long)(split + 1) * n_st / a.n_splits);
   const uint32_t ring0 = (uint32_t)(uintptr_t)ring;
   const uint32_t tok0 = ring0 + NS * STAGE_BYTES + (uint32_t)wave * (TPW * 4);       // this wave's ids of slot 0
   const int32_t* tokring = reinterpret_cast<const int32_t*>(ring + NS * STAGE_BYTES) + wave * TPW;
@@ -488,7 +560,59 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   }
   const bool writes_ml = hf == 0 && kg == 0;
   const int qi = r0 + l32;
-  if (qi >= L) return;
+  if constexpr (EVEN) {
+    // A place per workgroup: the registers of a piece as they are, and maximum and sum per lane. Stored and loaded at device
+    // scope, in front of and behind a flag (see wait_for_own_stores).
+    constexpr int NP = NMB * 8;                     // pairs of sums per lane
+    constexpr size_t PLACE = (size_t)NW * (NP + 1) * 64;
+    static_assert(PLACE * 8 == att_even_place_bytes(KS), "room of a piece");
+    unsigned long long* places = reinterpret_cast<unsigned long long*>(a.part);
+    auto place = [&](int k) { return places + (size_t)(share.xcd * share.per + k) * PLACE + (size_t)wave * (NP + 1) * 64 + lane; };
+    int32_t* flags = a.even_flags + share.xcd * share.per;
+    if (st1 < n_st) {                               // (uniform) the block goes on in the next share
+      unsigned long long* pp = place(share.k);
+#pragma unroll
+      for (int j = 0; j < NP; ++j)
+        __hip_atomic_store(pp + j * 64, ((unsigned long long)__float_as_uint(o[j >> 3][2 * (j & 7) + 1]) << 32) | __float_as_uint(o[j >> 3][2 * (j & 7)]),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(pp + NP * 64, ((unsigned long long)__float_as_uint(lt) << 32) | __float_as_uint(m_run), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      wait_for_own_stores();
+      __syncthreads();
+      if (tid == 0) __hip_atomic_store(flags + share.k, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      continue;
+    }
+    const long long total = __builtin_amdgcn_readfirstlane(pre[share.m]);
+    for (int k = share.k - 1; st0 > 0 && k >= 0; --k) {     // the shares before it, back to the block's first stage
+      const int v0 = (int)(total * k / share.per), v1 = (int)(total * (k + 1) / share.per);
+      if (v0 == v1) continue;
+      if (tid == 0) {
+        int left = ATT_EVEN_SPINS;
+        while (__hip_atomic_load(flags + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 && --left > 0) __builtin_amdgcn_s_sleep(4);
+        if (left <= 0) atomicCAS(&a.st.err[0], 0, LTRI_EHIP);
+        __hip_atomic_store(flags + k, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next launch
+      }
+      __syncthreads();
+      const unsigned long long* pp = place(k);
+      const unsigned long long ml = __hip_atomic_load(pp + NP * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned long long pv[NP];
+#pragma unroll
+      for (int j = 0; j < NP; ++j) pv[j] = __hip_atomic_load(pp + j * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const float om = __uint_as_float((uint32_t)ml), ol = __uint_as_float((uint32_t)(ml >> 32));
+      const float m_new = fmaxf(m_run, om);
+      const float f0 = __builtin_amdgcn_exp2f(m_run - m_new), f1 = __builtin_amdgcn_exp2f(om - m_new);
+      lt = lt * f0 + ol * f1;
+      m_run = m_new;
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        const int b = j >> 3, v = 2 * (j & 7);
+        o[b][v] = fmaf(__uint_as_float((uint32_t)pv[j]), f1, o[b][v] * f0);
+        o[b][v + 1] = fmaf(__uint_as_float((uint32_t)(pv[j] >> 32)), f1, o[b][v + 1] * f0);
+      }
+      if (v0 <= first_st) break;
+    }
+  }
+  auto write_rows = [&]() {
   if (a.n_splits > 1) {
     // unnormalised O, running maximum and sum of this split (the layout of part_row)
     const size_t row = part_row(a, bi, head, split, qi);
@@ -545,6 +669,9 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
       *reinterpret_cast<uint2*>(orow + b * 32 + 8 * a4) = u2;
     }
   if (a.lse && writes_ml) a.lse[rh] = (m_run + log2f(lt)) * 0.6931471805599453f;
+  };
+  if (qi < L) write_rows();
+  }                                                 // pieces
 }
 
 // ---- merge of the splits: O = sum_s w_s O_s / sum_s w_s l_s, w_s = 2^(m_s - max m) (the log-sum-exp identity).
@@ -891,7 +1018,10 @@ size_t attend_part_rows(const Dims& D) {
   if (!attend_on_matrix_cores(D)) return 0;
   const long long max_ctx = std::min(D.max_tokens, near_tokens(D, D.max_tokens) + far_tokens(D, D.max_tokens));
   const size_t short_rows = (size_t)D.n_seqs * D.Hq * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS;
-  return std::max(short_rows, attend_most_part_rows(D.Hq, D.Hkv, std::min(D.n_seqs, LTRI_MAX_BATCH), D.chunk_max, max_ctx, 256));
+  const int seqs = std::min(D.n_seqs, LTRI_MAX_BATCH);
+  const size_t row = (size_t)(D.d + 2) * sizeof(float);
+  const size_t even = (attend_most_even_bytes(D.Hq, D.Hkv, seqs, D.chunk_max, max_ctx, 256) + row - 1) / row;
+  return std::max(std::max(short_rows, even), attend_most_part_rows(D.Hq, D.Hkv, seqs, D.chunk_max, max_ctx, 256));
 }
 
 static hipError_t device_cus(int* n_cus) {
@@ -939,13 +1069,13 @@ hipError_t attend_static_scratch(float** ptr) {
 
 hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena, const void* v_arena,
                          const void* q, int layer, const BatchPos& bp, int seq_count, int n_q,
-                         void* out, float* lse, int stages, float* part, int part_mode, const int32_t* loclist,
-                         int loc_cap, const float* lse_a, hipStream_t s, hipEvent_t t_begin, hipEvent_t t_end) {
+                         void* out, float* lse, int stages, float* part, int32_t* even_flags, int part_mode,
+                         const int32_t* loclist, int loc_cap, const float* lse_a, hipStream_t s, hipEvent_t t_begin, hipEvent_t t_end) {
   if ((t_begin == nullptr) != (t_end == nullptr)) return hipErrorInvalidValue;
   AttArgs a;
   a.D = D; a.st = st; a.k_arena = k_arena; a.v_arena = v_arena; a.q = q; a.out = out; a.lse = lse;
   a.layer = layer; a.seq_count = seq_count; a.n_q = n_q; a.bp = bp;
-  a.n_splits = 1; a.part = part;
+  a.n_splits = 1; a.part = part; a.even_flags = even_flags;
   a.part_mode = part_mode; a.loclist = loclist; a.loc_cap = loc_cap; a.lse_a = lse_a;
   if (part_mode == ATT_RETRIEVED && !lse_a) return hipErrorInvalidValue;
   const bool mfma_ok = attend_on_matrix_cores(D);
@@ -970,37 +1100,47 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     const long long near = near_tokens(D, c0), far = far_tokens(D, c0);
     const long long n_ctx = part_mode == ATT_LOCAL ? near : part_mode == ATT_RETRIEVED ? far : std::min(near + far, c0);
     const size_t room = std::min((size_t)D.att_part_rows, ATT_PART_MAX_ROWS);
+    const int even = part && part_mode == ATT_ALL && n_q > ATT_SPLIT_MAX_ROWS && even_flags && n_cus <= ATT_EVEN_WGS
+                         ? attend_even(D.Hq, D.Hkv, seq_count, n_q, (int)n_ctx, (size_t)D.att_part_rows * (D.d + 2) * sizeof(float), room, n_cus) : 0;
     AttShape shape = attend_shape(D.Hq, D.Hkv, seq_count, n_q, (int)n_ctx, part_mode == ATT_RETRIEVED ? 0 : n_q,
                                   part && part_mode == ATT_ALL ? room : 0, n_cus);
     if (n_q <= ATT_SPLIT_MAX_ROWS) shape = AttShape{2, ns_short};
+    if (even) shape = AttShape{even, 1};
     const int ks = shape.ks, ns = shape.ns;
     const int HG = D.G < 4 ? D.G : 4;
     const int gpk = D.G / HG;
     const int RPB = 32 * (ATT_NW / ks / HG);
     a.n_splits = ns;
     dim3 g(D.Hkv * gpk, (n_q + RPB - 1) / RPB * ns, seq_count);
+    if (even) g = dim3(n_cus);
     static bool attr_set = false;
     if (!attr_set) {
-      for (const void* f : {reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 3>),
-                            reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2>)}) {
+      for (const void* f : {reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4, false>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 3, false>),
+                            reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2, false>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4, true>),
+                            reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2, true>)}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, att_lds_bytes(2, 2));
         if (e != hipSuccess) return e;
       }
       attr_set = true;
     }
-    auto launch = [&](auto ksc, auto nsc) {
+    auto launch = [&](auto ksc, auto nsc, auto evenc) {
       constexpr int KS = decltype(ksc)::value, NS = decltype(nsc)::value;
+      constexpr bool EVEN = decltype(evenc)::value;
       constexpr int lds = att_lds_bytes(KS, NS);
       // the events ride in the kernel's own dispatch; with a merge behind it the end is recorded after that
       if (t_begin)
-        hipExtLaunchKernelGGL((attend_bf16_kernel<KS, NS>), g, dim3(64 * ATT_NW), (uint32_t)lds, s, t_begin, ns > 1 ? nullptr : t_end, 0, a);
+        hipExtLaunchKernelGGL((attend_bf16_kernel<KS, NS, EVEN>), g, dim3(64 * ATT_NW), (uint32_t)lds, s, t_begin, ns > 1 ? nullptr : t_end, 0, a);
       else
-        attend_bf16_kernel<KS, NS><<<g, 64 * ATT_NW, lds, s>>>(a);
+        attend_bf16_kernel<KS, NS, EVEN><<<g, 64 * ATT_NW, lds, s>>>(a);
     };
     using std::integral_constant;
-    if (ks == 2)          launch(integral_constant<int, 2>{}, integral_constant<int, 2>{});
-    else if (stages == 3) launch(integral_constant<int, 1>{}, integral_constant<int, 3>{});
-    else                  launch(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    using std::true_type;
+    using std::false_type;
+    if (even == 2)        launch(integral_constant<int, 2>{}, integral_constant<int, 2>{}, true_type{});
+    else if (even == 1)   launch(integral_constant<int, 1>{}, integral_constant<int, 4>{}, true_type{});
+    else if (ks == 2)     launch(integral_constant<int, 2>{}, integral_constant<int, 2>{}, false_type{});
+    else if (stages == 3) launch(integral_constant<int, 1>{}, integral_constant<int, 3>{}, false_type{});
+    else                  launch(integral_constant<int, 1>{}, integral_constant<int, 4>{}, false_type{});
     if (ns > 1) {
       launch_merge(a, seq_count, s);
       if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }

@@ -29,8 +29,9 @@ constexpr size_t ATT_PART_MAX_ROWS = 65536;
 
 struct AttShape { int ks, ns; };
 
-// n_ctx context and n_chunk chunk tokens; part_rows: partial rows there is room for.
-inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, int n_chunk, size_t part_rows, int n_cus) {
+// n_ctx context and n_chunk chunk tokens; part_rows: partial rows there is room for. modelled (or NULL): the time it takes.
+inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, int n_chunk, size_t part_rows, int n_cus,
+                             float* modelled = nullptr) {
   const int G = Hq / Hkv, HG = G < 4 ? G : 4;
   AttShape best{1, 1};
   float best_cost = 0.f;
@@ -51,6 +52,7 @@ inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx,
       if ((ks == 1 && ns == 1) || cost < best_cost) { best_cost = cost; best = AttShape{ks, ns}; }
     }
   }
+  if (modelled) *modelled = best_cost;
   return best;
 }
 
@@ -72,6 +74,59 @@ inline size_t attend_most_part_rows(int Hq, int Hkv, int n_seqs, int chunk_max, 
         if (ctx >= max_ctx) break;
       }
       if (most > ATT_PART_MAX_ROWS - ATT_PART_MAX_ROWS / 16) return ATT_PART_MAX_ROWS;
+    }
+  return most;
+}
+
+// ---- even shares ----
+constexpr int ATT_EVEN_BLOCKS = 512;     // blocks of a die at most (one per thread of the workgroup that counts their stages)
+constexpr int ATT_EVEN_WGS = 256;        // workgroups (compute units) there are flags for
+// a piece that its workgroup does not finish: 32 / KS pairs of sums, and maximum and sum, per lane
+constexpr size_t att_even_place_bytes(int ks) { return (size_t)ATT_NW * (32 / ks + 1) * 64 * 8; }
+
+// Whether a launch is cut into even shares (attend.hip), and then its key groups (else 0). They help where an ordinary launch
+// ends with most of the chip idle: just over one round of workgroups, or a second or third round that is nearly empty. They
+// do not where it merely starts with some units idle: the chip is limited by power, and the others run faster meanwhile (700
+// rows behind 2052 tokens on 176 units take 1.3 us a stage, on all of them 2.3). Modelled as the share of a compute unit,
+// in stages of 256 pairs x 64 keys at 1.9 us (two groups 2.15), and 19 us for the count of the stages, a second piece, and
+// the partial result written, awaited and folded in; taken where that is below 0.86 of the ordinary shape's cost, which
+// is 5 to 10 % high. Measured in both forms at 131 launches (64 to 8 query heads, 1 to 8 sequences, 64 to 2048 rows behind 964
+// to 12292 tokens; profiles/attend_even_shares.txt): taken at 34 of them, 13 % faster there in the mean, 0.4 % slower at worst:
+// 12292 + 1100 rows 326 -> 254, 2052 + 1050 80 -> 65, 12292 + 700 177 -> 165, three sequences of 8196 + 700 392 -> 304.
+inline int attend_even(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, size_t part_bytes, size_t part_rows, int n_cus) {
+  const int G = Hq / Hkv, HG = G < 4 ? G : 4;
+  if (n_cus % 8 != 0) return 0;
+  float best = 0.f;
+  attend_shape(Hq, Hkv, seq_count, n_q, n_ctx, n_q, part_rows, n_cus, &best);
+  best *= 0.86f;
+  int even = 0;
+  for (int ks = 1; ks <= 2; ++ks) {
+    const int rs = ATT_NW / ks / HG, rpb = 32 * rs;
+    const long long blocks = (long long)Hkv * (G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
+    // (below 96 blocks a unit would fold in many pieces; above the limit a die's blocks would outnumber the threads)
+    if (blocks < 96 || blocks > (long long)8 * (ATT_EVEN_BLOCKS - 1) || (size_t)n_cus * att_even_place_bytes(ks) > part_bytes) continue;
+    const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_q + 63) / 64) * (rs == 1 ? 0.5f : 0.75f) + 0.5f;
+    const float cost = (float)blocks * tiles / (float)(ks * n_cus) * (ks == 2 ? 2.15f : 1.9f) + 19.f;
+    if (cost < best) { best = cost; even = ks; }
+  }
+  return even;
+}
+
+// The most room for pieces that the launches of a context can take: row counts by sixteenths of the longest chunk, contexts by
+// doubling (a launch that wants more keeps its ordinary shape).
+inline size_t attend_most_even_bytes(int Hq, int Hkv, int n_seqs, int chunk_max, long long max_ctx, int n_cus) {
+  const int step = chunk_max / 16 > 64 ? chunk_max / 16 : 64;
+  size_t most = 0;
+  for (int seqs = 1; seqs <= n_seqs; ++seqs)
+    for (int rows = step; rows < chunk_max + step; rows += step) {
+      const int n_q = rows < chunk_max ? rows : chunk_max;
+      if (n_q <= ATT_SPLIT_MAX_ROWS) continue;
+      for (long long ctx = 0;; ctx = ctx ? 2 * ctx : 512) {
+        const int ks = attend_even(Hq, Hkv, seqs, n_q, (int)(ctx < max_ctx ? ctx : max_ctx), (size_t)1 << 40, ATT_PART_MAX_ROWS, n_cus);
+        if (ks && (size_t)n_cus * att_even_place_bytes(ks) > most) most = (size_t)n_cus * att_even_place_bytes(ks);
+        if (ctx >= max_ctx) break;
+      }
+      if (most == (size_t)n_cus * att_even_place_bytes(1)) return most;
     }
   return most;
 }

@@ -178,6 +178,7 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   CL.att_lse2 = o;  o = align_up(o + (size_t)c.n_seqs * c.chunk_max * c.n_q_heads * 4, 256);
   CL.loclist = o;   o = align_up(o + (size_t)c.n_seqs * CL.loc_cap * 4, 256);
   CL.tickets = o;   o = align_up(o + ((size_t)P + (size_t)c.n_seqs * c.n_kv_heads) * 4, 256);
+  CL.even_flags = o; o = align_up(o + (size_t)ATT_EVEN_WGS * 4, 256);
   CL.total = o;
   CL.max_problems = P;
   return LTRI_OK;
@@ -266,7 +267,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
                      (int32_t*)(t + CL.tokspan), (double*)(t + CL.dyn), (double*)(t + CL.lpart),
                      (uint32_t*)(t + CL.qhist), (unsigned long long*)(t + CL.qstate),
                      (float*)(t + CL.att_lse2), (int32_t*)(t + CL.loclist), (unsigned long long*)(t + CL.qlist),
-                     (int32_t*)(t + CL.tickets)};
+                     (int32_t*)(t + CL.even_flags), (int32_t*)(t + CL.tickets)};
   const size_t n = (size_t)D.n_layers * D.n_seqs;
   c->n_tokens.assign(n, 0);
   c->last_len.assign(n, 0);
@@ -276,6 +277,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   if (!dry) {
     hipError_t e = launch_fill_zero(c->state, SL.total, c->stream);
     if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.tickets, align_up(((size_t)CL.max_problems + (size_t)D.n_seqs * D.Hkv) * 4, 256), c->stream);
+    if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.even_flags, (size_t)ATT_EVEN_WGS * 4, c->stream);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
     // the two events order streams of this device only: no timing, and a device-scope release when they are recorded
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming | hipEventReleaseToDevice);
@@ -722,7 +724,7 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
   }
   if (!c->dry) {
     r = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_q, out, lse,
-                                   c->attend_stages, part, 0, nullptr, 0, nullptr, c->stream), "attend");
+                                   c->attend_stages, part, c->dc.even_flags, 0, nullptr, 0, nullptr, c->stream), "attend");
     if (r != LTRI_OK) return r;
   }
   return LTRI_OK;
@@ -879,7 +881,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     if (r == LTRI_OK) r = timing_event(c, &t_end);
     if (r != LTRI_OK) return r;
     r = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_new, out, lse,
-                                   c->attend_stages, c->dc.att_part, 0, nullptr, 0, nullptr, c->stream, t_begin, t_end),
+                                   c->attend_stages, c->dc.att_part, c->dc.even_flags, 0, nullptr, 0, nullptr, c->stream, t_begin, t_end),
                   "attend");
     if (r == LTRI_OK) timing.keep();
     return r;
@@ -911,7 +913,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     e = timing_mark(c, c->stream);
     if (e == LTRI_OK)
       e = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_new, out, lse_a,
-                                     c->step_stages, nullptr, 1, c->dc.loclist, c->CL.loc_cap, nullptr, c->stream),
+                                     c->step_stages, nullptr, nullptr, 1, c->dc.loclist, c->CL.loc_cap, nullptr, c->stream),
                     "attend (initial, window, chunk)");
     if (e == LTRI_OK) e = timing_mark(c, c->stream);
     return e;
@@ -929,7 +931,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   r = timing_mark(c, c->stream);
   if (r != LTRI_OK) return r;
   r = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_new, out, lse,
-                                 c->step_stages, nullptr, 2, nullptr, 0, lse_a, c->stream),
+                                 c->step_stages, nullptr, nullptr, 2, nullptr, 0, lse_a, c->stream),
                 "attend (retrieved)");
   if (r != LTRI_OK) return r;
   r = timing_mark(c, c->stream);

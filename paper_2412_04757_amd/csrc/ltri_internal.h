@@ -79,6 +79,7 @@ struct ScratchLayout {
   size_t att_lse2; // float  [n_seqs][chunk_max][Hq]  log-sum-exp of the first part of a two-part step
   size_t loclist;  // int32  [n_seqs][loc_cap]  initial | window tokens (two-part step)
   size_t tickets;  // int32  [P] + [n_seqs * Hkv]  finished workgroups per problem (the two launches of step 2); zero between launches
+  size_t even_flags;  // int32 [ATT_EVEN_WGS]  pieces of an attention in even shares that are in place; zero between launches
   size_t total;
   int    loc_cap;       // entries of one sequence's initial | window list, whole tiles plus one
   int    max_problems;  // P the buffer was sized for
@@ -138,6 +139,7 @@ struct DevScratch {
   int32_t* tokspan; double* dyn; double* lpart; uint32_t* qhist; unsigned long long* qstate;
   float* att_lse2; int32_t* loclist;
   unsigned long long* qlist;
+  int32_t* even_flags;
   int32_t* tickets;   // [max_problems] and [n_seqs * Hkv] counters of finished workgroups; zero between launches
 };
 
@@ -212,8 +214,8 @@ hipError_t launch_force_list(const Dims& D, const DevState& st, int layer, int s
                              int n_ids, hipStream_t s);
 hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena, const void* v_arena,
                          const void* q, int layer, const BatchPos& bp, int seq_count, int n_q,
-                         void* out, float* lse, int stages, float* part, int part_mode, const int32_t* loclist,
-                         int loc_cap, const float* lse_a,
+                         void* out, float* lse, int stages, float* part, int32_t* even_flags, int part_mode,
+                         const int32_t* loclist, int loc_cap, const float* lse_a,
                          hipStream_t s, hipEvent_t t_begin = nullptr, hipEvent_t t_end = nullptr);
 // lse_a: the first part's log-sum-exp, for the retrieved part. t_begin / t_end (both or neither): timing events. The
 // matrix-core kernel carries them in its own dispatch (they take the kernel's start and end time stamps, and no

@@ -1,0 +1,104 @@
+"""The attention in even shares (blocks strung together and cut anywhere, partial results folded in by the workgroup with a
+block's last stage): rows and heads against the fp64 reference and a count of keys, at launches that the rule gives it."""
+import shutil
+import subprocess
+
+import pytest
+import torch
+
+import __graft_entry__ as build_entry
+from paper_2412_04757_amd import LtriContext, config_from_workload
+from tests.test_gpu_attend_shapes import BF16_ROW, attend_reference, worst_row
+from workloads import Workload, planted_stream, theta_default
+
+# (query heads, KV heads, window, budget, history of each sequence, query rows)
+LAUNCHES = [
+    (32, 8, 1024, 1024, [4096], 1050),
+    (32, 8, 1024, 4096, [8000], 1217),                 # two groups of keys or one, a ragged list
+    (24, 2, 1024, 2048, [6000], 1500),                 # three workgroups per KV head
+    (8, 8, 1500, 4096, [9000, 9000], 2048),            # one query head per KV head
+    (16, 8, 1024, 2048, [5000, 3000, 700], 750),       # sequences of different lengths
+    (32, 8, 1024, 1024, [4096, 1, 4096], 700),         # one of them without a context
+    (32, 8, 300, 300, [2100] * 4, 600),
+]
+RULE = r"""
+#include <stdio.h>
+#include "attend_shape.h"
+int main() {
+  int hq, hkv, seqs, rows, ctx;
+  while (scanf("%d %d %d %d %d", &hq, &hkv, &seqs, &rows, &ctx) == 5)
+    printf("%d\n", ltri::attend_even(hq, hkv, seqs, rows, ctx, (size_t)1 << 40, ltri::ATT_PART_MAX_ROWS, 256));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    if not shutil.which("g++"):
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("even")
+    (d / "a.cpp").write_text(RULE)
+    subprocess.run(["g++", "-O1", "-I" + build_entry.CSRC, str(d / "a.cpp"), "-o", str(d / "a")], check=True)
+
+    def run(launches):
+        text = "\n".join(" ".join(str(v) for v in x) for x in launches)
+        return [int(v) for v in subprocess.run([str(d / "a")], input=text, capture_output=True, text=True, check=True).stdout.split()]
+    return run
+
+
+def test_even_shares_are_taken_where_the_chip_would_idle(rule):
+    """The launches below, and those measured: never at a full chip or one that merely starts with idle units."""
+    got = rule([(hq, hkv, len(h), rows, min(max(h), 4 + window + budget)) for hq, hkv, window, budget, h, rows in LAUNCHES])
+    assert sum(k > 0 for k in got) >= 5 and {1, 2} <= set(got), got
+    assert rule([(32, 8, 1, 2048, 12292), (32, 8, 1, 1024, 8196), (32, 8, 1, 700, 2052), (32, 8, 4, 256, 2052), (8, 8, 1, 1024, 4100),
+                 (32, 8, 1, 1800, 12292), (32, 8, 1, 128, 2052)]) == [0] * 7
+    assert all(rule([(32, 8, 1, 1100, 8196), (32, 8, 1, 1300, 12292), (32, 8, 3, 700, 2052), (32, 8, 1, 700, 12292)]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv,window,budget,history,rows", LAUNCHES)
+def test_even_shares(gpu_device, hq, hkv, window, budget, history, rows):
+    S, longest = len(history), max(history)
+    w = Workload("even", hq, hkv, 128, "bf16", longest + rows, 2048, 4, window, 0, budget, "uniform", 16, 96)
+    ctx = LtriContext(config_from_workload(w, theta=theta_default(128), n_layers=1, n_seqs=S), gpu_device)
+    ka, va = ctx.arena_views()
+    q = []
+    for s in range(S):
+        K, V, Q, _ = planted_stream(w, 300 + s, device=str(gpu_device), context=longest + rows)
+        ka[0, s].copy_(K)
+        va[0, s].copy_(V)
+        q.append(Q[:rows])
+        for c0 in range(0, history[s], 1000):
+            ctx.append_chunk(0, s, 1, min(1000, history[s] - c0))
+    q = torch.stack(q).contiguous()
+    ctx.append_chunk(0, 0, S, rows)
+    ctx.retrieve(0, 0, S, q)
+    lse = torch.empty(q.shape[:3], dtype=torch.float32, device=gpu_device)
+    out = ctx.attend(0, 0, S, q, lse=lse)
+    for _ in range(3):                                   # the flags are left as they were found
+        again = torch.full_like(q, float("nan"))
+        ctx.attend(0, 0, S, q, out=again)
+        assert torch.equal(out, again)
+    for s in range(S):
+        want, want_lse = attend_reference(ctx, w, s, history[s], q[s])
+        assert worst_row(out[s], want) <= BF16_ROW
+        assert float((lse[s].double() - want_lse).abs().max()) <= 2e-3
+    # equal weights: an output times the number of keys counts the keys of a column (bf16 holds a hundred or so), the
+    # log-sum-exp is the logarithm of their number
+    gen = torch.Generator(device=gpu_device).manual_seed(21)
+    column = torch.randint(0, 128, va.shape[:-1], generator=gen, device=gpu_device)
+    ka.zero_(), va.zero_()
+    va.scatter_(-1, column.unsqueeze(-1), 1.0)
+    out = ctx.attend(0, 0, S, q, lse=lse).double()
+    G = hq // hkv
+    for s in range(S):
+        for h in range(hkv):
+            t = torch.from_numpy(ctx.get_token_list(0, s, h)).long().to(gpu_device)
+            one = torch.nn.functional.one_hot(column[0, s, h], 128).double()
+            count = one[t].sum(0) + one[history[s]:history[s] + rows].cumsum(0)
+            n = count.sum(1)
+            assert float(count.max()) < 120
+            got = out[s, :, h * G:(h + 1) * G] * n[:, None, None]
+            assert bool(((got - count[:, None]).abs() <= 2.0 ** -8 * count[:, None]).all())
+            assert float((lse[s, :, h * G:(h + 1) * G].double() - n.log()[:, None]).abs().max()) <= 2e-6
+    assert ctx.sync_status() == 0
