@@ -1015,7 +1015,7 @@ static long long far_tokens(const Dims& D, long long c0) {
 // Rows of partial results a context's scratch has room for: short query blocks at any batch, and as many as a launch of
 // longer ones takes within the context's limits (on 256 compute units).
 size_t attend_part_rows(const Dims& D) {
-  if (!attend_on_matrix_cores(D)) return 0;
+  if (!attend_on_matrix_cores(D)) return attend_f32_part_rows();
   const long long max_ctx = std::min(D.max_tokens, near_tokens(D, D.max_tokens) + far_tokens(D, D.max_tokens));
   const size_t short_rows = (size_t)D.n_seqs * D.Hq * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS;
   const int seqs = std::min(D.n_seqs, LTRI_MAX_BATCH);
@@ -1094,10 +1094,10 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }
     return hipGetLastError();
   }
+  long long c0 = 0;
+  for (int i = 0; i < seq_count; ++i) c0 = bp.c0[i] > c0 ? bp.c0[i] : c0;
+  const long long near = near_tokens(D, c0), far = far_tokens(D, c0);
   if (mfma_ok) {
-    long long c0 = 0;
-    for (int i = 0; i < seq_count; ++i) c0 = bp.c0[i] > c0 ? bp.c0[i] : c0;
-    const long long near = near_tokens(D, c0), far = far_tokens(D, c0);
     const long long n_ctx = part_mode == ATT_LOCAL ? near : part_mode == ATT_RETRIEVED ? far : std::min(near + far, c0);
     const size_t room = std::min((size_t)D.att_part_rows, ATT_PART_MAX_ROWS);
     const int even = part && part_mode == ATT_ALL && n_q > ATT_SPLIT_MAX_ROWS && even_flags && n_cus <= ATT_EVEN_WGS
@@ -1147,7 +1147,7 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     }
   } else {
     if (t_begin) { if (hipError_t e = hipEventRecord(t_begin, s); e != hipSuccess) return e; }
-    if (hipError_t e = launch_attend_f32(a, s); e != hipSuccess) return e;
+    if (hipError_t e = launch_attend_f32(a, std::min(near + far, c0), s); e != hipSuccess) return e;
     if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }
   }
   return hipGetLastError();

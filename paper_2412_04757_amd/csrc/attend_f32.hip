@@ -7,8 +7,12 @@
 // lanes as the B operand of O^T = V^T P^T; key k of a tile is fed as product step k % 4, lane group k / 4, which is the
 // order they come in. The partial results of the wavefronts (own maximum, sum and O) are merged in LDS at the end, in a
 // fixed order.
-// What bounds it: the fp32 matrix rate (256 flop per cycle and compute unit) of the compute units it reaches, 64 for
-// the chunk of 256 rows, plus the chain list -> rows -> products before and the merge after (10 us).
+// Launches that reach few compute units (256 rows x 4 heads: 64 workgroups) split the key range over workgroups as well: each
+// leaves its partial result (16 queries, 4 or 8 KB), and the one of a tile of pairs that finishes last (a ticket counter,
+// left at zero again) adds them up, in a fixed order.
+// What bounds it: the chain list -> rows -> products before and the merges after, and the fp32 matrix rate (256 flop per cycle
+// and compute unit) of the compute units it reaches. 256 rows of 4 / 1 heads x 64 behind some 900 tokens: 18.9 us without
+// splits, 13.2 with four.
 // Measured against one wavefront per row and head on the vector ALU, context + rows (us): 4 / 1 heads x 64
 // wide, 1028 + 256: 223 -> 22, 1540 + 1: 249 -> 22; 8 / 2 x 64, 1504 + 1000: 680 -> 75; 4 / 2 x 128, 1504 + 512:
 // 673 -> 61, two sequences of 1504 + 2048: 4692 -> 311. Error against fp64 there: 6e-7 .. 1e-6 -> 3e-7 .. 5e-7.
@@ -28,6 +32,8 @@ __device__ __forceinline__ float group_max(float v) {      // over the four lane
 }
 
 constexpr int F32_WAVES = 8;                                 // wavefronts per workgroup
+constexpr int F32_MAX_SPLITS = 4;
+constexpr int F32_SPLIT_WGS = 256;                           // workgroups of a split launch, at most (tickets: ATT_EVEN_WGS)
 constexpr int F32_PITCH = 68;                                // floats per query of a wavefront's 64 columns in LDS
 
 template <int DIM>
@@ -38,8 +44,10 @@ __global__ __launch_bounds__(64 * F32_WAVES, DIM == 64 ? 4 : 2) void attend_f32_
   __shared__ float s_m[F32_WAVES][16], s_l[F32_WAVES][16];
   const Dims& D = a.D;
   const int G = D.G, L = a.n_q;
-  const int h = blockIdx.y, bi = blockIdx.z;
-  const int p0 = (gridDim.x - 1 - blockIdx.x) * 16;          // the latest rows, which see the most keys, first
+  __shared__ int s_last;
+  const int h = blockIdx.y, bi = blockIdx.z, ns = a.n_splits;
+  const int n_blocks = (int)gridDim.x / ns, split = (int)blockIdx.x % ns, block = n_blocks - 1 - (int)blockIdx.x / ns;
+  const int p0 = block * 16;                                 // the latest rows, which see the most keys, first
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
   const int seq = a.bp.seq[bi], c0 = a.bp.c0[bi];
   const int slot = slot_of(D, a.layer, seq, h);
@@ -87,10 +95,11 @@ __global__ __launch_bounds__(64 * F32_WAVES, DIM == 64 ? 4 : 2) void attend_f32_
       for (int c = 0; c < NC; ++c) vf[v][c] = *reinterpret_cast<const f32x4_t*>(row + 64 * c);
     }
   };
-  int tok = token(wave), tok_next = token(wave + F32_WAVES);
+  const int step = F32_WAVES * ns, t0 = split * F32_WAVES + wave;
+  int tok = token(t0), tok_next = token(t0 + step);
   load_k(tok);
   load_v(tok);
-  for (int t = wave; t < n_tiles; t += F32_WAVES) {
+  for (int t = t0; t < n_tiles; t += step) {
     f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < NP; ++u)
@@ -99,7 +108,7 @@ __global__ __launch_bounds__(64 * F32_WAVES, DIM == 64 ? 4 : 2) void attend_f32_
     // the rows of the wavefront's next tile are requested as soon as this one's registers are free
     tok = tok_next;
     load_k(tok);
-    tok_next = token(t + 2 * F32_WAVES);
+    tok_next = token(t + 2 * step);
     const bool edge = 16 * t + 16 > n_open;                  // uniform: some row does not see the whole tile
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -182,17 +191,71 @@ __global__ __launch_bounds__(64 * F32_WAVES, DIM == 64 ? 4 : 2) void attend_f32_
           l = fmaf(s_l[w][q], expf(s_m[w][q] - m), l);
           sum += part[(w * 16 + q) * F32_PITCH + lane];
         }
+        if (ns > 1) {                                        // unnormalised, with its maximum and sum; device scope (see below)
+          float* pr = a.part + (((size_t)(bi * D.Hkv + h) * n_blocks + block) * ns + split) * (16 * (DIM + 2)) + q * (DIM + 2);
+          __hip_atomic_store(pr + 64 * c + lane, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (c == 0 && lane < 2) __hip_atomic_store(pr + DIM + lane, lane ? l : m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          continue;
+        }
         const size_t rh = ((size_t)bi * L + p / G) * D.Hq + h * G + p % G;
         reinterpret_cast<float*>(a.out)[rh * DIM + 64 * c + lane] = sum * (1.f / l);
         if (c == 0 && a.lse && lane == 0) a.lse[rh] = m + logf(l);
       }
     }
   }
+  if (ns == 1) return;
+  // the workgroup that takes the last ticket of its tile of pairs adds the splits up
+  wait_for_own_stores();
+  __syncthreads();
+  int32_t* ticket = a.even_flags + (size_t)(bi * D.Hkv + h) * n_blocks + block;
+  if (threadIdx.x == 0) s_last = atomicAdd(ticket, 1) == ns - 1;
+  __syncthreads();
+  if (!s_last) return;
+  if (threadIdx.x == 0) *ticket = 0;
+  const float* base = a.part + ((size_t)(bi * D.Hkv + h) * n_blocks + block) * ns * (16 * (DIM + 2));
+  auto get = [&](int s, int i) { return __hip_atomic_load(base + (size_t)s * (16 * (DIM + 2)) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  for (int q = wave; q < 16 && p0 + q <= last_pair; q += F32_WAVES) {
+    float mv[F32_MAX_SPLITS], lv[F32_MAX_SPLITS], ov[F32_MAX_SPLITS][NC];
+#pragma unroll
+    for (int s = 0; s < F32_MAX_SPLITS; ++s) {
+      const int ss = min(s, ns - 1);
+      mv[s] = get(ss, q * (DIM + 2) + DIM);
+      lv[s] = get(ss, q * (DIM + 2) + DIM + 1);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) ov[s][c] = get(ss, q * (DIM + 2) + 64 * c + lane);
+    }
+    float m = mv[0], l = 0.f, sum[NC] = {};
+#pragma unroll
+    for (int s = 1; s < F32_MAX_SPLITS; ++s) m = fmaxf(m, mv[s]);
+#pragma unroll
+    for (int s = 0; s < F32_MAX_SPLITS; ++s) {
+      const float f = expf(mv[s] - m);                       // 0 for a split without a key, whose sums are 0
+      l = s < ns ? fmaf(lv[s], f, l) : l;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) sum[c] = s < ns ? fmaf(ov[s][c], f, sum[c]) : sum[c];
+    }
+    const int p = p0 + q;
+    const size_t rh = ((size_t)bi * L + p / G) * D.Hq + h * G + p % G;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) reinterpret_cast<float*>(a.out)[rh * DIM + 64 * c + lane] = sum[c] * (1.f / l);
+    if (a.lse && lane == 0) a.lse[rh] = m + logf(l);
+  }
 }
 
-hipError_t launch_attend_f32(const AttArgs& a, hipStream_t s) {
+// Rows of partial results (of head_dim + 2 floats) a split launch takes, at most.
+size_t attend_f32_part_rows() { return (size_t)F32_SPLIT_WGS * 16; }
+
+// n_ctx: context tokens that the chunk is expected to attend. Splits while they fit one round of workgroups, one per compute
+// unit, and every wavefront keeps two tiles or more.
+hipError_t launch_attend_f32(const AttArgs& args, long long n_ctx, hipStream_t s) {
+  AttArgs a = args;
   const Dims& D = a.D;
-  const dim3 grid((a.n_q * D.G + 15) / 16, D.Hkv, a.seq_count);
+  const int blocks = (a.n_q * D.G + 15) / 16;
+  const long long wgs = (long long)blocks * D.Hkv * a.seq_count, tiles = (n_ctx + a.n_q + 15) / 16;
+  a.n_splits = 1;
+  while (a.part && a.even_flags && a.n_splits < F32_MAX_SPLITS && wgs * (a.n_splits + 1) <= F32_SPLIT_WGS &&
+         tiles >= 2LL * F32_WAVES * (a.n_splits + 1)) ++a.n_splits;
+  const dim3 grid(blocks * a.n_splits, D.Hkv, a.seq_count);
   if (D.d == 64) attend_f32_kernel<64><<<grid, 64 * F32_WAVES, 0, s>>>(a);
   else           attend_f32_kernel<128><<<grid, 64 * F32_WAVES, 0, s>>>(a);
   return hipGetLastError();

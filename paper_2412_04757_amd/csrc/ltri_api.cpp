@@ -714,7 +714,9 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
       return fail(c, LTRI_ESTATE, "sequence %d: no selection for the last chunk (call ltri_retrieve first)",
                   seq_begin + s);
   float* part = c->dc.att_part;
+  int32_t* flags = c->dc.even_flags;
   if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS) {
+    flags = nullptr;                     // nothing of the context's scratch: no splits in fp32
     // a dry context sizes the request for a device of 256 compute units
     const size_t bytes = attend_partial_bytes(c->D, seq_count, n_q, c->dry ? 256 : c->n_cus);
     if (bytes > ATT_STATIC_SCRATCH_BYTES)
@@ -724,7 +726,7 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
   }
   if (!c->dry) {
     r = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_q, out, lse,
-                                   c->attend_stages, part, c->dc.even_flags, 0, nullptr, 0, nullptr, c->stream), "attend");
+                                   c->attend_stages, part, flags, 0, nullptr, 0, nullptr, c->stream), "attend");
     if (r != LTRI_OK) return r;
   }
   return LTRI_OK;

@@ -28,11 +28,11 @@ namespace ltri {
 // (device-visible pinned memory), from which step 3 fetches the rows it retrieves.
 struct CopyArgs { Dims D; ChunkRows src; int layer; int n_new; BatchPos bp; };
 
-constexpr int COPY_UNROLL = 4;         // 16-byte pieces of K and of V per thread in flight
-// Workgroups of `threads` threads per (sequence, KV head) that copy a chunk.
+// Workgroups of `threads` threads per (sequence, KV head) that copy a chunk: one 16-byte piece of K and of V per thread, so
+// that the rows, which are in no cache, come in through as many compute units as there are (with four pieces per thread a
+// workgroup of 1024 took 9 us).
 inline int copy_chunk_wgs(const Dims& D, int n_new, int threads) {
-  const size_t n16 = (size_t)n_new * D.d * D.elt / 16, per = (size_t)threads * COPY_UNROLL;
-  const size_t w = (n16 + per - 1) / per;
+  const size_t n16 = (size_t)n_new * D.d * D.elt / 16, w = (n16 + threads - 1) / threads;
   return w < 1 ? 1 : w > 64 ? 64 : (int)w;
 }
 
@@ -57,31 +57,20 @@ __device__ __forceinline__ void copy_chunk_rows(const Dims& D, const ChunkRows& 
   uint4* kh = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.k_host) + host_off);
   uint4* vh = reinterpret_cast<uint4*>(reinterpret_cast<char*>(src.v_host) + host_off);
   const int ring = D.ring_mask + 1, pos0 = c0 & D.ring_mask;
-  const size_t stride = (size_t)n_wgs * blockDim.x;
-  for (size_t i0 = (size_t)wg * blockDim.x + threadIdx.x; i0 < n16; i0 += COPY_UNROLL * stride) {
-    uint4 kv[COPY_UNROLL], vv[COPY_UNROLL];
-#pragma unroll
-    for (int u = 0; u < COPY_UNROLL; ++u) {
-      const size_t i = i0 + u * stride;
-      if (i < n16) { kv[u] = ks[i]; vv[u] = vs[i]; }
+  for (size_t i = (size_t)wg * blockDim.x + threadIdx.x; i < n16; i += (size_t)n_wgs * blockDim.x) {
+    const uint4 kv = ks[i], vv = vs[i];
+    kd[i] = kv; vd[i] = vv;                                  // in place, or the ring (running on into its mirror rows)
+    if (!D.offload) continue;
+    const int r = (int)(i / r16), piece = (int)(i - (size_t)r * r16);
+    if (pos0 + r >= ring) {                                  // the part past the ring's end, again at its start
+      const size_t w = (size_t)(D.ring0 + pos0 + r - ring) * r16 + piece;
+      kp[w] = kv; vp[w] = vv;
     }
-#pragma unroll
-    for (int u = 0; u < COPY_UNROLL; ++u) {
-      const size_t i = i0 + u * stride;
-      if (i >= n16) continue;
-      kd[i] = kv[u]; vd[i] = vv[u];                          // in place, or the ring (running on into its mirror rows)
-      if (!D.offload) continue;
-      const int r = (int)(i / r16), piece = (int)(i - (size_t)r * r16);
-      if (pos0 + r >= ring) {                                // the part past the ring's end, again at its start
-        const size_t w = (size_t)(D.ring0 + pos0 + r - ring) * r16 + piece;
-        kp[w] = kv[u]; vp[w] = vv[u];
-      }
-      if (c0 + r < D.n_sink) {                               // initial tokens keep rows of their own
-        const size_t w = (size_t)(c0 + r) * r16 + piece;
-        kp[w] = kv[u]; vp[w] = vv[u];
-      }
-      if (src.k_host) { kh[i] = kv[u]; vh[i] = vv[u]; }      // host arenas: every token, in place
+    if (c0 + r < D.n_sink) {                                 // initial tokens keep rows of their own
+      const size_t w = (size_t)(c0 + r) * r16 + piece;
+      kp[w] = kv; vp[w] = vv;
     }
+    if (src.k_host) { kh[i] = kv; vh[i] = vv; }              // host arenas: every token, in place
   }
 }
 
@@ -1654,14 +1643,14 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
   a.copy_wgs = 0;
   if (src) {
     a.src = *src;
-    a.copy_wgs = copy_chunk_wgs(D, n_new, 1024 / COPY_UNROLL);      // (one piece per thread: as many compute units as there are)
+    a.copy_wgs = copy_chunk_wgs(D, n_new, 1024);
   }
   if (D.theta_quantile > 0.0) {
     a.quant_cells = (unsigned long long)n_new * (unsigned long long)(n_new + 1) / 2;
     a.quant_rank = (unsigned long long)floor(D.theta_quantile * ((double)a.quant_cells - 1.0));
   }
   if (n_new <= SEG_SHORT) {
-    if (src) a.copy_wgs = copy_chunk_wgs(D, n_new, SHORT_NT / COPY_UNROLL);
+    if (src) a.copy_wgs = copy_chunk_wgs(D, n_new, SHORT_NT);
     const dim3 g(P, 1 + a.copy_wgs);
     const bool lg = D.seg_map == LTRI_MAP_LOGIT;
     if (bf && lg)  seg_short_kernel<LTRI_BF16, LTRI_MAP_LOGIT><<<g, SHORT_NT, 0, s>>>(a);
