@@ -1020,7 +1020,7 @@ size_t attend_part_rows(const Dims& D) {
   const size_t short_rows = (size_t)D.n_seqs * D.Hq * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS;
   const int seqs = std::min(D.n_seqs, LTRI_MAX_BATCH);
   const size_t row = (size_t)(D.d + 2) * sizeof(float);
-  const size_t even = (attend_most_even_bytes(D.Hq, D.Hkv, seqs, D.chunk_max, max_ctx, 256) + row - 1) / row;
+  const size_t even = (attend_most_even_bytes(D.Hq, D.Hkv, seqs, D.chunk_max, 256) + row - 1) / row;
   return std::max(std::max(short_rows, even), attend_most_part_rows(D.Hq, D.Hkv, seqs, D.chunk_max, max_ctx, 256));
 }
 

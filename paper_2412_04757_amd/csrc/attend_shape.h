@@ -79,6 +79,7 @@ inline size_t attend_most_part_rows(int Hq, int Hkv, int n_seqs, int chunk_max, 
 }
 
 // ---- even shares ----
+constexpr int ATT_EVEN_LEAST = 96;       // fewest blocks of a launch: below, a compute unit would fold in many pieces
 constexpr int ATT_EVEN_BLOCKS = 512;     // blocks of a die at most (one per thread of the workgroup that counts their stages)
 constexpr int ATT_EVEN_WGS = 256;        // workgroups (compute units) there are flags for
 // a piece that its workgroup does not finish: 32 / KS pairs of sums, and maximum and sum, per lane
@@ -96,39 +97,31 @@ constexpr size_t att_even_place_bytes(int ks) { return (size_t)ATT_NW * (32 / ks
 inline int attend_even(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, size_t part_bytes, size_t part_rows, int n_cus) {
   const int G = Hq / Hkv, HG = G < 4 ? G : 4;
   if (n_cus % 8 != 0) return 0;
-  float best = 0.f;
-  attend_shape(Hq, Hkv, seq_count, n_q, n_ctx, n_q, part_rows, n_cus, &best);
-  best *= 0.86f;
+  float cost[3] = {};
   int even = 0;
   for (int ks = 1; ks <= 2; ++ks) {
     const int rs = ATT_NW / ks / HG, rpb = 32 * rs;
     const long long blocks = (long long)Hkv * (G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
-    // (below 96 blocks a unit would fold in many pieces; above the limit a die's blocks would outnumber the threads)
-    if (blocks < 96 || blocks > (long long)8 * (ATT_EVEN_BLOCKS - 1) || (size_t)n_cus * att_even_place_bytes(ks) > part_bytes) continue;
+    // (above the limit a die's blocks would outnumber the threads)
+    if (blocks < ATT_EVEN_LEAST || blocks > (long long)8 * (ATT_EVEN_BLOCKS - 1) || (size_t)n_cus * att_even_place_bytes(ks) > part_bytes) continue;
     const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_q + 63) / 64) * (rs == 1 ? 0.5f : 0.75f) + 0.5f;
-    const float cost = (float)blocks * tiles / (float)(ks * n_cus) * (ks == 2 ? 2.15f : 1.9f) + 19.f;
-    if (cost < best) { best = cost; even = ks; }
+    cost[ks] = (float)blocks * tiles / (float)(ks * n_cus) * (ks == 2 ? 2.15f : 1.9f) + 19.f;
+    if (!even || cost[ks] < cost[even]) even = ks;
   }
-  return even;
+  if (!even) return 0;
+  float ordinary = 0.f;
+  attend_shape(Hq, Hkv, seq_count, n_q, n_ctx, n_q, part_rows, n_cus, &ordinary);
+  return cost[even] < 0.86f * ordinary ? even : 0;
 }
 
-// The most room for pieces that the launches of a context can take: row counts by sixteenths of the longest chunk, contexts by
-// doubling (a launch that wants more keeps its ordinary shape).
-inline size_t attend_most_even_bytes(int Hq, int Hkv, int n_seqs, int chunk_max, long long max_ctx, int n_cus) {
-  const int step = chunk_max / 16 > 64 ? chunk_max / 16 : 64;
-  size_t most = 0;
-  for (int seqs = 1; seqs <= n_seqs; ++seqs)
-    for (int rows = step; rows < chunk_max + step; rows += step) {
-      const int n_q = rows < chunk_max ? rows : chunk_max;
-      if (n_q <= ATT_SPLIT_MAX_ROWS) continue;
-      for (long long ctx = 0;; ctx = ctx ? 2 * ctx : 512) {
-        const int ks = attend_even(Hq, Hkv, seqs, n_q, (int)(ctx < max_ctx ? ctx : max_ctx), (size_t)1 << 40, ATT_PART_MAX_ROWS, n_cus);
-        if (ks && (size_t)n_cus * att_even_place_bytes(ks) > most) most = (size_t)n_cus * att_even_place_bytes(ks);
-        if (ctx >= max_ctx) break;
-      }
-      if (most == (size_t)n_cus * att_even_place_bytes(1)) return most;
-    }
-  return most;
+// The most room for pieces that the launches of a context can take.
+inline size_t attend_most_even_bytes(int Hq, int Hkv, int n_seqs, int chunk_max, int n_cus) {
+  const int G = Hq / Hkv, HG = G < 4 ? G : 4;
+  for (int ks = 1; ks <= 2; ++ks) {                        // (the larger place first)
+    const int rpb = 32 * (ATT_NW / ks / HG);
+    if ((long long)Hkv * (G / HG) * ((chunk_max + rpb - 1) / rpb) * n_seqs >= ATT_EVEN_LEAST) return (size_t)n_cus * att_even_place_bytes(ks);
+  }
+  return 0;
 }
 
 }  // namespace ltri

@@ -3,6 +3,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <string>
 #include <vector>
@@ -432,7 +433,7 @@ static void append_commit(ltri_ctx* c, int layer, int seq_begin, int seq_count, 
 // running sums it reads were taken along.
 static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_count, const void* q_seg, int n_new,
                             const ChunkRows* src, bool rep_keys_later = false, const void* q_step2 = nullptr,
-                            bool* sums_ready = nullptr) {
+                            bool* sums_ready = nullptr, const std::function<int32_t(int, int)>& after_batch = {}) {
   int32_t r;
   if (src && !src->k_chunk) src = nullptr;
   if (sums_ready) *sums_ready = false;
@@ -447,8 +448,9 @@ static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_
   const int per = c->CL.max_problems / c->D.Hkv;     // sequences per segmentation launch
   const bool dynamic = c->D.rep_mode == LTRI_REP_DYNAMIC;
   const bool reps = segment_stores_reps(c->D, n_new);
-  // one batch of sequences only: the sums of a second batch would take the place of the first one's
-  const bool with_sums = q_step2 && sums_ready && seq_count <= per && retrieve_reads_running_sums(c->D, n_new);
+  // one batch of sequences only, or step 2 of a batch before the next: its sums take the place of the ones before
+  const bool with_sums = q_step2 && sums_ready && (seq_count <= per || after_batch) && retrieve_reads_running_sums(c->D, n_new);
+  const bool with_qrep = q_step2 && sums_ready && dynamic && !reps;
   RunSums sums;
   if (with_sums)
     sums = running_sums_of(c->D, c->dc, c->CL.max_problems, q_step2, rep_keys_later ? c->k_arena : nullptr, n_new);
@@ -459,12 +461,16 @@ static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_
     if (r != LTRI_OK) return r;
     if (dynamic && !reps) {
       r = check_hip(c, launch_dynamic_reps(c->D, c->ds, c->dc, c->k_arena, q_seg, layer, bp, off, cnt, n_new,
-                                           c->D.seg_map == LTRI_MAP_SOFTMAX, c->stream), "index vectors");
+                                           true, with_qrep ? q_step2 : nullptr, c->stream), "index vectors");
       if (r != LTRI_OK) return r;
     }
     c->theta_layer = layer; c->theta_seq0 = bp.seq[off]; c->theta_seqs = cnt;
+    if (after_batch) {
+      r = after_batch(off, cnt);
+      if (r != LTRI_OK) return r;
+    }
   }
-  if (with_sums) *sums_ready = true;
+  if (with_sums || with_qrep) *sums_ready = true;
   if (!dynamic && !reps && !rep_keys_later) {
     r = check_hip(c, launch_rep_keys(c->D, c->ds, c->k_arena, layer, bp, seq_count, n_new, c->stream),
                   "representative keys");
@@ -530,7 +536,7 @@ int32_t ltri_append_chunk_with_spans(ltri_ctx* c, int32_t layer, int32_t seq, co
     if (r != LTRI_OK) return r;
     if (c->D.rep_mode == LTRI_REP_DYNAMIC && n_new > 1)
       r = check_hip(c, launch_dynamic_reps(c->D, c->ds, c->dc, c->k_arena, nullptr, layer, bp, 0, 1, n_new, false,
-                                           c->stream), "index vectors");
+                                           nullptr, c->stream), "index vectors");
     else
       r = check_hip(c, launch_rep_keys(c->D, c->ds, c->k_arena, layer, bp, 1, n_new, c->stream),
                     "representative keys");
@@ -873,11 +879,31 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     // attention is one launch over initial | retrieved | window | chunk. Its workgroups are equal in work (row
     // sub-tiles paired from both ends of the chunk) and fill every compute unit, so a split that runs the first
     // part beside the small kernels of steps 1 and 2 only makes those wait for a free compute unit.
-    r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready);
-    if (r != LTRI_OK) return r;
-    append_commit(c, layer, seq_begin, seq_count, n_new);
-    r = retrieve_impl(c, layer, seq_begin, seq_count, q, n_new, nullptr, nullptr, keys_with_step2, sums_ready);
-    if (r != LTRI_OK) return r;
+    const int per = c->CL.max_problems / c->D.Hkv;      // sequences per segmentation launch
+    long long bound = 0;
+    for (int s = 0; s < seq_count; ++s)
+      bound = std::max(bound, std::min<long long>(c->span_bound[ls_index(c, layer, seq_begin + s)] + n_new, c->D.max_spans));
+    if (seq_count > per && retrieve_from_sums(c->D, n_new, (int)bound)) {
+      // Several batches: steps 1 and 2 of each in turn, so that the running sums of every one ride in its selections' launch
+      // (there is room for one batch's; taken in step 2 they are a launch per batch, 22 us for four sequences of 1024 rows).
+      r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready, [&](int off, int cnt) {
+        return check_hip(c, launch_retrieve(c->D, c->ds, c->dc, c->CL.max_problems, q, layer, bp, seq_count, n_new, (int)bound,
+                                            nullptr, nullptr, nullptr, nullptr, nullptr, keys_with_step2 ? c->k_arena : nullptr,
+                                            true, c->stream, off, cnt), "retrieve");
+      });
+      if (r != LTRI_OK) return r;
+      append_commit(c, layer, seq_begin, seq_count, n_new);
+      for (int s = 0; s < seq_count; ++s) {
+        c->have_sel[ls_index(c, layer, seq_begin + s)] = 0xFFFFFFFFu;
+        c->ever_sel[ls_index(c, layer, seq_begin + s)] = 0xFFFFFFFFu;
+      }
+    } else {
+      r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready);
+      if (r != LTRI_OK) return r;
+      append_commit(c, layer, seq_begin, seq_count, n_new);
+      r = retrieve_impl(c, layer, seq_begin, seq_count, q, n_new, nullptr, nullptr, keys_with_step2, sums_ready);
+      if (r != LTRI_OK) return r;
+    }
     hipEvent_t t_begin = nullptr, t_end = nullptr;     // the attention launch carries its timing events itself
     r = timing_event(c, &t_begin);
     if (r == LTRI_OK) r = timing_event(c, &t_end);

@@ -195,17 +195,21 @@ hipError_t launch_append_bounds(const Dims& D, const DevState& st, const DevScra
                                 int seq, int c0, int n_new, hipStream_t s);
 hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                                const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                               int n_new, bool lse_ready, hipStream_t s);
+                               int n_new, bool segmented, const void* q_step2, hipStream_t s);
+// segmented: launch_segment has run on the same chunk and arguments just before (else the spans were given); q_step2 (or NULL):
+// the query rows that step 2 will be called with right after, whose Q^R is stored as well
 hipError_t launch_rep_keys(const Dims& D, const DevState& st, const void* k_arena, int layer,
                            const BatchPos& bp, int seq_count, int n_new, hipStream_t s);
 hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& sc, int sc_max_problems,
                            const void* q, int layer, const BatchPos& bp, int seq_count, int n_q, int span_bound,
                            int32_t* sel_ids_out, int32_t* sel_cnt_out, const VoteArgs* votes, const void* append_k_arena,
-                           const ChunkRows* src, const void* rep_k_arena, bool sums_ready, hipStream_t s);
+                           const ChunkRows* src, const void* rep_k_arena, bool sums_ready, hipStream_t s, int first = 0, int count = 0);
 // append_k_arena (or NULL): a one-token chunk's step 1 runs in the same launch, which copies the rows of src (or NULL) as
 // well; rep_k_arena (or NULL): the step
 // also stores the chunk's mean keys (only where retrieve_stores_rep_keys says so); sums_ready: the running sums of
-// running_sums_of(D, sc, sc_max_problems, q, rep_k_arena, n_q) are in place (one batch of sequences only)
+// running_sums_of(D, sc, sc_max_problems, q, rep_k_arena, n_q) are in place (one batch of sequences only), or (dynamic index
+// vectors) Q^R is; count > 0 (only where retrieve_from_sums says so): sequences first .. first + count - 1 of the batch
+bool retrieve_from_sums(const Dims& D, int n_q, int span_bound);
 bool retrieve_stores_rep_keys(const Dims& D, int n_q);
 bool retrieve_is_one_launch(const Dims& D, int n_q, int span_bound);   // step 2 of a one-token chunk as a single kernel
 hipError_t launch_persist_list(const Dims& D, const DevState& st, int layer, const BatchPos& bp, int seq_count,

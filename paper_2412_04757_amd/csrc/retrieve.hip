@@ -1342,10 +1342,18 @@ bool retrieve_stores_rep_keys(const Dims& D, int n_q) {
   return n_q > QREP_PIECE && D.rep_mode == LTRI_REP_MEAN;
 }
 
+static bool retrieve_one_tail(int span_bound, int item_bound) {
+  return span_bound >= 1 && span_bound <= RT1_MAX_SPANS && item_bound <= RT1_MAX_SPANS && rt1_lds_bytes(item_bound) <= 116 * 1024;
+}
+
+bool retrieve_from_sums(const Dims& D, int n_q, int span_bound) {
+  return retrieve_reads_running_sums(D, n_q) && retrieve_one_tail(span_bound, span_bound);
+}
+
 hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& sc, int sc_max_problems,
                            const void* q, int layer, const BatchPos& bp, int seq_count, int n_q, int span_bound,
                            int32_t* sel_ids_out, int32_t* sel_cnt_out, const VoteArgs* votes, const void* append_k_arena,
-                           const ChunkRows* src, const void* rep_k_arena, bool sums_ready, hipStream_t s) {
+                           const ChunkRows* src, const void* rep_k_arena, bool sums_ready, hipStream_t s, int first, int count) {
   RetArgs a;
   a.D = D; a.st = st; a.sc = sc; a.q = q; a.layer = layer; a.seq_count = seq_count; a.n_q = n_q;
   a.k_arena = append_k_arena; a.append_first = append_k_arena != nullptr;
@@ -1386,8 +1394,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   // tokens by units with index vectors 27 -> 14.6; 2048 tokens 62 -> 41.
   const int unit_bound = D.unit > 0 ? (int)(D.max_tokens / D.unit) + 1 : 0;    // units a full stream has, at most
   const int item_bound = D.unit > 0 ? unit_bound : span_bound;
-  const bool one_tail = !votes && span_bound >= 1 && span_bound <= RT1_MAX_SPANS && item_bound <= RT1_MAX_SPANS &&
-                        rt1_lds_bytes(item_bound) <= 116 * 1024;
+  const bool one_tail = !votes && retrieve_one_tail(span_bound, item_bound);
   if (one_tail) {
     static bool attr_set = false;
     if (!attr_set) {
@@ -1405,8 +1412,11 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
     const int gx = QREP_GRID_X + (rep_k_arena ? QREP_GRID_X : 0);
     // Mean representatives in bf16 (whose sums are exact in fp64): Q^R and the chunk's mean keys come from running
     // sums of the query and key rows, which need no span boundaries (no piece sums, no ticket).
-    const bool from_sums = one_tail && retrieve_reads_running_sums(D, n_q);
-    if (sums_ready && (!from_sums || seq_count > piece_seqs)) sums_ready = false;     // not usable: taken here
+    const bool from_sums = !votes && retrieve_from_sums(D, n_q, span_bound);
+    const bool qrep_ready = sums_ready && D.rep_mode == LTRI_REP_DYNAMIC;
+    if (count == 0) count = seq_count;
+    else if (!from_sums || count > piece_seqs) return hipErrorInvalidValue;
+    if (sums_ready && (!from_sums || count > piece_seqs)) sums_ready = false;     // not usable: taken here
     const bool from_rows = one_tail && !from_sums && n_q <= QREP_SHORT;
     size_t lds = rt1_lds_bytes(item_bound);
     if (from_sums) {
@@ -1417,15 +1427,15 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
     if (from_rows && lds < short_sums_lds(D.d)) lds = short_sums_lds(D.d);
     a.qrep_mode = from_sums ? QREP_SUMS : from_rows ? QREP_ROWS : QREP_STORED;
     a.ticket_base = sc_max_problems;                        // the second part of the counters
-    const int per = from_rows ? seq_count : piece_seqs;
-    for (int off = 0; off < seq_count; off += per) {
-      const int cnt = seq_count - off < per ? seq_count - off : per;
+    const int per = from_rows || qrep_ready ? count : piece_seqs, end = first + count;
+    for (int off = first; off < end; off += per) {
+      const int cnt = end - off < per ? end - off : per;
       a.batch_off = off;
       dim3 gp(gx, cnt * D.Hkv), gf(n_q < 64 ? n_q : 64, cnt * D.Hkv);
       a.qrep_by_last = one_tail;
       if (from_sums) {
         if (!sums_ready) running_sums_kernel<<<dim3(running_sums_blocks(a.rs), cnt * D.Hkv), 1024, 0, s>>>(a);
-      } else if (!from_rows) {
+      } else if (!from_rows && !(one_tail && qrep_ready)) {
         if (bf) qrep_partial_kernel<LTRI_BF16><<<gp, 1024, 0, s>>>(a);
         else    qrep_partial_kernel<LTRI_F32><<<gp, 1024, 0, s>>>(a);
       }

@@ -87,6 +87,7 @@ struct SegArgs {
   // the copy took 5 us in front of everything else (256 to 1024 tokens); on workgroups of the first tile launch it made that
   // 3 us longer.
   ChunkRows src; int copy_wgs;
+  const void* q_step2;   // dyn_span_kernel: query rows of the chunk, whose sums over the index tokens it takes as well (or NULL)
 };
 
 // The chunk's key rows of sequence bi of the batch, KV head h.
@@ -571,11 +572,14 @@ __global__ __launch_bounds__(256) void quant_finish_kernel(SegArgs a) {
 // ---- pass 1: per-tile row sums, suffix-scanned column sums, total ----
 // QUANT (theta as a percentile of the map): the first tile pass of the selection rides here, on the same tile; the
 // sums do not depend on theta.
-template <int DT, int KIND, bool QUANT>
+// LSE (LOGIT maps of keys with index vectors, whose votes come from the softmax map): the rows' maxima and sums of exponentials
+// of the same tile, as lse_tile_kernel takes them.
+template <int DT, int KIND, bool QUANT, bool LSE>
 __global__ __launch_bounds__(256) void seg_tile_sums_kernel(SegArgs a) {
   __shared__ double Ms[64 * 65];
   __shared__ double cpart[4][64];
   __shared__ double rpart[4][64];
+  __shared__ double lred[LSE ? 4 : 1][64], lsum[LSE ? 4 : 1][64];
   __shared__ typename std::conditional<QUANT, QuantShared, int>::type S;
   const int p = blockIdx.y;
   int I, J;
@@ -588,12 +592,18 @@ __global__ __launch_bounds__(256) void seg_tile_sums_kernel(SegArgs a) {
     quant_tile_cells(a, p, I, J, status, Ms, S);       // (reads the tile; the sums below read it too)
   }
   const int tid = threadIdx.x;
+  double lmax = -INFINITY;
   {                                       // row sums: four threads per row, 16 columns each; a wavefront takes
     const int r = tid & 63, qd = tid >> 6;  // 64 consecutive rows (row pitch 65: no bank conflicts)
     double s = 0.0;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) s += Ms[r * 65 + qd * 16 + c];
+    for (int c = 0; c < 16; ++c) {
+      const double v = Ms[r * 65 + qd * 16 + c];
+      s += v;
+      if constexpr (LSE) lmax = fmax(lmax, J * 64 + qd * 16 + c <= I * 64 + r ? v : -INFINITY);
+    }
     rpart[qd][r] = s;
+    if constexpr (LSE) lred[qd][r] = lmax;
   }
   {                                       // column sums: four threads per column, 16 rows each
     const int c = tid & 63, qd = tid >> 6;
@@ -617,6 +627,21 @@ __global__ __launch_bounds__(256) void seg_tile_sums_kernel(SegArgs a) {
     // csuf is indexed [I][x]: block-row I's contribution restricted to this column block
     a.sc.csuf[((size_t)p * a.nb + I) * a.Lp + J * 64 + tid] = v;
     if (tid == 0) a.sc.tsum[((size_t)p * a.nb + I) * a.nb + J] = v;
+  }
+  if constexpr (LSE) {                    // (cells right of the diagonal do not count; rows past the chunk are not read)
+    const int r = tid & 63, qd = tid >> 6;
+    const double mx = fmax(fmax(lred[0][r], lred[1][r]), fmax(lred[2][r], lred[3][r]));
+    double sm = 0.0;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      const float e = exp2_f32(Ms[r * 65 + qd * 16 + c] - mx);
+      sm += J * 64 + qd * 16 + c <= I * 64 + r ? (double)e : 0.0;
+    }
+    lsum[qd][r] = sm;
+    __syncthreads();
+    if (qd == 0)
+      reinterpret_cast<double2*>(a.sc.lpart)[((size_t)p * a.nb + J) * a.Lp + I * 64 + r] =
+          make_double2(mx, ((lsum[0][r] + lsum[1][r]) + lsum[2][r]) + lsum[3][r]);
   }
 }
 
@@ -1055,7 +1080,21 @@ __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
     off += __popcll(m);
   }
   __syncthreads();
-  append_spans(D, a.st, slot_of(D, a.layer, seq, h), c0, L, cutlist, total);
+  const int slot = slot_of(D, a.layer, seq, h);
+  append_spans(D, a.st, slot, c0, L, cutlist, total);
+  if (D.rep_mode != LTRI_REP_DYNAMIC) return;
+  // what dyn_token_span_kernel leaves (a launch of its own took 4.7 us): every token's span, and a clear mask of index tokens
+  __syncthreads();
+  const bool stored = a.st.meta[(size_t)slot * META_WORDS + META_CHUNK_NSP] > 0;      // (0: the table was full)
+  for (int i = tid; i < a.Lp; i += blockDim.x) {
+    int lo = 0, hi = total - 2;                     // last span that starts at or before token i
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (cutlist[mid] <= i) lo = mid; else hi = mid - 1;
+    }
+    a.sc.tokspan[(size_t)p * a.Lp + i] = (i < L && stored) ? lo : -1;
+  }
+  if (tid < IDX_MASK_WORDS) a.st.idx_mask[(size_t)slot * IDX_MASK_WORDS + tid] = 0u;
 }
 
 // ============================================================================
@@ -1138,26 +1177,41 @@ __global__ __launch_bounds__(256) void lse_tile_kernel(SegArgs a) {
   }
 }
 
+// LSE_LANES lanes per row, each every LSE_LANES-th tile, whose pairs stay in registers. (One thread per row walked them twice,
+// 32 exponentials in fp64 one after the other on a quarter of the chip: 12.6 us for a chunk of 2048, now 4.7.)
+constexpr int LSE_LANES = 8;
 __global__ __launch_bounds__(256) void lse_reduce_kernel(SegArgs a) {
   // the launch before the map's first pass: the percentile's selection is set up here (a launch of its own, which LOGIT
   // maps take, is 2.4 us and a gap)
   if (a.quant_cells && blockIdx.x == 0) quant_init(a, blockIdx.y);
   const int p = blockIdx.y, nb = a.nb, Lp = a.Lp;
   const int n_h = a.q_seg ? a.D.G : 1;
-  const int id = blockIdx.x * blockDim.x + threadIdx.x;        // (g, i) flattened
-  if (id >= n_h * Lp) return;
+  const int id = (blockIdx.x * blockDim.x + threadIdx.x) / LSE_LANES, l = threadIdx.x % LSE_LANES;     // (g, i) flattened
+  if (id >= n_h * Lp) return;                                  // (whole groups of lanes)
   const int g = id / Lp, i = id - g * Lp, B = i / 64;
-  const double* pr = a.sc.lpart + (((size_t)p * n_h + g) * nb * Lp + i) * 2;
-  double mx = -INFINITY;
-#pragma unroll 8
-  for (int J = 0; J <= B; ++J) mx = fmax(mx, pr[(size_t)J * Lp * 2]);
-  double sm = 0.0;
-#pragma unroll 8
-  for (int J = 0; J <= B; ++J) {
-    const double m = pr[(size_t)J * Lp * 2], s2 = pr[(size_t)J * Lp * 2 + 1];
-    if (m > -INFINITY) sm += s2 * exp(m - mx);
+  const double2* pr = reinterpret_cast<const double2*>(a.sc.lpart) + ((size_t)p * n_h + g) * nb * Lp + i;
+  double2 v[SEG_MAX_NB / LSE_LANES];
+#pragma unroll
+  for (int k = 0; k < SEG_MAX_NB / LSE_LANES; ++k) {
+    const int J = l + LSE_LANES * k;
+    v[k] = pr[(size_t)min(J, B) * Lp];
+    if (J > B) v[k].x = -INFINITY;
   }
-  a.sc.lse[((size_t)p * n_h + g) * Lp + i] = i < a.n_new ? mx + log(sm) : 0.0;
+  double mx = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < SEG_MAX_NB / LSE_LANES; ++k) mx = fmax(mx, v[k].x);
+  mx = fmax(mx, lane_xor_f64<1>(mx));
+  mx = fmax(mx, lane_xor_f64<2>(mx));
+  mx = fmax(mx, lane_xor_f64<4>(mx));
+  double sm = 0.0;
+#pragma unroll
+  for (int k = 0; k < SEG_MAX_NB / LSE_LANES; ++k)
+    if (v[k].x > -INFINITY) sm += v[k].y * exp(v[k].x - mx);
+  sm += lane_xor_f64<1>(sm);
+  sm += lane_xor_f64<2>(sm);
+  sm += lane_xor_f64<4>(sm);
+  static_assert(LSE_LANES == 8 && SEG_MAX_NB % LSE_LANES == 0, "lane exchanges");
+  if (l == 0) a.sc.lse[((size_t)p * n_h + g) * Lp + i] = i < a.n_new ? mx + log(sm) : 0.0;
 }
 
 // span (within the chunk) of every token; clears the chunk's index-token mask
@@ -1423,6 +1477,13 @@ __global__ __launch_bounds__(1024) void dyn_span_kernel(SegArgs a) {
     }
     T* rep = reinterpret_cast<T*>(a.st.krep) + ((size_t)slot * D.max_spans + sid) * D.d;
     span_mean_block<DT>(Kb + (size_t)chunk_tok_row(D, c0, start) * D.d, (size_t)D.d, 1, len, D.d, rep, part, nullptr, smask, 0);
+    if (a.q_step2) {
+      // Q^R of the span, which step 2 of the same call asks for (its own launch, 21 us at 2048 tokens, found the spans' pieces and
+      // their marked rows again)
+      const T* Qb = reinterpret_cast<const T*>(a.q_step2) + ((size_t)bi * a.n_new + a0) * D.Hq * D.d + (size_t)h * D.G * D.d;
+      T* qrep = reinterpret_cast<T*>(a.sc.qrep) + ((size_t)(bi * D.Hkv + h) * a.Lp + q) * D.d;
+      span_mean_block<DT>(Qb, (size_t)D.Hq * D.d, D.G, len, D.d, qrep, part, nullptr, smask, 0);
+    }
   }
 }
 
@@ -1583,10 +1644,16 @@ hipError_t launch_fetch_retrieved(const Dims& D, const DevState& st, void* k_poo
   return hipGetLastError();
 }
 
+// Whether pass 1 of a LOGIT map leaves the pieces of the softmax map's row log-sum-exp, which the index vectors need.
+static bool segment_takes_row_sums(const Dims& D, int n_new, const void* q_seg) {
+  return D.seg_map == LTRI_MAP_LOGIT && D.rep_mode == LTRI_REP_DYNAMIC && !(D.theta_quantile > 0.0) && !q_seg && n_new > SEG_SHORT;
+}
+
 hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScratch& sc, const void* k_arena,
                                const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
-                               int n_new, bool lse_ready, hipStream_t s) {
+                               int n_new, bool segmented, const void* q_step2, hipStream_t s) {
   SegArgs a;
+  a.q_step2 = q_step2;
   a.D = D; a.st = st; a.sc = sc; a.k_arena = k_arena; a.q_seg = q_seg; a.layer = layer;
   a.batch_off = batch_off; a.n_new = n_new;
   a.nb = (n_new + SEG_TB - 1) / SEG_TB; a.Lp = a.nb * SEG_TB; a.ntiles = a.nb * (a.nb + 1) / 2;
@@ -1599,13 +1666,18 @@ hipError_t launch_dynamic_reps(const Dims& D, const DevState& st, const DevScrat
   const int P = seq_count * D.Hkv;
   const bool bf = D.dtype == LTRI_BF16;
   dim3 gl((a.Lp + 255) / 256, P), gt(a.ntiles, P);
+  // The segmentation has left the row log-sum-exp (softmax maps), or its pieces; chunks whose spans were given, and short
+  // ones with a LOGIT map, have nothing.
+  const bool lse_ready = segmented && D.seg_map == LTRI_MAP_SOFTMAX, own = !segmented || n_new <= SEG_SHORT;
   if (!lse_ready) {
     const int n_h = q_seg ? D.G : 1;
-    if (bf) lse_tile_kernel<LTRI_BF16><<<gt, 256, 0, s>>>(a);
-    else    lse_tile_kernel<LTRI_F32><<<gt, 256, 0, s>>>(a);
-    lse_reduce_kernel<<<dim3((n_h * a.Lp + 255) / 256, P), 256, 0, s>>>(a);
+    if (!segmented || !segment_takes_row_sums(D, n_new, q_seg)) {
+      if (bf) lse_tile_kernel<LTRI_BF16><<<gt, 256, 0, s>>>(a);
+      else    lse_tile_kernel<LTRI_F32><<<gt, 256, 0, s>>>(a);
+    }
+    lse_reduce_kernel<<<dim3((n_h * a.Lp * LSE_LANES + 255) / 256, P), 256, 0, s>>>(a);
   }
-  dyn_token_span_kernel<<<gl, 256, 0, s>>>(a);
+  if (own) dyn_token_span_kernel<<<gl, 256, 0, s>>>(a);
   if (bf) dyn_tile_kernel<LTRI_BF16><<<gt, 256, 0, s>>>(a);
   else    dyn_tile_kernel<LTRI_F32><<<gt, 256, 0, s>>>(a);
   dyn_reduce_kernel<<<gl, 256, 0, s>>>(a);
@@ -1623,6 +1695,7 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
                           const void* q_seg, int layer, const BatchPos& bp, int batch_off, int seq_count,
                           int n_new, const RunSums* sums, const ChunkRows* src, hipStream_t s) {
   SegArgs a;
+  a.q_step2 = nullptr;
   a.D = D; a.st = st; a.sc = sc; a.k_arena = k_arena; a.q_seg = q_seg; a.layer = layer;
   a.batch_off = batch_off; a.n_new = n_new;
   a.nb = (n_new + SEG_TB - 1) / SEG_TB; a.Lp = a.nb * SEG_TB; a.ntiles = a.nb * (a.nb + 1) / 2;
@@ -1663,14 +1736,14 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
     const int n_h = q_seg ? D.G : 1;
     if (bf) lse_tile_kernel<LTRI_BF16><<<gt, 256, 0, s>>>(a);
     else    lse_tile_kernel<LTRI_F32><<<gt, 256, 0, s>>>(a);
-    lse_reduce_kernel<<<dim3((n_h * a.Lp + 255) / 256, P), 256, 0, s>>>(a);
+    lse_reduce_kernel<<<dim3((n_h * a.Lp * LSE_LANES + 255) / 256, P), 256, 0, s>>>(a);
   }
   // one instantiation per element type and map kind
   auto tiles = [&](auto dt, auto kind) {
     constexpr int DT = decltype(dt)::value, KIND = decltype(kind)::value;
     if (D.theta_quantile > 0.0) {
       if (KIND == LTRI_MAP_LOGIT) quant_init_kernel<<<P, 256, 0, s>>>(a);
-      seg_tile_sums_kernel<DT, KIND, true><<<gt, 256, 0, s>>>(a);      // pass 1 and the selection's first tile pass
+      seg_tile_sums_kernel<DT, KIND, true, false><<<gt, 256, 0, s>>>(a);      // pass 1 and the selection's first tile pass
         quant_pick_kernel<<<P, 1024, 0, s>>>(a);
       // a map whose cells all fit the list (chunks of up to 180 tokens) was collected whole by the first pass, and
       // the pick has finished the selection: the other kernels would only find that out (4.5 us each)
@@ -1682,7 +1755,8 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
         quant_finish_kernel<DT, KIND><<<P, 256, 0, s>>>(a);
       }
     } else {
-      seg_tile_sums_kernel<DT, KIND, false><<<gt, 256, 0, s>>>(a);
+      if (KIND == LTRI_MAP_LOGIT && segment_takes_row_sums(D, n_new, q_seg)) seg_tile_sums_kernel<DT, LTRI_MAP_LOGIT, false, true><<<gt, 256, 0, s>>>(a);
+      else                                                                  seg_tile_sums_kernel<DT, KIND, false, false><<<gt, 256, 0, s>>>(a);
       }
     seg_tile_scan_kernel<DT, KIND><<<gt, 256, 0, s>>>(a);
   };

@@ -40,8 +40,13 @@ __device__ __forceinline__ void span_mean_block(const typename Elt<DT>::type* ba
       ok[u] = r < n_rows;
       const int rr = ok[u] ? r : r0;
       const int tok = rr / inner, g = rr - tok * inner;
-      if (tokmask) ok[u] = ok[u] && ((tokmask[(bit0 + tok) >> 5] >> ((bit0 + tok) & 31)) & 1u);
-      v[u] = *reinterpret_cast<const uint4*>(base + (size_t)tok * tok_stride + (size_t)g * d + piece * EPP);
+      const T* row = base + (size_t)tok * tok_stride + (size_t)g * d + piece * EPP;
+      if (tokmask) {                                 // few tokens are marked: only their rows are fetched
+        ok[u] = ok[u] && ((tokmask[(bit0 + tok) >> 5] >> ((bit0 + tok) & 31)) & 1u);
+        if (ok[u]) v[u] = *reinterpret_cast<const uint4*>(row);
+      } else {
+        v[u] = *reinterpret_cast<const uint4*>(row);
+      }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {

@@ -56,3 +56,39 @@ def test_rows_passed_equal_rows_in_place(gpu_device, dtype, dim, seqs, whole_ste
         assert a[:2] == b[:2] and torch.equal(a[2], b[2])
     for a, b in zip(oa, ob):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(rep_mode=1, lam=1.5, unit_tokens=128, index_block_max=12), dict(rep_mode=1, lam=1.5)])
+@pytest.mark.parametrize("seqs", [1, 6])
+def test_step_equals_calls(gpu_device, seqs, kw):
+    """Several batches of sequences (six, four to a segmentation launch) and index vectors: in one call, where steps 1 and 2 of a
+    batch follow each other and Q^R comes from step 1's launches, and in three. Sums of bf16 values are exact, so all is equal."""
+    sizes = [300, 129, 2048, 200]
+    T = sum(sizes)
+    w = Workload("mini-calls", 8, 2, 128, "bf16", T, max(sizes), 4, 100, 0, 500, "uniform", 16, 200)
+    gen = torch.Generator(device=gpu_device).manual_seed(9)
+    mean = torch.randn(seqs, 2, T // 50 + 1, 128, generator=gen, device=gpu_device).repeat_interleave(50, 2)[:, :, :T]
+    K = 0.5 * (mean + 0.3 * torch.randn(seqs, 2, T, 128, generator=gen, device=gpu_device))
+    V = torch.randn(seqs, 2, T, 128, generator=gen, device=gpu_device)
+    Q = torch.randn(seqs, T, 8, 128, generator=gen, device=gpu_device).bfloat16()
+    got = []
+    for step in (True, False):
+        ctx = LtriContext(config_from_workload(w, n_layers=1, n_seqs=seqs, max_tokens=T, theta=theta_default(128) / 4, **kw), gpu_device)
+        ka, va = ctx.arena_views()
+        ka[0].copy_(K), va[0].copy_(V)
+        res, at = [], 0
+        for n in sizes:
+            q = Q[:, at:at + n].contiguous()
+            if step:
+                out = ctx.step(0, 0, seqs, None, None, q)
+            else:
+                ctx.append_chunk(0, 0, seqs, n)
+                ctx.retrieve(0, 0, seqs, q)
+                out = ctx.attend(0, 0, seqs, q)
+            sel = [ctx.get_selection(0, s, h) for s in range(seqs) for h in range(2)]
+            res.append((out, [(list(i), list(x)) for i, x in sel], [list(ctx.get_token_list(0, s, h)) for s in range(seqs) for h in range(2)]))
+            at += n
+        assert ctx.sync_status() == 0
+        got.append(res)
+    for (oa, sa, la), (ob, sb, lb) in zip(*got):
+        assert sa == sb and la == lb and torch.equal(oa, ob)
