@@ -105,6 +105,12 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
+// Value of lane N of the lane's own row of 16.
+template <int N>
+__device__ __forceinline__ float row_lane(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x150 + N, 0xF, 0xF, true));      // row_newbcast
+}
+
 // Inclusive scan over the wavefront's lanes (DPP row shifts and broadcasts; a __shfl_up goes through the LDS crossbar, and six
 // of them one after the other are 0.3 us).
 template <int CTRL, int ROWS>

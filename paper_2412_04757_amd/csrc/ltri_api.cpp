@@ -179,7 +179,7 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   CL.att_lse2 = o;  o = align_up(o + (size_t)c.n_seqs * c.chunk_max * c.n_q_heads * 4, 256);
   CL.loclist = o;   o = align_up(o + (size_t)c.n_seqs * CL.loc_cap * 4, 256);
   CL.tickets = o;   o = align_up(o + ((size_t)P + (size_t)c.n_seqs * c.n_kv_heads) * 4, 256);
-  CL.even_flags = o; o = align_up(o + (size_t)ATT_EVEN_WGS * 4, 256);
+  CL.even_flags = o; o = align_up(o + attend_flag_count(D) * 4, 256);
   CL.total = o;
   CL.max_problems = P;
   return LTRI_OK;
@@ -278,7 +278,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   if (!dry) {
     hipError_t e = launch_fill_zero(c->state, SL.total, c->stream);
     if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.tickets, align_up(((size_t)CL.max_problems + (size_t)D.n_seqs * D.Hkv) * 4, 256), c->stream);
-    if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.even_flags, (size_t)ATT_EVEN_WGS * 4, c->stream);
+    if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.even_flags, align_up(attend_flag_count(D) * 4, 256), c->stream);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
     // the two events order streams of this device only: no timing, and a device-scope release when they are recorded
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming | hipEventReleaseToDevice);
@@ -722,7 +722,7 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
   float* part = c->dc.att_part;
   int32_t* flags = c->dc.even_flags;
   if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS) {
-    flags = nullptr;                     // nothing of the context's scratch: no splits in fp32
+    flags = nullptr;                     // nothing of the context's scratch: splits are merged by a launch, none in fp32
     // a dry context sizes the request for a device of 256 compute units
     const size_t bytes = attend_partial_bytes(c->D, seq_count, n_q, c->dry ? 256 : c->n_cus);
     if (bytes > ATT_STATIC_SCRATCH_BYTES)

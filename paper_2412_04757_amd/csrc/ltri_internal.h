@@ -79,7 +79,7 @@ struct ScratchLayout {
   size_t att_lse2; // float  [n_seqs][chunk_max][Hq]  log-sum-exp of the first part of a two-part step
   size_t loclist;  // int32  [n_seqs][loc_cap]  initial | window tokens (two-part step)
   size_t tickets;  // int32  [P] + [n_seqs * Hkv]  finished workgroups per problem (the two launches of step 2); zero between launches
-  size_t even_flags;  // int32 [ATT_EVEN_WGS]  pieces of an attention in even shares that are in place; zero between launches
+  size_t even_flags;  // int32 [attend_flag_count]  attention: pieces in place, or finished splits; zero between launches
   size_t total;
   int    loc_cap;       // entries of one sequence's initial | window list, whole tiles plus one
   int    max_problems;  // P the buffer was sized for
@@ -226,6 +226,11 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
 // marker is queued that the neighbouring launches would wait behind); other shapes record them around the launches.
 // bytes of partial results a launch over seq_count sequences with n_q query rows needs (0: the key range is not split)
 size_t attend_partial_bytes(const Dims& D, int seq_count, int n_q, int n_cus);
+// flags or tickets of an attention launch: one per workgroup in even shares, one per sequence and KV head when decoding
+inline size_t attend_flag_count(const Dims& D) {
+  const size_t slots = (size_t)D.n_seqs * D.Hkv;
+  return slots > (size_t)ATT_EVEN_WGS ? slots : (size_t)ATT_EVEN_WGS;
+}
 size_t attend_part_rows(const Dims& D);          // Dims::att_part_rows: rows of (head_dim + 2) floats
 // device address, on the current device, of the library's own buffer of ATT_STATIC_SCRATCH_BYTES for partial results
 hipError_t attend_static_scratch(float** ptr);
