@@ -840,29 +840,23 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   const int32_t* sstart = a.st.span_start + (size_t)slot * D.max_spans;
   const int32_t* slen = a.st.span_len + (size_t)slot * D.max_spans;
   constexpr int PPL = 128 / N / 4;                      // 16-byte pieces per lane (d = 128)
-  constexpr int PASSES = DT == LTRI_BF16 ? 2 : 1;       // spans per thread whose loads are in flight together (3 spill)
   const int part = tid & 3;
-  uint4 kv[PASSES][PPL];
-  int ss[PASSES], sl[PASSES];                           // the spans' extents travel with their keys
-  auto load_batch = [&](auto u0, auto u1, int i00, int last) {
+  // Four lanes per span, 256 spans at a time in two buffers: while one is scored, the other is on its way. The spans' extents
+  // travel with their keys.
+  struct Batch { uint4 kv[PPL]; int start, len; };
+  Batch b0, b1;
+  auto load_batch = [&](Batch& b, int i00, int last) {
+    const int ic = min(i00 + (tid >> 2), last);
+    const uint4* krow = reinterpret_cast<const uint4*>(krep + (size_t)ic * d);
 #pragma unroll
-    for (int u = decltype(u0)::value; u < decltype(u1)::value; ++u) {
-      const int ic = min(i00 + 256 * u + (tid >> 2), last);
-      const uint4* krow = reinterpret_cast<const uint4*>(krep + (size_t)ic * d);
-#pragma unroll
-      for (int q = 0; q < PPL; ++q) kv[u][q] = krow[part + 4 * q];
-      ss[u] = sstart[ic];
-      sl[u] = slen[ic];
-    }
+    for (int q = 0; q < PPL; ++q) b.kv[q] = krow[part + 4 * q];
+    b.start = sstart[ic];
+    b.len = slen[ic];
   };
-  // up to 256 spans go by one span per thread, more by PASSES of them. The first 128 are requested without waiting for the
-  // count (the table has room for `bound` spans; what lies past the count is not used), and so is the extent of
-  // the thread's own item for the list.
-  using None = std::integral_constant<int, 0>;
-  using One = std::integral_constant<int, 1>;
-  using All = std::integral_constant<int, PASSES>;
+  // The first 128 spans are requested without waiting for the count (the table has room for `bound` spans; what lies past the
+  // count is not used), and so is the extent of the thread's own item for the list.
   const bool ahead = tid < 512;                         // (uniform over a wavefront)
-  if (ahead) load_batch(None{}, One{}, 0, bound - 1);
+  if (ahead) load_batch(b0, 0, bound - 1);
   int own_start = sstart[min(tid, bound - 1)], own_len = slen[min(tid, bound - 1)];
   // Step 1 of a one-token chunk, if asked for: the token is appended as a span of one, its key is the
   // stored vector (what append_single_kernel does). The table entry written here is read back below by
@@ -902,14 +896,15 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
     if (fits && ahead && (tid >> 2) == base) {          // (four lanes)
       const uint4* krow = reinterpret_cast<const uint4*>(krep + (size_t)base * d);
 #pragma unroll
-      for (int q = 0; q < PPL; ++q) kv[0][q] = krow[part + 4 * q];
-      ss[0] = c0; sl[0] = 1;
+      for (int q = 0; q < PPL; ++q) b0.kv[q] = krow[part + 4 * q];
+      b0.start = c0; b0.len = 1;
     }
     if (fits && tid == base) { own_start = c0; own_len = 1; }
   }
   n = min(n, bound);
-  if (!ahead) load_batch(None{}, One{}, 0, max(n - 1, 0));
-  if (n > 256) load_batch(One{}, All{}, 0, n - 1);
+  if (!ahead) load_batch(b0, 0, max(n - 1, 0));
+  constexpr bool TWO = DT == LTRI_BF16;                 // (two buffers of fp32 rows spill)
+  if (TWO && n > 256) load_batch(b1, 256, n - 1);
   const int npow = rt1_pow2(n);
   uint64_t* skey = reinterpret_cast<uint64_t*>(rt1_lds);
   uint32_t* sidx = reinterpret_cast<uint32_t*>(rt1_lds + (size_t)rt1_pow2(bound) * 8);
@@ -927,58 +922,47 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   for (int w = tid; w < (n + 31) / 32 + 2; w += blockDim.x) selmask[w] = 0u;
   for (int i = n + tid; i < npow; i += blockDim.x) { skey[i] = ~0ull; sidx[i] = RT1_PAD; }
   __syncthreads();
-  auto score_batch = [&](auto uc, int i00) {
-    constexpr int U = decltype(uc)::value;
-    // the query's elements are read from LDS once for all spans of the thread (when every span had its own reads, in
-    // fp64, they bounded this loop: launch over 81 spans 13.9 us, now 12.2; 604 spans, 16 sequences 21.7 and 21.1).
-    // Spans past 256 * PASSES are requested after the first ones are used. With the vectors out of the caches, 16
-    // sequences, the launch with three spans in flight and the sorted selection against this one (us, with the events
-    // around it): 500 spans 27.7 and 24.2, 604 34.1 and 26.5, 760 35.7 and 27.4, 1200 59.3 and 34.8.
-    double accs[U];
+  // the query's elements of the lane's pieces stay in registers (read from LDS for every span, in fp64, they bounded this: a
+  // launch over 81 spans 13.9 us, in fp32 12.2)
+  float qf[PPL][N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) accs[u] = 0.0;
+  for (int q = 0; q < PPL; ++q)
+#pragma unroll
+    for (int e = 0; e < N; e += 4) *reinterpret_cast<float4*>(&qf[q][e]) = *reinterpret_cast<const float4*>(qv + (part + 4 * q) * N + e);
+  auto score_batch = [&](const Batch& b, int i00) {
+    double acc = 0.0;
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
-      const int pc = part + 4 * q;
-      float qf[N];
+      const uint32_t w[4] = {b.kv[q].x, b.kv[q].y, b.kv[q].z, b.kv[q].w};
 #pragma unroll
-      for (int e = 0; e < N; e += 4) *reinterpret_cast<float4*>(qf + e) = *reinterpret_cast<const float4*>(qv + pc * N + e);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t w[4] = {kv[u][q].x, kv[u][q].y, kv[u][q].z, kv[u][q].w};
-#pragma unroll
-        for (int e = 0; e < N; ++e) {
-          const uint32_t b = DT == LTRI_BF16 ? ((e & 1) ? (w[e / 2] & 0xffff0000u) : (w[e / 2] << 16)) : w[e & 3];
-          accs[u] = fma((double)__uint_as_float(b), (double)qf[e], accs[u]);
-        }
+      for (int e = 0; e < N; ++e) {
+        const uint32_t v = DT == LTRI_BF16 ? ((e & 1) ? (w[e / 2] & 0xffff0000u) : (w[e / 2] << 16)) : w[e & 3];
+        acc = fma((double)__uint_as_float(v), (double)qf[q][e], acc);
       }
       __builtin_amdgcn_sched_barrier(0);                  // (conversions of later pieces moved up here spill registers)
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = i00 + 256 * u + (tid >> 2);
-      double acc = accs[u];
-      acc += __shfl_xor(acc, 1, 64);
-      acc += __shfl_xor(acc, 2, 64);
-      if (part == 0 && i < n) {
-        int lo, hi;
-        clip_span(D, c0, ss[u], sl[u], lo, hi);
-        const int c = max(hi - lo, 0);
-        scores[i] = acc;
-        clip[i] = c;
-        // spans that cannot be retrieved go to the end of the order with the padding
-        skey[i] = c > 0 ? score_key(acc) : ~0ull;
-        sidx[i] = c > 0 ? (uint32_t)i : RT1_PAD;
-      }
+    const int i = i00 + (tid >> 2);
+    acc += lane_xor_f64<1>(acc);
+    acc += lane_xor_f64<2>(acc);
+    if (part == 0 && i < n) {
+      int lo, hi;
+      clip_span(D, c0, b.start, b.len, lo, hi);
+      const int c = max(hi - lo, 0);
+      scores[i] = acc;
+      clip[i] = c;
+      // spans that cannot be retrieved go to the end of the order with the padding
+      skey[i] = c > 0 ? score_key(acc) : ~0ull;
+      sidx[i] = c > 0 ? (uint32_t)i : RT1_PAD;
     }
   };
-  if (n <= 256) {
-    score_batch(One{}, 0);
-  } else {
-    for (int i00 = 0; i00 < n; i00 += 256 * PASSES) {
-      if (i00 > 0) load_batch(None{}, All{}, i00, n - 1);
-      score_batch(All{}, i00);
-    }
+  for (int i00 = 0; i00 < n; i00 += TWO ? 512 : 256) {
+    if (!TWO && i00 > 0) load_batch(b0, i00, n - 1);
+    score_batch(b0, i00);
+    if (!TWO) continue;
+    if (i00 + 256 >= n) break;
+    if (i00 + 512 < n) load_batch(b0, i00 + 512, n - 1);
+    score_batch(b1, i00 + 256);
+    if (i00 + 768 < n) load_batch(b1, i00 + 768, n - 1);
   }
   __syncthreads();
   select_prefix(D, skey, sidx, clip, n, npow, selmask, wave_tot, E);
