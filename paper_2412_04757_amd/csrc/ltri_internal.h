@@ -56,7 +56,7 @@ struct StateLayout {
 struct ScratchLayout {
   size_t rowsum;   // double [P][nb][Lp]   tile row sums, indexed [J][i]
   size_t csuf;     // double [P][nb][Lp]   suffix-scanned tile column sums, indexed [I][x]
-  size_t tsum;     // double [P][nb][nb]
+  size_t tsum;     // double [P][nb][nb]: [I][J] totals, [J][I] (I > J) a logit map's largest cells
   size_t rcar;     // double [P][nb][Lp]   row carry  RC[J][i]
   size_t ccar;     // double [P][nb][Lp]   column carry A[I][x]
   size_t pscore;   // double [P][ntiles][128]

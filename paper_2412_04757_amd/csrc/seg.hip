@@ -166,9 +166,10 @@ __device__ __forceinline__ float exp2_f32(double x) { return __builtin_amdgcn_ex
 
 // Leaves the head-summed map tile (rows I*64.., columns J*64..) in Ms[r * 65 + c] as doubles;
 // cells above the diagonal or outside the chunk are 0. Called by all 256 threads; Ms doubles as
-// the staging area of the operands (2 x 16 KB) before the tile values are written.
+// the staging area of the operands (2 x 16 KB) before the tile values are written. Returns the largest of the thread's sums
+// of a logit map before scaling (rows past the chunk repeat its last one).
 template <int DT, int KIND>
-__device__ __forceinline__ void compute_tile(const SegArgs& a, int p, int I, int J, double* Ms) {
+__device__ __forceinline__ float compute_tile(const SegArgs& a, int p, int I, int J, double* Ms) {
   typedef typename Elt<DT>::type T;
   const Dims& D = a.D;
   const int sl = p / D.Hkv, h = p - sl * D.Hkv, bi = a.batch_off + sl;
@@ -184,6 +185,7 @@ __device__ __forceinline__ void compute_tile(const SegArgs& a, int p, int I, int
   const double scale = 1.0 / sqrt((double)d);
   const int jcol = J * 64 + wj * 32 + l32;
   constexpr bool logit = KIND == LTRI_MAP_LOGIT;
+  float most = -INFINITY;
   double m[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) m[v] = 0.0;
@@ -213,11 +215,13 @@ __device__ __forceinline__ void compute_tile(const SegArgs& a, int p, int I, int
   if constexpr (logit) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) m[v] = (double)acc[v] * scale;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) most = fmaxf(most, acc[v]);
   }
   if (I > J && (I + 1) * 64 <= L) {             // a whole tile below the diagonal: nothing to mask (uniform)
 #pragma unroll
     for (int v = 0; v < 16; ++v) Ms[(wi * 32 + 8 * (v >> 2) + 4 * hf + (v & 3)) * 65 + wj * 32 + l32] = m[v];
-    return;
+    return most;
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -226,6 +230,7 @@ __device__ __forceinline__ void compute_tile(const SegArgs& a, int p, int I, int
     const bool ok = (jcol <= i) && (i < L);
     Ms[rl * 65 + wj * 32 + l32] = ok ? m[v] : 0.0;
   }
+  return most;
 }
 
 // ---- theta as a percentile of the map (Sec. 4, "Hyperparameter Tuning") ----
@@ -569,6 +574,8 @@ __global__ __launch_bounds__(256) void quant_finish_kernel(SegArgs a) {
   }
 }
 
+constexpr int MERGE_INLINE_NB = 16;                       // most tiles a side whose results the selection merges itself
+
 // ---- pass 1: per-tile row sums, suffix-scanned column sums, total ----
 // QUANT (theta as a percentile of the map): the first tile pass of the selection rides here, on the same tile; the
 // sums do not depend on theta.
@@ -585,7 +592,13 @@ __global__ __launch_bounds__(256) void seg_tile_sums_kernel(SegArgs a) {
   int I, J;
   tile_decode(blockIdx.x, I, J);
   if constexpr (QUANT) quant_tile_clear(S);
-  compute_tile<DT, KIND>(a, p, I, J, Ms);
+  __shared__ float smax[4];
+  const float most = compute_tile<DT, KIND>(a, p, I, J, Ms);
+  const bool bound = KIND == LTRI_MAP_LOGIT && a.nb > MERGE_INLINE_NB;
+  if (bound) {                            // the tile's largest cell, for pass 2's bound
+    const float m = lanes_max<64>(most);
+    if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = m;
+  }
   __syncthreads();
   if constexpr (QUANT) {
     const unsigned long long status = qload(a.sc.qstate + (size_t)p * QUANT_STATE_WORDS + 3);
@@ -626,7 +639,12 @@ __global__ __launch_bounds__(256) void seg_tile_sums_kernel(SegArgs a) {
     }
     // csuf is indexed [I][x]: block-row I's contribution restricted to this column block
     a.sc.csuf[((size_t)p * a.nb + I) * a.Lp + J * 64 + tid] = v;
-    if (tid == 0) a.sc.tsum[((size_t)p * a.nb + I) * a.nb + J] = v;
+    if (tid == 0) {
+      a.sc.tsum[((size_t)p * a.nb + I) * a.nb + J] = v;
+      if (bound && I > J)                 // (the other triangle of the same array)
+        a.sc.tsum[((size_t)p * a.nb + J) * a.nb + I] =
+            (double)fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3])) * (1.0 / sqrt((double)a.D.d));
+    }
   }
   if constexpr (LSE) {                    // (cells right of the diagonal do not count; rows past the chunk are not read)
     const int r = tid & 63, qd = tid >> 6;
@@ -647,45 +665,141 @@ __global__ __launch_bounds__(256) void seg_tile_sums_kernel(SegArgs a) {
 
 // ---- pass 2: the tile's carries from the sums of pass 1, then finish S inside the tile and reduce its
 //      anti-diagonals ----
-template <int DT, int KIND>
-__global__ __launch_bounds__(256) void seg_tile_scan_kernel(SegArgs a) {
+// The carries of tile (I, J):
+//   row carry of row i        = sum of the tile row sums of row i over the tiles right of J (J < J' <= I),
+//   column carry of column x  = sum over the block rows above I (J <= I' < I) of their suffix-scanned column
+//                               sum at x, plus the totals of their tiles right of J (one number per tile).
+// Four threads share a row / a column, each every fourth term, with the same (row or column, quarter) a thread has in
+// the two scans of the kernel.
+//
+// With the carries a bound on every score of the tile is at hand before the tile is:
+//   S(x, y) <= max over x of (column carry - theta tri(fewest tokens of a span from x)) + sum of the positive row carries
+//              + 64 * 64 * (largest cell, if positive: from pass 1; a softmax map's 64 rows sum up to at most 1 per head)
+// and only S > 0 makes a candidate. BOUND: a tile whose bound is negative is given up before its products. Rounding cannot lift a
+// score past it: what enters with a positive sign is taken 1e-10 larger, its errors are 1e-13 of it at most, and a negative
+// term lowers the score by more than the error it brings. A NaN or infinity never gives up a candidate (the scores that it reaches
+// are NaN, which is none, or the bound is infinite or NaN).
+// Chunks of 2048 tokens with planted spans of 16 to 1024 tokens (8 heads, 4224 tiles of which 45 of 100 are given up): launch
+// 40 us, now 34.5; with the operands requested before the carries are summed 37. The carries stand in front of the products then
+// instead of beside them, 1 us of a workgroup: at most 16 tiles a side, where the chip holds nearly all tiles at once, that is as
+// much as there is to gain (the streams by 1024 rows 0.5 % faster, by 640 rows 1.4 % and by 256 fp32 rows 1.6 % slower), so
+// those take the carries beside the products.
+template <int KIND, bool BOUND>
+struct TileCarries {
+  const SegArgs& a;
+  int p, I, J, li, part;
+  double (*rpart)[64];                  // the four threads' shares of a row's / a column's carry
+  double (*cpart)[64];
+  double* tpart;
+  double row = 0.0, col = 0.0;          // the carries of row and column li
+  double largest = 0.0;
+  static constexpr int TR = 256 / SEG_MAX_NB;                          // block rows per step of the totals
+  double rv[SEG_MAX_NB / 4], cv[SEG_MAX_NB / 4], tv[SEG_MAX_NB / TR];
+  __device__ __forceinline__ void request() {
+    const int n = I - J;
+    // loads on clamped (valid) indices, masked afterwards, so that all are in flight; with the bound, pieces past the last term
+    // are left out (uniform; in a short launch the branches cost more than the loads)
+    const double* rowsum = a.sc.rowsum + (size_t)p * a.nb * a.Lp + I * 64 + li;
+    const double* csuf = a.sc.csuf + (size_t)p * a.nb * a.Lp + J * 64 + li;
+    const double* tsum = a.sc.tsum + (size_t)p * a.nb * a.nb;
+    if (BOUND && KIND == LTRI_MAP_LOGIT) largest = tsum[(size_t)J * a.nb + I];          // (on the diagonal: not used)
+#pragma unroll
+    for (int k = 0; k < SEG_MAX_NB / 4; ++k) {
+      rv[k] = cv[k] = 0.0;
+      if (!BOUND || 4 * k < n) {
+        rv[k] = rowsum[min(J + 1 + part + 4 * k, I) * a.Lp];
+        cv[k] = csuf[min(J + part + 4 * k, I) * a.Lp];
+      }
+    }
+    const int Ip0 = threadIdx.x / SEG_MAX_NB, Jpp = threadIdx.x % SEG_MAX_NB;
+#pragma unroll
+    for (int k = 0; k < SEG_MAX_NB / TR; ++k) {                        // tiles (I', J'') with J < J'' <= I' < I
+      tv[k] = 0.0;
+      if (!BOUND || (TR * k + TR - 1 > J && TR * k < I)) tv[k] = tsum[min(Ip0 + TR * k, a.nb - 1) * a.nb + min(Jpp, a.nb - 1)];
+    }
+  }
+  __device__ __forceinline__ void sum_rows() {
+    double rs = 0.0;
+#pragma unroll
+    for (int k = 0; k < SEG_MAX_NB / 4; ++k) rs += part + 4 * k < I - J ? rv[k] : 0.0;
+    rpart[part][li] = rs;
+  }
+  __device__ __forceinline__ void sum_cols() {
+    const int Ip0 = threadIdx.x / SEG_MAX_NB, Jpp = threadIdx.x % SEG_MAX_NB;
+    double cs = 0.0;
+#pragma unroll
+    for (int k = 0; k < SEG_MAX_NB / 4; ++k) cs += part + 4 * k < I - J ? cv[k] : 0.0;
+#pragma unroll
+    for (int k = 0; k < SEG_MAX_NB / TR; ++k) {
+      const int Ip = Ip0 + TR * k;
+      tv[k] = (Jpp > J && Jpp <= Ip && Ip < I) ? tv[k] : 0.0;
+    }
+    static_assert(SEG_MAX_NB / TR == 4, "terms of the totals");
+    const double ts = wave_sum_f64((tv[0] + tv[1]) + (tv[2] + tv[3]));
+    cpart[part][li] = cs;
+    if (li == 0) tpart[part] = ts;
+  }
+  // (behind a barrier)
+  __device__ __forceinline__ void finish_rows() { row = ((rpart[0][li] + rpart[1][li]) + rpart[2][li]) + rpart[3][li]; }
+  __device__ __forceinline__ void finish_cols() {
+    col = (((cpart[0][li] + cpart[1][li]) + cpart[2][li]) + cpart[3][li]) + (((tpart[0] + tpart[1]) + tpart[2]) + tpart[3]);
+  }
+  // Eq. 5's theta per head, times the heads summed; a percentile of the map is already per summed cell
+  __device__ __forceinline__ double theta() const {
+    return a.D.theta_quantile > 0.0 ? __longlong_as_double((long long)a.sc.qstate[(size_t)p * QUANT_STATE_WORDS + 2])
+                                    : (double)a.D.theta * (double)(a.q_seg ? a.D.G : 1);
+  }
+  // true, in all threads alike: no cell of the tile can be a candidate
+  __device__ __forceinline__ bool hopeless() const {
+    if (I == J) return false;
+    const double th = theta();
+    const int x = J * 64 + li, n = (th >= 0.0 ? I * 64 : min(I * 64 + 63, a.n_new - 1)) - x + 1;
+    const double t = th * (double)(n * (n + 1) / 2);
+    constexpr double UP = 1e-10;
+    double most = col - t + UP * (fabs(col) + fabs(t)), right = fmax(row, 0.0);
+    const double inside = KIND == LTRI_MAP_LOGIT ? 4096.0 * fmax(largest, 0.0)
+                                                 : 64.0 * 1.001 * (double)(a.q_seg ? a.D.G : 1);
+    most = fmax(most, lane_xor_f64<32>(most));
+    most = fmax(most, lane_xor_f64<16>(most));
+    most = fmax(most, lane_xor_f64<8>(most));
+    most = fmax(most, lane_xor_f64<4>(most));
+    most = fmax(most, lane_xor_f64<2>(most));
+    most = fmax(most, lane_xor_f64<1>(most));
+    right = wave_sum_f64(right);
+    return most + (1.0 + UP) * (right + inside) < 0.0;          // (the same numbers in every wavefront)
+  }
+};
+
+template <int DT, int KIND, bool BOUND>
+__global__ __launch_bounds__(256, !BOUND ? 1 : KIND == LTRI_MAP_LOGIT ? 4 : DT == LTRI_BF16 ? 3 : 2) void seg_tile_scan_kernel(SegArgs a) {
   __shared__ double Ms[64 * 65];
   __shared__ double qsum[4][64];       // sums of the four 16-wide pieces of a row / of a column
-  __shared__ double cpart[4][64];      // the four threads' shares of a row's / a column's carry
+  __shared__ double rpart[BOUND ? 4 : 1][64], cpart[4][64];      // (without the bound the two are not in use together)
   __shared__ double tpart[4];
   const int p = blockIdx.y;
   int I, J;
   tile_decode(blockIdx.x, I, J);
   const int tid = threadIdx.x, L = a.n_new;
   const bool whole = I > J && (I + 1) * 64 <= L;      // the tile lies below the diagonal and inside the chunk
-  compute_tile<DT, KIND>(a, p, I, J, Ms);
-  // The carries of this tile, from the sums of pass 1:
-  //   row carry of row i        = sum of the tile row sums of row i over the tiles right of J (J < J' <= I),
-  //   column carry of column x  = sum over the block rows above I (J <= I' < I) of their suffix-scanned column
-  //                               sum at x, plus the totals of their tiles right of J (one number per tile).
-  // Four threads share a row / a column, each every fourth term, with the same (row or column, quarter) a thread
-  // has in the two scans below; the loads are requested here and used after the scans' first steps.
   const int li = tid & 63, part = tid >> 6;
-  double rv[SEG_MAX_NB / 4], cv[SEG_MAX_NB / 4], tv[SEG_MAX_NB * SEG_MAX_NB / 256];
-  {
-    // every load is unconditional on a clamped (valid) index and masked afterwards: no branches, all in flight
-    const double* rowsum = a.sc.rowsum + (size_t)p * a.nb * a.Lp + I * 64 + li;
-    const double* csuf = a.sc.csuf + (size_t)p * a.nb * a.Lp + J * 64 + li;
-    const double* tsum = a.sc.tsum + (size_t)p * a.nb * a.nb;
-#pragma unroll
-    for (int k = 0; k < SEG_MAX_NB / 4; ++k) {
-      const int Jp = J + 1 + part + 4 * k, Ip = J + part + 4 * k;
-      const double r = rowsum[min(Jp, I) * a.Lp], c = csuf[min(Ip, I) * a.Lp];
-      rv[k] = Jp <= I ? r : 0.0;
-      cv[k] = Ip < I ? c : 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < SEG_MAX_NB * SEG_MAX_NB / 256; ++k) {      // tiles (I', J'') with J < J'' <= I' < I
-      const int e = tid + 256 * k, Ip = e / SEG_MAX_NB, Jpp = e % SEG_MAX_NB;
-      const double t = tsum[min(Ip, a.nb - 1) * a.nb + min(Jpp, a.nb - 1)];
-      tv[k] = (Jpp > J && Jpp <= Ip && Ip < I) ? t : 0.0;
+  TileCarries<KIND, BOUND> carry{a, p, I, J, li, part, BOUND ? rpart : cpart, cpart, tpart};
+  if constexpr (BOUND) {
+    carry.request();
+    carry.sum_rows();
+    carry.sum_cols();
+    __syncthreads();
+    carry.finish_rows();
+    carry.finish_cols();
+    if (carry.hopeless()) {
+      if (tid < 128) {
+        a.sc.pscore[((size_t)p * a.ntiles + blockIdx.x) * 128 + tid] = -INFINITY;
+        a.sc.px[((size_t)p * a.ntiles + blockIdx.x) * 128 + tid] = (int8_t)-1;
+      }
+      return;
     }
   }
+  compute_tile<DT, KIND>(a, p, I, J, Ms);
+  if constexpr (!BOUND) carry.request();              // used after the first steps of the scans
   __syncthreads();
   {                                     // rows: suffix sums towards the left, four threads per row; a wavefront
     const int r = li, qd = part;        // takes 64 consecutive rows (row pitch 65: no bank conflicts)
@@ -695,13 +809,11 @@ __global__ __launch_bounds__(256) void seg_tile_scan_kernel(SegArgs a) {
     double s = 0.0;
 #pragma unroll
     for (int c = 0; c < 16; ++c) s += v[c];
-    double rs = 0.0;
-#pragma unroll
-    for (int k = 0; k < SEG_MAX_NB / 4; ++k) rs += rv[k];
     qsum[qd][r] = s;
-    cpart[qd][r] = rs;
+    if constexpr (!BOUND) carry.sum_rows();
     __syncthreads();
-    double run = ((cpart[0][r] + cpart[1][r]) + cpart[2][r]) + cpart[3][r];      // the row carry
+    if constexpr (!BOUND) carry.finish_rows();
+    double run = carry.row;
     for (int q2 = 3; q2 > qd; --q2) run += qsum[q2][r];
 #pragma unroll
     for (int c = 15; c >= 0; --c) { run += v[c]; Ms[r * 65 + qd * 16 + c] = run; }
@@ -715,21 +827,13 @@ __global__ __launch_bounds__(256) void seg_tile_scan_kernel(SegArgs a) {
     double s = 0.0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s += w[r];
-    double cs = 0.0;
-#pragma unroll
-    for (int k = 0; k < SEG_MAX_NB / 4; ++k) cs += cv[k];
-    const double ts = wave_sum_f64((tv[0] + tv[1]) + (tv[2] + tv[3]));
     qsum[qd][c] = s;
-    cpart[qd][c] = cs;
-    if (c == 0) tpart[qd] = ts;
+    if constexpr (!BOUND) carry.sum_cols();
     __syncthreads();
+    if constexpr (!BOUND) carry.finish_cols();
     const int x = J * 64 + c;
-    const int n_h = a.q_seg ? a.D.G : 1;
-    // Eq. 5's theta per head, times the heads summed; a percentile of the map is already per summed cell
-    const double th = a.D.theta_quantile > 0.0 ? __longlong_as_double((long long)a.sc.qstate[(size_t)p * QUANT_STATE_WORDS + 2])
-                                               : (double)a.D.theta * (double)n_h;
-    double run = (((cpart[0][c] + cpart[1][c]) + cpart[2][c]) + cpart[3][c]) +
-                 (((tpart[0] + tpart[1]) + tpart[2]) + tpart[3]);      // the column carry
+    const double th = carry.theta();
+    double run = carry.col;
     for (int q2 = 0; q2 < qd; ++q2) run += qsum[q2][c];
     // tri(n) = n (n + 1) / 2 of n = y - x + 1 by increments, tri(n + 1) = tri(n) + n + 1: small integers, exact
     // in fp64 (cells with n <= 0 lie above the diagonal and are masked)
@@ -906,7 +1010,6 @@ __global__ __launch_bounds__(256) void seg_merge_kernel(SegArgs a) {
 // kept, every candidate it suppresses (and the winner itself) dies. One workgroup per problem.
 // MT > 0: chunks of at most 2 MT tiles a side, whose partial results the threads merge themselves (pass 3a); else the
 // merged candidates are in place.
-constexpr int MERGE_INLINE_NB = 16;
 template <int MT>
 __global__ __launch_bounds__(1024) void seg_select_kernel(SegArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t kept[SEG_MAX_DIAG + 1];
@@ -1744,7 +1847,7 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
     if (D.theta_quantile > 0.0) {
       if (KIND == LTRI_MAP_LOGIT) quant_init_kernel<<<P, 256, 0, s>>>(a);
       seg_tile_sums_kernel<DT, KIND, true, false><<<gt, 256, 0, s>>>(a);      // pass 1 and the selection's first tile pass
-        quant_pick_kernel<<<P, 1024, 0, s>>>(a);
+      quant_pick_kernel<<<P, 1024, 0, s>>>(a);
       // a map whose cells all fit the list (chunks of up to 180 tokens) was collected whole by the first pass, and
       // the pick has finished the selection: the other kernels would only find that out (4.5 us each)
       if (a.quant_cells > (unsigned long long)QUANT_LIST_CAP) {
@@ -1757,8 +1860,9 @@ hipError_t launch_segment(const Dims& D, const DevState& st, const DevScratch& s
     } else {
       if (KIND == LTRI_MAP_LOGIT && segment_takes_row_sums(D, n_new, q_seg)) seg_tile_sums_kernel<DT, LTRI_MAP_LOGIT, false, true><<<gt, 256, 0, s>>>(a);
       else                                                                  seg_tile_sums_kernel<DT, KIND, false, false><<<gt, 256, 0, s>>>(a);
-      }
-    seg_tile_scan_kernel<DT, KIND><<<gt, 256, 0, s>>>(a);
+    }
+    if (a.nb > MERGE_INLINE_NB) seg_tile_scan_kernel<DT, KIND, true><<<gt, 256, 0, s>>>(a);
+    else                        seg_tile_scan_kernel<DT, KIND, false><<<gt, 256, 0, s>>>(a);
   };
   using std::integral_constant;
   const bool lg = D.seg_map == LTRI_MAP_LOGIT;
