@@ -29,6 +29,8 @@ __host__ __device__ inline int running_sums_blocks(const RunSums& r) {
 // an otherwise idle chip, 10 MB in and 16 MB out) is bound by the latency of a workgroup. With 8 columns and two tokens
 // per lane, whose sums went through 48 lane exchanges and left in 16-byte pieces 64 bytes apart, it took 12 us and the
 // launch it rides in 19.4; now that launch takes 13.5 (700 tokens: 18.1 and 10.4) and its selections bound it.
+// The sums leave past the caches: other dies read them, and a launch ends when its writes are out (2048 tokens, 32 MB: that
+// launch 18.4 -> 16.6 us and step 2, which reads them, 18.4 -> 18.75; 1024 tokens 18.1 -> 17.1 and 13.75 -> 14.1).
 __device__ __forceinline__ void running_sums_one(const Dims& D, const BatchPos& bp, int layer, int batch_off,
                                                  const RunSums& r, int blk, bool keys, int p, double* wt) {
   constexpr int TOK = RUNSUM_BLOCK / 16;                // tokens per wavefront
@@ -79,10 +81,11 @@ __device__ __forceinline__ void running_sums_one(const Dims& D, const BatchPos& 
     cx += u.x;
     cy += u.y;
   }
+  typedef double f64x2_t __attribute__((ext_vector_type(2)));
   double* out = r.out + (keys ? r.keys_off : (size_t)0) + ((size_t)p * r.rows + t0) * d + col;
 #pragma unroll
   for (int t = 0; t < TOK; ++t)
-    if (t0 + t < r.n_q) *reinterpret_cast<double2*>(out + (size_t)t * d) = make_double2(cx + x[t], cy + y[t]);
+    if (t0 + t < r.n_q) __builtin_nontemporal_store(f64x2_t{cx + x[t], cy + y[t]}, reinterpret_cast<f64x2_t*>(out + (size_t)t * d));
 }
 
 // Workgroup `w` (0 .. running_sums_blocks - 1) of problem p.
