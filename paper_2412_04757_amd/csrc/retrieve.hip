@@ -975,6 +975,7 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
   emit_selection(D, a.st, slot, c0, 1, selmask, n, own, ids_out, cnt_out, E);
 }
 
+constexpr int CHUNK_WGS = 256;                     // workgroups of retrieve_chunk_kernel that the chip holds at once
 constexpr int QREP_SHORT = SHORT_SUMS_TOKENS;      // longest chunk whose query rows every scoring workgroup sums itself
 
 // ---- step 2 of a chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
@@ -1428,7 +1429,10 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
         // one workgroup per 128 spans that there can be: the bound is about twice the spans there are, so that is about
         // one tile per SIMD (with 256 spans per workgroup, held together, a launch over 100 to 300 spans took 18.7 us,
         // now 16.6)
-        const dim3 gt(cnt * D.Hkv, (span_bound + 127) / 128);
+        // But no more than one round over the chip: a compute unit holds one, and the bound can be many times the spans (12
+        // sequences of 8 heads, 3 rows after 25K tokens: 672 workgroups 29.4 us, 192 17.3)
+        const int wgs = (span_bound + 127) / 128, room = CHUNK_WGS / (cnt * D.Hkv);
+        const dim3 gt(cnt * D.Hkv, wgs < room ? wgs : room > 1 ? room : 1);
         if (bf) retrieve_chunk_kernel<LTRI_BF16><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
         else    retrieve_chunk_kernel<LTRI_F32><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
       } else {

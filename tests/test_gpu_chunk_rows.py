@@ -92,3 +92,31 @@ def test_step_equals_calls(gpu_device, seqs, kw):
         got.append(res)
     for (oa, sa, la), (ob, sb, lb) in zip(*got):
         assert sa == sb and la == lb and torch.equal(oa, ob)
+
+
+@pytest.mark.parametrize("seqs,rows", [(3, 3), (12, 3), (33, 2), (40, 4), (12, 100)])
+def test_retrieve_of_many_sequences(gpu_device, seqs, rows):
+    """The scoring workgroups of a sequence and KV head become fewer as there are more of those (24, 96, 264, 320): the
+    selections of a call for all sequences are those of a call for each."""
+    spans = 400 + 16 * torch.arange(seqs) % 300          # stored spans of a sequence, 3 tokens each
+    T = 3 * 700 + 40 + rows
+    w = Workload("mini-many", 8, 8, 128, "bf16", T, 256, 4, 40, 0, 300, "uniform", 16, 200)
+    ctx = LtriContext(config_from_workload(w, n_layers=1, n_seqs=seqs, max_tokens=T, theta=1e30, max_spans=1024), gpu_device)
+    gen = torch.Generator(device=gpu_device).manual_seed(seqs)
+    for a in ctx.arena_views():
+        a.copy_(torch.randn(a.shape, generator=gen, device=gpu_device))
+    for s in range(seqs):
+        for at in range(0, int(spans[s]), 80):
+            n = min(80, int(spans[s]) - at)
+            ctx.append_chunk_with_spans(0, s, 3 * n, [list(range(0, 3 * n + 1, 3))] * 8)
+        ctx.append_chunk_with_spans(0, s, 40, [[0, 40]] * 8)
+    ctx.append_chunk(0, 0, seqs, rows)
+    q = torch.randn(seqs, rows, 8, 128, generator=gen, device=gpu_device).bfloat16()
+    lists = lambda s: [(list(ctx.get_selection(0, s, h)[0]), list(ctx.get_token_list(0, s, h))) for h in range(8)]
+    ctx.retrieve(0, 0, seqs, q)
+    together = [lists(s) for s in range(seqs)]
+    for s in range(seqs):
+        ctx.retrieve(0, s, 1, q[s:s + 1].contiguous())
+        assert lists(s) == together[s], s
+    assert ctx.sync_status() == 0
+    assert len({tuple(l[0]) for t in together for l in t}) > seqs
