@@ -873,7 +873,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   const bool keys_with_step2 = retrieve_stores_rep_keys(c->D, n_new);
   const ChunkRows src = chunk_rows(c, k_chunk, v_chunk, false);        // (offloaded: the fetch's launch writes the host rows)
   StepTiming timing(c);
-  bool sums_ready = false;               // step 2's running sums of the query and key rows ride in step 1's first launch
+  bool sums_ready = false;               // step 2's running sums of the query and key rows rode in the selections' launch
   if (!c->D.offload) {
     // Keys and values resident on the device: the three steps follow each other on the context's stream and the
     // attention is one launch over initial | retrieved | window | chunk. Its workgroups are equal in work (row
