@@ -10,6 +10,7 @@
 #include "device_common.h"
 #include "span_mean.h"
 #include "running_sums.h"
+#include "retrieve_shape.h"
 
 namespace ltri {
 
@@ -61,7 +62,6 @@ __global__ __launch_bounds__(1024) void qrep_kernel(RetArgs a) {
 // Long chunks: a query span is cut into pieces of QREP_PIECE tokens, one workgroup per piece
 // (so that a 1024-token span is read by eight compute units instead of one); a second kernel
 // adds the pieces of every span in ascending order.
-constexpr int QREP_PIECE = 128;
 
 // Piece u of the chunk's spans -> (span q, first token, token count); returns false past the end.
 // Called by whole wavefronts with the same u: the spans' piece counts are scanned 64 at a time
@@ -577,11 +577,7 @@ __global__ __launch_bounds__(1024) void select_emit_kernel(RetArgs a) {
 // stored precision. Scores as in score_kernel. The selection rule is the one of select_rank_kernel,
 // reached by comparing or counting the items (select_prefix). Spans: at most RT1_MAX_SPANS (the
 // launcher checks its bound).
-constexpr int RT1_MAX_SPANS = 8192;
 constexpr uint32_t RT1_PAD = 0xffffffffu;
-__host__ __device__ constexpr int rt1_pow2(int n) { int m = 64; while (m < n) m <<= 1; return m; }
-// dynamic LDS: keys, ids, clipped lengths
-__host__ __device__ constexpr size_t rt1_lds_bytes(int bound) { return (size_t)rt1_pow2(bound) * 12 + (size_t)bound * 4; }
 
 // The selection rule by sorting (one workgroup of 1024 threads): skey / sidx[0..npow) hold the order
 // keys and ids of the eligible items (the others and the padding: key ~0, id RT1_PAD), clip[id]
@@ -976,7 +972,7 @@ __global__ __launch_bounds__(1024) void retrieve_one_token_kernel(RetArgs a, int
 }
 
 constexpr int CHUNK_WGS = 256;                     // workgroups of retrieve_chunk_kernel that the chip holds at once
-constexpr int QREP_SHORT = SHORT_SUMS_TOKENS;      // longest chunk whose query rows every scoring workgroup sums itself
+static_assert(QREP_SHORT <= SHORT_SUMS_TOKENS, "rows that a workgroup sums");
 
 // ---- step 2 of a chunk in one launch: the scores of all stored spans (Eq. 8, maximum over the query spans as
 //      in Eq. 9), the budgeted selection and the lists. gridDim.x = (sequence, KV head) problems;
@@ -1321,15 +1317,11 @@ bool retrieve_is_one_launch(const Dims& D, int n_q, int span_bound) {
 
 bool retrieve_reads_running_sums(const Dims& D, int n_q) {
   return n_q > QREP_PIECE && D.d == 128 && D.unit == 0 && D.dtype == LTRI_BF16 && D.rep_mode == LTRI_REP_MEAN &&
-         (size_t)n_q * 16 + 2048 <= 116 * 1024;     // the readers' table of block sums shares the LDS of the sort
+         (size_t)n_q * 16 + 2048 <= RETRIEVE_LDS;   // the readers' table of block sums shares the LDS of the sort
 }
 
 bool retrieve_stores_rep_keys(const Dims& D, int n_q) {
   return n_q > QREP_PIECE && D.rep_mode == LTRI_REP_MEAN;
-}
-
-static bool retrieve_one_tail(int span_bound, int item_bound) {
-  return span_bound >= 1 && span_bound <= RT1_MAX_SPANS && item_bound <= RT1_MAX_SPANS && rt1_lds_bytes(item_bound) <= 116 * 1024;
 }
 
 bool retrieve_from_sums(const Dims& D, int n_q, int span_bound) {
@@ -1372,7 +1364,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
     else    retrieve_one_token_kernel<LTRI_F32><<<P, 1024, lds, s>>>(a, span_bound);
     return hipGetLastError();
   }
-  a.units_cap = n_q / QREP_PIECE + n_q;                  // pieces of all spans of a chunk, at most
+  a.units_cap = qrep_units(n_q);
   // One launch per batch of sequences for everything, or everything but the sums of the query rows (retrieve_chunk_kernel):
   // all but collaborative retrieval and very long tables (its arrays of keys, ids and lengths share the 160 KB of LDS with
   // 26 KB of masks and list scratch). The launches it replaces on other than 128-wide heads, chunks of up to 128 tokens and
@@ -1380,30 +1372,31 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   // tokens by units with index vectors 27 -> 14.6; 2048 tokens 62 -> 41.
   const int unit_bound = D.unit > 0 ? (int)(D.max_tokens / D.unit) + 1 : 0;    // units a full stream has, at most
   const int item_bound = D.unit > 0 ? unit_bound : span_bound;
-  const bool one_tail = !votes && retrieve_one_tail(span_bound, item_bound);
+  const int piece_seqs = sc_max_problems / D.Hkv;          // sequences the buffer of pieces or running sums is for
+  const bool whole = count == 0;
+  if (whole) count = seq_count;
+  // Mean representatives in bf16 (whose sums are exact in fp64): Q^R and the chunk's mean keys come from running
+  // sums of the query and key rows, which need no span boundaries (no piece sums, no ticket).
+  const RetrieveShape shape = retrieve_shape(retrieve_reads_running_sums(D, n_q), votes != nullptr, sums_ready && D.rep_mode == LTRI_REP_DYNAMIC,
+                                             n_q, span_bound, item_bound, count, piece_seqs);
+  const bool one_tail = shape.one_tail;
+  if (!whole && (!shape.from_sums || count > piece_seqs)) return hipErrorInvalidValue;
   if (one_tail) {
     static bool attr_set = false;
     if (!attr_set) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&retrieve_chunk_kernel<LTRI_BF16>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 116 * 1024);
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)RETRIEVE_LDS);
       if (e != hipSuccess) return e;
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(&retrieve_chunk_kernel<LTRI_F32>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 116 * 1024);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)RETRIEVE_LDS);
       if (e != hipSuccess) return e;
       attr_set = true;
     }
   }
   if (one_tail || n_q > QREP_PIECE) {
-    const int piece_seqs = sc_max_problems / D.Hkv;        // sequences the buffer of pieces or running sums is for
     const int gx = QREP_GRID_X + (rep_k_arena ? QREP_GRID_X : 0);
-    // Mean representatives in bf16 (whose sums are exact in fp64): Q^R and the chunk's mean keys come from running
-    // sums of the query and key rows, which need no span boundaries (no piece sums, no ticket).
-    const bool from_sums = !votes && retrieve_from_sums(D, n_q, span_bound);
-    const bool qrep_ready = sums_ready && D.rep_mode == LTRI_REP_DYNAMIC;
-    if (count == 0) count = seq_count;
-    else if (!from_sums || count > piece_seqs) return hipErrorInvalidValue;
-    if (sums_ready && (!from_sums || count > piece_seqs)) sums_ready = false;     // not usable: taken here
-    const bool from_rows = one_tail && !from_sums && n_q <= QREP_SHORT;
+    const bool from_sums = shape.from_sums, from_rows = shape.from_rows;
+    const bool sums_in_place = sums_ready && from_sums && count <= piece_seqs;    // else they are taken here
     size_t lds = rt1_lds_bytes(item_bound);
     if (from_sums) {
       const size_t carry_bytes = (size_t)((n_q + RUNSUM_BLOCK - 1) / RUNSUM_BLOCK) * 2 * 128 * 8;
@@ -1413,15 +1406,15 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
     if (from_rows && lds < short_sums_lds(D.d)) lds = short_sums_lds(D.d);
     a.qrep_mode = from_sums ? QREP_SUMS : from_rows ? QREP_ROWS : QREP_STORED;
     a.ticket_base = sc_max_problems;                        // the second part of the counters
-    const int per = from_rows || qrep_ready ? count : piece_seqs, end = first + count;
+    const int per = shape.per, end = first + count;
     for (int off = first; off < end; off += per) {
       const int cnt = end - off < per ? end - off : per;
       a.batch_off = off;
       dim3 gp(gx, cnt * D.Hkv), gf(n_q < 64 ? n_q : 64, cnt * D.Hkv);
       a.qrep_by_last = one_tail;
       if (from_sums) {
-        if (!sums_ready) running_sums_kernel<<<dim3(running_sums_blocks(a.rs), cnt * D.Hkv), 1024, 0, s>>>(a);
-      } else if (!from_rows && !(one_tail && qrep_ready)) {
+        if (!sums_in_place) running_sums_kernel<<<dim3(running_sums_blocks(a.rs), cnt * D.Hkv), 1024, 0, s>>>(a);
+      } else if (shape.pieces) {
         if (bf) qrep_partial_kernel<LTRI_BF16><<<gp, 1024, 0, s>>>(a);
         else    qrep_partial_kernel<LTRI_F32><<<gp, 1024, 0, s>>>(a);
       }

@@ -1,0 +1,49 @@
+// How a launch of step 2 is shaped (retrieve.hip): what its Q^R is made of, whether one kernel does everything behind that, and
+// how many sequences a launch takes. Plain C++, so that the host tests can look at every size.
+#pragma once
+#include <stddef.h>
+
+namespace ltri {
+
+constexpr int RT1_MAX_SPANS = 8192;
+constexpr int rt1_pow2(int n) { int m = 64; while (m < n) m <<= 1; return m; }
+// dynamic LDS of the selection: keys, ids, clipped lengths
+constexpr size_t rt1_lds_bytes(int bound) { return (size_t)rt1_pow2(bound) * 12 + (size_t)bound * 4; }
+
+constexpr int QREP_PIECE = 128;                    // tokens of a piece of a query span
+constexpr int QREP_SHORT = 128;                    // longest chunk whose query rows every scoring workgroup sums itself
+constexpr size_t RETRIEVE_LDS = 116 * 1024;        // dynamic LDS of retrieve_chunk_kernel, at most
+
+// Partial sums of the query rows that a launch of qrep_partial_kernel leaves per problem, at most.
+constexpr int qrep_units(int n_q) { return n_q / QREP_PIECE + n_q; }
+
+// Whether retrieve_chunk_kernel takes the table: its arrays of keys, ids and lengths share the 160 KB of LDS with 26 KB of masks
+// and list scratch.
+inline bool retrieve_one_tail(int span_bound, int item_bound) {
+  return span_bound >= 1 && span_bound <= RT1_MAX_SPANS && item_bound <= RT1_MAX_SPANS && rt1_lds_bytes(item_bound) <= RETRIEVE_LDS;
+}
+
+struct RetrieveShape {
+  bool one_tail;        // one launch (retrieve_chunk_kernel) for everything behind the sums
+  bool from_sums;       // Q^R from the running sums of the query rows
+  bool from_rows;       // Q^R by every scoring workgroup for itself
+  bool pieces;          // Q^R from sums of pieces, launched first
+  int per;              // sequences a trip of launches takes
+};
+
+// reads_sums: running sums serve the configuration and chunk length (retrieve_reads_running_sums); votes: collaborative retrieval;
+// stored: Q^R of the chunk's spans is in place already; count: sequences of the call; buffer_seqs: sequences that the buffer of
+// pieces and running sums has room for.
+inline RetrieveShape retrieve_shape(bool reads_sums, bool votes, bool stored, int n_q, int span_bound, int item_bound, int count,
+                                    int buffer_seqs) {
+  RetrieveShape s;
+  s.one_tail = !votes && retrieve_one_tail(span_bound, item_bound);
+  s.from_sums = s.one_tail && reads_sums;
+  s.from_rows = s.one_tail && !s.from_sums && n_q <= QREP_SHORT;
+  // The kernels of very long tables read pieces whatever is in place.
+  s.pieces = !s.from_sums && !s.from_rows && !(s.one_tail && stored);
+  s.per = s.from_sums || s.pieces ? buffer_seqs : count;
+  return s;
+}
+
+}  // namespace ltri
