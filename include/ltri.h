@@ -134,9 +134,10 @@ typedef struct {
 } ltri_config;
 
 /* Sizes (bytes) of the two device buffers a context needs: `state` holds the index
- * memory (span table, representative keys, selections, token lists; lives as long as
- * the context; ltri_create enqueues a kernel that zero-fills it), `scratch` holds per-call
- * temporaries, among them the partial results of attention launches whose key range is split
+ * memory (span table, representative keys, selections, token lists, the launches' counters; lives as
+ * long as the context; ltri_create enqueues a kernel that zero-fills it), `scratch` holds per-call
+ * temporaries: between calls it may be overwritten, or lent to other contexts, as long as calls do not
+ * overlap (only ltri_get_theta reads what an earlier call left there). Among them are the partial results of attention launches whose key range is split
  * (bf16: up to 34 MB, by the context's heads, sequences, chunk length, window and budget).
  * EINVAL on an unsupported configuration. */
 int32_t ltri_workspace_bytes(const ltri_config* cfg, size_t* state_bytes, size_t* scratch_bytes);

@@ -133,6 +133,7 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   }
 
   const size_t n_slots = (size_t)c.n_layers * c.n_seqs * c.n_kv_heads;
+  const int P = std::min(c.n_seqs, 4) * c.n_kv_heads;     // segmentation problems in one launch: up to 4 sequences
   size_t o = 0;
   SL.meta = o;       o = align_up(o + n_slots * META_WORDS * 4, 256);
   SL.span_start = o; o = align_up(o + n_slots * D.max_spans * 4, 256);
@@ -143,13 +144,14 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   SL.tok_list = o;   o = align_up(o + n_slots * (size_t)D.list_cap * 4, 256);
   SL.err = o;        o = align_up(o + 16, 256);
   SL.idx_mask = o;   o = align_up(o + n_slots * IDX_MASK_WORDS * 4, 256);
+  SL.tickets = o;    o = align_up(o + ((size_t)P + (size_t)c.n_seqs * c.n_kv_heads) * 4, 256);
+  SL.even_flags = o; o = align_up(o + attend_flag_count(D) * 4, 256);
   SL.row_list = o;   o = align_up(o + (D.offload ? n_slots * (size_t)D.list_cap * 4 : 0), 256);
   SL.k_pool = o;     o = align_up(o + (D.offload ? n_slots * (size_t)D.arena_rows * D.d * D.elt : 0), 256);
   SL.v_pool = o;     o = align_up(o + (D.offload ? n_slots * (size_t)D.arena_rows * D.d * D.elt : 0), 256);
   SL.total = o;
 
-  // scratch: segmentation temporaries for up to 4 sequences at a time
-  const int P = std::min(c.n_seqs, 4) * c.n_kv_heads;
+  // scratch: temporaries of a call, those of the segmentation for P problems at a time
   const size_t nb = (c.chunk_max + SEG_TB - 1) / SEG_TB, Lp = nb * SEG_TB, nt = nb * (nb + 1) / 2;
   o = 0;
   CL.rowsum = o; o = align_up(o + (size_t)P * nb * Lp * 8, 256);
@@ -178,8 +180,6 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   CL.loc_cap = (int)align_up((size_t)c.n_sink + c.window, ATT_BN) + ATT_BN;
   CL.att_lse2 = o;  o = align_up(o + (size_t)c.n_seqs * c.chunk_max * c.n_q_heads * 4, 256);
   CL.loclist = o;   o = align_up(o + (size_t)c.n_seqs * CL.loc_cap * 4, 256);
-  CL.tickets = o;   o = align_up(o + ((size_t)P + (size_t)c.n_seqs * c.n_kv_heads) * 4, 256);
-  CL.even_flags = o; o = align_up(o + attend_flag_count(D) * 4, 256);
   CL.total = o;
   CL.max_problems = P;
   return LTRI_OK;
@@ -259,7 +259,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   c->ds = DevState{(int32_t*)(s + SL.meta), (int32_t*)(s + SL.span_start), (int32_t*)(s + SL.span_len),
                    (void*)(s + SL.krep), (double*)(s + SL.scores), (int32_t*)(s + SL.sel_ids),
                    (int32_t*)(s + SL.tok_list), (int32_t*)(s + SL.err), (uint32_t*)(s + SL.idx_mask),
-                   (int32_t*)(s + (D.offload ? SL.row_list : SL.tok_list))};
+                   (int32_t*)(s + (D.offload ? SL.row_list : SL.tok_list)), (int32_t*)(s + SL.even_flags), (int32_t*)(s + SL.tickets)};
   char* t = c->scratch;
   c->dc = DevScratch{(double*)(t + CL.rowsum), (double*)(t + CL.csuf), (double*)(t + CL.tsum),
                      (double*)(t + CL.rcar), (double*)(t + CL.ccar), (double*)(t + CL.pscore),
@@ -267,8 +267,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
                      (double*)(t + CL.qpart), (int32_t*)(t + CL.bounds), (uint8_t*)(t + CL.selflag), (float*)(t + CL.att_part),
                      (int32_t*)(t + CL.tokspan), (double*)(t + CL.dyn), (double*)(t + CL.lpart),
                      (uint32_t*)(t + CL.qhist), (unsigned long long*)(t + CL.qstate),
-                     (float*)(t + CL.att_lse2), (int32_t*)(t + CL.loclist), (unsigned long long*)(t + CL.qlist),
-                     (int32_t*)(t + CL.even_flags), (int32_t*)(t + CL.tickets)};
+                     (float*)(t + CL.att_lse2), (int32_t*)(t + CL.loclist), (unsigned long long*)(t + CL.qlist)};
   const size_t n = (size_t)D.n_layers * D.n_seqs;
   c->n_tokens.assign(n, 0);
   c->last_len.assign(n, 0);
@@ -277,8 +276,6 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   c->ever_sel.assign(n, 0u);
   if (!dry) {
     hipError_t e = launch_fill_zero(c->state, SL.total, c->stream);
-    if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.tickets, align_up(((size_t)CL.max_problems + (size_t)D.n_seqs * D.Hkv) * 4, 256), c->stream);
-    if (e == hipSuccess) e = launch_fill_zero(c->scratch + CL.even_flags, align_up(attend_flag_count(D) * 4, 256), c->stream);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
     // the two events order streams of this device only: no timing, and a device-scope release when they are recorded
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming | hipEventReleaseToDevice);
@@ -720,9 +717,9 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
       return fail(c, LTRI_ESTATE, "sequence %d: no selection for the last chunk (call ltri_retrieve first)",
                   seq_begin + s);
   float* part = c->dc.att_part;
-  int32_t* flags = c->dc.even_flags;
+  int32_t* flags = c->ds.even_flags;
   if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS) {
-    flags = nullptr;                     // nothing of the context's scratch: splits are merged by a launch, none in fp32
+    flags = nullptr;                     // nothing of the context's: splits are merged by a launch, none in fp32
     // a dry context sizes the request for a device of 256 compute units
     const size_t bytes = attend_partial_bytes(c->D, seq_count, n_q, c->dry ? 256 : c->n_cus);
     if (bytes > ATT_STATIC_SCRATCH_BYTES)
@@ -909,7 +906,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     if (r == LTRI_OK) r = timing_event(c, &t_end);
     if (r != LTRI_OK) return r;
     r = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_new, out, lse,
-                                   c->attend_stages, c->dc.att_part, c->dc.even_flags, 0, nullptr, 0, nullptr, c->stream, t_begin, t_end),
+                                   c->attend_stages, c->dc.att_part, c->ds.even_flags, 0, nullptr, 0, nullptr, c->stream, t_begin, t_end),
                   "attend");
     if (r == LTRI_OK) timing.keep();
     return r;

@@ -45,6 +45,9 @@ struct StateLayout {
   size_t tok_list;    // int32  [n_slots][list_cap]
   size_t err;         // int32  [4]
   size_t idx_mask;    // uint32 [n_slots][IDX_MASK_WORDS]  index tokens of the chunk appended last (dynamic index vectors)
+  // Zero between launches. They lie here and not in the scratch, which may hold anything when a call begins:
+  size_t tickets;     // int32  [P] + [n_seqs * Hkv]  finished workgroups per problem (the two launches of step 2)
+  size_t even_flags;  // int32  [attend_flag_count]  attention: pieces in place, or finished splits
   // host-offloaded KV only (else row_list == tok_list and the pools are empty):
   size_t row_list;    // int32  [n_slots][list_cap]  the context list as rows of the device pool
   size_t k_pool;      // dtype  [n_slots][pool_rows][d]  initial tokens | ring of the latest tokens | retrieved rows
@@ -78,8 +81,6 @@ struct ScratchLayout {
   size_t lpart;    // double [P][G][nb][Lp][2]  per tile: row maximum and sum of exponentials (row log-sum-exp in pieces)
   size_t att_lse2; // float  [n_seqs][chunk_max][Hq]  log-sum-exp of the first part of a two-part step
   size_t loclist;  // int32  [n_seqs][loc_cap]  initial | window tokens (two-part step)
-  size_t tickets;  // int32  [P] + [n_seqs * Hkv]  finished workgroups per problem (the two launches of step 2); zero between launches
-  size_t even_flags;  // int32 [attend_flag_count]  attention: pieces in place, or finished splits; zero between launches
   size_t total;
   int    loc_cap;       // entries of one sequence's initial | window list, whole tiles plus one
   int    max_problems;  // P the buffer was sized for
@@ -132,6 +133,8 @@ struct DevState {
   int32_t* meta; int32_t* span_start; int32_t* span_len; void* krep; double* scores;
   int32_t* sel_ids; int32_t* tok_list; int32_t* err; uint32_t* idx_mask;
   int32_t* row_list;       // what the attention walks: tok_list itself, or (host-offloaded KV) the same list as pool rows
+  int32_t* even_flags;
+  int32_t* tickets;        // [max_problems] and [n_seqs * Hkv] counters of finished workgroups; zero between launches
 };
 struct DevScratch {
   double* rowsum; double* csuf; double* tsum; double* rcar; double* ccar;
@@ -139,8 +142,6 @@ struct DevScratch {
   int32_t* tokspan; double* dyn; double* lpart; uint32_t* qhist; unsigned long long* qstate;
   float* att_lse2; int32_t* loclist;
   unsigned long long* qlist;
-  int32_t* even_flags;
-  int32_t* tickets;   // [max_problems] and [n_seqs * Hkv] counters of finished workgroups; zero between launches
 };
 
 // Running sums of a chunk's query and key rows (running_sums.h), which step 2 of long chunks with mean
