@@ -15,6 +15,7 @@
 #include <hip/hip_ext.h>
 #include "device_common.h"
 #include "attend_args.h"
+#include "handoff.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -129,6 +130,14 @@ __device__ __forceinline__ void lds_wait(u32x4_t& a, u32x4_t& b, u32x4_t& c, u32
 // its last, so that the wait is short; and as it waits only for lower ids, which were dispatched before it and never wait
 // before they have written, it ends whatever else runs on the chip (and is bounded besides).
 constexpr int ATT_EVEN_SPINS = 1 << 22;         // polls of a partial result that does not come (some seconds): an error is raised
+
+struct EvenFlag {
+  int32_t* p;
+  __device__ __forceinline__ int load() const { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ void store(int v) const { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ int add(int v) const { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ void pause() const { __builtin_amdgcn_s_sleep(4); }
+};
 
 struct EvenShare {
   int xcd, k, per, b0, m;                       // the die's place, this workgroup's among its `per`; first block, blocks
@@ -579,20 +588,26 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
                          __HIP_MEMORY_SCOPE_AGENT);
       wait_for_own_stores();
       __syncthreads();
-      if (tid == 0) __hip_atomic_store(flags + share.k, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) handoff_give(EvenFlag{flags + share.k});
       continue;
     }
     const long long total = __builtin_amdgcn_readfirstlane(pre[share.m]);
+    __shared__ int came[2];                         // in turn: one may still be read while the next share is waited for
+    int turn = 0;
     for (int k = share.k - 1; st0 > 0 && k >= 0; --k) {     // the shares before it, back to the block's first stage
       const int v0 = (int)(total * k / share.per), v1 = (int)(total * (k + 1) / share.per);
       if (v0 == v1) continue;
       if (tid == 0) {
-        int left = ATT_EVEN_SPINS;
-        while (__hip_atomic_load(flags + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 && --left > 0) __builtin_amdgcn_s_sleep(4);
-        if (left <= 0) atomicCAS(&a.st.err[0], 0, LTRI_EHIP);
-        __hip_atomic_store(flags + k, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next launch
+        came[turn] = handoff_take(EvenFlag{flags + k}, ATT_EVEN_SPINS);
+        if (!came[turn]) atomicCAS(&a.st.err[0], 0, LTRI_EHIP);
       }
       __syncthreads();
+      const bool there = came[turn];
+      turn ^= 1;
+      if (!there) {                                 // (the others are still taken: their flags have to be)
+        if (v0 <= first_st) break;
+        continue;
+      }
       const unsigned long long* pp = place(k);
       const unsigned long long ml = __hip_atomic_load(pp + NP * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned long long pv[NP];
