@@ -265,10 +265,10 @@ int32_t ltri_attend(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int32_t seq
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, same results. Where
  * ltri_attend keeps the partial results of a split key range of such a block in the context's scratch, this call
  * keeps them in a buffer of 2 MiB that the library itself holds on every GPU it runs on, from load until the
- * process ends. Blocks of more than 4 rows are ltri_attend's launch, partial results in the context's scratch
+ * process ends (fp32 contexts: in the context's state). Blocks of more than 4 rows are ltri_attend's launch, partial results in the context's scratch
  * included. The call allocates and frees nothing. LTRI_ECAPACITY if the partial results of this call need more than 2 MiB (they take
  * seq_count * n_q_heads * splits * n_q * (head_dim + 2) * 4 bytes; 16 sequences of one token at 32 query
- * heads take 1.1 MB); other errors as ltri_attend. All contexts on one GPU share the buffer: calls that
+ * heads take 1.1 MB); other errors as ltri_attend. All bf16 contexts on one GPU share the buffer: calls that
  * overlap on one GPU (different streams or contexts) race; on one stream they are ordered. Nothing in the
  * buffer has to start at zero, every word a call reads was written by that call. */
 int32_t ltri_attend_static(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int32_t seq_count,

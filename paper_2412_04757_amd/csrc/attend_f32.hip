@@ -245,6 +245,13 @@ __global__ __launch_bounds__(64 * F32_WAVES, DIM == 64 ? 4 : 2) void attend_f32_
 // Rows of partial results (of head_dim + 2 floats) a split launch takes, at most.
 size_t attend_f32_part_rows() { return (size_t)F32_SPLIT_WGS * 16; }
 
+size_t attend_f32_short_bytes(const Dims& D) {
+  if (D.dtype != LTRI_F32) return 0;
+  const size_t wgs = (size_t)((ATT_SPLIT_MAX_ROWS * D.G + 15) / 16) * D.Hkv * (D.n_seqs < LTRI_MAX_BATCH ? D.n_seqs : LTRI_MAX_BATCH);
+  const size_t split = wgs * F32_MAX_SPLITS;
+  return (split < (size_t)F32_SPLIT_WGS ? split : (size_t)F32_SPLIT_WGS) * 16 * (D.d + 2) * sizeof(float);
+}
+
 // n_ctx: context tokens that the chunk is expected to attend. Splits while they fit one round of workgroups, one per compute
 // unit, and every wavefront keeps two tiles or more.
 hipError_t launch_attend_f32(const AttArgs& args, long long n_ctx, hipStream_t s) {

@@ -146,6 +146,7 @@ static int32_t derive(const ltri_config* cfg, Dims& D, StateLayout& SL, ScratchL
   SL.idx_mask = o;   o = align_up(o + n_slots * IDX_MASK_WORDS * 4, 256);
   SL.tickets = o;    o = align_up(o + ((size_t)P + (size_t)c.n_seqs * c.n_kv_heads) * 4, 256);
   SL.even_flags = o; o = align_up(o + attend_flag_count(D) * 4, 256);
+  SL.f32_part = o;   o = align_up(o + attend_f32_short_bytes(D), 256);
   SL.row_list = o;   o = align_up(o + (D.offload ? n_slots * (size_t)D.list_cap * 4 : 0), 256);
   SL.k_pool = o;     o = align_up(o + (D.offload ? n_slots * (size_t)D.arena_rows * D.d * D.elt : 0), 256);
   SL.v_pool = o;     o = align_up(o + (D.offload ? n_slots * (size_t)D.arena_rows * D.d * D.elt : 0), 256);
@@ -259,7 +260,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   c->ds = DevState{(int32_t*)(s + SL.meta), (int32_t*)(s + SL.span_start), (int32_t*)(s + SL.span_len),
                    (void*)(s + SL.krep), (double*)(s + SL.scores), (int32_t*)(s + SL.sel_ids),
                    (int32_t*)(s + SL.tok_list), (int32_t*)(s + SL.err), (uint32_t*)(s + SL.idx_mask),
-                   (int32_t*)(s + (D.offload ? SL.row_list : SL.tok_list)), (int32_t*)(s + SL.even_flags), (int32_t*)(s + SL.tickets)};
+                   (int32_t*)(s + (D.offload ? SL.row_list : SL.tok_list)), (float*)(s + SL.f32_part), (int32_t*)(s + SL.even_flags), (int32_t*)(s + SL.tickets)};
   char* t = c->scratch;
   c->dc = DevScratch{(double*)(t + CL.rowsum), (double*)(t + CL.csuf), (double*)(t + CL.tsum),
                      (double*)(t + CL.rcar), (double*)(t + CL.ccar), (double*)(t + CL.pscore),
@@ -718,8 +719,10 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
                   seq_begin + s);
   float* part = c->dc.att_part;
   int32_t* flags = c->ds.even_flags;
-  if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS) {
-    flags = nullptr;                     // nothing of the context's: splits are merged by a launch, none in fp32
+  if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS && !attend_on_matrix_cores(c->D)) {
+    part = c->ds.f32_part;               // (same launch, same results)
+  } else if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS) {
+    flags = nullptr;                     // splits are merged by a launch of their own
     // a dry context sizes the request for a device of 256 compute units
     const size_t bytes = attend_partial_bytes(c->D, seq_count, n_q, c->dry ? 256 : c->n_cus);
     if (bytes > ATT_STATIC_SCRATCH_BYTES)

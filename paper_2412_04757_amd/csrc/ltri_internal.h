@@ -48,6 +48,7 @@ struct StateLayout {
   // Zero between launches. They lie here and not in the scratch, which may hold anything when a call begins:
   size_t tickets;     // int32  [P] + [n_seqs * Hkv]  finished workgroups per problem (the two launches of step 2)
   size_t even_flags;  // int32  [attend_flag_count]  attention: pieces in place, or finished splits
+  size_t f32_part;    // float  partial results of fp32 blocks of a few rows (attend_f32_short_bytes), for ltri_attend_static
   // host-offloaded KV only (else row_list == tok_list and the pools are empty):
   size_t row_list;    // int32  [n_slots][list_cap]  the context list as rows of the device pool
   size_t k_pool;      // dtype  [n_slots][pool_rows][d]  initial tokens | ring of the latest tokens | retrieved rows
@@ -133,6 +134,7 @@ struct DevState {
   int32_t* meta; int32_t* span_start; int32_t* span_len; void* krep; double* scores;
   int32_t* sel_ids; int32_t* tok_list; int32_t* err; uint32_t* idx_mask;
   int32_t* row_list;       // what the attention walks: tok_list itself, or (host-offloaded KV) the same list as pool rows
+  float* f32_part;
   int32_t* even_flags;
   int32_t* tickets;        // [max_problems] and [n_seqs * Hkv] counters of finished workgroups; zero between launches
 };
@@ -232,6 +234,8 @@ inline size_t attend_flag_count(const Dims& D) {
   const size_t slots = (size_t)D.n_seqs * D.Hkv;
   return slots > (size_t)ATT_EVEN_WGS ? slots : (size_t)ATT_EVEN_WGS;
 }
+// room that splits of an fp32 context's blocks of up to ATT_SPLIT_MAX_ROWS rows take, at most (0 in bf16)
+size_t attend_f32_short_bytes(const Dims& D);
 size_t attend_part_rows(const Dims& D);          // Dims::att_part_rows: rows of (head_dim + 2) floats
 // device address, on the current device, of the library's own buffer of ATT_STATIC_SCRATCH_BYTES for partial results
 hipError_t attend_static_scratch(float** ptr);

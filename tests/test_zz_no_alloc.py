@@ -103,3 +103,33 @@ def test_attend_static_refuses_what_its_buffer_cannot_hold(gpu_device):
     ctx.attend_static(0, 1, 1, q[1:2].contiguous(), one)          # one sequence fits
     assert torch.equal(one[0], want[1])
     assert ctx.sync_status() == 0
+
+
+# (query heads, KV heads, head_dim, sequences, history, query rows): the launches split their keys four, four, four, three times and not at all
+@pytest.mark.parametrize("hq,hkv,dim,n_seqs,history,rows", [
+    (4, 1, 64, 1, 1500, 1), (4, 2, 128, 3, 1500, 1), (24, 2, 128, 1, 1500, 3), (8, 2, 64, 2, 800, 4), (4, 1, 64, 2, 100, 2),
+])
+def test_attend_static_matches_attend_in_fp32(gpu_device, hq, hkv, dim, n_seqs, history, rows):
+    """Same arguments, same results: to the bit, with the scratch buffer out of bounds for the static call."""
+    w = Workload("mini-static-f32", hq, hkv, dim, "f32", history + rows, 256, 4, 512, 0, 512, "uniform", 16, 64)
+    ctx = LtriContext(config_from_workload(w, theta=theta_default(dim), n_layers=1, n_seqs=n_seqs), gpu_device)
+    ka, va = ctx.arena_views()
+    qs = []
+    for s in range(n_seqs):
+        K, V, Q, _ = planted_stream(w, 70 + s, device=str(gpu_device), context=w.context)
+        ka[0, s].copy_(K), va[0, s].copy_(V)
+        qs.append(Q[history:])
+    for c0 in range(0, history, 256):
+        ctx.append_chunk(0, 0, n_seqs, min(256, history - c0))
+    q = torch.stack(qs).contiguous()
+    ctx.append_chunk(0, 0, n_seqs, rows)
+    ctx.retrieve(0, 0, n_seqs, q)
+    lse_a = torch.empty(q.shape[:3], dtype=torch.float32, device=gpu_device)
+    want = ctx.attend(0, 0, n_seqs, q, lse=lse_a)
+    ctx.scratch.fill_(0xFF)
+    for _ in range(3):                                   # the counters are left as they were found
+        got, lse_b = torch.full_like(want, float("nan")), torch.full_like(lse_a, float("nan"))
+        ctx.attend_static(0, 0, n_seqs, q, got, lse=lse_b)
+        assert torch.equal(got, want) and torch.equal(lse_a, lse_b)
+    assert bool((ctx.scratch == 0xFF).all())
+    assert ctx.sync_status() == 0
