@@ -427,11 +427,12 @@ static void append_commit(ltri_ctx* c, int layer, int seq_begin, int seq_count, 
 
 // Step 1 of a chunk: segmentation and index vectors. Its rows are in the arenas already, or (src) a launch of the segmentation
 // copies them there. rep_keys_later: step 2 stores the mean keys.
-// q_step2 (or NULL): the query rows that step 2 will be called with right after; *sums_ready then says whether the
-// running sums it reads were taken along.
+// q_step2 (or NULL): the query rows that step 2 will be called with right after, over at most span_bound spans; *sums_ready then
+// says whether the running sums it reads were taken along, or (index vectors) its Q^R.
 static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_count, const void* q_seg, int n_new,
                             const ChunkRows* src, bool rep_keys_later = false, const void* q_step2 = nullptr,
-                            bool* sums_ready = nullptr, const std::function<int32_t(int, int)>& after_batch = {}) {
+                            int span_bound = 0, bool* sums_ready = nullptr,
+                            const std::function<int32_t(int, int)>& after_batch = {}) {
   int32_t r;
   if (src && !src->k_chunk) src = nullptr;
   if (sums_ready) *sums_ready = false;
@@ -448,7 +449,7 @@ static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_
   const bool reps = segment_stores_reps(c->D, n_new);
   // one batch of sequences only, or step 2 of a batch before the next: its sums take the place of the ones before
   const bool with_sums = q_step2 && sums_ready && (seq_count <= per || after_batch) && retrieve_reads_running_sums(c->D, n_new);
-  const bool with_qrep = q_step2 && sums_ready && dynamic && !reps;
+  const bool with_qrep = q_step2 && sums_ready && dynamic && !reps && retrieve_reads_stored_qrep(c->D, n_new, span_bound);
   RunSums sums;
   if (with_sums)
     sums = running_sums_of(c->D, c->dc, c->CL.max_problems, q_step2, rep_keys_later ? c->k_arena : nullptr, n_new);
@@ -873,6 +874,9 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   const bool keys_with_step2 = retrieve_stores_rep_keys(c->D, n_new);
   const ChunkRows src = chunk_rows(c, k_chunk, v_chunk, false);        // (offloaded: the fetch's launch writes the host rows)
   StepTiming timing(c);
+  long long bound = 0;                   // spans that step 2 may find
+  for (int s = 0; s < seq_count; ++s)
+    bound = std::max(bound, std::min<long long>(c->span_bound[ls_index(c, layer, seq_begin + s)] + n_new, c->D.max_spans));
   bool sums_ready = false;               // step 2's running sums of the query and key rows rode in the selections' launch
   if (!c->D.offload) {
     // Keys and values resident on the device: the three steps follow each other on the context's stream and the
@@ -880,13 +884,10 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     // sub-tiles paired from both ends of the chunk) and fill every compute unit, so a split that runs the first
     // part beside the small kernels of steps 1 and 2 only makes those wait for a free compute unit.
     const int per = c->CL.max_problems / c->D.Hkv;      // sequences per segmentation launch
-    long long bound = 0;
-    for (int s = 0; s < seq_count; ++s)
-      bound = std::max(bound, std::min<long long>(c->span_bound[ls_index(c, layer, seq_begin + s)] + n_new, c->D.max_spans));
     if (seq_count > per && retrieve_from_sums(c->D, n_new, (int)bound)) {
       // Several batches: steps 1 and 2 of each in turn, so that the running sums of every one ride in its selections' launch
       // (there is room for one batch's; taken in step 2 they are a launch per batch, 22 us for four sequences of 1024 rows).
-      r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready, [&](int off, int cnt) {
+      r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, (int)bound, &sums_ready, [&](int off, int cnt) {
         return check_hip(c, launch_retrieve(c->D, c->ds, c->dc, c->CL.max_problems, q, layer, bp, seq_count, n_new, (int)bound,
                                             nullptr, nullptr, nullptr, nullptr, nullptr, keys_with_step2 ? c->k_arena : nullptr,
                                             true, c->stream, off, cnt), "retrieve");
@@ -898,7 +899,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
         c->ever_sel[ls_index(c, layer, seq_begin + s)] = 0xFFFFFFFFu;
       }
     } else {
-      r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready);
+      r = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, (int)bound, &sums_ready);
       if (r != LTRI_OK) return r;
       append_commit(c, layer, seq_begin, seq_count, n_new);
       r = retrieve_impl(c, layer, seq_begin, seq_count, q, n_new, nullptr, nullptr, keys_with_step2, sums_ready);
@@ -928,7 +929,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
   auto both_streams = [&]() -> int32_t {
     int32_t e = check_hip(c, launch_local_list(c->D, bp, seq_count, c->dc.loclist, c->CL.loc_cap, c->stream), "local list");
     if (e != LTRI_OK) return e;
-    e = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, &sums_ready);
+    e = append_spans(c, layer, bp, seq_count, q_seg, n_new, &src, keys_with_step2, q, (int)bound, &sums_ready);
     if (e != LTRI_OK) return e;
     append_commit(c, layer, seq_begin, seq_count, n_new);
     side_queued = true;                  // (from here on the second stream may hold work of this step)

@@ -1328,6 +1328,13 @@ bool retrieve_from_sums(const Dims& D, int n_q, int span_bound) {
   return retrieve_reads_running_sums(D, n_q) && retrieve_one_tail(span_bound, span_bound);
 }
 
+// Items of a selection, at most: the spans, or the units that a full stream has.
+static int item_bound_of(const Dims& D, int span_bound) { return D.unit > 0 ? (int)(D.max_tokens / D.unit) + 1 : span_bound; }
+
+bool retrieve_reads_stored_qrep(const Dims& D, int n_q, int span_bound) {
+  return D.rep_mode == LTRI_REP_DYNAMIC && retrieve_reads_stored(n_q, span_bound, item_bound_of(D, span_bound));
+}
+
 hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& sc, int sc_max_problems,
                            const void* q, int layer, const BatchPos& bp, int seq_count, int n_q, int span_bound,
                            int32_t* sel_ids_out, int32_t* sel_cnt_out, const VoteArgs* votes, const void* append_k_arena,
@@ -1370,8 +1377,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   // 26 KB of masks and list scratch). The launches it replaces on other than 128-wide heads, chunks of up to 128 tokens and
   // retrieval by units (Q^R, scores, ranks or units, lists: 3 to 5 of them): 256 fp32 tokens, 64 wide, 25.6 us -> 17.2; 128
   // tokens by units with index vectors 27 -> 14.6; 2048 tokens 62 -> 41.
-  const int unit_bound = D.unit > 0 ? (int)(D.max_tokens / D.unit) + 1 : 0;    // units a full stream has, at most
-  const int item_bound = D.unit > 0 ? unit_bound : span_bound;
+  const int item_bound = item_bound_of(D, span_bound);
   const int piece_seqs = sc_max_problems / D.Hkv;          // sequences the buffer of pieces or running sums is for
   const bool whole = count == 0;
   if (whole) count = seq_count;
@@ -1447,6 +1453,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   if (bf) score_kernel<LTRI_BF16><<<gs, 256, qs_bytes, s>>>(a);
   else    score_kernel<LTRI_F32><<<gs, 256, qs_bytes, s>>>(a);
   if (D.unit > 0) {
+    const int unit_bound = item_bound;
     static bool attr_set = false;
     if (!attr_set) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&unit_select_kernel),

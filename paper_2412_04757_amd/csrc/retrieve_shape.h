@@ -46,4 +46,11 @@ inline RetrieveShape retrieve_shape(bool reads_sums, bool votes, bool stored, in
   return s;
 }
 
+// Whether step 2 of a chunk with index vectors reads a Q^R that is in place: not where its workgroups sum the rows themselves, nor
+// with very long tables, so that the step before need not take it there.
+inline bool retrieve_reads_stored(int n_q, int span_bound, int item_bound) {
+  const RetrieveShape s = retrieve_shape(false, false, true, n_q, span_bound, item_bound, 1, 1);
+  return !s.from_rows && !s.pieces;
+}
+
 }  // namespace ltri

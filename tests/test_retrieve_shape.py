@@ -19,7 +19,8 @@ int main() {
   int sums, votes, stored, n_q, spans, items, count, room;
   while (scanf("%d %d %d %d %d %d %d %d", &sums, &votes, &stored, &n_q, &spans, &items, &count, &room) == 8) {
     const ltri::RetrieveShape s = ltri::retrieve_shape(sums, votes, stored, n_q, spans, items, count, room);
-    printf("%d %d %d %d %d %d\n", s.one_tail, s.from_sums, s.from_rows, s.pieces, s.per, ltri::qrep_units(n_q));
+    printf("%d %d %d %d %d %d %d\n", s.one_tail, s.from_sums, s.from_rows, s.pieces, s.per, ltri::qrep_units(n_q),
+           ltri::retrieve_reads_stored(n_q, spans, items));
   }
 }
 """
@@ -42,9 +43,13 @@ def test_pieces_and_running_sums_stay_inside_their_buffer(tmp_path):
     lines = subprocess.run([str(tmp_path / "a")], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
     assert len(lines) == len(calls)
     for (sums, votes, stored, n_q, spans, items, count, room), line in zip(calls, lines):
-        one, from_sums, from_rows, pieces, per, units = (int(v) for v in line.split())
+        one, from_sums, from_rows, pieces, per, units, reads_stored = (int(v) for v in line.split())
         case = (sums, votes, stored, n_q, spans, items, count)
         assert one == (not votes and spans <= 8192 and items <= LONGEST), case
+        # what step 1 takes along is read by step 2, and not taken by it again
+        assert reads_stored == (spans <= 8192 and items <= LONGEST and n_q > 128), case
+        if stored:
+            assert reads_stored == (not from_rows and not pieces), case
         assert per >= 1 and from_sums + from_rows + pieces + (one and not from_sums and not from_rows and not pieces) == 1, case
         # buffer: two times `room` sequences' (Lp / 128 + Lp) rows, Lp the chunk rounded up to 64
         Lp = -(-n_q // 64) * 64
