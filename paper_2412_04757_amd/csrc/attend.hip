@@ -604,15 +604,15 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
       __syncthreads();
       const bool there = came[turn];
       turn ^= 1;
-      if (!there) {                                 // (the others are still taken: their flags have to be)
-        if (v0 <= first_st) break;
-        continue;
-      }
-      const unsigned long long* pp = place(k);
+      const unsigned long long* pp = place(k);      // (requested whether it is there or not: the place is the context's)
       const unsigned long long ml = __hip_atomic_load(pp + NP * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned long long pv[NP];
 #pragma unroll
       for (int j = 0; j < NP; ++j) pv[j] = __hip_atomic_load(pp + j * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!there) {                                 // (the others are still taken: their flags have to be)
+        if (v0 <= first_st) break;
+        continue;
+      }
       const float om = __uint_as_float((uint32_t)ml), ol = __uint_as_float((uint32_t)(ml >> 32));
       const float m_new = fmaxf(m_run, om);
       const float f0 = __builtin_amdgcn_exp2f(m_run - m_new), f1 = __builtin_amdgcn_exp2f(om - m_new);
