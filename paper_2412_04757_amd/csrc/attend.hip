@@ -1199,7 +1199,7 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     if (!attr_set) {
       for (const void* f : {reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4, false>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 3, false>),
                             reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2, false>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4, true>),
-                            reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2, true>)}) {
+                            reinterpret_cast<const void*>(&attend_bf16_kernel<1, 3, true>), reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2, true>)}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, att_lds_bytes(2, 2));
         if (e != hipSuccess) return e;
       }
@@ -1219,7 +1219,8 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     using std::true_type;
     using std::false_type;
     if (even == 2)        launch(integral_constant<int, 2>{}, integral_constant<int, 2>{}, true_type{});
-    else if (even == 1)   launch(integral_constant<int, 1>{}, integral_constant<int, 4>{}, true_type{});
+    else if (even && stages == 3) launch(integral_constant<int, 1>{}, integral_constant<int, 3>{}, true_type{});
+    else if (even)        launch(integral_constant<int, 1>{}, integral_constant<int, 4>{}, true_type{});
     else if (ks == 2)     launch(integral_constant<int, 2>{}, integral_constant<int, 2>{}, false_type{});
     else if (stages == 3) launch(integral_constant<int, 1>{}, integral_constant<int, 3>{}, false_type{});
     else                  launch(integral_constant<int, 1>{}, integral_constant<int, 4>{}, false_type{});

@@ -79,6 +79,10 @@ def test_even_shares(gpu_device, hq, hkv, window, budget, history, rows):
         again = torch.full_like(q, float("nan"))
         ctx.attend(0, 0, S, q, out=again)
         assert torch.equal(out, again)
+    ctx.set_attend_stages(3)                             # the shorter ring: same results
+    ctx.attend(0, 0, S, q, out=again.fill_(float("nan")))
+    assert torch.equal(out, again)
+    ctx.set_attend_stages(4)
     for s in range(S):
         want, want_lse = attend_reference(ctx, w, s, history[s], q[s])
         assert worst_row(out[s], want) <= BF16_ROW
