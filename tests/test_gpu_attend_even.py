@@ -16,18 +16,29 @@ LAUNCHES = [
     (32, 8, 1024, 1024, [4096], 1050),
     (32, 8, 1024, 4096, [8000], 1217),                 # two groups of keys or one, a ragged list
     (24, 2, 1024, 2048, [6000], 1500),                 # three workgroups per KV head
-    (8, 8, 1500, 4096, [9000, 9000], 2048),            # one query head per KV head
+    (8, 8, 1024, 1024, [3000, 2500, 4000, 3500], 1057),  # one query head per KV head, four sequences, eight ragged row sub-tiles
+    (32, 8, 250, 262, [1100, 900, 1000], 700),         # two groups of keys, three sequences
     (16, 8, 1024, 2048, [5000, 3000, 700], 750),       # sequences of different lengths
     (32, 8, 1024, 1024, [4096, 1, 4096], 700),         # one of them without a context
+]
+# the rule leaves these alone: same checks, ordinary shapes
+ORDINARY = [
+    (8, 8, 1500, 4096, [9000, 9000], 2048),
     (32, 8, 300, 300, [2100] * 4, 600),
 ]
 RULE = r"""
 #include <stdio.h>
+#include <algorithm>
 #include "attend_shape.h"
+using namespace ltri;
 int main() {
   int hq, hkv, seqs, rows, ctx;
-  while (scanf("%d %d %d %d %d", &hq, &hkv, &seqs, &rows, &ctx) == 5)
-    printf("%d\n", ltri::attend_even(hq, hkv, seqs, rows, ctx, (size_t)1 << 40, ltri::ATT_PART_MAX_ROWS, 256));
+  while (scanf("%d %d %d %d %d", &hq, &hkv, &seqs, &rows, &ctx) == 5) {
+    // the room that a context of as many sequences, chunks of 2048 and this many context tokens has
+    const size_t row = 130 * sizeof(float), even = (attend_most_even_bytes(hq, hkv, seqs, 2048, 256) + row - 1) / row;
+    const size_t room = std::max({(size_t)seqs * hq * ATT_MAX_SPLITS * ATT_SPLIT_MAX_ROWS, even, attend_most_part_rows(hq, hkv, seqs, 2048, ctx, 256)});
+    printf("%d\n", attend_even(hq, hkv, seqs, rows, ctx, room * row, std::min(room, ATT_PART_MAX_ROWS), 256));
+  }
 }
 """
 
@@ -48,15 +59,18 @@ def rule(tmp_path_factory):
 
 def test_even_shares_are_taken_where_the_chip_would_idle(rule):
     """The launches below, and those measured: never at a full chip or one that merely starts with idle units."""
-    got = rule([(hq, hkv, len(h), rows, min(max(h), 4 + window + budget)) for hq, hkv, window, budget, h, rows in LAUNCHES])
-    assert sum(k > 0 for k in got) >= 5 and {1, 2} <= set(got), got
+    as_launched = lambda launches: [(hq, hkv, len(h), rows, min(max(h), 4 + window + budget)) for hq, hkv, window, budget, h, rows in launches]
+    got = rule(as_launched(LAUNCHES))
+    assert all(got) and got.count(1) >= 2 and got.count(2) >= 2, got
+    assert got[[x[:2] for x in LAUNCHES].index((8, 8))] == 1
+    assert rule(as_launched(ORDINARY)) == [0] * len(ORDINARY)
     assert rule([(32, 8, 1, 2048, 12292), (32, 8, 1, 1024, 8196), (32, 8, 1, 700, 2052), (32, 8, 4, 256, 2052), (8, 8, 1, 1024, 4100),
                  (32, 8, 1, 1800, 12292), (32, 8, 1, 128, 2052)]) == [0] * 7
     assert all(rule([(32, 8, 1, 1100, 8196), (32, 8, 1, 1300, 12292), (32, 8, 3, 700, 2052), (32, 8, 1, 700, 12292)]))
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("hq,hkv,window,budget,history,rows", LAUNCHES)
+@pytest.mark.parametrize("hq,hkv,window,budget,history,rows", LAUNCHES + ORDINARY)
 def test_even_shares(gpu_device, hq, hkv, window, budget, history, rows):
     S, longest = len(history), max(history)
     w = Workload("even", hq, hkv, 128, "bf16", longest + rows, 2048, 4, window, 0, budget, "uniform", 16, 96)
