@@ -31,9 +31,6 @@ __device__ __forceinline__ float group_max(float v) {      // over the four lane
   return fmaxf(v, __uint_as_float(lane_xor_c<32>(__float_as_uint(v))));
 }
 
-constexpr int F32_WAVES = 8;                                 // wavefronts per workgroup
-constexpr int F32_MAX_SPLITS = 4;
-constexpr int F32_SPLIT_WGS = 256;                           // workgroups of a split launch, at most (tickets: ATT_EVEN_WGS)
 constexpr int F32_PITCH = 68;                                // floats per query of a wavefront's 64 columns in LDS
 
 template <int DIM>
@@ -252,16 +249,12 @@ size_t attend_f32_short_bytes(const Dims& D) {
   return (split < (size_t)F32_SPLIT_WGS ? split : (size_t)F32_SPLIT_WGS) * 16 * (D.d + 2) * sizeof(float);
 }
 
-// n_ctx: context tokens that the chunk is expected to attend. Splits while they fit one round of workgroups, one per compute
-// unit, and every wavefront keeps two tiles or more.
+// n_ctx: context tokens that the chunk is expected to attend.
 hipError_t launch_attend_f32(const AttArgs& args, long long n_ctx, hipStream_t s) {
   AttArgs a = args;
   const Dims& D = a.D;
   const int blocks = (a.n_q * D.G + 15) / 16;
-  const long long wgs = (long long)blocks * D.Hkv * a.seq_count, tiles = (n_ctx + a.n_q + 15) / 16;
-  a.n_splits = 1;
-  while (a.part && a.even_flags && a.n_splits < F32_MAX_SPLITS && wgs * (a.n_splits + 1) <= F32_SPLIT_WGS &&
-         tiles >= 2LL * F32_WAVES * (a.n_splits + 1)) ++a.n_splits;
+  a.n_splits = a.part && a.even_flags ? attend_f32_splits(D.G, D.Hkv, a.seq_count, a.n_q, n_ctx) : 1;
   const dim3 grid(blocks * a.n_splits, D.Hkv, a.seq_count);
   if (D.d == 64) attend_f32_kernel<64><<<grid, 64 * F32_WAVES, 0, s>>>(a);
   else           attend_f32_kernel<128><<<grid, 64 * F32_WAVES, 0, s>>>(a);

@@ -78,6 +78,19 @@ inline size_t attend_most_part_rows(int Hq, int Hkv, int n_seqs, int chunk_max, 
   return most;
 }
 
+// ---- fp32 (attend_f32.hip) ----
+constexpr int F32_WAVES = 8;             // wavefronts per workgroup, which has 16 (row, head) pairs and takes tiles of 16 keys
+constexpr int F32_MAX_SPLITS = 4;
+constexpr int F32_SPLIT_WGS = 256;       // workgroups of a split launch, at most (tickets: ATT_EVEN_WGS)
+
+// Splits of the key range: as many as fit one round of workgroups, one per compute unit, while every wavefront keeps two tiles.
+inline int attend_f32_splits(int G, int Hkv, int seq_count, int n_q, long long n_ctx) {
+  const long long wgs = (long long)((n_q * G + 15) / 16) * Hkv * seq_count, tiles = (n_ctx + n_q + 15) / 16;
+  int ns = 1;
+  while (ns < F32_MAX_SPLITS && wgs * (ns + 1) <= F32_SPLIT_WGS && tiles >= 2LL * F32_WAVES * (ns + 1)) ++ns;
+  return ns;
+}
+
 // ---- even shares ----
 constexpr int ATT_EVEN_LEAST = 96;       // fewest blocks of a launch: below, a compute unit would fold in many pieces
 constexpr int ATT_EVEN_BLOCKS = 512;     // blocks of a die at most (one per thread of the workgroup that counts their stages)
