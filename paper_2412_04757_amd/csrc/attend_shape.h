@@ -29,9 +29,18 @@ constexpr size_t ATT_PART_MAX_ROWS = 65536;
 
 struct AttShape { int ks, ns; };
 
-// n_ctx context and n_chunk chunk tokens; part_rows: partial rows there is room for. modelled (or NULL): the time it takes.
-inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, int n_chunk, size_t part_rows, int n_cus,
-                             float* modelled = nullptr) {
+// Modelled time of a launch in ks groups and ns splits; chunk: share of the chunk's tiles that a workgroup walks.
+inline float attend_cost(int Hq, int seq_count, int n_q, int n_ctx, int n_chunk, long long blocks, int ks, int ns, float chunk, int n_cus) {
+  const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * chunk;
+  const long long rounds = (blocks * ns + n_cus - 1) / n_cus;
+  const float fill = (float)(blocks * ns) / (float)(rounds * n_cus);
+  const float stages = ceilf(tiles / (float)(ks * ns));
+  return (float)rounds * (stages * (1.5f + 0.35f * fill) * (ks == 2 ? 1.07f : 1.f) + 4.f) +
+         (ns > 1 ? 5.f + 1.7e-4f * (float)((size_t)seq_count * Hq * n_q * ns) : 0.f);
+}
+
+// n_ctx context and n_chunk chunk tokens; part_rows: partial rows there is room for.
+inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, int n_chunk, size_t part_rows, int n_cus) {
   const int G = Hq / Hkv, HG = G < 4 ? G : 4;
   AttShape best{1, 1};
   float best_cost = 0.f;
@@ -41,18 +50,14 @@ inline AttShape attend_shape(int Hq, int Hkv, int seq_count, int n_q, int n_ctx,
     for (int ns = 1; ns <= ATT_MAX_SPLITS; ++ns) {
       // The causal part: workgroups end at rows all over the chunk or its upper half. In a single round the longest walks
       // set the pace, in several they average out.
-      const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * (blocks * ns > n_cus ? 0.75f : 0.85f);
+      const float chunk = blocks * ns > n_cus ? 0.75f : 0.85f;
+      const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_chunk + 63) / 64) * chunk;
       const size_t rows = (size_t)seq_count * Hq * n_q * ns;
       if (ns > 1 && (rows > part_rows || ns * ks > tiles)) break;
-      const long long rounds = (blocks * ns + n_cus - 1) / n_cus;
-      const float fill = (float)(blocks * ns) / (float)(rounds * n_cus);
-      const float stages = ceilf(tiles / (float)(ks * ns));
-      const float cost = (float)rounds * (stages * (1.5f + 0.35f * fill) * (ks == 2 ? 1.07f : 1.f) + 4.f) +
-                         (ns > 1 ? 5.f + 1.7e-4f * (float)rows : 0.f);
+      const float cost = attend_cost(Hq, seq_count, n_q, n_ctx, n_chunk, blocks, ks, ns, chunk, n_cus);
       if ((ks == 1 && ns == 1) || cost < best_cost) { best_cost = cost; best = AttShape{ks, ns}; }
     }
   }
-  if (modelled) *modelled = best_cost;
   return best;
 }
 
@@ -98,14 +103,35 @@ constexpr int ATT_EVEN_WGS = 256;        // workgroups (compute units) there are
 // a piece that its workgroup does not finish: 32 / KS pairs of sums, and maximum and sum, per lane
 constexpr size_t att_even_place_bytes(int ks) { return (size_t)ATT_NW * (32 / ks + 1) * 64 * 8; }
 
+// Modelled time of a launch in even shares of ks groups, and its blocks.
+inline float attend_even_cost(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, int ks, int n_cus, long long* blocks) {
+  const int G = Hq / Hkv, HG = G < 4 ? G : 4, rs = ATT_NW / ks / HG, rpb = 32 * rs, n_rb = (n_q + rpb - 1) / rpb;
+  const long long slots = (long long)Hkv * (G / HG) * seq_count;
+  long long stages = 0;
+  for (int y = 0; y < n_rb; ++y) {                         // (as the kernel counts them, but for the lists' lengths)
+    const int end = rs == 1 ? (n_rb - y) * 32 : (n_rb * rs - y * (rs / 2)) * 32;
+    stages += ((n_ctx + 63) / 64 + ((end < n_q ? end : n_q) + 63) / 64 + ks - 1) / ks;
+  }
+  *blocks = slots * n_rb;
+  const float cu = 1.f / (float)n_cus;
+  const float block = ks == 2 ? 8.f : HG == 4 ? 4.5f : 0.5f;
+  return (float)(slots * stages) * cu * (ks == 2 ? 2.13f : 1.9f) + (float)*blocks * cu * block + (ks == 2 ? 13.f : 19.f);
+}
+
 // Whether a launch is cut into even shares (attend.hip), and then its key groups (else 0). They help where an ordinary launch
 // ends with most of the chip idle: just over one round of workgroups, or a second or third round that is nearly empty. They
 // do not where it merely starts with some units idle: the chip is limited by power, and the others run faster meanwhile (700
-// rows behind 2052 tokens on 176 units take 1.3 us a stage, on all of them 2.3). Modelled as the share of a compute unit,
-// in stages of 256 pairs x 64 keys at 1.9 us (two groups 2.15), and 19 us for the count of the stages, a second piece, and
-// the partial result written, awaited and folded in; taken where that is below 0.86 of the ordinary shape's cost, which
-// is 5 to 10 % high. Measured in both forms at 131 launches (64 to 8 query heads, 1 to 8 sequences, 64 to 2048 rows behind 964
-// to 12292 tokens; profiles/attend_even_shares.txt): taken at 34 of them, 13 % faster there in the mean, 0.4 % slower at worst:
+// rows behind 2052 tokens on 176 units take 1.3 us a stage, on all of them 2.3). Nor for a chunk without much of a context: its
+// blocks are short, and a share that goes through several of them pays for the start and end of each, which ordinary workgroups
+// of several rounds spend beside each other's walks (1121 rows of two sequences, no context, 32 heads: 47 us, in even shares 82).
+// Modelled as the share of a compute unit, in stages of 256 pairs x 64 keys at 1.9 us (two groups 2.13), its blocks at 4.5 (less
+// than four heads per KV head 0.5, two groups 8), and 19 us (13) for the count of the stages, a second piece, and the partial
+// result written, awaited and folded in. Taken where that is below 0.88 of the ordinary shape's cost, which is some 8 % high (and
+// more where a workgroup has one sub-tile and several rounds average half the chunk: 0.6 of it counts here). Two groups behind a
+// context of less than half the chunk were slower whatever the model said, and are left out.
+// Measured in all forms at 1101 launches (64 to 4 query heads, 1 to 24 sequences, 64 to 2048 rows behind 0 to 12292 tokens;
+// profiles/attend_even_shares.txt), most of them near the line: taken at 506, 12 % faster there in the mean, at five more than 2 %
+// slower (6 at worst). With one constant for all blocks the rule took 797 of them, 1 % slower in the mean and 45 % at worst.
 // 12292 + 1100 rows 326 -> 254, 2052 + 1050 80 -> 65, 12292 + 700 177 -> 165, three sequences of 8196 + 700 392 -> 304.
 inline int attend_even(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, size_t part_bytes, size_t part_rows, int n_cus) {
   const int G = Hq / Hkv, HG = G < 4 ? G : 4;
@@ -113,18 +139,19 @@ inline int attend_even(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, size_
   float cost[3] = {};
   int even = 0;
   for (int ks = 1; ks <= 2; ++ks) {
-    const int rs = ATT_NW / ks / HG, rpb = 32 * rs;
-    const long long blocks = (long long)Hkv * (G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
+    long long blocks;
+    cost[ks] = attend_even_cost(Hq, Hkv, seq_count, n_q, n_ctx, ks, n_cus, &blocks);
     // (above the limit a die's blocks would outnumber the threads)
     if (blocks < ATT_EVEN_LEAST || blocks > (long long)8 * (ATT_EVEN_BLOCKS - 1) || (size_t)n_cus * att_even_place_bytes(ks) > part_bytes) continue;
-    const float tiles = (float)((n_ctx + 63) / 64) + (float)((n_q + 63) / 64) * (rs == 1 ? 0.5f : 0.75f) + 0.5f;
-    cost[ks] = (float)blocks * tiles / (float)(ks * n_cus) * (ks == 2 ? 2.15f : 1.9f) + 19.f;
+    if (ks == 2 && 2 * n_ctx < n_q) continue;
     if (!even || cost[ks] < cost[even]) even = ks;
   }
   if (!even) return 0;
-  float ordinary = 0.f;
-  attend_shape(Hq, Hkv, seq_count, n_q, n_ctx, n_q, part_rows, n_cus, &ordinary);
-  return cost[even] < 0.86f * ordinary ? even : 0;
+  const AttShape s = attend_shape(Hq, Hkv, seq_count, n_q, n_ctx, n_q, part_rows, n_cus);
+  const int rs = ATT_NW / s.ks / HG, rpb = 32 * rs;
+  const long long blocks = (long long)Hkv * (G / HG) * ((n_q + rpb - 1) / rpb) * seq_count;
+  const float chunk = blocks * s.ns <= n_cus ? 0.85f : rs == 1 ? 0.6f : 0.75f;
+  return cost[even] < 0.88f * attend_cost(Hq, seq_count, n_q, n_ctx, n_q, blocks, s.ks, s.ns, chunk, n_cus) ? even : 0;
 }
 
 // The most room for pieces that the launches of a context can take.
