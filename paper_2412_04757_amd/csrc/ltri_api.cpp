@@ -449,7 +449,7 @@ static int32_t append_spans(ltri_ctx* c, int layer, const BatchPos& bp, int seq_
   const bool reps = segment_stores_reps(c->D, n_new);
   // one batch of sequences only, or step 2 of a batch before the next: its sums take the place of the ones before
   const bool with_sums = q_step2 && sums_ready && (seq_count <= per || after_batch) && retrieve_reads_running_sums(c->D, n_new);
-  const bool with_qrep = q_step2 && sums_ready && dynamic && !reps && retrieve_reads_stored_qrep(c->D, n_new, span_bound);
+  const bool with_qrep = q_step2 && sums_ready && dynamic && !reps && retrieve_reads_stored_qrep(c->D, n_new, span_bound, seq_count);
   RunSums sums;
   if (with_sums)
     sums = running_sums_of(c->D, c->dc, c->CL.max_problems, q_step2, rep_keys_later ? c->k_arena : nullptr, n_new);

@@ -213,7 +213,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
 // running_sums_of(D, sc, sc_max_problems, q, rep_k_arena, n_q) are in place (one batch of sequences only), or (dynamic index
 // vectors) Q^R is; count > 0 (only where retrieve_from_sums says so): sequences first .. first + count - 1 of the batch
 bool retrieve_from_sums(const Dims& D, int n_q, int span_bound);
-bool retrieve_reads_stored_qrep(const Dims& D, int n_q, int span_bound);    // step 2 reads a Q^R that launch_dynamic_reps has stored
+bool retrieve_reads_stored_qrep(const Dims& D, int n_q, int span_bound, int seq_count);    // step 2 reads a Q^R that launch_dynamic_reps has stored
 bool retrieve_stores_rep_keys(const Dims& D, int n_q);
 bool retrieve_is_one_launch(const Dims& D, int n_q, int span_bound);   // step 2 of a one-token chunk as a single kernel
 hipError_t launch_persist_list(const Dims& D, const DevState& st, int layer, const BatchPos& bp, int seq_count,

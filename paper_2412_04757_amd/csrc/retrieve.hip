@@ -108,6 +108,10 @@ __device__ __forceinline__ int qrep_first_unit(const int32_t* slen, int q) {
 }
 
 constexpr int QREP_GRID_X = 64;            // workgroups per problem that walk the pieces
+// Problems up to which the last workgroup of each adds its pieces up. With more, the launch is several rounds of workgroups that
+// all wait for their stores and a ticket, and a launch for the sums costs less: 32 problems (four sequences of 129 fp32 rows, 16 / 8
+// heads) 48.2 us with tickets, 42.3 without; 24 sequences of 512, 250 and 200.
+constexpr int QREP_LAST_PROBLEMS = 16;
 
 template <int DT>
 __global__ __launch_bounds__(1024) void qrep_partial_kernel(RetArgs a) {
@@ -1331,8 +1335,8 @@ bool retrieve_from_sums(const Dims& D, int n_q, int span_bound) {
 // Items of a selection, at most: the spans, or the units that a full stream has.
 static int item_bound_of(const Dims& D, int span_bound) { return D.unit > 0 ? (int)(D.max_tokens / D.unit) + 1 : span_bound; }
 
-bool retrieve_reads_stored_qrep(const Dims& D, int n_q, int span_bound) {
-  return D.rep_mode == LTRI_REP_DYNAMIC && retrieve_reads_stored(n_q, span_bound, item_bound_of(D, span_bound));
+bool retrieve_reads_stored_qrep(const Dims& D, int n_q, int span_bound, int seq_count) {
+  return D.rep_mode == LTRI_REP_DYNAMIC && retrieve_reads_stored(n_q, D.G * D.d * D.elt, span_bound, item_bound_of(D, span_bound), seq_count, D.Hkv);
 }
 
 hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& sc, int sc_max_problems,
@@ -1384,7 +1388,7 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
   // Mean representatives in bf16 (whose sums are exact in fp64): Q^R and the chunk's mean keys come from running
   // sums of the query and key rows, which need no span boundaries (no piece sums, no ticket).
   const RetrieveShape shape = retrieve_shape(retrieve_reads_running_sums(D, n_q), votes != nullptr, sums_ready && D.rep_mode == LTRI_REP_DYNAMIC,
-                                             n_q, span_bound, item_bound, count, piece_seqs);
+                                             n_q, D.G * D.d * D.elt, span_bound, item_bound, count, D.Hkv, piece_seqs);
   const bool one_tail = shape.one_tail;
   if (!whole && (!shape.from_sums || count > piece_seqs)) return hipErrorInvalidValue;
   if (one_tail) {
@@ -1399,7 +1403,12 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
       attr_set = true;
     }
   }
-  if (one_tail || n_q > QREP_PIECE) {
+  if (shape.spans) {
+    dim3 gq(n_q < 64 ? n_q : 64, P);
+    if (bf) qrep_kernel<LTRI_BF16><<<gq, 1024, 0, s>>>(a);
+    else    qrep_kernel<LTRI_F32><<<gq, 1024, 0, s>>>(a);
+  }
+  if (one_tail || shape.pieces) {
     const int gx = QREP_GRID_X + (rep_k_arena ? QREP_GRID_X : 0);
     const bool from_sums = shape.from_sums, from_rows = shape.from_rows;
     const bool sums_in_place = sums_ready && from_sums && count <= piece_seqs;    // else they are taken here
@@ -1413,38 +1422,41 @@ hipError_t launch_retrieve(const Dims& D, const DevState& st, const DevScratch& 
     a.qrep_mode = from_sums ? QREP_SUMS : from_rows ? QREP_ROWS : QREP_STORED;
     a.ticket_base = sc_max_problems;                        // the second part of the counters
     const int per = shape.per, end = first + count;
+    auto tail = [&](int off, int cnt) {
+      a.batch_off = off;
+      // one workgroup per 128 spans that there can be: the bound is about twice the spans there are, so that is about
+      // one tile per SIMD (with 256 spans per workgroup, held together, a launch over 100 to 300 spans took 18.7 us,
+      // now 16.6)
+      // But no more than one round over the chip: a compute unit holds one, and the bound can be many times the spans (12
+      // sequences of 8 heads, 3 rows after 25K tokens: 672 workgroups 29.4 us, 192 17.3)
+      const int wgs = (span_bound + 127) / 128, room = CHUNK_WGS / (cnt * D.Hkv);
+      const dim3 gt(cnt * D.Hkv, wgs < room ? wgs : room > 1 ? room : 1);
+      if (bf) retrieve_chunk_kernel<LTRI_BF16><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
+      else    retrieve_chunk_kernel<LTRI_F32><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
+    };
     for (int off = first; off < end; off += per) {
       const int cnt = end - off < per ? end - off : per;
       a.batch_off = off;
       dim3 gp(gx, cnt * D.Hkv), gf(n_q < 64 ? n_q : 64, cnt * D.Hkv);
-      a.qrep_by_last = one_tail;
+      a.qrep_by_last = one_tail && count <= per && count * D.Hkv <= QREP_LAST_PROBLEMS;
       if (from_sums) {
         if (!sums_in_place) running_sums_kernel<<<dim3(running_sums_blocks(a.rs), cnt * D.Hkv), 1024, 0, s>>>(a);
+        tail(off, cnt);                                     // (the next trip's sums take the place of these)
       } else if (shape.pieces) {
         if (bf) qrep_partial_kernel<LTRI_BF16><<<gp, 1024, 0, s>>>(a);
         else    qrep_partial_kernel<LTRI_F32><<<gp, 1024, 0, s>>>(a);
-      }
-      if (one_tail) {
-        // one workgroup per 128 spans that there can be: the bound is about twice the spans there are, so that is about
-        // one tile per SIMD (with 256 spans per workgroup, held together, a launch over 100 to 300 spans took 18.7 us,
-        // now 16.6)
-        // But no more than one round over the chip: a compute unit holds one, and the bound can be many times the spans (12
-        // sequences of 8 heads, 3 rows after 25K tokens: 672 workgroups 29.4 us, 192 17.3)
-        const int wgs = (span_bound + 127) / 128, room = CHUNK_WGS / (cnt * D.Hkv);
-        const dim3 gt(cnt * D.Hkv, wgs < room ? wgs : room > 1 ? room : 1);
-        if (bf) retrieve_chunk_kernel<LTRI_BF16><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
-        else    retrieve_chunk_kernel<LTRI_F32><<<gt, 1024, lds, s>>>(a, span_bound, item_bound);
-      } else {
-        if (bf) qrep_final_kernel<LTRI_BF16><<<gf, 128, 0, s>>>(a);
-        else    qrep_final_kernel<LTRI_F32><<<gf, 128, 0, s>>>(a);
+        if (!a.qrep_by_last) {
+          if (bf) qrep_final_kernel<LTRI_BF16><<<gf, 128, 0, s>>>(a);
+          else    qrep_final_kernel<LTRI_F32><<<gf, 128, 0, s>>>(a);
+        }
       }
     }
+    // Q^R has room for all sequences, so one launch takes what the trips have left there: a launch per trip, each of which waits
+    // for its slowest problem, was slower (24 sequences of 200 fp32 rows, 4 / 1 heads: 69 us with the general kernels behind the
+    // pieces, 99 with this one behind every trip, 63 now).
+    if (one_tail && !from_sums) tail(first, count);
     a.batch_off = 0;
     if (one_tail) return hipGetLastError();
-  } else {
-    dim3 gq(n_q < 64 ? n_q : 64, P);
-    if (bf) qrep_kernel<LTRI_BF16><<<gq, 1024, 0, s>>>(a);
-    else    qrep_kernel<LTRI_F32><<<gq, 1024, 0, s>>>(a);
   }
   int gx = (span_bound + 63) / 64;
   if (gx < 1) gx = 1;

@@ -16,11 +16,11 @@ PROGRAM = r"""
 #include <stdio.h>
 #include "retrieve_shape.h"
 int main() {
-  int sums, votes, stored, n_q, spans, items, count, room;
-  while (scanf("%d %d %d %d %d %d %d %d", &sums, &votes, &stored, &n_q, &spans, &items, &count, &room) == 8) {
-    const ltri::RetrieveShape s = ltri::retrieve_shape(sums, votes, stored, n_q, spans, items, count, room);
-    printf("%d %d %d %d %d %d %d\n", s.one_tail, s.from_sums, s.from_rows, s.pieces, s.per, ltri::qrep_units(n_q),
-           ltri::retrieve_reads_stored(n_q, spans, items));
+  int sums, votes, stored, n_q, bytes, spans, items, count, heads, room;
+  while (scanf("%d %d %d %d %d %d %d %d %d %d", &sums, &votes, &stored, &n_q, &bytes, &spans, &items, &count, &heads, &room) == 10) {
+    const ltri::RetrieveShape s = ltri::retrieve_shape(sums, votes, stored, n_q, bytes, spans, items, count, heads, room);
+    printf("%d %d %d %d %d %d %d %d\n", s.one_tail, s.from_sums, s.from_rows, s.spans, s.pieces, s.per, ltri::qrep_units(n_q),
+           ltri::retrieve_reads_stored(n_q, bytes, spans, items, count, heads));
   }
 }
 """
@@ -38,19 +38,21 @@ def test_pieces_and_running_sums_stay_inside_their_buffer(tmp_path):
             for n_q in (2, 128, 129, 1000, 2048):
                 for sums, votes, stored, items in ((0, 0, 0, spans), (0, 0, 1, spans), (1, 0, 0, spans), (0, 1, 0, 100), (0, 0, 1, 100),
                                                    (0, 0, 1, 8192)):
-                    calls.append((sums and n_q > 128, votes, stored, n_q, spans, items, count, min(count, 4)))
+                    bytes_ = (256, 2048, 4096)[(count + n_q) % 3]
+                    calls.append((sums and n_q > 128, votes, stored, n_q, bytes_, spans, items, count, 2, min(count, 4)))
     text = "\n".join(" ".join(str(int(v)) for v in x) for x in calls)
     lines = subprocess.run([str(tmp_path / "a")], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
     assert len(lines) == len(calls)
-    for (sums, votes, stored, n_q, spans, items, count, room), line in zip(calls, lines):
-        one, from_sums, from_rows, pieces, per, units, reads_stored = (int(v) for v in line.split())
-        case = (sums, votes, stored, n_q, spans, items, count)
+    for (sums, votes, stored, n_q, bytes_, spans, items, count, heads, room), line in zip(calls, lines):
+        one, from_sums, from_rows, spans_, pieces, per, units, reads_stored = (int(v) for v in line.split())
+        case = (sums, votes, stored, n_q, bytes_, spans, items, count)
         assert one == (not votes and spans <= 8192 and items <= LONGEST), case
         # what step 1 takes along is read by step 2, and not taken by it again
-        assert reads_stored == (spans <= 8192 and items <= LONGEST and n_q > 128), case
+        assert reads_stored == (spans <= 8192 and items <= LONGEST and (n_q > 128 or n_q * bytes_ > 256 << 10 and count <= 4)), case
         if stored:
-            assert reads_stored == (not from_rows and not pieces), case
-        assert per >= 1 and from_sums + from_rows + pieces + (one and not from_sums and not from_rows and not pieces) == 1, case
+            assert reads_stored == (not from_rows and not spans_ and not pieces), case
+        # Q^R has one source
+        assert per >= 1 and from_sums + from_rows + spans_ + pieces == (not (stored and reads_stored)), case
         # buffer: two times `room` sequences' (Lp / 128 + Lp) rows, Lp the chunk rounded up to 64
         Lp = -(-n_q // 64) * 64
         for off in range(0, count, per):
