@@ -114,3 +114,35 @@ def test_step_of_many_sequences_with_a_long_table(gpu_device, kv_offload):
         assert sa == sb and la == lb
         # (the offloaded step rounds the first part's output once more: 2^-8 of it and of the result)
         assert torch.equal(oa, ob) if not kv_offload else float((oa - ob).norm() / ob.norm()) <= 2.0 ** -7
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,dtype,dim,kw", [
+    (100, "bf16", 128, {}), (128, "bf16", 128, dict(rep_mode=1, lam=1.5)),                  # 16 heads: rows summed on the way, or before
+    (200, "bf16", 128, dict(rep_mode=1, lam=1.5)), (300, "bf16", 128, dict(rep_mode=1, lam=1.5, unit_tokens=64)), (129, "f32", 64, {}),
+])
+def test_sequences_together_and_alone(gpu_device, rows, dtype, dim, kw):
+    """Q^R comes from different launches for 18 sequences and for one, and several trips of sums share one selection: the selections
+    are the same (sums of bf16 values are exact; fp32 ones in fp64 differ by less than the scores do)."""
+    S, hist = 18, 900
+    w = Workload("mini-together", 16, 1, dim, dtype, hist + rows, 300, 4, 60, 0, 300, "uniform", 16, 200)
+    ctx = LtriContext(config_from_workload(w, n_layers=1, n_seqs=S, max_tokens=hist + rows, max_spans=hist + rows,
+                                           theta=theta_default(dim) / 4, **kw), gpu_device)
+    gen = torch.Generator(device=gpu_device).manual_seed(rows)
+    ka, va = ctx.arena_views()
+    T = hist + rows
+    mean = torch.randn(S, 1, T // 30 + 1, dim, generator=gen, device=gpu_device).repeat_interleave(30, 2)[:, :, :T]
+    ka[0].copy_(0.5 * (mean + 0.3 * torch.randn(S, 1, T, dim, generator=gen, device=gpu_device)))
+    va.copy_(torch.randn(va.shape, generator=gen, device=gpu_device))
+    for c0 in range(0, hist, 300):
+        ctx.append_chunk(0, 0, S, 300)
+    ctx.append_chunk(0, 0, S, rows)
+    q = torch.randn(S, rows, 16, dim, generator=gen, device=gpu_device).to(ka.dtype)
+    lists = lambda s: (list(ctx.get_selection(0, s, 0)[0]), list(ctx.get_token_list(0, s, 0)))
+    ctx.retrieve(0, 0, S, q)
+    together = [lists(s) for s in range(S)]
+    for s in range(S):
+        ctx.retrieve(0, s, 1, q[s:s + 1].contiguous())
+        assert lists(s) == together[s], s
+    assert ctx.sync_status() == 0
+    assert len({tuple(t[0]) for t in together}) > S // 2
