@@ -187,6 +187,11 @@ __device__ __forceinline__ EvenShare even_share(const AttArgs& a, int n_blocks, 
   return e;
 }
 
+// Partial results from this size on are stored past the caches. 355 split launches (2 to 1024 rows, 1 to 12 sequences), past them
+// against through them: up to 1 MB 4 % slower in the mean (two rows of 16 / 1 heads 12.3 us against 11.4), 1 to 3 MB 2 %, 3 to 6 MB
+// the same, 6 to 24 MB 2 to 4 % faster.
+constexpr size_t ATT_FAR_BYTES = (size_t)4 << 20;
+
 // KS groups of ATT_NW / KS wavefronts, each wavefront with 32 query rows of one head; a ring stage holds KS tiles of
 // 64 keys, one per group. NS ring stages. EVEN: even shares, else a block (or a split of it) per workgroup.
 template <int KS, int NS, bool EVEN>
@@ -630,17 +635,25 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   auto write_rows = [&]() {
   if (a.n_splits > 1) {
     // unnormalised O, running maximum and sum of this split (the layout of part_row)
-    // Past the caches: the launch ends when its writes are out, and 12.6 MB of them (128 rows of 32 heads in six splits) went out
-    // at its end, 19.4 us, now 17.8. (Rows put together in LDS first, so that a store covers 256 bytes of a row instead of 32 of
-    // every row, on top of that: no difference.)
+    // Many of them past the caches: the launch ends when its writes are out, and 12.6 MB (128 rows of 32 heads in six splits) went
+    // out at its end, 19.4 us, now 17.8. Few of them into the caches, where the merge finds them (ATT_FAR_BYTES). (Rows put together
+    // in LDS first, so that a store covers 256 bytes of a row instead of 32 of every row, on top of that: no difference.)
     const size_t row = part_row(a, bi, head, split, qi);
     float* pr = a.part + row * d + mb0 * 32 + 4 * hf;
+    auto each = [&](auto put) {
 #pragma unroll
-    for (int b = 0; b < NMB; ++b)
+      for (int b = 0; b < NMB; ++b)
 #pragma unroll
-      for (int a4 = 0; a4 < 4; ++a4)
-        __builtin_nontemporal_store(f32x4_t{o[b][4 * a4 + 0], o[b][4 * a4 + 1], o[b][4 * a4 + 2], o[b][4 * a4 + 3]},
-                                    reinterpret_cast<f32x4_t*>(pr + b * 32 + 8 * a4));
+        for (int a4 = 0; a4 < 4; ++a4)
+          put(f32x4_t{o[b][4 * a4 + 0], o[b][4 * a4 + 1], o[b][4 * a4 + 2], o[b][4 * a4 + 3]}, reinterpret_cast<f32x4_t*>(pr + b * 32 + 8 * a4));
+    };
+    if (a.part_far) {
+      asm volatile("" ::: "memory");                // (without the two the compiler joins both branches' stores into ordinary ones)
+      each([](f32x4_t v, f32x4_t* to) { __builtin_nontemporal_store(v, to); });
+      asm volatile("" ::: "memory");
+    } else {
+      each([](f32x4_t v, f32x4_t* to) { *to = v; });
+    }
     if (writes_ml) part_ml(a)[row] = make_float2(m_run, lt);
     return;
   }
@@ -1149,7 +1162,7 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
   AttArgs a;
   a.D = D; a.st = st; a.k_arena = k_arena; a.v_arena = v_arena; a.q = q; a.out = out; a.lse = lse;
   a.layer = layer; a.seq_count = seq_count; a.n_q = n_q; a.bp = bp;
-  a.n_splits = 1; a.part = part; a.even_flags = even_flags;
+  a.n_splits = 1; a.part = part; a.part_far = 0; a.even_flags = even_flags;
   a.part_mode = part_mode; a.loclist = loclist; a.loc_cap = loc_cap; a.lse_a = lse_a;
   if (part_mode == ATT_RETRIEVED && !lse_a) return hipErrorInvalidValue;
   const bool mfma_ok = attend_on_matrix_cores(D);
@@ -1193,6 +1206,7 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     const int gpk = D.G / HG;
     const int RPB = 32 * (ATT_NW / ks / HG);
     a.n_splits = ns;
+    a.part_far = (size_t)seq_count * n_q * D.Hq * ns * D.d * sizeof(float) >= ATT_FAR_BYTES;
     dim3 g(D.Hkv * gpk, (n_q + RPB - 1) / RPB * ns, seq_count);
     if (even) g = dim3(n_cus);
     static bool attr_set = false;
