@@ -17,6 +17,7 @@
 #include "attend_args.h"
 #include "handoff.h"
 #include <algorithm>
+#include <array>
 #include <type_traits>
 
 namespace ltri {
@@ -193,8 +194,11 @@ __device__ __forceinline__ EvenShare even_share(const AttArgs& a, int n_blocks, 
 constexpr size_t ATT_FAR_BYTES = (size_t)4 << 20;
 
 // KS groups of ATT_NW / KS wavefronts, each wavefront with 32 query rows of one head; a ring stage holds KS tiles of
-// 64 keys, one per group. NS ring stages. EVEN: even shares, else a block (or a split of it) per workgroup.
-template <int KS, int NS, bool EVEN>
+// 64 keys, one per group. NS ring stages. FORM: a block per workgroup, even shares, or a split of a block per workgroup, stored
+// through or past the caches. One kernel each: the launches of a stream of ragged chunks (32 / 8 heads, up to 700 tokens, 1 in 26
+// in splits) took 55.9 us each from one kernel that can also split, 56.6 from one with both kinds of stores, 54.1 from one per form.
+enum : int { ATT_WHOLE = 0, ATT_EVEN = 1, ATT_SPLIT = 2, ATT_SPLIT_FAR = 3 };
+template <int KS, int NS, int FORM>
 __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   constexpr int NW = ATT_NW, NWQ = NW / KS;         // wavefronts in all, and per group (they cover the workgroup's rows)
   constexpr int TOK_AHEAD = 2 * (NS - 1) + 1;       // token ids of stage t + TOK_AHEAD are requested in iteration t
@@ -202,6 +206,7 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   constexpr int LPT = 2 * NI;                       // K/V requests per lane and stage
   constexpr int IN_FLIGHT = (NS - 2) * (LPT + 1);   // requests that may be pending when a stage is used
   constexpr int TPW = 64 * KS / NW;                 // token ids a wave fetches per stage (those of its own rows)
+  constexpr bool EVEN = FORM == ATT_EVEN, SPLIT = FORM >= ATT_SPLIT;
   constexpr int STAGE_BYTES = KS * 2 * TILE_BYTES, TOK_SLOT_BYTES = KS * 256;
   static_assert(NS >= 2 && NS <= 4 && TOK_AHEAD < TOK_SLOTS && (NI == 2 || NI == 4), "request pattern");
   extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
@@ -214,12 +219,13 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   // KV head run on one XCD and share its K/V rows in that XCD's L2
   // (even shares give each die consecutive blocks, and these are numbered by KV head first)
   const int L = a.n_q, d = 128;
-  const int n_rb = EVEN ? (L + RPB - 1) / RPB : (int)gridDim.y / a.n_splits;     // row blocks
+  const int n_splits = SPLIT ? a.n_splits : 1;
+  const int n_rb = EVEN ? (L + RPB - 1) / RPB : (int)gridDim.y / n_splits;       // row blocks
   __shared__ int pre[EVEN ? ATT_EVEN_BLOCKS + 1 : 1];
   EvenShare share{};
   if constexpr (EVEN) share = even_share<KS>(a, D.Hkv * gpk * a.seq_count * n_rb, n_rb, pre);
   for (int blk = EVEN ? share.hi : 0; blk >= (EVEN ? share.lo : 0); --blk) {
-  int bi = blockIdx.z, hk = blockIdx.x, yb = (int)blockIdx.y / a.n_splits;
+  int bi = blockIdx.z, hk = blockIdx.x, yb = (int)blockIdx.y / n_splits;
   if constexpr (EVEN) {
     const int block = share.b0 + blk, sidx = block / n_rb;
     yb = block - sidx * n_rb;
@@ -234,7 +240,7 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   const int kg = wave / NWQ, wq = wave % NWQ;       // the wave's key group, and its place among the group's waves
   const int l32 = lane & 31, hf = lane >> 5;
   const int head = h * D.G + gsub * HG + (wq % HG);
-  const int split = EVEN ? 0 : (int)blockIdx.y % a.n_splits;
+  const int split = SPLIT ? (int)blockIdx.y % n_splits : 0;
   // Query rows of the workgroup. The chunk's rows are cut into sub-tiles of 32; workgroup y takes RS / 2 of them
   // from the low end and RS / 2 from the high end (sub-tiles y RS / 2 .. and their mirror images), so that under
   // the causal mask every workgroup has about the same number of (sub-tile, chunk tile) pairs to compute: the
@@ -268,8 +274,8 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
   // stages of KS tiles; with splits, this workgroup takes the stages [st0, st1) of context and chunk
   const int n_st = (n_tiles + KS - 1) / KS;
   const int first_st = EVEN ? __builtin_amdgcn_readfirstlane(pre[blk]) : 0;       // (of the block, among the die's)
-  const int st0 = EVEN ? max(share.u0 - first_st, 0) : (int)((long long)split * n_st / a.n_splits);
-  const int st1 = EVEN ? min(share.u1 - first_st, n_st) : (int)((long long)(split + 1) * n_st / a.n_splits);
+  const int st0 = EVEN ? max(share.u0 - first_st, 0) : (int)((long long)split * n_st / n_splits);
+  const int st1 = EVEN ? min(share.u1 - first_st, n_st) : (int)((long long)(split + 1) * n_st / n_splits);
   const uint32_t ring0 = (uint32_t)(uintptr_t)ring;
   const uint32_t tok0 = ring0 + NS * STAGE_BYTES + (uint32_t)wave * (TPW * 4);       // this wave's ids of slot 0
   const int32_t* tokring = reinterpret_cast<const int32_t*>(ring + NS * STAGE_BYTES) + wave * TPW;
@@ -633,27 +639,22 @@ __global__ __launch_bounds__(64 * ATT_NW) void attend_bf16_kernel(AttArgs a) {
     }
   }
   auto write_rows = [&]() {
-  if (a.n_splits > 1) {
+  if constexpr (SPLIT) {
     // unnormalised O, running maximum and sum of this split (the layout of part_row)
     // Many of them past the caches: the launch ends when its writes are out, and 12.6 MB (128 rows of 32 heads in six splits) went
     // out at its end, 19.4 us, now 17.8. Few of them into the caches, where the merge finds them (ATT_FAR_BYTES). (Rows put together
     // in LDS first, so that a store covers 256 bytes of a row instead of 32 of every row, on top of that: no difference.)
     const size_t row = part_row(a, bi, head, split, qi);
     float* pr = a.part + row * d + mb0 * 32 + 4 * hf;
-    auto each = [&](auto put) {
 #pragma unroll
-      for (int b = 0; b < NMB; ++b)
+    for (int b = 0; b < NMB; ++b)
 #pragma unroll
-        for (int a4 = 0; a4 < 4; ++a4)
-          put(f32x4_t{o[b][4 * a4 + 0], o[b][4 * a4 + 1], o[b][4 * a4 + 2], o[b][4 * a4 + 3]}, reinterpret_cast<f32x4_t*>(pr + b * 32 + 8 * a4));
-    };
-    if (a.part_far) {
-      asm volatile("" ::: "memory");                // (without the two the compiler joins both branches' stores into ordinary ones)
-      each([](f32x4_t v, f32x4_t* to) { __builtin_nontemporal_store(v, to); });
-      asm volatile("" ::: "memory");
-    } else {
-      each([](f32x4_t v, f32x4_t* to) { *to = v; });
-    }
+      for (int a4 = 0; a4 < 4; ++a4) {
+        const f32x4_t v = {o[b][4 * a4 + 0], o[b][4 * a4 + 1], o[b][4 * a4 + 2], o[b][4 * a4 + 3]};
+        f32x4_t* to = reinterpret_cast<f32x4_t*>(pr + b * 32 + 8 * a4);
+        if constexpr (FORM == ATT_SPLIT_FAR) __builtin_nontemporal_store(v, to);
+        else                                 *to = v;
+      }
     if (writes_ml) part_ml(a)[row] = make_float2(m_run, lt);
     return;
   }
@@ -1162,7 +1163,7 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
   AttArgs a;
   a.D = D; a.st = st; a.k_arena = k_arena; a.v_arena = v_arena; a.q = q; a.out = out; a.lse = lse;
   a.layer = layer; a.seq_count = seq_count; a.n_q = n_q; a.bp = bp;
-  a.n_splits = 1; a.part = part; a.part_far = 0; a.even_flags = even_flags;
+  a.n_splits = 1; a.part = part; a.even_flags = even_flags;
   a.part_mode = part_mode; a.loclist = loclist; a.loc_cap = loc_cap; a.lse_a = lse_a;
   if (part_mode == ATT_RETRIEVED && !lse_a) return hipErrorInvalidValue;
   const bool mfma_ok = attend_on_matrix_cores(D);
@@ -1206,38 +1207,46 @@ hipError_t launch_attend(const Dims& D, const DevState& st, const void* k_arena,
     const int gpk = D.G / HG;
     const int RPB = 32 * (ATT_NW / ks / HG);
     a.n_splits = ns;
-    a.part_far = (size_t)seq_count * n_q * D.Hq * ns * D.d * sizeof(float) >= ATT_FAR_BYTES;
     dim3 g(D.Hkv * gpk, (n_q + RPB - 1) / RPB * ns, seq_count);
     if (even) g = dim3(n_cus);
     static bool attr_set = false;
     if (!attr_set) {
-      for (const void* f : {reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4, false>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 3, false>),
-                            reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2, false>), reinterpret_cast<const void*>(&attend_bf16_kernel<1, 4, true>),
-                            reinterpret_cast<const void*>(&attend_bf16_kernel<1, 3, true>), reinterpret_cast<const void*>(&attend_bf16_kernel<2, 2, true>)}) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, att_lds_bytes(2, 2));
-        if (e != hipSuccess) return e;
-      }
+      auto of = [](auto ksc, auto nsc) {
+        constexpr int KS = decltype(ksc)::value, NS = decltype(nsc)::value;
+        return std::array<const void*, 4>{reinterpret_cast<const void*>(&attend_bf16_kernel<KS, NS, ATT_WHOLE>),
+                                          reinterpret_cast<const void*>(&attend_bf16_kernel<KS, NS, ATT_EVEN>),
+                                          reinterpret_cast<const void*>(&attend_bf16_kernel<KS, NS, ATT_SPLIT>),
+                                          reinterpret_cast<const void*>(&attend_bf16_kernel<KS, NS, ATT_SPLIT_FAR>)};
+      };
+      using std::integral_constant;
+      for (const auto& forms : {of(integral_constant<int, 1>{}, integral_constant<int, 4>{}), of(integral_constant<int, 1>{}, integral_constant<int, 3>{}),
+                                of(integral_constant<int, 2>{}, integral_constant<int, 2>{})})
+        for (const void* f : forms) {
+          const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, att_lds_bytes(2, 2));
+          if (e != hipSuccess) return e;
+        }
       attr_set = true;
     }
-    auto launch = [&](auto ksc, auto nsc, auto evenc) {
-      constexpr int KS = decltype(ksc)::value, NS = decltype(nsc)::value;
-      constexpr bool EVEN = decltype(evenc)::value;
+    auto launch = [&](auto ksc, auto nsc, auto formc) {
+      constexpr int KS = decltype(ksc)::value, NS = decltype(nsc)::value, FORM = decltype(formc)::value;
       constexpr int lds = att_lds_bytes(KS, NS);
       // the events ride in the kernel's own dispatch; with a merge behind it the end is recorded after that
       if (t_begin)
-        hipExtLaunchKernelGGL((attend_bf16_kernel<KS, NS, EVEN>), g, dim3(64 * ATT_NW), (uint32_t)lds, s, t_begin, ns > 1 ? nullptr : t_end, 0, a);
+        hipExtLaunchKernelGGL((attend_bf16_kernel<KS, NS, FORM>), g, dim3(64 * ATT_NW), (uint32_t)lds, s, t_begin, ns > 1 ? nullptr : t_end, 0, a);
       else
-        attend_bf16_kernel<KS, NS, EVEN><<<g, 64 * ATT_NW, lds, s>>>(a);
+        attend_bf16_kernel<KS, NS, FORM><<<g, 64 * ATT_NW, lds, s>>>(a);
     };
     using std::integral_constant;
-    using std::true_type;
-    using std::false_type;
-    if (even == 2)        launch(integral_constant<int, 2>{}, integral_constant<int, 2>{}, true_type{});
-    else if (even && stages == 3) launch(integral_constant<int, 1>{}, integral_constant<int, 3>{}, true_type{});
-    else if (even)        launch(integral_constant<int, 1>{}, integral_constant<int, 4>{}, true_type{});
-    else if (ks == 2)     launch(integral_constant<int, 2>{}, integral_constant<int, 2>{}, false_type{});
-    else if (stages == 3) launch(integral_constant<int, 1>{}, integral_constant<int, 3>{}, false_type{});
-    else                  launch(integral_constant<int, 1>{}, integral_constant<int, 4>{}, false_type{});
+    auto form = [&](auto ksc, auto nsc) {
+      if (even)                                  launch(ksc, nsc, integral_constant<int, ATT_EVEN>{});
+      else if (ns == 1)                          launch(ksc, nsc, integral_constant<int, ATT_WHOLE>{});
+      else if ((size_t)seq_count * n_q * D.Hq * ns * D.d * sizeof(float) < ATT_FAR_BYTES)
+                                                 launch(ksc, nsc, integral_constant<int, ATT_SPLIT>{});
+      else                                       launch(ksc, nsc, integral_constant<int, ATT_SPLIT_FAR>{});
+    };
+    if (ks == 2)          form(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    else if (stages == 3) form(integral_constant<int, 1>{}, integral_constant<int, 3>{});
+    else                  form(integral_constant<int, 1>{}, integral_constant<int, 4>{});
     if (ns > 1) {
       launch_merge(a, seq_count, s);
       if (t_end) { if (hipError_t e = hipEventRecord(t_end, s); e != hipSuccess) return e; }

@@ -8,7 +8,6 @@ struct AttArgs {
   Dims D; DevState st; const void* k_arena; const void* v_arena; const void* q;
   void* out; float* lse; int layer; int seq_count; int n_q;
   int n_splits; float* part;             // > 1: the key range is split over workgroups, partial results in part
-  int part_far;                          // partial results are stored past the caches
   int32_t* even_flags;                   // even shares: a flag per workgroup's place in part; fp32 splits: tickets. Zero between launches
   int part_mode;                         // ATT_ALL, or one of the two parts of a two-part step
   const int32_t* loclist; int loc_cap;   // ATT_LOCAL: initial | window tokens per sequence [seq_count][loc_cap]
