@@ -137,8 +137,10 @@ typedef struct {
  * memory (span table, representative keys, selections, token lists, the launches' counters; lives as
  * long as the context; ltri_create enqueues a kernel that zero-fills it), `scratch` holds per-call
  * temporaries: between calls it may be overwritten, or lent to other contexts, as long as calls do not
- * overlap (only ltri_get_theta reads what an earlier call left there). Among them are the partial results of attention launches whose key range is split
- * (bf16: up to 34 MB, by the context's heads, sequences, chunk length, window and budget).
+ * overlap (only ltri_get_theta reads what an earlier call left there). Among them are the partial results
+ * of attention launches that share a row's keys out over workgroups (bf16: up to 34.6 MB, by the context's
+ * heads, sequences, chunk length, window and budget; fp32: 2.1 MB; fp32 blocks of up to 4 rows have as
+ * much as they need in `state` too, for ltri_attend_static).
  * EINVAL on an unsupported configuration. */
 int32_t ltri_workspace_bytes(const ltri_config* cfg, size_t* state_bytes, size_t* scratch_bytes);
 
@@ -265,8 +267,9 @@ int32_t ltri_attend(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int32_t seq
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, same results. Where
  * ltri_attend keeps the partial results of a split key range of such a block in the context's scratch, this call
  * keeps them in a buffer of 2 MiB that the library itself holds on every GPU it runs on, from load until the
- * process ends (fp32 contexts: in the context's state). Blocks of more than 4 rows are ltri_attend's launch, partial results in the context's scratch
- * included. The call allocates and frees nothing. LTRI_ECAPACITY if the partial results of this call need more than 2 MiB (they take
+ * process ends (fp32 contexts: in the context's state). Blocks of more than 4 rows are ltri_attend's launch,
+ * partial results in the context's scratch included. The call allocates and frees nothing. LTRI_ECAPACITY if
+ * the partial results of this call need more than the 2 MiB (they take
  * seq_count * n_q_heads * splits * n_q * (head_dim + 2) * 4 bytes; 16 sequences of one token at 32 query
  * heads take 1.1 MB); other errors as ltri_attend. All bf16 contexts on one GPU share the buffer: calls that
  * overlap on one GPU (different streams or contexts) race; on one stream they are ordered. Nothing in the
@@ -283,9 +286,13 @@ int32_t ltri_attend_static(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int3
  * stream without a return to the host. With mean representatives in bf16 (head_dim 128) step 2 is one launch:
  * running sums of the chunk's query and key rows, which need no span boundaries, are taken by further workgroups
  * of step 1's last launch, and step 2 forms Q^R of every query span and the mean keys of the chunk's spans as
- * differences of two of their rows before it scores, selects and writes the lists. Other configurations sum the
- * rows per span in a launch of their own. The attention is one launch over initial | retrieved | window |
- * chunk, and one that merges partial results where the key range is split; results identical to the three calls.
+ * differences of two of their rows before it scores, selects and writes the lists. Chunks of up to 128 tokens
+ * sum the query rows of a span inside that launch, unless few KV heads have many rows each. With dynamic index
+ * vectors Q^R comes from step 1's launches. What is left sums the rows per span in launches of its own, and tables
+ * of more than 5120 spans (or units) are scored and selected by launches of their own. The attention is one launch
+ * over initial | retrieved | window | chunk. Where workgroups share a row's keys out, the partial results are
+ * added by one launch more, or (one token, fp32, and launches whose last round would leave most of the chip idle)
+ * inside the launch itself. Results identical to the three calls.
  * In host memory (kv_offload = 1): the fetch of the retrieved rows over the host link is the longest part of the
  * step. It is queued on a second stream the context owns, behind step 2; the attention over initial tokens,
  * window and the chunk itself, which needs none of those rows, follows step 2 on the context's stream and runs
@@ -308,9 +315,10 @@ int32_t ltri_step(ltri_ctx* ctx, int32_t layer, int32_t seq_begin, int32_t seq_c
  * writes two durations (milliseconds) per step for up to `cap` steps since the last read, oldest first, to the
  * host arrays, sets *n to the count and forgets the records. With resident keys and values the first array
  * holds the attention launch (two events per step, carried by the launch's own dispatch: they take the
- * kernel's start and end; with a merge behind it the second event follows the merge) and the second 0; with kv_offload = 1 the first holds the launch over initial | window
- * | chunk (which shares the chip with the fetch) and the second the launch over the retrieved rows. Steps that run the plain calls (one-token chunks, fp32) leave no record. Turning timing on or off also
- * forgets pending records. */
+ * kernel's start and end; with a merge behind it the second event follows the merge) and the second 0; with
+ * kv_offload = 1 the first holds the launch over initial | window | chunk (which shares the chip with the fetch)
+ * and the second the launch over the retrieved rows. Steps that run the plain calls (one-token chunks, fp32)
+ * leave no record. Turning timing on or off also forgets pending records. */
 int32_t ltri_set_step_timing(ltri_ctx* ctx, int32_t on);
 int32_t ltri_read_step_timing(ltri_ctx* ctx, float* local_ms_host, float* retrieved_ms_host, int32_t cap, int32_t* n);
 

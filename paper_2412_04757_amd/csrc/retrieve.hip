@@ -178,7 +178,7 @@ __global__ __launch_bounds__(1024) void qrep_partial_kernel(RetArgs a) {
 }
 
 // ---- long chunks, mean representatives: the running sums as a launch of their own (when the segmentation's
-//      first launch has not taken them along) ----
+//      launch of the selections has not taken them along) ----
 __global__ __launch_bounds__(1024) void running_sums_kernel(RetArgs a) {
   __shared__ __attribute__((aligned(16))) double wt[16 * 128];
   running_sums_block(a.D, a.bp, a.layer, a.batch_off, a.rs, blockIdx.x, blockIdx.y, wt);

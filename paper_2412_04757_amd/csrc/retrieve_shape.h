@@ -13,7 +13,8 @@ constexpr size_t rt1_lds_bytes(int bound) { return (size_t)rt1_pow2(bound) * 12 
 constexpr int QREP_PIECE = 128;                    // tokens of a piece of a query span
 // Chunks whose query rows every scoring workgroup sums itself: their tokens; and for calls of few sequences and KV heads, whose
 // sums a launch spreads over the chip, bytes of a KV head's rows. A compute unit's reading bounds it: 128 rows of 8 heads of 128 bf16
-// (256 KB) are as fast as with a launch before, of 16 heads 27.4 us against 24.9; but 24 sequences of 100 such rows 38.5 us with a launch before, 23.3 without.
+// (256 KB) are as fast as with a launch before, of 16 heads 27.4 us against 24.9; but 24 sequences of 100 such rows 38.5 us with a
+// launch before, 23.3 without.
 constexpr int QREP_SHORT = 128;
 constexpr int QREP_ROWS_BYTES = 256 * 1024;
 constexpr int QREP_FEW_PROBLEMS = 8;
