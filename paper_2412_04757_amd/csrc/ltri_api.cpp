@@ -260,7 +260,7 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
   c->ds = DevState{(int32_t*)(s + SL.meta), (int32_t*)(s + SL.span_start), (int32_t*)(s + SL.span_len),
                    (void*)(s + SL.krep), (double*)(s + SL.scores), (int32_t*)(s + SL.sel_ids),
                    (int32_t*)(s + SL.tok_list), (int32_t*)(s + SL.err), (uint32_t*)(s + SL.idx_mask),
-                   (int32_t*)(s + (D.offload ? SL.row_list : SL.tok_list)), (float*)(s + SL.f32_part), (int32_t*)(s + SL.even_flags), (int32_t*)(s + SL.tickets)};
+                   (int32_t*)(s + (D.offload ? SL.row_list : SL.tok_list))};
   char* t = c->scratch;
   c->dc = DevScratch{(double*)(t + CL.rowsum), (double*)(t + CL.csuf), (double*)(t + CL.tsum),
                      (double*)(t + CL.rcar), (double*)(t + CL.ccar), (double*)(t + CL.pscore),
@@ -268,7 +268,8 @@ static int32_t create_impl(const ltri_config* cfg, void* k_arena, void* v_arena,
                      (double*)(t + CL.qpart), (int32_t*)(t + CL.bounds), (uint8_t*)(t + CL.selflag), (float*)(t + CL.att_part),
                      (int32_t*)(t + CL.tokspan), (double*)(t + CL.dyn), (double*)(t + CL.lpart),
                      (uint32_t*)(t + CL.qhist), (unsigned long long*)(t + CL.qstate),
-                     (float*)(t + CL.att_lse2), (int32_t*)(t + CL.loclist), (unsigned long long*)(t + CL.qlist)};
+                     (float*)(t + CL.att_lse2), (int32_t*)(t + CL.loclist), (unsigned long long*)(t + CL.qlist),
+                     (int32_t*)(s + SL.even_flags), (int32_t*)(s + SL.tickets)};
   const size_t n = (size_t)D.n_layers * D.n_seqs;
   c->n_tokens.assign(n, 0);
   c->last_len.assign(n, 0);
@@ -719,9 +720,9 @@ static int32_t attend_impl(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_
       return fail(c, LTRI_ESTATE, "sequence %d: no selection for the last chunk (call ltri_retrieve first)",
                   seq_begin + s);
   float* part = c->dc.att_part;
-  int32_t* flags = c->ds.even_flags;
+  int32_t* flags = c->dc.even_flags;
   if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS && !attend_on_matrix_cores(c->D)) {
-    part = c->ds.f32_part;               // (same launch, same results)
+    part = (float*)(c->state + c->SL.f32_part);               // (same launch, same results)
   } else if (own_buffer && n_q <= ATT_SPLIT_MAX_ROWS) {
     flags = nullptr;                     // splits are merged by a launch of their own
     // a dry context sizes the request for a device of 256 compute units
@@ -910,7 +911,7 @@ int32_t ltri_step(ltri_ctx* c, int32_t layer, int32_t seq_begin, int32_t seq_cou
     if (r == LTRI_OK) r = timing_event(c, &t_end);
     if (r != LTRI_OK) return r;
     r = check_hip(c, launch_attend(c->D, c->ds, c->k_arena, c->v_arena, q, layer, bp, seq_count, n_new, out, lse,
-                                   c->attend_stages, c->dc.att_part, c->ds.even_flags, 0, nullptr, 0, nullptr, c->stream, t_begin, t_end),
+                                   c->attend_stages, c->dc.att_part, c->dc.even_flags, 0, nullptr, 0, nullptr, c->stream, t_begin, t_end),
                   "attend");
     if (r == LTRI_OK) timing.keep();
     return r;

@@ -134,9 +134,6 @@ struct DevState {
   int32_t* meta; int32_t* span_start; int32_t* span_len; void* krep; double* scores;
   int32_t* sel_ids; int32_t* tok_list; int32_t* err; uint32_t* idx_mask;
   int32_t* row_list;       // what the attention walks: tok_list itself, or (host-offloaded KV) the same list as pool rows
-  float* f32_part;
-  int32_t* even_flags;
-  int32_t* tickets;        // [max_problems] and [n_seqs * Hkv] counters of finished workgroups; zero between launches
 };
 struct DevScratch {
   double* rowsum; double* csuf; double* tsum; double* rcar; double* ccar;
@@ -144,6 +141,11 @@ struct DevScratch {
   int32_t* tokspan; double* dyn; double* lpart; uint32_t* qhist; unsigned long long* qstate;
   float* att_lse2; int32_t* loclist;
   unsigned long long* qlist;
+  // What launches hand over by, in the state's memory and zero between launches: flags of even shares and tickets of the attention;
+  // [max_problems] and [n_seqs * Hkv] counters of finished workgroups. (Here and not in DevState, which every kernel's arguments
+  // begin with: 24 bytes more there made a stream of small fp32 chunks, 112 launches, 3 us longer.)
+  int32_t* even_flags;
+  int32_t* tickets;
 };
 
 // Running sums of a chunk's query and key rows (running_sums.h), which step 2 of long chunks with mean

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(1024) void qrep_partial_kernel(RetArgs a) {
   __shared__ int s_last;
   wait_for_own_stores();
   __syncthreads();
-  if (threadIdx.x == 0) s_last = atomicAdd(&a.st.tickets[p], 1) == QREP_GRID_X - 1;
+  if (threadIdx.x == 0) s_last = atomicAdd(&a.sc.tickets[p], 1) == QREP_GRID_X - 1;
   __syncthreads();
   if (!s_last) return;
   T* qrep = reinterpret_cast<T*>(a.sc.qrep) + (size_t)(bi * D.Hkv + h) * a.Lp * d;
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(1024) void qrep_partial_kernel(RetArgs a) {
       qrep[(size_t)q * d + c] = Elt<DT>::from_f64(summed ? sum : sum / (double)len);
     }
   }
-  if (threadIdx.x == 0) a.st.tickets[p] = 0;
+  if (threadIdx.x == 0) a.sc.tickets[p] = 0;
 }
 
 // ---- long chunks, mean representatives: the running sums as a launch of their own (when the segmentation's
@@ -1108,10 +1108,10 @@ __global__ __launch_bounds__(1024) void retrieve_chunk_kernel(RetArgs a, int bou
   wait_for_own_stores();                                  // the last workgroup reads them once every ticket is taken
   __syncthreads();
   if (n_score > 1) {
-    if (tid == 0) s_last = atomicAdd(&a.st.tickets[a.ticket_base + pl], 1) == n_score - 1;
+    if (tid == 0) s_last = atomicAdd(&a.sc.tickets[a.ticket_base + pl], 1) == n_score - 1;
     __syncthreads();
     if (!s_last) return;
-    if (tid == 0) a.st.tickets[a.ticket_base + pl] = 0;
+    if (tid == 0) a.sc.tickets[a.ticket_base + pl] = 0;
   }
   const int n_new = meta[META_CHUNK_LEN];
   const int ni = D.unit > 0 ? min(item_count(D, meta), item_bound) : n;      // items: units, or spans
