@@ -130,9 +130,9 @@ inline float attend_even_cost(int Hq, int Hkv, int seq_count, int n_q, int n_ctx
 // more where a workgroup has one sub-tile and several rounds average half the chunk: 0.6 of it counts here). Two groups behind a
 // context of less than half the chunk were slower whatever the model said, and are left out.
 // Measured in all forms at 1101 launches (64 to 4 query heads, 1 to 24 sequences, 64 to 2048 rows behind 0 to 12292 tokens;
-// profiles/attend_even_shares.txt), most of them near the line: taken at 506, 12 % faster there in the mean, at five more than 2 %
-// slower (6 at worst). With one constant for all blocks the rule took 797 of them, 1 % slower in the mean and 45 % at worst.
-// 12292 + 1100 rows 326 -> 254, 2052 + 1050 80 -> 65, 12292 + 700 177 -> 165, three sequences of 8196 + 700 392 -> 304.
+// profiles/attend_even_shares.txt), most of them near the line: taken at 506, 14 % faster there in the mean, at one more than 2 %
+// slower (4). With one constant for all blocks the rule took 797 of them, 1 % slower in the mean and 46 % at worst.
+// 12292 + 1100 rows 331 -> 245, 2052 + 1050 81 -> 63, 12292 + 700 178 -> 162, three sequences of 8196 + 700 388 -> 299.
 inline int attend_even(int Hq, int Hkv, int seq_count, int n_q, int n_ctx, size_t part_bytes, size_t part_rows, int n_cus) {
   const int G = Hq / Hkv, HG = G < 4 ? G : 4;
   if (n_cus % 8 != 0) return 0;
