@@ -9,10 +9,10 @@
 // the write-back of the rows at the end of the kernel).
 // Measured at 173 launches (64, 32, 16 and 8 query heads on 8 or 2 KV heads, 1 to 16 sequences, 64 to 2048 rows behind up to
 // 12300 context tokens; profiles/attend_shapes.txt) in every shape: the model is 8 % low with 11 % of scatter, what it takes is
-// 1.1 % above the best shape in the geometric mean, and never slower than one group without splits, which all launches were
-// before. That one against what is taken, context + rows, 32 heads: 12292 + 1024 337 -> 230 (two groups), 2052 + 700
-// 77 -> 50, four sequences of 2052 + 256 74 -> 51, 12292 + 512 316 -> 126 (two groups, two splits), 2052 + 128 63 -> 24,
-// 0 + 700 23 -> 20. A full chip keeps one group (12292 + 2048: 438 against 463 with two, 2052 + 2048: 119 against 125).
+// 0.9 % above the best shape in the geometric mean, and never slower than one group without splits, which all launches were
+// before. That one against what is taken, context + rows, 32 heads: 12292 + 1024 326 -> 225 (two groups), 2052 + 700
+// 74 -> 47, four sequences of 2052 + 256 69 -> 49, 12292 + 512 315 -> 119 (four splits), 2052 + 128 63 -> 22 (two groups, six
+// splits), 0 + 700 22 -> 19. A full chip keeps one group (12292 + 2048: 427 against 452 with two, 2052 + 2048: 116 against 119).
 #pragma once
 #include <math.h>
 #include <stddef.h>
@@ -24,7 +24,7 @@ constexpr int ATT_MAX_SPLITS = 16;       // key-range splits of an attention lau
 constexpr int ATT_SPLIT_MAX_ROWS = 4;    // longest query block whose split does not depend on the context (decoding)
 // Partial rows of a longer block, at most (34 MB at head_dim 128). Twice what one round of workgroups writes: with more,
 // 1100 to 1536 rows of 32 heads would be split into three rounds of workgroups, which the model favours over the two
-// rounds of one group but which took 1 to 5 % longer (12292 + 1400: 354 against 337, 12292 + 1536: 368 against 358).
+// rounds of one group but which took 1 to 5 % longer (two groups and splits, 12292 + 1400: 342 against 336, 12292 + 1536: 363 against 348).
 constexpr size_t ATT_PART_MAX_ROWS = 65536;
 
 struct AttShape { int ks, ns; };
